@@ -65,6 +65,25 @@ def test_image_loss_and_gradient_match_oracle():
     _check(sim, np.zeros((2, 0)), 32, 32, rng.uniform(0, 1, size=(16, 16)), 1.0, 1.0, "no nodes")
 
 
+# (nodes, world, image, sigma) on each side of the choices between the tile-wise
+# and the node-wise sum and between a wavefront and a thread per node, with
+# image sides that are no multiple of a tile; FP32 sums of the same terms: the
+# bounds of _check
+@pytest.mark.parametrize("n, nx, ny, W, H, sigma", [
+    (1, 64, 64, 9, 17, 2.0),                 # tiles, one node
+    (1025, 90, 70, 45, 35, 2.0),             # tiles, one node past a chunk
+    (700, 24, 24, 48, 48, 2.5),              # tiles, windows over the whole image
+    (6000, 128, 120, 64, 60, 2.0),           # node-wise image by wavefronts
+    (40000, 512, 480, 32, 30, 2.0),          # node-wise image and gradient by threads
+    (30, 100, 100, 1, 3, 4.0),               # fewer pixels than a tile holds
+])
+def test_image_sums_and_gradient_lanes(n, nx, ny, W, H, sigma):
+    sim = _sim()
+    rng = np.random.default_rng(n)
+    x = rng.uniform(0, 1, size=(2, n)) * [[nx], [ny]]
+    _check(sim, x, nx, ny, rng.uniform(0, 1, size=(H, W)), sigma, 0.2, f"{n} nodes, {nx}x{ny} / {W}x{H}")
+
+
 def _pipeline(sim, w, T, sigma, amp, n, k):
     """GPU: rollout (checkpointed) + density loss; gradient in the rest angles."""
     W = sim.World(w, sim.Params(nx=w.nx, ny=w.ny))
