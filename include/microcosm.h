@@ -58,9 +58,9 @@ typedef enum sim_status {
 
 /* sim_params.flags */
 /* Particle -> grid transfer (deposit and force spread).  Default (no flag):
- * nodes are binned by the grid tile (side tile_side) of their home cell; every tile
- * reads the bins of its neighbourhood, sums the contributions that reach it
- * in on-chip memory (integer fixed point: results are bitwise reproducible)
+ * every grid tile has a list of the nodes that reach it, which the step before
+ * made (worlds of few nodes, or with little workspace, test every node instead),
+ * sums their contributions in on-chip memory (integer fixed point: results are bitwise reproducible)
  * and writes each cell once.  The two flags are exclusive. */
 enum {
   SIM_SPLAT_SORTED = 1u << 0, /* deterministic: counting sort by home cell, fixed-order
@@ -84,9 +84,10 @@ typedef struct sim_params {
   float u_max;             /* Mach guard: |u| above this flags the world unstable    */
   uint32_t flags;          /* SIM_SPLAT_SORTED or SIM_SPLAT_DIRECT, else binned      */
   int32_t tile_side;       /* side of the square grid tiles the transfer and filter
-                              kernels work on (and of the node bins): 16, 32 or 64;
-                              0 means 32.  A tuning choice: results do not depend
-                              on it beyond rounding (binned: not at all).          */
+                              kernels work on: 16, 32 or 64; 0 means 32.  A tuning
+                              choice: results do not depend on it beyond rounding
+                              (binned: not at all, and a world may run with
+                              another side where that is faster).                  */
   float energy_rate;       /* energy field (sim_arrays.energy): fraction of the
                               sensed energy a node collects per step, in [0, 1];
                               0 disables the field                                 */
@@ -301,10 +302,9 @@ sim_status sim_rest_effort(int32_t n_filaments, const int32_t *fil_offset, const
                            void *stream);
 
 /* Wait for the world's stream; report asynchronous HIP errors, the sticky
- * Mach/NaN flag (SIM_E_UNSTABLE), and SIM_E_STATE if the tile bins did not
- * match the positions (a node found its bin full, or the bin counts did not
- * add up to the node count), which only happens when sub-steps are run out
- * of order. */
+ * Mach/NaN flag (SIM_E_UNSTABLE), and SIM_E_STATE if the tile lists did not
+ * match the positions, which only happens when sub-steps are run out of
+ * order. */
 sim_status sim_sync(sim_world *w);
 /* Clear the sticky Mach/NaN flag (enqueued on the stream). */
 sim_status sim_clear_flags(sim_world *w);
@@ -361,7 +361,7 @@ sim_status sim_debug_buffer(sim_world *w, int32_t which, void **ptr);
  * launched directly, not from a graph) with HIP events on the world's stream
  * around every kernel group, and write the mean device time in milliseconds
  * of each group to ms_out[6]: 0 elastic force, 1 transfer preparation
- * (sorting; the tile bins are built by groups 0 and 5), 2 deposit + filter,
+ * (sorting; the tile lists are made by group 5), 2 deposit + filter,
  * 3 repulsion + spread, 4 fluid update, 5 gather + integrate.  Group 4 is the
  * fluid kernel's own execution time (its dispatch's start and end
  * timestamps); the other groups are event pairs around their launches and

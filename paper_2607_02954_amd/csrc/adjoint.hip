@@ -23,7 +23,7 @@
 //                     atan2 of the initial edge angles and the actuation ->
 //                     dL/dx_t and dL/d(rest angle)
 // Every forward field the adjoint needs (x_t, g_t, G_t, F_t, F_grid, u_t, the
-// tile bins of x_t and the filter's spread lists) is taken from the tape
+// tile lists of x_t) is taken from the tape
 // written by the recomputed forward step; the descriptor passed in points at
 // that tape slot.
 #include "device_util.h"
@@ -37,7 +37,7 @@ static __device__ __forceinline__ const AdjDev& adj_of(const AdjArg& a, int worl
 }
 
 // ---------------------------------------------------------------------------
-// Node -> grid spreads of adjoint node vectors (u~ and G~), tile-binned.
+// Node -> grid spreads of adjoint node vectors (u~ and G~) over the tiles' lists.
 // ---------------------------------------------------------------------------
 // out = add + scale S[v], the operands chosen by `which`: 0 u~ = S[x~'],
 // 1 G~ = -k_rep S[F~], 2 the MDF iterate F_grid_1 = S[F], 3 the iterate
@@ -46,10 +46,10 @@ template <int TILE>
 __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_adj_spread(const WorldDev* __restrict__ W, Tables T,
                                                                          AdjArg AA, int which, int k) {
   using C = TileCfg<TILE>;
-  constexpr int kThreads = C::kThreads, kSpreadCells = C::kSpreadCells;
-  __shared__ __align__(16) long long s_x[kSpreadCells];
-  __shared__ __align__(16) long long s_y[kSpreadCells];
-  __shared__ vi4 s_list[(kThreads / 64) * kWaveList];
+  using SW = SpreadWin<TILE>;
+  constexpr int kThreads = C::kThreads;
+  __shared__ __align__(16) long long s_x[SW::kCells];
+  __shared__ __align__(16) long long s_y[SW::kCells];
   const int nt = n_tiles<TILE>(T);
   const XcdLoop tiles(nt);
   for (int it = tiles.first; it < tiles.end; it += tiles.step) {
@@ -80,37 +80,17 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_adj_spread(const Wo
       add = A.Fgk + (size_t)(k - 1) * ncell;
       out = A.Fgk + (size_t)k * ncell;
     }
-    zero_lds_u64(s_x, kSpreadCells);
-    zero_lds_u64(s_y, kSpreadCells);
-    __syncthreads();
-    // the step's spread list (written by the recomputed filter into the
-    // tape), or the bins if it overflowed (and for the test hook, which runs
-    // on a world's own buffers)
     const int tix = tile_y(tl.y) * w.ntx + tile_x(tl.y);
-    const int cnt = which != 4 ? glb(w.sp_cnt)[tix] : -1;
-    BinFetch lf;
-    lf.n = 1;
-    lf.b0 = tix * C::kSpreadCap;
-    lf.len = __lane_id() == 0 ? cnt : 0;
-    const bool list = cnt >= 0 && cnt <= C::kSpreadCap;
-    const MC_GLOBAL vi4* lrec = glbv<const vi4>(w.sp_rec);
-    const MC_GLOBAL vi4* brec = glbv<const vi4>(w.bin_rec);
+    SpreadNodes<TILE> nodes(w, tix, glb(v));
+    zero_lds_u64(s_x, SW::kCells);
+    zero_lds_u64(s_y, SW::kCells);
+    __syncthreads();
     // the transfers of the node<->grid coupling act through two-layer
     // markers where a world has them; the repulsion (G~) stays at the node
-    if (w.d_marker && which != 1 && which != 4) {
-      if (list)
-        tile_spread_markers<TILE, false, true>(w, x0, y0, tw, th, glb(v), scale, s_x, s_y, s_list, lrec, lf, nullptr);
-      else
-        tile_spread_markers<TILE, false>(w, x0, y0, tw, th, glb(v), scale, s_x, s_y, s_list, brec,
-                                         spread_fetch<TILE>(w, x0, y0), nullptr);
-    } else if (list && !w.d_marker) {
-      tile_spread_vec<TILE, false, true>(w, x0, y0, tw, th, glb(v), scale, s_x, s_y, s_list, lrec, lf, nullptr);
-    } else if (list) {                 // a two-layer world's list also holds nodes one cell further out
-      tile_spread_vec<TILE, false>(w, x0, y0, tw, th, glb(v), scale, s_x, s_y, s_list, lrec, lf, nullptr);
-    } else {
-      tile_spread_vec<TILE, false>(w, x0, y0, tw, th, glb(v), scale, s_x, s_y, s_list, brec,
-                                   spread_fetch<TILE>(w, x0, y0), nullptr);
-    }
+    if (w.d_marker && which != 1 && which != 4)
+      tile_spread_markers<TILE, false>(w, nodes, x0, y0, tw, th, scale, s_x, s_y, nullptr);
+    else
+      tile_spread_vec<TILE, false>(w, nodes, x0, y0, tw, th, scale, s_x, s_y, nullptr);
     __syncthreads();
     MC_GLOBAL vf2* o = glbv<vf2>(out);
     for (int k = threadIdx.x; k < TILE * TILE; k += kThreads) {
@@ -119,8 +99,8 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_adj_spread(const Wo
       const size_t c = (size_t)(y0 + ly) * nx + x0 + lx;
       vf2 val = {0.f, 0.f};
       if (add) val = glbv<const vf2>(add)[c];
-      val.x += fix_to_float(spread_cell<TILE>(s_x, lx, ly, nx, ny));
-      val.y += fix_to_float(spread_cell<TILE>(s_y, lx, ly, nx, ny));
+      val.x += fix_to_float(spread_cell<SW::kSide>(s_x, lx, ly, nx, ny));
+      val.y += fix_to_float(spread_cell<SW::kSide>(s_y, lx, ly, nx, ny));
       o[c] = val;
     }
     __syncthreads();
@@ -238,7 +218,7 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_adj_force(const Wor
                                                                         AdjArg AA) {
   // per tile: u, dL/dF_grid and the density gradient staged over the cells
   // the supports of the tile's own nodes (and of their markers: MK) reach,
-  // then one thread per node of the tile's bin
+  // then one thread per node of the tile
   constexpr int kE = MK ? 1 : 0;
   constexpr int kStage = TILE + 3 + 2 * kE, kThreads = TileCfg<TILE>::kThreads, kCells = kStage * kStage;
   __shared__ vf2 s_u[kCells];
@@ -253,6 +233,7 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_adj_force(const Wor
     const AdjDev& A = adj_of(AA, tl.x);
     const int N = w.n_part, nx = w.nx, ny = w.ny;
     const int x0 = tile_x(tl.y) * TILE, y0 = tile_y(tl.y) * TILE;
+    const int tile = tile_y(tl.y) * w.ntx + tile_x(tl.y);
     const MC_GLOBAL vf2* u = glbv<const vf2>(w.u);
     const MC_GLOBAL vf2* Fgb = glbv<const vf2>(A.Fgbar);
     const MC_GLOBAL vf2* Gr = glbv<const vf2>(w.grad);
@@ -279,11 +260,7 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_adj_force(const Wor
       }
     }
     __syncthreads();
-    const int tile = tile_y(tl.y) * w.ntx + tile_x(tl.y);
-    const int e0 = glb(w.bin_start)[tile], e1 = glb(w.bin_start)[tile + 1];
-    const MC_GLOBAL vi4* recs = glbv<const vi4>(w.bin_rec);
-    for (int e = e0 + (int)threadIdx.x; e < e1; e += kThreads) {
-      const vi4 rec = recs[e];
+    for_own_records<kThreads>(w, tile, x0, y0, min(TILE, nx - x0), min(TILE, ny - y0), [&](const vi4& rec) {
       const int lx = (rec.x & 0xffff) - x0, ly = (rec.x >> 16) - y0;   // home cell in the tile
       const int gi = rec.w;
       const float nfx = __int_as_float(rec.y), nfy = __int_as_float(rec.z);
@@ -373,7 +350,7 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_adj_force(const Wor
       A.Fbar[N + gi] = fby;
       A.xbar[gi] = xbx + sux + sfx - kr * srx + mx;
       A.xbar[N + gi] = xby + suy + sfy - kr * sry + my;
-    }
+    });
     __syncthreads();
   }
 }
@@ -947,7 +924,7 @@ __global__ __launch_bounds__(PACK) void k_adj_pbd(const WorldDev* __restrict__ W
 // G~ += u_k~ / (2 rho), j~ += u_k~ / rho, rho~ -= u_k~ . u_k / rho.  Then U_d:
 // F~ += U_d~ / 2 (in k_adj_force), x~ from I[j / rho], v~ = S[U_d~] gives
 // j~ += v~ / rho, rho~ -= v~ . (j / rho) / rho, and finally g~_q += rho~ + c_q . j~.
-// Node passes gather over each tile's own-bin nodes from fields staged over
+// Node passes gather over each tile's own nodes from fields staged over
 // the tile with one cell before it and two after on each axis (one more on
 // each side with markers); the spreads are the tile spread in 64-bit
 // fixed point.  The recomputed iterates use the forward's arithmetic and sums,
@@ -1035,6 +1012,7 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_adj_mdf_fwd_gather(
     const float2* Fgk = A.Fgk + (size_t)(k > 0 ? k - 1 : 0) * ((size_t)w.nx * w.ny);   // iterate k (k >= 1)
     const int nx = w.nx, ny = w.ny, N = w.n_part;
     const int x0 = tile_x(tl.y) * TILE, y0 = tile_y(tl.y) * TILE;
+    const int tile = tile_y(tl.y) * w.ntx + tile_x(tl.y);
     const MC_GLOBAL vf4* m = glbv<const vf4>(w.rho_j);
     const MC_GLOBAL vf2* Fg = glbv<const vf2>(Fgk);
     adj_stage<TILE, kE>(nx, ny, x0, y0, s_u, [&](size_t c) {
@@ -1052,11 +1030,7 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_adj_mdf_fwd_gather(
       return u;
     });
     __syncthreads();
-    const int tile = tile_y(tl.y) * w.ntx + tile_x(tl.y);
-    const int e0 = glb(w.bin_start)[tile], e1 = glb(w.bin_start)[tile + 1];
-    const MC_GLOBAL vi4* recs = glbv<const vi4>(w.bin_rec);
-    for (int e = e0 + (int)threadIdx.x; e < e1; e += kThreads) {
-      const vi4 r = recs[e];
+    for_own_records<kThreads>(w, tile, x0, y0, min(TILE, nx - x0), min(TILE, ny - y0), [&](const vi4& r) {
       const int lx = (r.x & 0xffff) - x0, ly = (r.x >> 16) - y0;
       const int gi = r.w;
       float gx = 0.f, gy = 0.f;
@@ -1097,7 +1071,7 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_adj_mdf_fwd_gather(
         A.mc[gi] = 2.0f * (A.Ud[gi] - gx);
         A.mc[N + gi] = 2.0f * (A.Ud[N + gi] - gy);
       }
-    }
+    });
     __syncthreads();
   }
 }
@@ -1124,6 +1098,7 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_adj_mdf_node(const 
     const float2* Fgk = A.Fgk + (size_t)(k > 0 ? k - 1 : 0) * ((size_t)w.nx * w.ny);   // iterate k (k >= 1)
     const int nx = w.nx, ny = w.ny, N = w.n_part;
     const int x0 = tile_x(tl.y) * TILE, y0 = tile_y(tl.y) * TILE;
+    const int tile = tile_y(tl.y) * w.ntx + tile_x(tl.y);
     const MC_GLOBAL vf4* m = glbv<const vf4>(w.rho_j);
     const MC_GLOBAL vf2* Fg = glbv<const vf2>(Fgk);
     const MC_GLOBAL vf2* Gb = glbv<const vf2>(A.Fgbar);
@@ -1143,11 +1118,7 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_adj_mdf_node(const 
       return u;
     });
     __syncthreads();
-    const int tile = tile_y(tl.y) * w.ntx + tile_x(tl.y);
-    const int e0 = glb(w.bin_start)[tile], e1 = glb(w.bin_start)[tile + 1];
-    const MC_GLOBAL vi4* recs = glbv<const vi4>(w.bin_rec);
-    for (int e = e0 + (int)threadIdx.x; e < e1; e += kThreads) {
-      const vi4 r = recs[e];
+    for_own_records<kThreads>(w, tile, x0, y0, min(TILE, nx - x0), min(TILE, ny - y0), [&](const vi4& r) {
       const int lx = (r.x & 0xffff) - x0, ly = (r.x >> 16) - y0;
       const float nfx = __int_as_float(r.y), nfy = __int_as_float(r.z);
       const int gi = r.w;
@@ -1221,7 +1192,7 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_adj_mdf_node(const 
         A.dbar_m[gi] += dx;
         A.dbar_m[N + gi] += dy;
       }
-    }
+    });
     __syncthreads();
   }
 }
@@ -1233,10 +1204,10 @@ template <int TILE, int MODE>
 __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_adj_mdf_cell(const WorldDev* __restrict__ W, Tables T,
                                                                            AdjArg AA, int k) {
   using C = TileCfg<TILE>;
-  constexpr int kThreads = C::kThreads, kSpreadCells = C::kSpreadCells;
-  __shared__ __align__(16) long long s_x[kSpreadCells];
-  __shared__ __align__(16) long long s_y[kSpreadCells];
-  __shared__ vi4 s_list[(kThreads / 64) * kWaveList];
+  using SW = SpreadWin<TILE>;
+  constexpr int kThreads = C::kThreads;
+  __shared__ __align__(16) long long s_x[SW::kCells];
+  __shared__ __align__(16) long long s_y[SW::kCells];
   const int nt = n_tiles<TILE>(T);
   const XcdLoop tiles(nt);
   for (int it = tiles.first; it < tiles.end; it += tiles.step) {
@@ -1249,23 +1220,23 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_adj_mdf_cell(const 
     const int ncell = nx * ny;
     const int x0 = tile_x(tl.y) * TILE, y0 = tile_y(tl.y) * TILE;
     const int tw = min(TILE, nx - x0), th = min(TILE, ny - y0);
-    zero_lds_u64(s_x, kSpreadCells);
-    zero_lds_u64(s_y, kSpreadCells);
+    const int tix = tile_y(tl.y) * w.ntx + tile_x(tl.y);
+    SpreadNodes<TILE> nodes(w, tix, glb(nodevec));
+    zero_lds_u64(s_x, SW::kCells);
+    zero_lds_u64(s_y, SW::kCells);
     __syncthreads();
     if (w.d_marker)                     // two layers: the nodes' vectors spread from their markers
-      tile_spread_markers<TILE, false>(w, x0, y0, tw, th, glb(nodevec), 1.0f, s_x, s_y, s_list,
-                                       glbv<const vi4>(w.bin_rec), spread_fetch<TILE>(w, x0, y0), nullptr);
+      tile_spread_markers<TILE, false>(w, nodes, x0, y0, tw, th, 1.0f, s_x, s_y, nullptr);
     else
-      tile_spread_vec<TILE, false>(w, x0, y0, tw, th, glb(nodevec), 1.0f, s_x, s_y, s_list,
-                                   glbv<const vi4>(w.bin_rec), spread_fetch<TILE>(w, x0, y0), nullptr);
+      tile_spread_vec<TILE, false>(w, nodes, x0, y0, tw, th, 1.0f, s_x, s_y, nullptr);
     __syncthreads();
     const MC_GLOBAL vf4* m = glbv<const vf4>(w.rho_j);
     for (int k = threadIdx.x; k < TILE * TILE; k += kThreads) {
       const int ly = k >> C::kShift, lx = k & (TILE - 1);
       if (lx >= tw || ly >= th) continue;
       const size_t c = (size_t)(y0 + ly) * nx + x0 + lx;
-      const float wbx = fix_to_float(spread_cell<TILE>(s_x, lx, ly, nx, ny));
-      const float wby = fix_to_float(spread_cell<TILE>(s_y, lx, ly, nx, ny));
+      const float wbx = fix_to_float(spread_cell<SW::kSide>(s_x, lx, ly, nx, ny));
+      const float wby = fix_to_float(spread_cell<SW::kSide>(s_y, lx, ly, nx, ny));
       const vf4 mv = m[c];
       const float inv = 1.0f / mv.x;
       vf2 u;

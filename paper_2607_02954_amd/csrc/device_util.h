@@ -4,6 +4,7 @@
 #include <math.h>
 
 #include <type_traits>
+#include <utility>
 
 #include "engine.h"
 
@@ -11,6 +12,17 @@ namespace mc {
 
 constexpr float kPi = 3.14159265358979323846f;
 constexpr float kTwoPi = 6.28318530717958647692f;
+
+// f(0), ..., f(N - 1) with compile-time arguments (integral constants): arrays
+// indexed by them stay in registers.
+template <int... I, class F>
+static __device__ __forceinline__ void static_for_seq(std::integer_sequence<int, I...>, F f) {
+  (f(std::integral_constant<int, I>()), ...);
+}
+template <int N, class F>
+static __device__ __forceinline__ void static_for(F f) {
+  static_for_seq(std::make_integer_sequence<int, N>(), f);
+}
 
 // i mod n in [0, n) for any i; integer division only outside [-n, 2n).
 static __device__ __forceinline__ int wrap_index(int i, int n) {
@@ -22,26 +34,12 @@ static __device__ __forceinline__ int wrap_index(int i, int n) {
 }
 
 // Compile-time shape of the tile kernels for tiles of side TILE.
-constexpr int kWaveList = 64;              // records per wavefront list (for_bin_records)
 template <int TILE>
 struct TileCfg {
   static constexpr int kTile = TILE;
   static constexpr int kShift = tile_shift_of_side(TILE);
   static constexpr int kFamily = tile_family_of_side(TILE);
   static constexpr int kThreads = TILE == 64 ? 1024 : 256;   // threads per tile block
-  // bin columns (and rows) a reader's home range can touch, and bin runs
-  // it reads: the filter's range is the tile plus R + 3 <= 11 < TILE cells
-  // on each side, so it touches the tile and one neighbour per side, and
-  // one tile more where that neighbour is the partial last tile of an axis
-  // (shorter than the margin) on one side: at most 4; a row of bins needs at
-  // most two runs (its cyclic column list is broken once at most)
-  static constexpr int kMaxCols = 4;
-  static constexpr int kRanges = 2 * kMaxCols;
-  static constexpr int kSpreadSide = TILE + 6;              // spread window side
-  static constexpr int kSpreadCells = kSpreadSide * kSpreadSide;
-  static constexpr int kSpreadCap = spread_cap_of_side(TILE);
-  static constexpr int kListBytes = (kThreads / 64) * kWaveList * 16;
-  static_assert(kRanges <= kRunStride, "run table too narrow");
 };
 
 // Tile table entry it of a tile family: (world, tx | ty << 16); computed
@@ -241,35 +239,6 @@ static __device__ __forceinline__ vf2 gather_vec(const MC_GLOBAL vf2* field, int
 static __constant__ int kCX[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
 static __constant__ int kCY[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
 
-// Bin (home tile) of a wrapped home cell (bx, by) of a world with ntx tiles
-// per row of side 1 << shift, and the bin at tile column sx, row sy.
-static __device__ __forceinline__ int bin_of(int bx, int by, int ntx, int shift) {
-  return (by >> shift) * ntx + (bx >> shift);
-}
-static __device__ __forceinline__ int bin_at(int sx, int sy, int ntx) { return sy * ntx + sx; }
-
-// Distinct tile columns holding the cells lo..hi of a periodic axis of n
-// cells (at most TileCfg<TILE>::kMaxCols for the ranges the readers use).
-template <int TILE>
-static __device__ __forceinline__ int bins_covering(int lo, int hi, int n, int* t) {
-  constexpr int kMax = TileCfg<TILE>::kMaxCols;
-  int cnt = 0;
-  if (hi - lo + 1 >= n) {                       // whole axis (a short one)
-    for (int k = 0; k * TILE < n && cnt < kMax; ++k) t[cnt++] = k;
-    return cnt;
-  }
-  int c = lo;
-  while (c <= hi && cnt < kMax) {
-    const int cc = wrap_index(c, n);
-    const int tt = cc / TILE;
-    bool seen = false;
-    for (int k = 0; k < cnt; ++k) seen |= (t[k] == tt);
-    if (!seen) t[cnt++] = tt;
-    c += min((tt + 1) * TILE, n) - cc;          // jump to the next tile boundary
-  }
-  return cnt;
-}
-
 // 64-bit fixed-point accumulation in LDS (2^-36 resolution, range +-2^27).
 constexpr float kFixScale = 68719476736.0f;           // 2^36
 constexpr float kFixInv = 1.4551915228366852e-11f;    // 2^-36
@@ -314,12 +283,13 @@ static __device__ __forceinline__ float density_to_float(unsigned long long v) {
 // Work-item order of the tile kernels.  The hardware hands workgroups to the
 // eight XCDs in turn (block b to XCD b mod 8) and each XCD has its own L2, so
 // a plain grid-stride loop puts neighbouring tiles, which read each other's
-// halos and bins, on different XCDs.  Here the blocks of each XCD take one
+// halos and list segments, on different XCDs.  Here the blocks of each XCD take one
 // contiguous share of the item list instead.
 struct XcdLoop {
   int first, end, step;
-  __device__ __forceinline__ explicit XcdLoop(int n) {
-    const int G = gridDim.x, b = blockIdx.x;
+  __device__ __forceinline__ explicit XcdLoop(int n) : XcdLoop(n, blockIdx.x, gridDim.x) {}
+  // block b of G (b mod 8 its XCD) of a list of n items
+  __device__ __forceinline__ XcdLoop(int n, int b, int G) {
     if (G < 8) {
       first = b;
       end = n;
@@ -342,25 +312,37 @@ static __device__ __forceinline__ void zero_lds_u64(void* p, int n) {
   if ((n & 1) && threadIdx.x == 0) ((long long*)p)[n - 1] = 0;
 }
 
+// The lanes with `has` that share a lane's key: their first lane, their number
+// and the lane's rank among them.  Formed by every active lane at once, so that
+// all groups' atomics can be issued before the first result is waited for.
+struct AggGroup {
+  int leader, count, rank;
+  __device__ __forceinline__ AggGroup(int key, bool has) : leader(__lane_id()), count(0), rank(0) {
+    const int lane = __lane_id();
+    unsigned long long pending = __ballot(has);
+    while (pending) {
+      const int first = __ffsll(pending) - 1;
+      const int k = __shfl(key, first);
+      const unsigned long long match = __ballot(has && key == k) & pending;
+      if ((match >> lane) & 1ull) {
+        leader = first;
+        count = __popcll(match);
+        rank = __popcll(match & ((1ull << lane) - 1ull));
+      }
+      pending &= ~match;
+    }
+  }
+};
+
 // Wavefront-aggregated atomic increment: lanes that target the same counter
 // are served by one atomic from a leader lane.  Returns, for lanes with `has`,
 // a distinct slot (the counter's old value plus the lane's rank among the
 // matching lanes).  Must be called by every lane of the wavefront.
 static __device__ __forceinline__ int agg_atomic_inc(MC_GLOBAL int* counters, int key, bool has) {
-  const int lane = __lane_id();
-  unsigned long long pending = __ballot(has);
-  int slot = 0;
-  while (pending) {
-    const int leader = __ffsll((unsigned long long)pending) - 1;
-    const int lkey = __shfl(key, leader);
-    const unsigned long long match = __ballot(has && key == lkey) & pending;
-    int base = 0;
-    if (lane == leader) base = atomicAdd((int*)(counters + lkey), __popcll(match));
-    base = __shfl(base, leader);
-    if ((match >> lane) & 1ull) slot = base + __popcll(match & ((1ull << lane) - 1ull));
-    pending &= ~match;
-  }
-  return slot;
+  const AggGroup g(key, has);
+  int base = 0;
+  if (has && g.leader == (int)__lane_id()) base = atomicAdd((int*)(counters + key), g.count);
+  return __shfl(base, g.leader) + g.rank;
 }
 
 // Block-wide exclusive scan of one int per thread (NT threads), wave
@@ -394,163 +376,252 @@ static __device__ __forceinline__ int block_scan256(int v, int* s_wave, int* tot
 }
 
 
-// Records of a set of home-tile bins.  Every wavefront streams its share of
-// the records (PER loads in flight per lane) and appends those for which
-// keep(r) holds to its own LDS list (one ballot per record batch); whenever
-// the list reaches a full wavefront of records the wavefront runs body(r) on
-// them and starts the list again with the batch's overflow.  No block barrier
-// is needed until all records are done, body always runs on full wavefronts
-// (except for the last partial one), and lanes holding irrelevant records
-// never idle through it.  body(r) may only use per-lane work and LDS atomics.
-// A bin set as every wavefront holds it, in scalar registers: range j (of
-// NR) covers flat record numbers [pre[j], pre[j + 1]) (pre = 2^31 - 1 past
-// the last range), and flat number f of range j is record f + delta[j].
-template <int NR>
-struct BinSet {
-  int total;
-  int pre[NR];
-  int delta[NR];
+// ---------------------------------------------------------------------------
+// Tile lists (binned worlds; their layout: WorldDev).  A tile's list holds a
+// record of every node its kernels need, once each.  A segment that overflowed
+// its capacity (its count says so), or a world without lists, is read by
+// testing every node instead.
+// ---------------------------------------------------------------------------
+// Class of home cell h (in [0, n)) for the tile [x0, x0 + tw) of a periodic
+// axis: 0 own, 1 near, 2 far, 3 out of reach.
+struct Reach {
+  int near_, before, after;
+  __device__ __forceinline__ explicit Reach(const WorldDev& w) {
+    const bool mk = w.d_marker != nullptr;
+    near_ = near_reach(mk);
+    before = far_reach_before(w.radius, mk);
+    after = far_reach_after(w.radius, mk);
+  }
+  __device__ __forceinline__ int of_cell(int h, int x0, int tw, int n) const {
+    if (h >= x0 && h < x0 + tw) return 0;
+    const int a = h < x0 ? x0 - h : x0 - h + n;                  // cells before / after the tile (1 = next to it)
+    const int b = h >= x0 + tw ? h - (x0 + tw - 1) : h - (x0 + tw - 1) + n;
+    return a <= near_ || b <= near_ ? 1 : (a <= before || b <= after ? 2 : 3);
+  }
 };
 
-static __device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
+// Neighbour q (0..7) of a tile: sides first (-x, +x, -y, +y), then corners.
+static __device__ __forceinline__ constexpr int nb_dx(int q) { return q == 0 ? -1 : q == 1 ? 1 : q < 4 ? 0 : ((q & 1) ? 1 : -1); }
+static __device__ __forceinline__ constexpr int nb_dy(int q) { return q < 2 ? 0 : q == 2 ? -1 : q == 3 ? 1 : (q < 6 ? -1 : 1); }
+// Whether an axis of nt tiles has a neighbour in direction d of its own (two
+// tiles are each other's neighbour once: in direction +1).
+static __device__ __forceinline__ bool nb_exists(int d, int nt) { return d == 0 || nt >= 3 || (nt == 2 && d == 1); }
+static __device__ __forceinline__ int nb_tile(int t, int d, int nt) { return wrap_near(t + d, nt); }
+
+// First record of neighbour q's segments (near, far): strays and own
+// nodes come first, then the sides, then the corners.
+static __device__ __forceinline__ int nb_first(const WorldDev& w, int q) {
+  const int s = w.tl_near_s + w.tl_far_s, c = w.tl_near_c + w.tl_far_c;
+  return w.tl_strays + w.tl_own + (q < 4 ? q * s : 4 * s + (q - 4) * c);
 }
 
-// A bin set in flight: lane i < n of every wavefront holds the first record
-// and the length of range i.  Fetching it only issues loads; committing forms
-// the prefix and moves the set into scalar registers, then synchronises the
-// block.
-struct BinFetch {
-  int n;
-  int b0, len;
+// f(tx, ty, class) for every tile that a node with home cell (hx, hy) reaches:
+// the up to five tiles around its own per axis are tested (a reach of at most
+// 11 cells spans a narrow last tile and the one beyond it).
+template <int TILE, class F>
+static __device__ __forceinline__ void for_reached_tiles(const WorldDev& w, int hx, int hy, F f) {
+  constexpr int sh = TileCfg<TILE>::kShift;
+  const Reach R(w);
+  const int cx = hx >> sh, cy = hy >> sh;
+  const int nx = w.nx, ny = w.ny, ntx = w.ntx, nty = w.nty;
+  const int mx = min(ntx, 5), my = min(nty, 5);
+  for (int j = 0; j < my; ++j) {
+    const int ty = nty <= 5 ? j : wrap_near(cy - 2 + j, nty);
+    const int y0 = ty << sh, ky = R.of_cell(hy, y0, min(TILE, ny - y0), ny);
+    if (ky > 2) continue;
+    for (int i = 0; i < mx; ++i) {
+      const int tx = ntx <= 5 ? i : wrap_near(cx - 2 + i, ntx);
+      const int x0 = tx << sh, kx = R.of_cell(hx, x0, min(TILE, nx - x0), nx);
+      if (kx <= 2) f(tx, ty, max(kx, ky));
+    }
+  }
+}
+
+// A tile's list counts (block-uniform: scalar loads; nothing in a kernel that
+// reads them writes them).
+typedef const __attribute__((address_space(4))) int* ListCounts;
+static __device__ __forceinline__ ListCounts list_counts(const WorldDev& w, int tile) {
+  return (ListCounts)(const int*)w.tl_cnt + (size_t)tile * kListCounts;
+}
+
+// The runs of records that one wavefront of a block takes from a tile's list,
+// all in scalar registers: its share of the strays and own nodes and (SEGS 2)
+// the near and (3) the far nodes of one side and one corner neighbour, shared
+// by the wavefronts that have the same pair.  Alone (SEGS 1), the own nodes go
+// out in rounds of 64, so that one wavefront and not all has the last, short
+// round.  Flat record f is record f + d[j], j the last run with pre[j] <= f.
+// mode 0: as said; 1: a segment overflowed: the two neighbours' own nodes in
+// place of their segments; 2: every node of the world.
+template <int SEGS>
+struct WaveRuns {
+  int mode, total;
+  int p1, p2, p3, p4;                            // pre of runs 1 .. (SEGS 3: 4, else 2)
+  int d0, e1, e2, e3, e4;                        // d of run 0, and what each run adds to the one before
+  // record number of flat record f (clamped by the caller to [0, total))
+  __device__ __forceinline__ int record(int f) const {
+    int x = f + d0;
+    if constexpr (SEGS > 1) x += (f >= p1 ? e1 : 0) + (f >= p2 ? e2 : 0);
+    if constexpr (SEGS == 3) x += (f >= p3 ? e3 : 0) + (f >= p4 ? e4 : 0);
+    return x;
+  }
 };
-
-// The bins holding homes in [lox, hix] x [loy, hiy] (periodic), as runs of
-// consecutive bins (first, end), written to out[kRunStride] and padded with
-// (0, 0).  Bins of one tile row are stored by increasing column, so a run of
-// consecutive columns is one contiguous record range; the column list is a
-// cyclic run, broken at most once where it wraps: at most two runs per row.
-template <int TILE>
-static __device__ void tile_runs(int lox, int hix, int loy, int hiy, int nx, int ny, int ntx, int2* out) {
-  int tx[TileCfg<TILE>::kMaxCols], ty[TileCfg<TILE>::kMaxCols];
-  const int ncx = bins_covering<TILE>(lox, hix, nx, tx);
-  const int ncy = bins_covering<TILE>(loy, hiy, ny, ty);
-  int n = 0;
-  for (int r = 0; r < ncy; ++r) {
-    int c = 0;
-    while (c < ncx) {
-      int m = 1;
-      while (c + m < ncx && tx[c + m] == tx[c + m - 1] + 1) ++m;
-      const int first = bin_at(tx[c], ty[r], ntx);
-      out[n++] = make_int2(first, first + m);
-      c += m;
+// The part of the wavefronts that share n records: number `part` of `of`.
+struct RunPart {
+  int a, n;
+  __device__ __forceinline__ RunPart(int all, int part, int of) : a(all * part / of), n(all * (part + 1) / of - a) {}
+};
+// A neighbour's segments as runs: near nodes, far nodes.
+template <int SEGS>
+static __device__ __forceinline__ void neighbour_runs(const WorldDev& w, int tile, ListCounts c, int mode, int q,
+                                                      int* first, int* n, int* far_first, int* far_n) {
+  *first = *n = *far_first = *far_n = 0;
+  if (!nb_exists(nb_dx(q), w.ntx) || !nb_exists(nb_dy(q), w.nty)) return;   // (nobody writes its counts)
+  if (mode == 0) {
+    *first = nb_first(w, q);
+    *n = c[kCntNear + q];
+    if (SEGS == 3) {
+      *far_first = *first + (q < 4 ? w.tl_near_s : w.tl_near_c);
+      *far_n = c[kCntFar + q];
     }
+  } else {
+    const int ty = tile / w.ntx, tx = tile - ty * w.ntx;
+    const int t = nb_tile(ty, nb_dy(q), w.nty) * w.ntx + nb_tile(tx, nb_dx(q), w.ntx);
+    *n = list_counts(w, t)[kCntOwn];
+    *first = (t - tile) * w.tl_stride + w.tl_strays;
   }
-  for (; n < kRunStride; ++n) out[n] = make_int2(0, 0);
 }
-
-// Fetch of the bin set of tile `tile` (row-major index) for reader `kind`
-// (0 filter, 1 spread) from the world's run table (NR runs).
-template <int NR>
-static __device__ __forceinline__ BinFetch binset_fetch(const WorldDev& w, int tile, int kind) {
-  const int lane = __lane_id();
-  BinFetch f;
-  f.n = NR;
-  f.b0 = 0;
-  f.len = 0;
-  if (lane < NR) {
-    const vi2 run = glbv<const vi2>(w.tile_rng)[((size_t)tile * 2 + kind) * kRunStride + lane];
-    const MC_GLOBAL int* bstart = glb(w.bin_start);
-    f.b0 = bstart[run.x];
-    f.len = bstart[run.y] - f.b0;
-  }
-  return f;
-}
-
-template <int NR>
-static __device__ __forceinline__ BinSet<NR> binset_commit(const BinFetch& f) {
-  const int lane = __lane_id();
-  const int len = lane < f.n ? f.len : 0;
-  int x = len;                                 // inclusive prefix over lanes 0..NR-1
-#pragma unroll
-  for (int off = 1; off < NR; off <<= 1) {
-    const int y = __shfl_up(x, off);
-    if (lane >= off) x += y;
-  }
-  const int excl = x - len;
-  const int pre = lane < f.n ? excl : 0x7fffffff;
-  const int del = f.b0 - excl;
-  BinSet<NR> bs;
-  bs.total = __builtin_amdgcn_readlane(x, NR - 1);
-#pragma unroll
-  for (int j = 0; j < NR; ++j) {
-    bs.pre[j] = __builtin_amdgcn_readlane(pre, j);
-    bs.delta[j] = __builtin_amdgcn_readlane(del, j);
-  }
-  __syncthreads();
-  return bs;
-}
-
-// A list whose every record is needed (the spread lists the filter writes):
-// the NT threads take the records in turn, with no keep test and no compaction.
-template <int NT, int NR, class Body>
-static __device__ __forceinline__ void for_list_records(const MC_GLOBAL vi4* recs, const BinSet<NR>& bs, Body body) {
-  const int total = bs.total, off = bs.delta[0];
-  for (int f = (int)threadIdx.x; f < total; f += NT) {
-    const vi4 r = recs[f + off];
-    body(r);
-  }
-  __syncthreads();
-}
-
-template <int PER, int NT, int NR, class Keep, class Body>
-static __device__ __forceinline__ void for_bin_records(const MC_GLOBAL vi4* recs, const BinSet<NR>& bs, vi4* s_list,
-                                                       Keep keep, Body body) {
-  const int total = bs.total;
-  const int lane = __lane_id();
-  const unsigned long long below = (1ull << lane) - 1ull;
-  vi4* wl = s_list + (threadIdx.x >> 6) * kWaveList;
-  int cnt = 0;                                 // wavefront-uniform list length (< 64)
-  for (int base = 0; base < total; base += PER * NT) {
-    // record indices first, then every load unconditionally (lanes past the
-    // end reload the last record and drop it), so all PER loads are in flight
-    // together instead of each waiting inside its own branch
-    int idx[PER];
-    bool k[PER];
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int f = base + i * NT + (int)threadIdx.x;
-      k[i] = f < total;
-      const int fc = k[i] ? f : total - 1;
-      int d = bs.delta[0];
-#pragma unroll
-      for (int j = 1; j < NR; ++j) d = fc >= bs.pre[j] ? bs.delta[j] : d;
-      idx[i] = fc + d;
-    }
-    vi4 r[PER];
-#pragma unroll
-    for (int i = 0; i < PER; ++i) r[i] = recs[idx[i]];
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const bool kk = k[i] && keep(r[i]);
-      const unsigned long long m = __ballot(kk);
-      const int pos = cnt + __popcll(m & below);
-      if (kk && pos < kWaveList) wl[pos] = r[i];
-      cnt += __popcll(m);
-      if (cnt >= kWaveList) {
-        wave_sync();
-        body(wl[lane]);
-        wave_sync();
-        if (kk && pos >= kWaveList) wl[pos - kWaveList] = r[i];
-        cnt -= kWaveList;
-        wave_sync();
+template <int NT, int SEGS>
+static __device__ __forceinline__ WaveRuns<SEGS> wave_runs(const WorldDev& w, int tile) {
+  constexpr int kWaves = NT / 64, kShare = kWaves / 4;
+  static_assert(kWaves % 4 == 0, "four neighbour pairs");
+  int mode = 2, all = 0, first = 0, fs = 0, ns = 0, ffs = 0, nfs = 0, fc = 0, nc = 0, ffc = 0, nfc = 0;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), pair = kWaves == 4 ? wave : wave & 3,
+            share = kWaves == 4 ? 0 : wave >> 2;
+  if (w.tl_own > 0) {
+    const ListCounts c = list_counts(w, tile);
+    const int flags = c[kCntFlags];
+    if (!(flags & kOverOwn)) {
+      mode = SEGS > 1 && (flags & kOverSegment) ? 1 : 0;
+      const int strays = c[kCntStrays];
+      all = strays + c[kCntOwn];
+      first = w.tl_strays - strays;
+      if constexpr (SEGS > 1) {
+        neighbour_runs<SEGS>(w, tile, c, mode, pair, &fs, &ns, &ffs, &nfs);
+        neighbour_runs<SEGS>(w, tile, c, mode, pair + 4, &fc, &nc, &ffc, &nfc);
       }
     }
   }
-  wave_sync();
-  if (lane < cnt) body(wl[lane]);
-  __syncthreads();
+  if constexpr (SEGS == 1) {
+    const int rounds = (all + 63) >> 6, each = rounds / kWaves, more = rounds % kWaves;
+    const int a = min(64 * (wave * each + min(wave, more)), all), n = min(64 * (each + (wave < more ? 1 : 0)), all - a);
+    return {mode, n, 0, 0, 0, 0, first + a, 0, 0, 0, 0};
+  } else {
+    RunPart r0(all, wave, kWaves);
+    // (with some 20 more scalar instructions the own nodes go out so that the
+    // wavefronts' totals fill as few rounds of 64 as the tile needs, in the
+    // tiles where equal shares may take more: 8 rounds for 256 own nodes, now 6)
+    if (kWaves == 4 && mode == 0 && all > 128 && w.ntx > 2 && w.nty > 2) {
+      const ListCounts c = list_counts(w, tile);
+      const auto pair_n = [&](int q) {
+        return c[kCntNear + q] + c[kCntNear + q + 4] + (SEGS == 3 ? c[kCntFar + q] + c[kCntFar + q + 4] : 0);
+      };
+      const int n0 = pair_n(0), n1 = pair_n(1), n2 = pair_n(2), n3 = pair_n(3);
+      const int rounds = (unsigned)(all + n0 + n1 + n2 + n3 + 63) >> 6, each = rounds >> 2, more = rounds & 3;
+      const int a0 = max(64 * (each + (more > 0 ? 1 : 0)) - n0, 0), a1 = max(64 * (each + (more > 1 ? 1 : 0)) - n1, 0),
+                a2 = max(64 * (each + (more > 2 ? 1 : 0)) - n2, 0);
+      const int b1 = min(a0, all), b2 = min(a0 + a1, all), b3 = min(a0 + a1 + a2, all);
+      r0.a = wave == 0 ? 0 : (wave == 1 ? b1 : (wave == 2 ? b2 : b3));
+      r0.n = (wave == 0 ? b1 : (wave == 1 ? b2 : (wave == 2 ? b3 : all))) - r0.a;
+    }
+    const RunPart r1(ns, share, kShare), r2(nfs, share, kShare), r3(nc, share, kShare),
+        r4(nfc, share, kShare);
+    const int d0 = first + r0.a, p1 = r0.n, d1 = fs + r1.a - p1;
+    if constexpr (SEGS == 3) {
+      const int p2 = p1 + r1.n, d2 = ffs + r2.a - p2, p3 = p2 + r2.n, d3 = fc + r3.a - p3, p4 = p3 + r3.n,
+                d4 = ffc + r4.a - p4;
+      return {mode, p4 + r4.n, p1, p2, p3, p4, d0, d1 - d0, d2 - d1, d3 - d2, d4 - d3};
+    } else {
+      const int p2 = p1 + r1.n, d2 = fc + r3.a - p2;
+      return {mode, p2 + r3.n, p1, p2, 0, 0, d0, d1 - d0, d2 - d1, 0, 0};
+    }
+  }
+}
+
+// The records of a tile's list (SEGS as in WaveRuns) for the NT threads of a
+// block, in any order, PER per thread in flight with the values v[node] (VALS
+// 1) and v[N + node] (2) of their nodes.  The first round is loaded where the
+// object is made, so that its chain of loads (counts, records, values) runs
+// beside what the block does before it needs them: at the sizes where a launch
+// lasts as long as that chain, and where the blocks of a CU go through their
+// phases together.
+template <int NT, int SEGS, int PER, int VALS = 0>
+struct TileRecords {
+  const MC_GLOBAL float* v;
+  WaveRuns<SEGS> L;
+  const MC_GLOBAL vi4* rec;
+  int N, tile;
+  vi4 r[PER];
+  vf2 val[PER];
+  __device__ __forceinline__ vf2 value(int node) const {
+    const vf2 x = {VALS > 0 ? v[node] : 0.f, VALS > 1 ? v[N + node] : 0.f};
+    return x;
+  }
+  __device__ __forceinline__ void load(int base) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i)                 // clamped, so that every load is issued at once
+      r[i] = rec[L.record(min(base + i * 64 + (int)(threadIdx.x & 63), L.total - 1))];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) val[i] = value(r[i].w);
+  }
+  __device__ __forceinline__ TileRecords(const WorldDev& w, int tile, const MC_GLOBAL float* values = nullptr)
+      : v(values), L(wave_runs<NT, SEGS>(w, tile)), rec(glbv<const vi4>(w.tl_rec) + (size_t)tile * w.tl_stride),
+        N(w.n_part), tile(tile) {
+    if (L.mode < 2 && L.total > 0) load(0);
+  }
+  // Whether flat record f counts: a neighbour's own node that has moved to this
+  // tile is one of its strays as well.
+  __device__ __forceinline__ bool counts(const WorldDev& w, int f, const vi4& q) const {
+    if (f >= L.total) return false;
+    if (SEGS == 1 || L.mode == 0 || f < L.p1) return true;
+    return ((q.x >> 16) >> w.tile_shift) * w.ntx + ((q.x & 0xffff) >> w.tile_shift) != tile;
+  }
+  // body(record, value) for each.  body must itself drop the records its window
+  // does not hold (the list may hold more than needed, and where it cannot be
+  // used body gets other nodes too).  No barrier; body may only use per-lane
+  // work and LDS atomics.
+  template <class Body>
+  __device__ __forceinline__ void each(const WorldDev& w, Body body) {
+    if (L.mode < 2) {
+      for (int base = 0; base < L.total; base += PER * 64) {
+        if (base > 0) load(base);
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+          if (counts(w, base + i * 64 + (int)(threadIdx.x & 63), r[i])) body(r[i], val[i]);
+      }
+      return;
+    }
+    const MC_GLOBAL int* cell = glb(w.cell_in);
+    const MC_GLOBAL float* frac = glb(w.frac_in);
+    for (int i = threadIdx.x; i < N; i += NT) {
+      const int hx = wrap_index(cell[i], w.nx), hy = wrap_index(cell[N + i], w.ny);
+      const vi4 q = {hx | (hy << 16), __float_as_int(frac[i]), __float_as_int(frac[N + i]), i};
+      body(q, value(i));
+    }
+  }
+};
+// (what a tile spread goes through)
+template <int TILE, bool SCALAR = false>
+using SpreadNodes = TileRecords<TileCfg<TILE>::kThreads, 2, 2, SCALAR ? 1 : 2>;
+
+// body(record) for the own nodes of the tile [x0, x0 + tw) x [y0, y0 + th).
+template <int NT, class Body>
+static __device__ __forceinline__ void for_own_records(const WorldDev& w, int tile, int x0, int y0,
+                                                       int tw, int th, Body body) {
+  TileRecords<NT, 1, 1> nodes(w, tile);
+  nodes.each(w, [&](const vi4& r, const vf2&) {
+    const int lx = (r.x & 0xffff) - x0, ly = (r.x >> 16) - y0;
+    if (lx >= 0 && lx < tw && ly >= 0 && ly < th) body(r);
+  });
 }
 
 // Node -> grid accumulation over a padded window.  A window of side
@@ -563,7 +634,7 @@ static __device__ __forceinline__ void for_bin_records(const MC_GLOBAL vi4* recs
 //     cells (its support lies past them, and the part that wraps lands in
 //     cells 0..2), so only nodes with d <= need + 2 are kept: their cells
 //     reach at most need + 5;
-//   * otherwise (small grids, n < need + 3) every node of the bins is kept,
+//   * otherwise (small grids, n < need + 3) every node of the list is kept,
 //     its cells reach at most n + 2 < S, and window cells that are the same
 //     grid cell are summed when read.
 // The first three and last three window cells only catch the spill of nodes
@@ -576,45 +647,50 @@ static __device__ __forceinline__ int first_image(int i, int n) {
   return c < n ? c : c % n;
 }
 
-// Tile spread: for every node whose 4x4 support meets the tile [x0, x0+tw) x
-// [y0, y0+th), add scale * W(c - x_i) * (v[i], v[N + i]) to the window
-// accumulators s_x, s_y (64-bit fixed point, side kSpreadSide, origin
-// (x0 - 3, y0 - 3)).  Nodes are read from the home-tile bins of the
-// neighbourhood.  All threads of the block call it; the accumulators must be
-// zeroed (and synchronised) beforehand.  Values whose fixed-point image fits
-// 32 bits (|scale v| < 1/8, as nearly all forces) are converted by one
-// truncating 32-bit conversion; larger ones by the exact 64-bit split.
-
-// Whether a node with home cell (hx, hy) reaches the spread window of the
-// tile at (x0, y0) of size tw x th (the keep rule of tile_spread_vec).  With
-// two-layer markers (a world with marker displacements) a node counts if one
-// of its markers can: the markers' homes lie within one cell of the node's,
-// so the kept homes reach one cell further on every side.
-struct SpreadKeep {
-  int ox, oy, kx, ky, nx, ny;
-  __device__ __forceinline__ SpreadKeep(const WorldDev& w, int x0, int y0, int tw, int th) {
-    const int m = w.d_marker ? 1 : 0;
-    nx = w.nx;
-    ny = w.ny;
-    ox = wrap_index(x0 - 3 - m, nx);
-    oy = wrap_index(y0 - 3 - m, ny);
-    kx = tw + 3 + 2 * m <= nx ? tw + 2 + 2 * m : nx;
-    ky = th + 3 + 2 * m <= ny ? th + 2 + 2 * m : ny;
+// A vector field over the SIDE x SIDE cells from (ox, oy) (periodic) on its way
+// to LDS: every load is in flight once the object is made, store() waits for
+// them.  No barrier.
+template <int NT, int SIDE>
+struct WindowLoads {
+  static constexpr int kCells = SIDE * SIDE, kIt = (kCells + NT - 1) / NT;
+  vf2 v[kIt];
+  __device__ __forceinline__ WindowLoads(const MC_GLOBAL vf2* f, int nx, int ny, int ox, int oy) {
+    const int wx = wrap_index(ox, nx), wy = wrap_index(oy, ny);
+#pragma unroll
+    for (int i = 0; i < kIt; ++i) {
+      const int k = min((int)threadIdx.x + NT * i, kCells - 1);
+      const int r = k / SIDE, c = k - (k / SIDE) * SIDE;
+      v[i] = f[(size_t)wrap_index(wy + r, ny) * nx + wrap_index(wx + c, nx)];
+    }
   }
-  __device__ __forceinline__ bool operator()(const vi4& r) const {
-    return wrap_near((r.x & 0xffff) - 1 - ox, nx) <= kx && wrap_near((r.x >> 16) - 1 - oy, ny) <= ky;
+  __device__ __forceinline__ void store(vf2* st) const {
+#pragma unroll
+    for (int i = 0; i < kIt; ++i) {
+      const int k = (int)threadIdx.x + NT * i;
+      if (k < kCells) st[k] = v[i];
+    }
   }
 };
-
-// The bin set a tile spread reads: homes in [x0 - 3, x0 + tw + 1] x
-// [y0 - 3, y0 + th + 1] (run table kind 1: the homes whose support, or one of
-// whose two-layer markers' supports, meets the tile; one-layer readers keep
-// the narrower range [x0 - 2, x0 + tw] of it by their keep test).
-template <int TILE>
-static __device__ __forceinline__ BinFetch spread_fetch(const WorldDev& w, int x0, int y0) {
-  constexpr int sh = TileCfg<TILE>::kShift;
-  return binset_fetch<TileCfg<TILE>::kRanges>(w, (y0 >> sh) * w.ntx + (x0 >> sh), 1);
+template <int NT, int SIDE>
+static __device__ __forceinline__ void stage_window(const MC_GLOBAL vf2* f, int nx, int ny, int ox, int oy, vf2* st) {
+  WindowLoads<NT, SIDE>(f, nx, ny, ox, oy).store(st);
 }
+
+// Tile spread: for every node whose 4x4 support meets the needed cells
+// [x0 - LO, x0 + tw + HI) x [y0 - LO, y0 + th + HI) of the tile [x0, x0 + tw) x
+// [y0, y0 + th), add scale * W(c - x_i) * (v[i], v[N + i]) to the window
+// accumulators s_x, s_y (64-bit fixed point, side TILE + LO + HI + 6, origin
+// (x0 - LO - 3, y0 - LO - 3)).  Nodes are read from the tile's own and near
+// lists.  All threads of the block call it; the accumulators must be zeroed
+// (and synchronised) beforehand, and the caller synchronises after it.
+// Values whose fixed-point image fits 32 bits (|scale v| < 1/8, as nearly all
+// forces) are converted by one truncating 32-bit conversion; larger ones by
+// the exact 64-bit split.
+template <int TILE, int LO = 0, int HI = 0>
+struct SpreadWin {
+  static constexpr int kSide = TILE + LO + HI + 6, kCells = kSide * kSide;
+  static constexpr int kGSide = kSide + 2, kGCells = kGSide * kGSide;   // gradient of a two-layer world
+};
 
 // One point's 4x4 contribution W * (Vx, Vy) to two 64-bit fixed-point LDS
 // windows of row length SIDE at the point's support origin (px, py).
@@ -654,32 +730,24 @@ static __device__ __forceinline__ void spread_point(long long* sx, long long* sy
 // support, read from s_g, the gradient staged over the same window; the home
 // tile of a node (the one tile holding its home cell) also writes that total
 // to w.fel.  The gradient sum runs in the same order as the repulsion gather
-// of the node kernels, so the forces are the same.  With LIST, `bins` names
-// one range of records that the tile needs, every one of them (its spread
-// list), so they skip the keep test.  SCALAR spreads scale * v[i] alone into
-// s_x (s_y is not touched and may be null).
-template <int TILE, bool REP, bool LIST = false, bool SCALAR = false>
-static __device__ void tile_spread_vec(const WorldDev& w, int x0, int y0, int tw, int th,
-                                       const MC_GLOBAL float* v, float scale, long long* s_x,
-                                       long long* s_y, vi4* s_list, const MC_GLOBAL vi4* recs,
-                                       const BinFetch& bins, const vf2* s_g) {
-  using C = TileCfg<TILE>;
-  constexpr int kSpreadSide = C::kSpreadSide;
+// of the node kernels, so the forces are the same.  SCALAR spreads
+// scale * v[i] alone into s_x (s_y is not touched and may be null).
+template <int TILE, bool REP, bool SCALAR = false, int LO = 0, int HI = 0>
+static __device__ __forceinline__ void tile_spread_vec(const WorldDev& w, SpreadNodes<TILE, SCALAR>& nodes, int x0,
+                                                       int y0, int tw, int th, float scale,
+                                                       long long* s_x, long long* s_y, const vf2* s_g) {
+  constexpr int kSide = SpreadWin<TILE, LO, HI>::kSide;
   const int nx = w.nx, ny = w.ny, N = w.n_part;
-  const auto bs = binset_commit<C::kRanges>(bins);
-  const int ox = wrap_index(x0 - 3, nx), oy = wrap_index(y0 - 3, ny);
-  const int keep_x = tw + 3 <= nx ? tw + 2 : nx;     // largest kept home offset
-  const int keep_y = th + 3 <= ny ? th + 2 : ny;
+  const int ox = wrap_index(x0 - LO - 3, nx), oy = wrap_index(y0 - LO - 3, ny);
+  const int nw = tw + LO + HI, nh = th + LO + HI;
+  const int keep_x = nw + 3 <= nx ? nw + 2 : nx;     // largest kept home offset
+  const int keep_y = nh + 3 <= ny ? nh + 2 : ny;
   const float kr = w.k_rep;
   MC_GLOBAL float* ftot = glb(w.fel);
-  const auto keep = [&](const vi4& r) {
+  nodes.each(w, [&](const vi4& r, const vf2& v) {
     const int dx = wrap_near((r.x & 0xffff) - 1 - ox, nx);
     const int dy = wrap_near((r.x >> 16) - 1 - oy, ny);
-    return dx <= keep_x && dy <= keep_y;
-  };
-  const auto body = [&](const vi4& r) {
-    const int dx = wrap_near((r.x & 0xffff) - 1 - ox, nx);
-    const int dy = wrap_near((r.x >> 16) - 1 - oy, ny);
+    if (dx > keep_x || dy > keep_y) return;
     float wx[4], wy[4];
     peskin4(__int_as_float(r.y), wx);
     peskin4(__int_as_float(r.z), wy);
@@ -688,7 +756,7 @@ static __device__ void tile_spread_vec(const WorldDev& w, int x0, int y0, int tw
       float gx = 0.f, gy = 0.f;
 #pragma unroll
       for (int b = 0; b < 4; ++b) {
-        const vf2* row = s_g + (dy + b) * kSpreadSide + dx;
+        const vf2* row = s_g + (dy + b) * kSide + dx;
         float ax = 0.f, ay = 0.f;
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
@@ -699,60 +767,52 @@ static __device__ void tile_spread_vec(const WorldDev& w, int x0, int y0, int tw
         gx += wy[b] * ax;
         gy += wy[b] * ay;
       }
-      Vx = v[r.w] - kr * gx;
-      Vy = v[N + r.w] - kr * gy;
+      Vx = v.x - kr * gx;
+      Vy = v.y - kr * gy;
       const int hx = r.x & 0xffff, hy = r.x >> 16;
       if (hx >= x0 && hx < x0 + tw && hy >= y0 && hy < y0 + th) {
         ftot[r.w] = Vx;
         ftot[N + r.w] = Vy;
       }
     } else {
-      Vx = scale * v[r.w];
-      Vy = SCALAR ? 0.f : scale * v[N + r.w];
+      Vx = scale * v.x;
+      Vy = SCALAR ? 0.f : scale * v.y;
     }
-    spread_point<kSpreadSide, SCALAR>(s_x + dy * kSpreadSide + dx, s_y + dy * kSpreadSide + dx, wx, wy, Vx, Vy);
-  };
-  if constexpr (LIST) for_list_records<C::kThreads>(recs, bs, body);
-  else for_bin_records<4, C::kThreads>(recs, bs, s_list, keep, body);
+    spread_point<kSide, SCALAR>(s_x + dy * kSide + dx, s_y + dy * kSide + dx, wx, wy, Vx, Vy);
+  });
 }
 
 // The tile spread of a two-layer world: each node acts through its markers
 // X = x +- d (d from w.d_marker), each taking half of the node's value.  The
 // node's value is formed as in tile_spread_vec, with the gradient s_g staged
-// over a window one cell wider on every side (side kSpreadSide + 2, origin
-// (x0 - 4, y0 - 4)), since a node whose marker reaches the tile can lie one
-// cell further out.  The accumulators keep side kSpreadSide and origin
-// (x0 - 3, y0 - 3): a marker goes in by the one-layer keep rule applied to
-// its own home cell, and the others cannot touch the tile.
-template <int TILE, bool REP, bool LIST = false>
-static __device__ void tile_spread_markers(const WorldDev& w, int x0, int y0, int tw, int th,
-                                           const MC_GLOBAL float* v, float scale, long long* s_x,
-                                           long long* s_y, vi4* s_list, const MC_GLOBAL vi4* recs,
-                                           const BinFetch& bins, const vf2* s_g) {
-  using C = TileCfg<TILE>;
-  constexpr int kSpreadSide = C::kSpreadSide, kGSide = C::kSpreadSide + 2;
+// over a window one cell wider on every side (side kSide + 2, origin
+// (x0 - LO - 4, y0 - LO - 4)), since a node whose marker reaches the needed
+// cells can lie one cell further out.  The accumulators keep their side and
+// origin: a marker goes in by the one-layer keep rule applied to its own home
+// cell, and the others cannot touch the needed cells.
+template <int TILE, bool REP, int LO = 0, int HI = 0>
+static __device__ __forceinline__ void tile_spread_markers(const WorldDev& w, SpreadNodes<TILE>& nodes, int x0, int y0,
+                                                           int tw, int th, float scale, long long* s_x, long long* s_y,
+                                                           const vf2* s_g) {
+  constexpr int kSide = SpreadWin<TILE, LO, HI>::kSide, kGSide = SpreadWin<TILE, LO, HI>::kGSide;
   const int nx = w.nx, ny = w.ny, N = w.n_part;
-  const auto bs = binset_commit<C::kRanges>(bins);
-  const int ox = wrap_index(x0 - 3, nx), oy = wrap_index(y0 - 3, ny);
-  const int gox = wrap_index(x0 - 4, nx), goy = wrap_index(y0 - 4, ny);
-  const int keep_x = tw + 3 <= nx ? tw + 2 : nx;     // markers: largest kept home offset
-  const int keep_y = th + 3 <= ny ? th + 2 : ny;
-  const int nkeep_x = tw + 5 <= nx ? tw + 4 : nx;    // nodes: one cell more on each side
-  const int nkeep_y = th + 5 <= ny ? th + 4 : ny;
+  const int ox = wrap_index(x0 - LO - 3, nx), oy = wrap_index(y0 - LO - 3, ny);
+  const int gox = wrap_index(x0 - LO - 4, nx), goy = wrap_index(y0 - LO - 4, ny);
+  const int nw = tw + LO + HI, nh = th + LO + HI;
+  const int keep_x = nw + 3 <= nx ? nw + 2 : nx;     // markers: largest kept home offset
+  const int keep_y = nh + 3 <= ny ? nh + 2 : ny;
+  const int nkeep_x = nw + 5 <= nx ? nw + 4 : nx;    // nodes: one cell more on each side
+  const int nkeep_y = nh + 5 <= ny ? nh + 4 : ny;
   const float kr = w.k_rep;
   MC_GLOBAL float* ftot = glb(w.fel);
   const MC_GLOBAL float* dm = glb(w.d_marker);
-  const auto keep = [&](const vi4& r) {
-    const int dx = wrap_near((r.x & 0xffff) - 1 - gox, nx);
-    const int dy = wrap_near((r.x >> 16) - 1 - goy, ny);
-    return dx <= nkeep_x && dy <= nkeep_y;
-  };
-  const auto body = [&](const vi4& r) {
+  nodes.each(w, [&](const vi4& r, const vf2& v) {
     const int hx = r.x & 0xffff, hy = r.x >> 16;
+    const int dx = wrap_near(hx - 1 - gox, nx), dy = wrap_near(hy - 1 - goy, ny);
+    if (dx > nkeep_x || dy > nkeep_y) return;
     const float fx = __int_as_float(r.y), fy = __int_as_float(r.z);
     float Vx, Vy;
     if constexpr (REP) {
-      const int dx = wrap_near(hx - 1 - gox, nx), dy = wrap_near(hy - 1 - goy, ny);
       float wx[4], wy[4];
       peskin4(fx, wx);
       peskin4(fy, wy);
@@ -770,15 +830,15 @@ static __device__ void tile_spread_markers(const WorldDev& w, int x0, int y0, in
         gx += wy[b] * ax;
         gy += wy[b] * ay;
       }
-      Vx = v[r.w] - kr * gx;
-      Vy = v[N + r.w] - kr * gy;
+      Vx = v.x - kr * gx;
+      Vy = v.y - kr * gy;
       if (hx >= x0 && hx < x0 + tw && hy >= y0 && hy < y0 + th) {
         ftot[r.w] = Vx;
         ftot[N + r.w] = Vy;
       }
     } else {
-      Vx = scale * v[r.w];
-      Vy = scale * v[N + r.w];
+      Vx = scale * v.x;
+      Vy = scale * v.y;
     }
     const float ddx = dm[r.w], ddy = dm[N + r.w];
     const float hVx = 0.5f * Vx, hVy = 0.5f * Vy;
@@ -794,23 +854,20 @@ static __device__ void tile_spread_markers(const WorldDev& w, int x0, int y0, in
         float wx[4], wy[4];
         peskin4(mx, wx);
         peskin4(my, wy);
-        spread_point<kSpreadSide>(s_x + mdy * kSpreadSide + mdx, s_y + mdy * kSpreadSide + mdx, wx, wy, hVx, hVy);
+        spread_point<kSide>(s_x + mdy * kSide + mdx, s_y + mdy * kSide + mdx, wx, wy, hVx, hVy);
       }
     }
-  };
-  if constexpr (LIST) for_list_records<C::kThreads>(recs, bs, body);
-  else for_bin_records<4, C::kThreads>(recs, bs, s_list, keep, body);
+  });
 }
 
-// The accumulated value of tile cell (lx, ly) of a spread window.
-template <int TILE>
-static __device__ __forceinline__ long long spread_cell(const long long* s, int lx, int ly, int nx, int ny) {
-  constexpr int kSpreadSide = TileCfg<TILE>::kSpreadSide;
-  const int cx0 = first_image(lx, nx), cy0 = first_image(ly, ny);
-  if (cx0 + nx >= kSpreadSide && cy0 + ny >= kSpreadSide) return s[cy0 * kSpreadSide + cx0];
+// The accumulated value of needed cell (i, j) of a spread window of side SIDE.
+template <int SIDE>
+static __device__ __forceinline__ long long spread_cell(const long long* s, int i, int j, int nx, int ny) {
+  const int cx0 = first_image(i, nx), cy0 = first_image(j, ny);
+  if (cx0 + nx >= SIDE && cy0 + ny >= SIDE) return s[cy0 * SIDE + cx0];
   long long acc = 0;
-  for (int cy = cy0; cy < kSpreadSide; cy += ny)
-    for (int cx = cx0; cx < kSpreadSide; cx += nx) acc += s[cy * kSpreadSide + cx];
+  for (int cy = cy0; cy < SIDE; cy += ny)
+    for (int cx = cx0; cx < SIDE; cx += nx) acc += s[cy * SIDE + cx];
   return acc;
 }
 

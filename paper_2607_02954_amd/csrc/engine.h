@@ -32,7 +32,7 @@ __device__ __forceinline__ MC_GLOBAL V* glbv(T* p) {
   return (MC_GLOBAL V*)p;
 }
 
-// Square grid tiles of the tile kernels (filter, spread, integrate; node bins
+// Square grid tiles of the tile kernels (filter, spread, integrate; node lists
 // of the binned transfer): side 16, 32 or 64 cells, chosen per world.  Each
 // side is a family of kernel instances; a table of worlds launches the
 // families it holds.
@@ -40,15 +40,28 @@ constexpr int kTileFamilies = 3;
 __host__ __device__ constexpr int tile_side_of_family(int f) { return 16 << f; }
 __host__ __device__ constexpr int tile_family_of_side(int side) { return side == 16 ? 0 : side == 64 ? 2 : 1; }
 __host__ __device__ constexpr int tile_shift_of_side(int side) { return side == 16 ? 4 : side == 64 ? 6 : 5; }
-// records a tile's spread list holds (else it reads the bins): one per cell
-__host__ __device__ constexpr int spread_cap_of_side(int side) { return side * side; }
-constexpr int kRunStride = 8;        // bin runs stored per tile and reader
+// How far (cells) a home lies outside a tile, before and after it, at most for
+// the tile's list: the near nodes (what its spread, its fluid halo and their
+// two-layer markers can need) and the far ones (what else its filter of radius
+// R can need: supports that meet the tile, its ring and R cells of filter).
+__host__ __device__ constexpr int near_reach(bool markers) { return markers ? 5 : 3; }
+__host__ __device__ constexpr int far_reach_before(int R, bool markers) { return R + 3 > near_reach(markers) ? R + 3 : near_reach(markers); }
+__host__ __device__ constexpr int far_reach_after(int R, bool markers) { return R + 2 > near_reach(markers) ? R + 2 : near_reach(markers); }
+// Ints of a tile's list counts: the nodes its block integrated, the strays (those
+// that came in from another tile, and those that reach it from beyond its
+// neighbours), the near and the far nodes of its eight neighbours, and the
+// overflow flags.
+constexpr int kListCounts = 20;      // (19 used)
+constexpr int kCntOwn = 0, kCntStrays = 1, kCntNear = 2, kCntFar = 10, kCntFlags = 18;
+constexpr int kOverSegment = 1;      // a neighbour's near or far nodes overflowed: read the neighbours' own nodes
+constexpr int kOverOwn = 2;          // its own nodes, a neighbour's or strays did: test every node
+constexpr int kSmallMove = 4;        // cells beyond its tile up to which a node reaches no farther than the neighbours
 constexpr int kCellsPerItem = 256;   // contiguous cells per fluid work item
 constexpr int kMaxRadius = 8;        // largest Gaussian truncation radius
 
 // Particle -> grid transfer modes (per world).
 enum TransferMode : int {
-  kBinned = 0,   // nodes binned by home tile; sums formed in LDS, tiles written whole
+  kBinned = 0,   // node lists per tile; sums formed in LDS, tiles written whole
   kSorted = 1,   // counting sort by home cell; fixed-order segmented sums
   kDirect = 2    // global float atomics into HBM accumulators
 };
@@ -56,8 +69,8 @@ constexpr int kMaxFilament = 1024;   // longest filament a node pack can hold
 
 // Sticky per-world flag bits.
 constexpr unsigned kFlagUnstable = 1u;   // NaN or |u| > u_max
-constexpr unsigned kFlagBins = 2u;       // a node found its tile bin full (positions changed
-                                         // without a bin pre-pass); the record was dropped
+constexpr unsigned kFlagBins = 2u;       // a node was not where its tile list said (positions changed
+                                         // without a list pre-pass)
 
 // Per-world control word, double-buffered by step parity: kernels of a step
 // read ctl_src; the fluid kernel writes the next step's values to ctl_dst.
@@ -117,18 +130,24 @@ struct WorldDev {
   int* perm;                            // [N] node index of each sorted slot
   float4* rec;                          // [N] sorted records (frac x, frac y, Fx, Fy)
   int* part;                            // scan partials
-  // tile bins (binned mode): one record per node, grouped by home tile
-  int* bin_cnt;                         // [ntx*nty] nodes per tile (zeroed after use)
-  int* bin_fill;                        // [ntx*nty] fill cursors (zeroed after use)
-  int* bin_start;                       // [ntx*nty + 1] exclusive prefix of bin_cnt
-  int* bin_start_next;                  // where the scan after integrate puts the next step's
-                                        // starts (bin_start itself, except on the adjoint tape)
-  int4* bin_rec;                        // [N] record: (x | y << 16 home cell, frac x, frac y, node)
-  int4* sp_rec;                         // [ntx*nty][side^2] the records each tile's spread reads,
-  int* sp_cnt;                          // [ntx*nty] and their number: both written by the filter
-  const int2* tile_rng;                 // [ntx*nty][2][kRunStride] bin runs (first, end) that the
-                                        // filter (0) and the spread (1) of each tile read; unused
-                                        // runs (0, 0)
+  // tile lists (binned mode): the nodes each tile's kernels need, as records
+  // (x | y << 16 home cell, frac x, frac y, node).  The lists of a step's
+  // starting positions, and those its integration makes for the next step:
+  // the block that integrated a tile's nodes writes them all to the tile's own
+  // segment, and those that a neighbour needs to its segments in that
+  // neighbour's list, the near and the far ones.  No slot of these is shared
+  // between blocks; a node that left for another tile, and one that reaches a
+  // tile beyond the neighbours, goes to that tile's strays by an atomic.
+  // (Strays fill their segment from its end: with the own nodes they are one
+  // run.)
+  int4* tl_rec;                         // [ntx*nty][tl_stride]
+  int* tl_cnt;                          // [ntx*nty][kListCounts]
+  int4* tl_rec_next;
+  int* tl_cnt_next;
+  int tl_own, tl_strays;                // segment capacities; tl_own 0: no lists, the tiles test every node
+  int tl_near_s, tl_far_s, tl_near_c, tl_far_c;   // of a side neighbour and of a corner neighbour
+  int tl_stride;
+  int keep_force;                       // the fused step kernel writes the grid force too (the adjoint's tape)
 };
 
 // A node pack: whole filaments with at most `pack` nodes, run by one block.
@@ -155,6 +174,8 @@ struct Grid {
   int any_sorted, any_binned, any_node;      // which transfer families the table holds
                                              // (any_node: a world not in binned mode)
   int max_radius;                            // largest Gaussian radius of any world (LDS sizing)
+  int any_lists;                             // a binned world keeps tile lists
+  int fused;                                 // S4 - S7 run as one tile kernel (few tiles, all worlds binned without MDF)
   int any_energy;                            // a world has an energy field
   int any_markers;                           // a world broadcasts two-layer markers
   int mk_only;                               // every world of the tile kernels has markers (the
@@ -212,18 +233,21 @@ void launch_adjoint_debug(const WorldDev* W, const Tables& T, const Grid& G, int
 // Forward step launchers (kernels.hip).  `W` points at a device array of
 // world descriptors.
 void launch_elastic(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);
-void launch_bin_prepass(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);
+// elastic force and filter: one launch where every world is binned
+void launch_prepare(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);
+void launch_list_prepass(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);
 void launch_sort(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);
 void launch_filter(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);
 void launch_repulse(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);
 void launch_spread(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);
+void launch_fluid_tiles(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);   // S4 - S7 (Grid::fused)
 void launch_lbm(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);
 // the same launch with the dispatch's own start and end timestamps in two events
 void launch_lbm_timed(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s, hipEvent_t start,
                       hipEvent_t stop);
 void launch_integrate(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);
-// two-layer markers (before the force spread) and MDF corrections of the grid
-// force (after it, before the fluid update); direct-transfer worlds
+// two-layer markers alone (launch_elastic and launch_prepare form them too), and
+// the MDF corrections of the grid force (after the spread, before the fluid update)
 void launch_markers(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);
 void launch_mdf(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);
 // energy field: sensing and collection at the step's starting positions
@@ -232,8 +256,6 @@ void launch_energy(const WorldDev* W, const Tables& T, const Grid& G, hipStream_
 // add Gaussian packets to a field
 void launch_energy_packets(int nx, int ny, int n_packets, const float* centres, const float* amps,
                            const float* widths, float* field, hipStream_t s);
-// set-up: the bin runs of every tile (side `tile`) of an nx x ny world of Gaussian radius R
-void launch_tile_ranges(int nx, int ny, int R, int tile, int2* out, hipStream_t s);
 void launch_set_ctl(Ctl* c, long long t, int remaining, hipStream_t s);
 
 // Folding objective (loss.hip): Gaussian-splatted node density on a W x H

@@ -1,26 +1,24 @@
 // Forward kernels of the filament-fluid step for gfx950 (CDNA4).
 //
-// Step order (one launch per sub-step, all worlds of a table at once):
-//   k_elastic     S0 actuation + S1 PBD Cosserat projection (Eqs. 1-4) -> node
-//                 elastic force; writes each node's record into its
-//                 home-tile bin (binned transfer)
-//   k_filter      S2 deposit + S3 separable circular Gaussian filter on a
-//                 32x32 tile with an (R+1)-cell halo, all in LDS; writes the
-//                 central difference G = D s~ of the filtered density
+// Step order (all worlds of a table at once):
+//   k_prepare     binned worlds: S0 actuation + S1 PBD Cosserat projection
+//                 (Eqs. 1-4) -> node elastic force, beside S2 deposit + S3
+//                 separable circular Gaussian filter on a tile with an
+//                 (R+1)-cell halo, all in LDS, which writes the central
+//                 difference G = D s~ of the filtered density
+//                 (k_elastic and k_filter: the two alone)
 //   k_repulse     S4 repulsion -k_rep sum W G -> total node force (sorted
 //                 and direct transfers)
-//   k_spread      S5 force spread onto a 32x32 tile, summed in LDS; for the
+//   k_spread      S5 force spread onto a tile, summed in LDS; for the
 //                 binned transfer it also forms S4 for the nodes it spreads
 //   k_lbm         S6 D2Q9 TRT/Guo collision and push streaming over
 //                 contiguous cells; exports u
-//   k_integrate   S7 gather u at the nodes and move them; counts the nodes
-//                 of every home tile at the new positions (binned transfer)
-//   k_bin_scan    per-world prefix of those counts: the bin starts of the
-//                 next step (binned transfer)
+//   k_integrate   S7 gather u at the nodes and move them; appends every node
+//                 to the tile lists of the next step (binned transfer)
 //
 // Particle -> grid transfer has three modes, chosen per world:
-//   binned  nodes are binned by the 32x32 tile of their home cell; each tile
-//           reads the bins of its neighbourhood and sums the contributions in
+//   binned  every grid tile has a list of the nodes it needs (its own and those
+//           around it) and sums their contributions in
 //           LDS as 64-bit fixed point (integer adds: order-independent, so
 //           results are bitwise reproducible, and on this chip integer LDS
 //           atomics are far faster than float ones), then writes every cell
@@ -36,6 +34,8 @@
 // physics needs (edge vectors, kernel offsets) are formed from small numbers.
 #include <hip/hip_ext.h>
 
+#include <algorithm>
+
 #include "device_util.h"
 
 namespace mc {
@@ -46,6 +46,21 @@ namespace mc {
 // node's record in its home-tile bin (binned), home-cell key and rank
 // (sorted) or the density deposit with global atomics (direct).
 // ---------------------------------------------------------------------------
+// Two-layer marker displacement of node gi (markers at x +- d): offset times
+// the unit normal of the tangent x_b - x_a, a and b its neighbours (or the node
+// itself at a chain end; zero for a lone node).
+static __device__ __forceinline__ void marker_displacement(const WorldDev& w, int gi, int a, int b) {
+  const int N = w.n_part;
+  const MC_GLOBAL int* cell = glb(w.cell_in);
+  const MC_GLOBAL float* frac = glb(w.frac_in);
+  const float tx = (float)(cell[b] - cell[a]) + (frac[b] - frac[a]);
+  const float ty = (float)(cell[N + b] - cell[N + a]) + (frac[N + b] - frac[N + a]);
+  const float len = sqrtf(tx * tx + ty * ty);
+  const float sc = len > 0.f ? w.marker_offset / len : 0.f;
+  glb(w.d_marker)[gi] = -ty * sc;
+  glb(w.d_marker)[N + gi] = tx * sc;
+}
+
 // GEN: worlds may pass closed-loop flags and per-edge stiffness arrays, BR
 // (with GEN) branches as well; the plain variant serves open chains with the
 // world's scalar stiffnesses.
@@ -57,22 +72,26 @@ namespace mc {
 // those at the first nodes (bending), and the attachment edges (position).
 // A node carries at most one attachment, so each of those phases touches
 // every angle and node once at most.
-template <int PACK, bool GEN, bool BR>
-__global__ __launch_bounds__(PACK) void k_elastic(const WorldDev* __restrict__ W, Tables T) {
-  static_assert(GEN || !BR, "branches take the general variant");
-  __shared__ float s_th[PACK];
-  __shared__ float s_dx[PACK];
-  __shared__ float s_dy[PACK];
-  __shared__ float s_ta[BR ? PACK : 1];
-  __shared__ int s_off[PACK + 1];
+template <int PACK, bool BR>
+struct ElasticLds {
+  float th[PACK];
+  float dx[PACK];
+  float dy[PACK];
+  float ta[BR ? PACK : 1];
+  int off[PACK + 1];
+};
 
-  const int npk = *T.n_packs;
+template <int PACK, bool GEN, bool BR>
+static __device__ __forceinline__ void elastic_pack(const WorldDev& w, const Pack& pk, const Ctl& ctl,
+                                                    ElasticLds<PACK, BR>& lds) {
+  static_assert(GEN || !BR, "branches take the general variant");
+  float* s_th = lds.th;
+  float* s_dx = lds.dx;
+  float* s_dy = lds.dy;
+  float* s_ta = lds.ta;
+  int* s_off = lds.off;
   const int li = threadIdx.x;
-  for (int it = blockIdx.x; it < npk; it += gridDim.x) {
-    const Pack pk = T.packs[it];
-    const WorldDev& w = W[pk.world];
-    const Ctl ctl = *w.ctl_src;
-    if (ctl.remaining <= 0) continue;           // block-uniform
+  {
     const int N = w.n_part, nx = w.nx, ny = w.ny, mode = w.mode;
     const MC_GLOBAL int* cell = glb(w.cell_in);
     const MC_GLOBAL float* frac = glb(w.frac_in);
@@ -279,26 +298,18 @@ __global__ __launch_bounds__(PACK) void k_elastic(const WorldDev* __restrict__ W
       fel[gi] = w.k_el * s_dx[li];
       fel[N + gi] = w.k_el * s_dy[li];
     }
-    if (mode == kBinned) {
-      // this node's record in its home-tile bin (bins sized by the counts
-      // of these positions: the previous step's integrate or the pre-pass)
-      const int tile = bin_of(bx, by, w.ntx, w.tile_shift);
-      const int slot = agg_atomic_inc(glb(w.bin_fill), tile, active);
+    if (w.d_marker) {                            // block-uniform: two-layer markers of the pack
+      const int before = k > 0 ? li - 1 : (ring ? o + n - 1 : li);
+      const int after = k < n - 1 ? li + 1 : (ring ? o : li);
+      if (active) marker_displacement(w, gi, pk.node_begin + before, pk.node_begin + after);
+    }
+    if (mode == kSorted) {
       if (active) {
-        const MC_GLOBAL int* bstart = glb(w.bin_start);
-        const int e = bstart[tile] + slot;
-        if (e < bstart[tile + 1]) {
-          const vi4 rec = {bx | (by << 16), __float_as_int(fx), __float_as_int(fy), gi};
-          glbv<vi4>(w.bin_rec)[e] = rec;
-        } else {
-          atomicOr((unsigned*)glb(w.flags), kFlagBins);
-        }
+        const int key = by * nx + bx;
+        glb(w.key)[gi] = key;
+        glb(w.rank)[gi] = atomicAdd((int*)(glb(w.cnt) + key), 1);
       }
-    } else if (active && mode == kSorted) {
-      const int key = by * nx + bx;
-      glb(w.key)[gi] = key;
-      glb(w.rank)[gi] = atomicAdd((int*)(glb(w.cnt) + key), 1);
-    } else if (active) {
+    } else if (active && mode == kDirect) {
       float wx[4], wy[4];
       peskin4(fx, wx);
       peskin4(fy, wy);
@@ -312,100 +323,268 @@ __global__ __launch_bounds__(PACK) void k_elastic(const WorldDev* __restrict__ W
         for (int a = 0; a < 4; ++a) unsafeAtomicAdd((float*)(row + ix[a]), wx[a] * wy[b]);
       }
     }
-    __syncthreads();
   }
 }
 
-// ---------------------------------------------------------------------------
-// Binned transfer: per-world exclusive scan of the home-tile counts; every
-// node then writes one record (home cell, fractions, index) into its bin.
-// ---------------------------------------------------------------------------
-// next: write the starts for the next step's bins (bin_start_next; after
-// integrate) rather than for the current positions (bin_start; pre-pass).
-// Every node has exactly one record, so the counts must add up to the
-// world's node count: the starts are clamped to it (no bin range can leave
-// the record buffer) and a mismatch raises kFlagBins.
-__global__ __launch_bounds__(1024) void k_bin_scan(const WorldDev* __restrict__ W, Tables T, int next) {
-  // every thread sums 4 consecutive bins (one 16-byte load), the wavefronts
-  // scan those sums with shuffles, one exchange of the 16 wavefront totals;
-  // a round covers 4096 bins
-  __shared__ int s_tot[16];
-  const int nw = *T.n_worlds;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  for (int it = blockIdx.x; it < nw; it += gridDim.x) {
-    const WorldDev& w = W[T.worlds[it].x];
-    if (w.mode != kBinned || w.ctl_src->remaining <= 0) continue;
-    MC_GLOBAL int* cnt = glb(w.bin_cnt);
-    MC_GLOBAL int* fill = glb(w.bin_fill);
-    MC_GLOBAL int* start = glb(next ? w.bin_start_next : w.bin_start);
-    const int nt = w.ntx * w.nty;               // bins (one per tile)
-    const int N = w.n_part;
-    int carry = 0;
-    for (int c0 = 0; c0 < nt; c0 += 4096) {
-      const int i0 = c0 + 4 * tid;              // a multiple of 4: 16-byte aligned
-      const bool whole = i0 + 3 < nt;
-      vi4 v = {0, 0, 0, 0};
-      if (whole) {
-        v = *(const MC_GLOBAL vi4*)(cnt + i0);
-      } else {
-        if (i0 < nt) v.x = cnt[i0];
-        if (i0 + 1 < nt) v.y = cnt[i0 + 1];
-        if (i0 + 2 < nt) v.z = cnt[i0 + 2];
-      }
-      const int sum = v.x + v.y + v.z + v.w;
-      int x = sum;
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const int y = __shfl_up(x, off);
-        if (lane >= off) x += y;
-      }
-      if (lane == 63) s_tot[wv] = x;
-      __syncthreads();
-      int before = carry, all = 0;
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int t = s_tot[j];
-        before += j < wv ? t : 0;
-        all += t;
-      }
-      __syncthreads();
-      const int e = before + x - sum;           // start of bin i0
-      const vi4 st = {min(e, N), min(e + v.x, N), min(e + v.x + v.y, N), min(e + v.x + v.y + v.z, N)};
-      const vi4 zero = {0, 0, 0, 0};
-      if (whole) {
-        *(MC_GLOBAL vi4*)(start + i0) = st;
-        *(MC_GLOBAL vi4*)(cnt + i0) = zero;
-        *(MC_GLOBAL vi4*)(fill + i0) = zero;
-      } else {
-        if (i0 < nt) { start[i0] = st.x; cnt[i0] = 0; fill[i0] = 0; }
-        if (i0 + 1 < nt) { start[i0 + 1] = st.y; cnt[i0 + 1] = 0; fill[i0 + 1] = 0; }
-        if (i0 + 2 < nt) { start[i0 + 2] = st.z; cnt[i0 + 2] = 0; fill[i0 + 2] = 0; }
-      }
-      carry += all;
-    }
-    if (tid == 0) {
-      start[nt] = min(carry, N);
-      if (carry != N) atomicOr((unsigned*)glb(w.flags), kFlagBins);
-    }
-  }
-}
-
-// Pre-pass: tile-bin counts of the current positions (a rollout's first step
-// needs them; later steps get them from the previous step's integrate).
-template <int PACK>
-__global__ __launch_bounds__(PACK) void k_bin_count(const WorldDev* __restrict__ W, Tables T) {
+template <int PACK, bool GEN, bool BR>
+__global__ __launch_bounds__(PACK) void k_elastic(const WorldDev* __restrict__ W, Tables T) {
+  __shared__ ElasticLds<PACK, BR> lds;
   const int npk = *T.n_packs;
   for (int it = blockIdx.x; it < npk; it += gridDim.x) {
     const Pack pk = T.packs[it];
     const WorldDev& w = W[pk.world];
-    if (w.mode != kBinned || w.ctl_src->remaining <= 0) continue;
-    const int N = w.n_part;
+    const Ctl ctl = *w.ctl_src;
+    if (ctl.remaining <= 0) continue;           // block-uniform
+    elastic_pack<PACK, GEN, BR>(w, pk, ctl, lds);
+    __syncthreads();
+  }
+}
+
+
+// ---------------------------------------------------------------------------
+// Binned transfer, pre-pass of a run: the tile lists of the current positions
+// (each step's integration then appends the next step's).
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void k_lists_zero(const WorldDev* __restrict__ W, Tables T) {
+  for (int k = blockIdx.y; k < *T.n_worlds; k += gridDim.y) {
+    const WorldDev& w = W[T.worlds[k].x];
+    if (w.mode != kBinned || w.tl_own == 0 || w.ctl_src->remaining <= 0) continue;
+    const int n = w.ntx * w.nty * kListCounts;
+    for (int t = blockIdx.x * 256 + threadIdx.x; t < n; t += gridDim.x * 256) glb(w.tl_cnt)[t] = 0;
+  }
+}
+
+// Whether tile (tx, ty) is (cx, cy) or one of its eight neighbours.
+static __device__ __forceinline__ bool next_to(const WorldDev& w, int cx, int cy, int tx, int ty) {
+  const int dx = abs(tx - cx), dy = abs(ty - cy);
+  return (dx <= 1 || dx == w.ntx - 1) && (dy <= 1 || dy == w.nty - 1);
+}
+
+// Flags of the lists that cannot be used when segment seg of tile (tx, ty)'s
+// list is full.
+static __device__ __forceinline__ void flag_overflow(const WorldDev& w, MC_GLOBAL int* counts, int tx, int ty, int seg) {
+  const bool segment = seg >= kCntNear;          // (of near or far nodes)
+  atomicOr((int*)(counts + (ty * w.ntx + tx) * kListCounts + kCntFlags), segment ? kOverSegment : kOverOwn);
+  if (seg == kCntOwn)                            // the neighbours may have to read these own nodes
+#pragma unroll 1
+    for (int q = 0; q < 8; ++q) {
+      const int t = nb_tile(ty, nb_dy(q), w.nty) * w.ntx + nb_tile(tx, nb_dx(q), w.ntx);
+      atomicOr((int*)(counts + t * kListCounts + kCntFlags), kOverOwn);
+    }
+}
+
+// Record `slot` of the own nodes (kCntOwn), the strays (kCntStrays) or neighbour
+// q's near (kCntNear + q) or far nodes (kCntFar + q) in tile (tx, ty)'s list, or the flags of the lists that cannot be used
+// without it.
+static __device__ __forceinline__ void write_record(const WorldDev& w, MC_GLOBAL vi4* lists, MC_GLOBAL int* counts,
+                                                    int tx, int ty, int seg, int slot, const vi4& rec) {
+  const int tile = ty * w.ntx + tx;
+  int at, cap;
+  if (seg == kCntOwn) {
+    cap = w.tl_own;
+    at = w.tl_strays + slot;
+  } else if (seg == kCntStrays) {
+    cap = w.tl_strays;
+    at = w.tl_strays - 1 - slot;
+  } else {
+    const int q = (seg - kCntNear) & 7;
+    cap = q < 4 ? w.tl_near_s : w.tl_near_c;
+    at = nb_first(w, q) + slot;
+    if (seg >= kCntFar) {
+      at += cap;
+      cap = q < 4 ? w.tl_far_s : w.tl_far_c;
+    }
+  }
+  if (slot < cap) {
+    lists[(size_t)tile * w.tl_stride + at] = rec;
+    return;
+  }
+  flag_overflow(w, counts, tx, ty, seg);
+}
+
+// Classes of a node with home (hx, hy) for the eight neighbours of tile
+// (cx, cy), its home or the tile it just left, and whether it may reach a tile
+// beyond them.
+struct Classes {
+  int kx, ky;                                    // for the tiles before, at and after, 2 bits each
+  bool beyond;
+  __device__ __forceinline__ int of(int q) const {
+    return max((kx >> (2 * nb_dx(q) + 2)) & 3, (ky >> (2 * nb_dy(q) + 2)) & 3);
+  }
+};
+// Classes along one axis of nt tiles of a node at place l of a tile of t cells
+// (beside it by at most kSmallMove cells) that reaches no tile beyond its
+// neighbours (Place).
+static __device__ __forceinline__ int axis_classes(const Reach& R, int l, int t, int nt) {
+  int k0 = l < 0 ? 0 : (l < R.near_ ? 1 : (l < R.after ? 2 : 3));
+  int k1 = l < 0 ? (-l <= R.near_ ? 1 : 2) : (l >= t ? (l - t < R.near_ ? 1 : 2) : 0);
+  int k2 = l >= t ? 0 : (t - l <= R.near_ ? 1 : (t - l <= R.before ? 2 : 3));
+  if (nt < 3) {                                  // two tiles are neighbours on both sides
+    k2 = nt == 2 ? min(k0, k2) : 3;
+    k0 = 3;
+    if (nt == 1) k1 = 0;
+    else k1 = min(k1, 1);                        // (it may be nearer the other way round)
+  }
+  return k0 | (k1 << 2) | (k2 << 4);
+}
+// Place of home (hx, hy) relative to tile (cx, cy), the short way round, and
+// whether it is one from which a node reaches no tile beyond the neighbours:
+// at most kSmallMove cells beside the tile and, where a neighbour is the axis'
+// narrow last tile, no nearer to it than the reach past it.  (Testing every
+// tile around such nodes' own, as done for all nodes of a world with a narrow
+// last tile before: 700 nodes on 72 x 50, 30.8 us per step; now 27.5.)
+struct Place {
+  int lx, ly;
+  bool inside;
+  static __device__ __forceinline__ bool fits(const Reach& R, int l, int t, int c, int nt, int last) {
+    const int lo = nt > 2 && c == 0 ? max(-kSmallMove, R.after - last) : -kSmallMove;
+    const int hi = t + (nt > 2 && c == nt - 2 ? min(kSmallMove, last - R.before) : kSmallMove);
+    return l >= lo && l < hi;
+  }
+  __device__ __forceinline__ Place(const WorldDev& w, int side, int cx, int cy, int hx, int hy) {
+    const Reach R(w);
+    const int nx = w.nx, ny = w.ny, x0 = cx * side, y0 = cy * side, tw = min(side, nx - x0), th = min(side, ny - y0);
+    lx = hx - x0;
+    ly = hy - y0;
+    lx += lx >= tw && 2 * lx > nx ? -nx : (lx < 0 && -2 * lx > nx ? nx : 0);
+    ly += ly >= th && 2 * ly > ny ? -ny : (ly < 0 && -2 * ly > ny ? ny : 0);
+    inside = fits(R, lx, tw, cx, w.ntx, nx - (w.ntx - 1) * side) && fits(R, ly, th, cy, w.nty, ny - (w.nty - 1) * side);
+  }
+};
+template <int TILE>
+static __device__ __forceinline__ Classes neighbour_classes(const WorldDev& w, int cx, int cy, int hx, int hy) {
+  constexpr int sh = TileCfg<TILE>::kShift;
+  const Reach R(w);
+  const int nx = w.nx, ny = w.ny, ntx = w.ntx, nty = w.nty;
+  const Place p(w, TILE, cx, cy, hx, hy);
+  Classes c;
+  c.beyond = !p.inside;
+  if (!c.beyond) {
+    c.kx = axis_classes(R, p.lx, min(TILE, nx - cx * TILE), ntx);
+    c.ky = axis_classes(R, p.ly, min(TILE, ny - cy * TILE), nty);
+  } else {
+    c.kx = c.ky = 0;
+    for (int d = -1; d <= 1; ++d) {
+      const int tx = nb_tile(cx, d, ntx) << sh, ty = nb_tile(cy, d, nty) << sh;
+      c.kx |= (nb_exists(d, ntx) ? R.of_cell(hx, tx, min(TILE, nx - tx), nx) : 3) << (2 * d + 2);
+      c.ky |= (nb_exists(d, nty) ? R.of_cell(hy, ty, min(TILE, ny - ty), ny) : 3) << (2 * d + 2);
+    }
+  }
+  return c;
+}
+
+// Segment of neighbour q's nodes of class 1 (near) or 2 (far).
+static __device__ __forceinline__ int class_segment(int cls, int q) {
+  return kCntNear - 8 + 8 * cls + q;
+}
+
+// What a node has to do with the neighbours along one axis: its class for the
+// one that it reaches (2 bits), for the tile itself (2), which side that is,
+// and whether it reaches both.
+static __device__ __forceinline__ int axis_pairs(int classes) {
+  const int k0 = classes & 3, k1 = (classes >> 2) & 3, k2 = classes >> 4;
+  return min(k0, k2) | (k1 << 2) | (k0 < 3 ? 0 : 16) | (max(k0, k2) < 3 ? 32 : 0);
+}
+// The neighbours of a node that reaches at most one tile along each axis
+// (more: it may reach others), as nearly all do: one beside it along x, one
+// along y and the corner between them, with their classes.
+struct Pairs {
+  int dx, dy, side_x, side_y, corner;
+  bool more;
+  __device__ __forceinline__ Pairs(int x, int y, bool beyond) {
+    const int kx = x & 3, ky = y & 3;
+    more = beyond || ((x | y) & 32) != 0;
+    dx = ((x >> 3) & 2) - 1;
+    dy = ((y >> 3) & 2) - 1;
+    side_x = max(kx, (y >> 2) & 3);
+    side_y = max((x >> 2) & 3, ky);
+    corner = max(kx, ky);
+  }
+  __device__ __forceinline__ explicit Pairs(const Classes& c) : Pairs(axis_pairs(c.kx), axis_pairs(c.ky), c.beyond) {}
+  __device__ __forceinline__ int qx() const { return dx > 0; }
+  __device__ __forceinline__ int qy() const { return 2 + (dy > 0); }
+  __device__ __forceinline__ int qc() const { return 4 + (dx > 0) + 2 * (dy > 0); }
+};
+
+static __device__ __forceinline__ void append_stray(const WorldDev& w, MC_GLOBAL vi4* lists, MC_GLOBAL int* counts,
+                                                    int tx, int ty, const vi4& rec) {
+  const int k = atomicAdd((int*)(counts + (ty * w.ntx + tx) * kListCounts + kCntStrays), 1);
+  write_record(w, lists, counts, tx, ty, kCntStrays, k, rec);
+}
+// The record as a stray of every tile it reaches beyond the 3x3 around (cx, cy).
+template <int TILE>
+static __device__ __forceinline__ void append_strays(const WorldDev& w, MC_GLOBAL vi4* lists, MC_GLOBAL int* counts,
+                                                     int cx, int cy, const vi4& rec) {
+  for_reached_tiles<TILE>(w, rec.x & 0xffff, rec.x >> 16, [&](int tx, int ty, int) {
+    if (next_to(w, cx, cy, tx, ty)) return;
+    append_stray(w, lists, counts, tx, ty, rec);
+  });
+}
+
+template <int TILE>
+static __device__ __forceinline__ void build_lists_of_node(const WorldDev& w, int gi) {
+  constexpr int sh = TileCfg<TILE>::kShift;
+  const int N = w.n_part;
+  const int hx = wrap_index(glb(w.cell_in)[gi], w.nx), hy = wrap_index(glb(w.cell_in)[N + gi], w.ny);
+  const vi4 rec = {hx | (hy << 16), __float_as_int(glb(w.frac_in)[gi]), __float_as_int(glb(w.frac_in)[N + gi]), gi};
+  const int cx = hx >> sh, cy = hy >> sh, own = cy * w.ntx + cx;
+  MC_GLOBAL vi4* lists = glbv<vi4>(w.tl_rec);
+  MC_GLOBAL int* counts = glb(w.tl_cnt);
+  const Classes c = neighbour_classes<TILE>(w, cx, cy, hx, hy);
+  const Pairs a(c);
+  // one atomic per list segment and wavefront, whose nodes share few tiles;
+  // every one is issued before the first result is used (1,048,576 nodes:
+  // 32 us, 65.7 with one per node)
+  const auto at = [&](int q, int dx, int dy, int cls) {
+    return (nb_tile(cy, dy, w.nty) * w.ntx + nb_tile(cx, dx, w.ntx)) * kListCounts + class_segment(cls, q);
+  };
+  const int k0 = kListCounts * own, k1 = at(a.qx(), a.dx, 0, a.side_x), k2 = at(a.qy(), 0, a.dy, a.side_y),
+            k3 = at(a.qc(), a.dx, a.dy, a.corner);
+  const bool h1 = !a.more && a.side_x < 3, h2 = !a.more && a.side_y < 3, h3 = !a.more && a.corner < 3;
+  const AggGroup g0(k0, true), g1(k1, h1), g2(k2, h2), g3(k3, h3);
+  const int lane = __lane_id();
+  int s0 = 0, s1 = 0, s2 = 0, s3 = 0;
+  if (g0.leader == lane) s0 = atomicAdd((int*)(counts + k0), g0.count);
+  if (h1 && g1.leader == lane) s1 = atomicAdd((int*)(counts + k1), g1.count);
+  if (h2 && g2.leader == lane) s2 = atomicAdd((int*)(counts + k2), g2.count);
+  if (h3 && g3.leader == lane) s3 = atomicAdd((int*)(counts + k3), g3.count);
+  s0 = __shfl(s0, g0.leader) + g0.rank;
+  s1 = __shfl(s1, g1.leader) + g1.rank;
+  s2 = __shfl(s2, g2.leader) + g2.rank;
+  s3 = __shfl(s3, g3.leader) + g3.rank;
+  const auto put = [&](int dx, int dy, int seg, int slot) {
+    write_record(w, lists, counts, nb_tile(cx, dx, w.ntx), nb_tile(cy, dy, w.nty), seg, slot, rec);
+  };
+  put(0, 0, kCntOwn, s0);
+  if (h1) put(a.dx, 0, class_segment(a.side_x, a.qx()), s1);
+  if (h2) put(0, a.dy, class_segment(a.side_y, a.qy()), s2);
+  if (h3) put(a.dx, a.dy, class_segment(a.corner, a.qc()), s3);
+  if (!a.more) return;
+  int slot[8];
+  static_for<8>([&](auto qq) {
+    constexpr int q = decltype(qq)::value;
+    slot[q] = 0;
+    if (c.of(q) <= 2) slot[q] = atomicAdd((int*)(counts + at(q, nb_dx(q), nb_dy(q), c.of(q))), 1);
+  });
+  static_for<8>([&](auto qq) {
+    constexpr int q = decltype(qq)::value;
+    if (c.of(q) <= 2) put(nb_dx(q), nb_dy(q), class_segment(c.of(q), q), slot[q]);
+  });
+  if (c.beyond) append_strays<TILE>(w, lists, counts, cx, cy, rec);
+}
+
+template <int PACK>
+__global__ __launch_bounds__(PACK) void k_lists_build(const WorldDev* __restrict__ W, Tables T) {
+  const int npk = *T.n_packs;
+  for (int it = blockIdx.x; it < npk; it += gridDim.x) {
+    const Pack pk = T.packs[it];
+    const WorldDev& w = W[pk.world];
+    if (w.mode != kBinned || w.tl_own == 0 || w.ctl_src->remaining <= 0) continue;
     const int gi = pk.node_begin + threadIdx.x;
-    const bool active = gi < pk.node_end;
-    int tile = 0;
-    if (active)
-      tile = bin_of(wrap_index(glb(w.cell_in)[gi], w.nx), wrap_index(glb(w.cell_in)[N + gi], w.ny), w.ntx, w.tile_shift);
-    agg_atomic_inc(glb(w.bin_cnt), tile, active);
+    if (gi >= pk.node_end) continue;
+    if (w.tile_shift == 4) build_lists_of_node<16>(w, gi);
+    else if (w.tile_shift == 5) build_lists_of_node<32>(w, gi);
+    else build_lists_of_node<64>(w, gi);
   }
 }
 
@@ -588,7 +767,7 @@ __device__ __forceinline__ vf2 gather_force(const MC_GLOBAL int* start, const MC
 // spare cells per side, see the window note with tile_spread_vec) as exact
 // integer products of quantised weights, so the sums are order-independent
 // and the inner loop is two 24-bit multiplies and an LDS add per cell.
-// Dynamic LDS: [window: filter_window_bytes(max radius) | list / density].
+// LDS: [window: filter_window_bytes(max radius) | density].
 // ---------------------------------------------------------------------------
 // Window rows are kWinPad elements longer than the window side: an even
 // row length of 64-bit words puts vertically adjacent cells, which nodes
@@ -599,10 +778,8 @@ static __host__ __device__ constexpr int filter_window_bytes(int max_radius) {
   return (TILE + 2 + 2 * max_radius + 6) * (TILE + 2 + 2 * max_radius + 6 + kWinPad) * 8;
 }
 template <int TILE>
-static __host__ __device__ constexpr int filter_list_bytes(int max_radius) {
-  return (TILE + 2 + 2 * max_radius) * (TILE + 2 + 2 * max_radius) * 4 > TileCfg<TILE>::kListBytes
-             ? (TILE + 2 + 2 * max_radius) * (TILE + 2 + 2 * max_radius) * 4
-             : TileCfg<TILE>::kListBytes;
+static __host__ __device__ constexpr int filter_density_bytes(int max_radius) {
+  return (TILE + 2 + 2 * max_radius) * (TILE + 2 + 2 * max_radius) * 4;
 }
 // the passes' intermediate rows (region x ring) and the filtered ring fit the window
 static_assert(filter_window_bytes<16>(1) >= ((16 + 2 + 2 * kMaxRadius) * 18 + 18 * 18) * 4, "window");
@@ -615,37 +792,15 @@ static __device__ __forceinline__ int div_small(int k, float inv_d) {
   return (int)(((float)k + 0.5f) * inv_d);
 }
 
-// The bin set a filter tile reads: homes in [xo - 2, xo + reg] per axis
-// (xo = x0 - R - 1, reg = TILE + 2 + 2R), whose supports meet the density
-// region (run table kind 0).
-template <int TILE>
-static __device__ __forceinline__ BinFetch filter_fetch(const WorldDev& w, int tile) {
-  return binset_fetch<TileCfg<TILE>::kRanges>(w, tile_y(tile) * w.ntx + tile_x(tile), 0);
-}
-
-// Set-up: the runs of bins that the filter and the spread of every tile read
-// (they depend on the grid, the tile side and the radius only).
-template <int TILE>
-__global__ void k_tile_ranges(int nx, int ny, int R, int2* out) {
-  const int ntx = (nx + TILE - 1) / TILE, nty = (ny + TILE - 1) / TILE;
-  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < ntx * nty; t += gridDim.x * blockDim.x) {
-    const int x0 = (t % ntx) * TILE, y0 = (t / ntx) * TILE;
-    const int tw = min(TILE, nx - x0), th = min(TILE, ny - y0);
-    const int reg = TILE + 2 + 2 * R, xo = x0 - R - 1, yo = y0 - R - 1;
-    tile_runs<TILE>(xo - 2, xo + reg, yo - 2, yo + reg, nx, ny, ntx, out + (size_t)(2 * t) * kRunStride);
-    tile_runs<TILE>(x0 - 3, x0 + tw + 1, y0 - 3, y0 + th + 1, nx, ny, ntx, out + (size_t)(2 * t + 1) * kRunStride);
-  }
-}
-
 // The two passes of the separable Gaussian (radius R) over the density
 // region s_regf (reg x reg, reg = ring + 2R) into the filtered tile-plus-ring
 // s_st (ring x ring, ring = TILE + 2), through s_mid (reg rows x ring).
 // Every thread forms two adjacent outputs from taps read as aligned pairs
 // (rows have even lengths); each output is summed in the same order as a
 // one-output loop would.  Ends with a barrier.
-template <int TILE, int R>
+template <int TILE, int NT, int R>
 static __device__ __forceinline__ void filter_passes(const float* s_regf, float* s_mid, float* s_st, const float* g) {
-  constexpr int kRing = TILE + 2, kThreads = TileCfg<TILE>::kThreads;
+  constexpr int kRing = TILE + 2, kThreads = NT;
   constexpr int reg = kRing + 2 * R, kHalf = kRing / 2;
   const int tid = threadIdx.x;
   for (int k = tid; k < reg * kHalf; k += kThreads) {
@@ -686,78 +841,52 @@ static __device__ __forceinline__ void filter_passes(const float* s_regf, float*
   __syncthreads();
 }
 
-template <int TILE>
-__global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_filter(const WorldDev* __restrict__ W, Tables T,
-                                                                     int window_bytes) {
+template <int TILE, int NT>
+static __device__ __forceinline__ void filter_tile(const WorldDev& w, int packed, unsigned char* smem,
+                                                   int window_bytes) {
   using C = TileCfg<TILE>;
-  constexpr int kRing = TILE + 2, kThreads = C::kThreads, kSpreadCap = C::kSpreadCap;
-  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int kRing = TILE + 2, kThreads = NT;
   unsigned long long* s_win = (unsigned long long*)smem;
-  vi4* s_list = (vi4*)(smem + window_bytes);
   float* s_regf = (float*)(smem + window_bytes);
   float* s_mid = (float*)smem;
-  __shared__ int s_spn;                          // records appended to the spread list
-  const int nt = n_tiles<TILE>(T);
   const int tid = threadIdx.x;
-  const XcdLoop tiles(nt);
-  for (int it = tiles.first; it < tiles.end; it += tiles.step) {
-    const int2 tl = tile_entry<TILE>(T, it);
-    const WorldDev& w = W[tl.x];
-    if (w.ctl_src->remaining <= 0) continue;
+  {
     const int R = w.radius, mode = w.mode;
     const int nx = w.nx, ny = w.ny;
-    const int x0 = tile_x(tl.y) * TILE;
-    const int y0 = tile_y(tl.y) * TILE;
+    const int x0 = tile_x(packed) * TILE;
+    const int y0 = tile_y(packed) * TILE;
     const int reg = kRing + 2 * R;
     const float inv_reg = 1.0f / (float)reg;
     const int xo = x0 - R - 1, yo = y0 - R - 1;   // region origin (unwrapped)
     float* s_st = s_mid + reg * kRing;
     if (mode == kBinned) {
+      const int tix = tile_y(packed) * w.ntx + tile_x(packed);
       const int S = reg + 6;                      // window side; window origin (xo - 3, yo - 3)
       const int P = S + kWinPad;                  // row pitch
+      TileRecords<NT, 3, NT == 256 && TILE == 32 ? 3 : 2> nodes(w, tix);
       zero_lds_u64(s_win, S * P);
-      if (tid == 0) s_spn = 0;
-      const auto bs = binset_commit<C::kRanges>(filter_fetch<TILE>(w, tl.y));
+      if (tid == 0 && w.tl_own > 0 && w.ctl_src->remaining > 1) {   // (the other segments have one writer each)
+        glb(w.tl_cnt_next)[tix * kListCounts + kCntStrays] = 0;
+        glb(w.tl_cnt_next)[tix * kListCounts + kCntFlags] = 0;
+      }
       const int ox = wrap_index(xo - 3, nx), oy = wrap_index(yo - 3, ny);
       const int keep_x = reg + 3 <= nx ? reg + 2 : nx;
       const int keep_y = reg + 3 <= ny ? reg + 2 : ny;
-      // the records this tile's spread needs (a subset of the filter's: its
-      // window lies inside the filter's) go to the tile's spread list
-      const int tix = tile_y(tl.y) * w.ntx + tile_x(tl.y);
-      const SpreadKeep sp_keep(w, x0, y0, min(TILE, nx - x0), min(TILE, ny - y0));
-      MC_GLOBAL vi4* sp_rec = glbv<vi4>(w.sp_rec) + (size_t)tix * kSpreadCap;
-      for_bin_records<4, kThreads>(
-          glbv<const vi4>(w.bin_rec), bs, s_list,
-          [&](const vi4& r) {
-            const int dx = wrap_near((r.x & 0xffff) - 1 - ox, nx);
-            const int dy = wrap_near((r.x >> 16) - 1 - oy, ny);
-            return dx <= keep_x && dy <= keep_y;
-          },
-          [&](const vi4& r) {
-            const int dx = wrap_near((r.x & 0xffff) - 1 - ox, nx);
-            const int dy = wrap_near((r.x >> 16) - 1 - oy, ny);
-            unsigned qx[4], qy[4];
-            peskin4_quant(__int_as_float(r.y), qx);
-            peskin4_quant(__int_as_float(r.z), qy);
-            unsigned long long* p = s_win + dy * P + dx;
+      __syncthreads();
+      nodes.each(w, [&](const vi4& r, const vf2&) {
+        const int dx = wrap_near((r.x & 0xffff) - 1 - ox, nx);
+        const int dy = wrap_near((r.x >> 16) - 1 - oy, ny);
+        if (dx > keep_x || dy > keep_y) return;
+        unsigned qx[4], qy[4];
+        peskin4_quant(__int_as_float(r.y), qx);
+        peskin4_quant(__int_as_float(r.z), qy);
+        unsigned long long* p = s_win + dy * P + dx;
 #pragma unroll
-            for (int b = 0; b < 4; ++b)
+        for (int b = 0; b < 4; ++b)
 #pragma unroll
-              for (int a = 0; a < 4; ++a) atomicAdd(p + b * P + a, weight_product(qx[a], qy[b]));
-            // append to the spread list: one LDS atomic per wavefront
-            const bool sp = sp_keep(r);
-            const unsigned long long m = __ballot(sp);
-            if (m) {
-              const int leader = __ffsll((unsigned long long)m) - 1;
-              int base = 0;
-              if (__lane_id() == leader) base = atomicAdd(&s_spn, __popcll(m));
-              base = __shfl(base, leader);
-              const int slot = base + __popcll(m & ((1ull << __lane_id()) - 1ull));
-              if (sp && slot < kSpreadCap) sp_rec[slot] = r;
-            }
-          });
-      if (tid == 0) glb(w.sp_cnt)[tix] = s_spn;   // (for_bin_records ended with a barrier)
-      // (the list area is free again after the barrier that ends for_bin_records)
+          for (int a = 0; a < 4; ++a) atomicAdd(p + b * P + a, weight_product(qx[a], qy[b]));
+      });
+      __syncthreads();
       const bool single = reg + 3 <= nx && reg + 3 <= ny;   // one image per needed cell
       for (int k = tid; k < reg * reg; k += kThreads) {
         const int r = div_small(k, inv_reg), c = k - r * reg;
@@ -790,14 +919,14 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_filter(const WorldD
     for (int m = 0; m <= kMaxRadius; ++m) g[m] = w.gtap[m];
     __syncthreads();
     switch (R) {                                  // uniform: the world's radius
-      case 1: filter_passes<TILE, 1>(s_regf, s_mid, s_st, g); break;
-      case 2: filter_passes<TILE, 2>(s_regf, s_mid, s_st, g); break;
-      case 3: filter_passes<TILE, 3>(s_regf, s_mid, s_st, g); break;
-      case 4: filter_passes<TILE, 4>(s_regf, s_mid, s_st, g); break;
-      case 5: filter_passes<TILE, 5>(s_regf, s_mid, s_st, g); break;
-      case 6: filter_passes<TILE, 6>(s_regf, s_mid, s_st, g); break;
-      case 7: filter_passes<TILE, 7>(s_regf, s_mid, s_st, g); break;
-      default: filter_passes<TILE, 8>(s_regf, s_mid, s_st, g); break;
+      case 1: filter_passes<TILE, NT, 1>(s_regf, s_mid, s_st, g); break;
+      case 2: filter_passes<TILE, NT, 2>(s_regf, s_mid, s_st, g); break;
+      case 3: filter_passes<TILE, NT, 3>(s_regf, s_mid, s_st, g); break;
+      case 4: filter_passes<TILE, NT, 4>(s_regf, s_mid, s_st, g); break;
+      case 5: filter_passes<TILE, NT, 5>(s_regf, s_mid, s_st, g); break;
+      case 6: filter_passes<TILE, NT, 6>(s_regf, s_mid, s_st, g); break;
+      case 7: filter_passes<TILE, NT, 7>(s_regf, s_mid, s_st, g); break;
+      default: filter_passes<TILE, NT, 8>(s_regf, s_mid, s_st, g); break;
     }
     MC_GLOBAL vf2* grad = glbv<vf2>(w.grad);
     for (int k = tid; k < TILE * TILE; k += kThreads) {
@@ -809,7 +938,54 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_filter(const WorldD
         grad[(size_t)gy * nx + gx] = gr;
       }
     }
+  }
+}
+
+template <int TILE>
+__global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_filter(const WorldDev* __restrict__ W, Tables T,
+                                                                     int window_bytes) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const XcdLoop tiles(n_tiles<TILE>(T));
+  for (int it = tiles.first; it < tiles.end; it += tiles.step) {
+    const int2 tl = tile_entry<TILE>(T, it);
+    const WorldDev& w = W[tl.x];
+    if (w.ctl_src->remaining <= 0) continue;
+    filter_tile<TILE, TileCfg<TILE>::kThreads>(w, tl.y, smem, window_bytes);
     __syncthreads();
+  }
+}
+
+// S0 - S3 of binned worlds in one launch: the elastic force and the filter both
+// follow from the step's positions alone, so pack blocks and tile blocks run
+// side by side (a pack block waits at barriers and for its neighbours' data
+// most of its time, a tile block issues).  Rounds of eight blocks, one per
+// XCD, alternate between the two kinds until one has run out.
+template <int TILE, int PACK, bool GEN, bool BR>
+__global__ __launch_bounds__(PACK) void k_prepare(const WorldDev* __restrict__ W, Tables T, int window_bytes,
+                                                  int tile_rounds, int pack_rounds) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int round = blockIdx.x >> 3, x = blockIdx.x & 7, both = 2 * min(tile_rounds, pack_rounds);
+  const bool tile_role = round < both ? (round & 1) != 0 : tile_rounds > pack_rounds;
+  const int b = ((round < both ? round >> 1 : round - (both >> 1)) << 3) + x;
+  if (tile_role) {
+    const XcdLoop tiles(n_tiles<TILE>(T), b, tile_rounds << 3);
+    for (int it = tiles.first; it < tiles.end; it += tiles.step) {
+      const int2 tl = tile_entry<TILE>(T, it);
+      const WorldDev& w = W[tl.x];
+      if (w.ctl_src->remaining <= 0) continue;
+      filter_tile<TILE, PACK>(w, tl.y, smem, window_bytes);
+      __syncthreads();
+    }
+  } else {
+    const XcdLoop packs(*T.n_packs, b, pack_rounds << 3);
+    for (int it = packs.first; it < packs.end; it += packs.step) {
+      const Pack pk = T.packs[it];
+      const WorldDev& w = W[pk.world];
+      const Ctl ctl = *w.ctl_src;
+      if (ctl.remaining <= 0) continue;
+      elastic_pack<PACK, GEN, BR>(w, pk, ctl, *(ElasticLds<PACK, BR>*)smem);
+      __syncthreads();
+    }
   }
 }
 
@@ -893,8 +1069,75 @@ __global__ __launch_bounds__(PACK) void k_repulse(const WorldDev* __restrict__ W
   }
 }
 
+// Fluid velocity of a cell from its shifted populations g (the lattice weights
+// have zero first moment, so the shift does not change the momentum sum) and
+// its grid force F; drho = rho - 1.
+static __device__ __forceinline__ vf2 fluid_velocity(const float* g, const vf2& F, float* drho) {
+  const float d = ((g[0] + g[1]) + (g[2] + g[3])) + ((g[4] + g[5]) + (g[6] + g[7])) + g[8];
+  const float jx = (g[1] - g[3]) + (g[5] - g[6]) + (g[8] - g[7]);
+  const float jy = (g[2] - g[4]) + (g[5] - g[8]) + (g[6] - g[7]);
+  const float inv = 1.0f / (1.0f + d);
+  *drho = d;
+  const vf2 u = {(jx + 0.5f * F.x) * inv, (jy + 0.5f * F.y) * inv};
+  return u;
+}
+
+// Pushes the post-collision populations of cell (x, y) to its neighbours.  The
+// wrapped rows and columns are formed once (in the loop over q the compiler
+// formed them per population: 247 vector instructions a
+// wavefront of k_lbm, now 221).
+template <class Store>
+static __device__ __forceinline__ void push(int x, int y, int nx, int ny, const float* out, Store store) {
+  const int xs[3] = {x > 0 ? x - 1 : nx - 1, x, x + 1 < nx ? x + 1 : 0};
+  const int rows[3] = {(y > 0 ? y - 1 : ny - 1) * nx, y * nx, (y + 1 < ny ? y + 1 : 0) * nx};
+  static_for<9>([&](auto qq) {
+    constexpr int q = qq, cx = (q == 1 || q == 5 || q == 8) - (q == 3 || q == 6 || q == 7),
+                  cy = (q == 2 || q == 5 || q == 6) - (q == 4 || q == 7 || q == 8);
+    store(q, rows[cy + 1] + xs[cx + 1], out[q]);
+  });
+}
+
+// Post-collision populations of a cell.  Equilibrium minus weights: w_q (drho +
+// rho (3 cu + 4.5 cu^2 - 1.5 u^2)); Guo source: w_q (3 (c - u) + 9 (c.u) c) . F;
+// split into the parts symmetric and antisymmetric under q <-> opposite(q).
+static __device__ __forceinline__ void collide(const WorldDev& w, const float* g, const vf2& F, const vf2& u,
+                                               float drho, float* out) {
+  const float Fx = F.x, Fy = F.y, ux = u.x, uy = u.y;
+  const float rho = 1.0f + drho;
+  const float usq = ux * ux + uy * uy;
+  const float op = w.om_p, om = w.om_m;
+  const float sp = 1.0f - 0.5f * op, sm = 1.0f - 0.5f * om;
+  const float base = 1.5f * usq;
+  const float uF = ux * Fx + uy * Fy;
+  {
+    const float w0 = 4.0f / 9.0f;
+    const float geq0 = w0 * (drho - rho * base);
+    const float S0 = w0 * (-3.0f * uF);
+    out[0] = g[0] - op * (g[0] - geq0) + sp * S0;
+  }
+#pragma unroll
+  for (int pr = 0; pr < 4; ++pr) {
+    const int q = pr < 2 ? 1 + pr : 5 + (pr - 2);
+    const int qb = q + 2;
+    const float wq = pr < 2 ? (1.0f / 9.0f) : (1.0f / 36.0f);
+    const float cxq = (float)kCX[q], cyq = (float)kCY[q];
+    const float cu = cxq * ux + cyq * uy;
+    const float cF = cxq * Fx + cyq * Fy;
+    const float eqp = wq * (drho + rho * (4.5f * cu * cu - base));
+    const float eqm = wq * rho * 3.0f * cu;
+    const float Sp = wq * (9.0f * cu * cF - 3.0f * uF);
+    const float Sm = wq * 3.0f * cF;
+    const float gp = 0.5f * (g[q] + g[qb]);
+    const float gm = 0.5f * (g[q] - g[qb]);
+    const float relp = -op * (gp - eqp) + sp * Sp;
+    const float relm = -om * (gm - eqm) + sm * Sm;
+    out[q] = g[q] + relp + relm;
+    out[qb] = g[qb] + relp - relm;
+  }
+}
+
 // ---------------------------------------------------------------------------
-// S5: grid force of a tile, summed in LDS over the tile's bin (binned)
+// S5: grid force of a tile, summed in LDS over the tile's list (binned)
 // or by fixed-order gathers over sorted segments (sorted); every cell of the
 // tile is written once.  Direct mode accumulates in k_repulse instead.
 // ---------------------------------------------------------------------------
@@ -904,12 +1147,11 @@ __global__ __launch_bounds__(PACK) void k_repulse(const WorldDev* __restrict__ W
 template <int TILE, bool MK>
 __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_spread(const WorldDev* __restrict__ W, Tables T) {
   using C = TileCfg<TILE>;
-  constexpr int kThreads = C::kThreads, kSpreadCells = C::kSpreadCells;
-  constexpr int kGSide = C::kSpreadSide + (MK ? 2 : 0), kGCells = kGSide * kGSide;
-  constexpr int kSpreadCap = C::kSpreadCap;
-  __shared__ __align__(16) long long s_fx[kSpreadCells];   // 64-bit fixed point, padded window
-  __shared__ __align__(16) long long s_fy[kSpreadCells];
-  __shared__ vi4 s_list[(kThreads / 64) * kWaveList];
+  using SW = SpreadWin<TILE>;
+  constexpr int kThreads = C::kThreads;
+  constexpr int kGSide = MK ? SW::kGSide : SW::kSide, kGCells = kGSide * kGSide;
+  __shared__ __align__(16) long long s_fx[SW::kCells];   // 64-bit fixed point, padded window
+  __shared__ __align__(16) long long s_fy[SW::kCells];
   __shared__ vf2 s_g[kGCells];                  // gradient over the window (binned)
   const int nt = n_tiles<TILE>(T);
   const int tid = threadIdx.x;
@@ -925,51 +1167,20 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_spread(const WorldD
     const int y0 = tile_y(tl.y) * TILE;
     const int tw = min(TILE, nx - x0), th = min(TILE, ny - y0);
     if (mode == kBinned) {
-      // S4 repulsion is formed here, per node, from the gradient staged over
-      // the window (grid cells (x0 - 3 + i, y0 - 3 + j), periodic); all loads
-      // first, then the stores (the barrier in the bin set commit follows)
-      {
-        constexpr int kIt = (kGCells + kThreads - 1) / kThreads;
-        const MC_GLOBAL vf2* grad = glbv<const vf2>(w.grad);
-        const int gx0 = wrap_index(x0 - (MK ? 4 : 3), nx), gy0 = wrap_index(y0 - (MK ? 4 : 3), ny);
-        vf2 gv[kIt];
-#pragma unroll
-        for (int i = 0; i < kIt; ++i) {
-          const int k = min(tid + kThreads * i, kGCells - 1);
-          const int j = k / kGSide, c = k - (k / kGSide) * kGSide;
-          gv[i] = grad[(size_t)wrap_index(gy0 + j, ny) * nx + wrap_index(gx0 + c, nx)];
-        }
-#pragma unroll
-        for (int i = 0; i < kIt; ++i) {
-          const int k = tid + kThreads * i;
-          if (k < kGCells) s_g[k] = gv[i];
-        }
-      }
-      zero_lds_u64(s_fx, kSpreadCells);
-      zero_lds_u64(s_fy, kSpreadCells);
-      // the tile's record list from the filter (one range), or, if it
-      // overflowed, the bins of the neighbourhood
       const int tix = tile_y(tl.y) * w.ntx + tile_x(tl.y);
-      const int cnt = glb(w.sp_cnt)[tix];
-      if (cnt >= 0 && cnt <= kSpreadCap) {
-        BinFetch f;
-        f.n = 1;
-        f.b0 = tix * kSpreadCap;
-        f.len = __lane_id() == 0 ? cnt : 0;
-        if constexpr (MK)
-          tile_spread_markers<TILE, true, true>(w, x0, y0, tw, th, glb(w.fel_el), 1.0f, s_fx, s_fy, s_list,
-                                                glbv<const vi4>(w.sp_rec), f, s_g);
-        else
-          tile_spread_vec<TILE, true, true>(w, x0, y0, tw, th, glb(w.fel_el), 1.0f, s_fx, s_fy, s_list,
-                                            glbv<const vi4>(w.sp_rec), f, s_g);
-      } else {
-        if constexpr (MK)
-          tile_spread_markers<TILE, true>(w, x0, y0, tw, th, glb(w.fel_el), 1.0f, s_fx, s_fy, s_list,
-                                          glbv<const vi4>(w.bin_rec), spread_fetch<TILE>(w, x0, y0), s_g);
-        else
-          tile_spread_vec<TILE, true>(w, x0, y0, tw, th, glb(w.fel_el), 1.0f, s_fx, s_fy, s_list,
-                                      glbv<const vi4>(w.bin_rec), spread_fetch<TILE>(w, x0, y0), s_g);
-      }
+      // S4 repulsion is formed here, per node, from the gradient staged over
+      // the window (grid cells (x0 - 3 + i, y0 - 3 + j), periodic)
+      // (the gradient's loads first: they need no other, and loads return in order)
+      const WindowLoads<kThreads, kGSide> grad(glbv<const vf2>(w.grad), nx, ny, x0 - (MK ? 4 : 3), y0 - (MK ? 4 : 3));
+      SpreadNodes<TILE> nodes(w, tix, glb(w.fel_el));
+      zero_lds_u64(s_fx, SW::kCells);
+      zero_lds_u64(s_fy, SW::kCells);
+      grad.store(s_g);
+      __syncthreads();
+      if constexpr (MK)
+        tile_spread_markers<TILE, true>(w, nodes, x0, y0, tw, th, 1.0f, s_fx, s_fy, s_g);
+      else
+        tile_spread_vec<TILE, true>(w, nodes, x0, y0, tw, th, 1.0f, s_fx, s_fy, s_g);
       __syncthreads();
     }
     MC_GLOBAL vf2* Fg = glbv<vf2>(w.Fg);
@@ -980,8 +1191,8 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_spread(const WorldD
       if (lx >= tw || ly >= th) continue;
       vf2 F;
       if (mode == kBinned) {
-        F.x = fix_to_float(spread_cell<TILE>(s_fx, lx, ly, nx, ny));
-        F.y = fix_to_float(spread_cell<TILE>(s_fy, lx, ly, nx, ny));
+        F.x = fix_to_float(spread_cell<SW::kSide>(s_fx, lx, ly, nx, ny));
+        F.y = fix_to_float(spread_cell<SW::kSide>(s_fy, lx, ly, nx, ny));
       } else {
         F = gather_force(start, rec, nx, ny, x0 + lx, y0 + ly);
       }
@@ -1044,62 +1255,16 @@ __global__ __launch_bounds__(256) void k_lbm(const WorldDev* __restrict__ W, Tab
         glbv<vf2>(w.Fg)[c] = zero;
         glb(w.s)[c] = 0.f;
       }
-      const float Fx = F.x, Fy = F.y;
-      // moments (the lattice weights have zero first moment, so the shift does
-      // not change the momentum sum)
-      const float drho = ((g[0] + g[1]) + (g[2] + g[3])) + ((g[4] + g[5]) + (g[6] + g[7])) + g[8];
-      const float rho = 1.0f + drho;
-      const float jx = (g[1] - g[3]) + (g[5] - g[6]) + (g[8] - g[7]);
-      const float jy = (g[2] - g[4]) + (g[5] - g[8]) + (g[6] - g[7]);
-      const float inv = 1.0f / rho;
-      const float ux = (jx + 0.5f * Fx) * inv;
-      const float uy = (jy + 0.5f * Fy) * inv;
-      const float usq = ux * ux + uy * uy;
-      const vf2 uv = {ux, uy};
+      float drho, out[9];
+      const vf2 uv = fluid_velocity(g, F, &drho);
       glbv<vf2>(w.u)[c] = uv;
-      if (!(usq <= w.u_max2)) atomicOr((unsigned*)glb(w.flags), kFlagUnstable);
-
-      // equilibrium minus weights: w_q (drho + rho (3 cu + 4.5 cu^2 - 1.5 u^2));
-      // Guo source: w_q (3 (c - u) + 9 (c.u) c) . F; split into the parts
-      // symmetric and antisymmetric under q <-> opposite(q)
-      const float op = w.om_p, om = w.om_m;
-      const float sp = 1.0f - 0.5f * op, sm = 1.0f - 0.5f * om;
-      const float base = 1.5f * usq;
-      const float uF = ux * Fx + uy * Fy;
-      float out[9];
-      {
-        const float w0 = 4.0f / 9.0f;
-        const float geq0 = w0 * (drho - rho * base);
-        const float S0 = w0 * (-3.0f * uF);
-        out[0] = g[0] - op * (g[0] - geq0) + sp * S0;
-      }
-  #pragma unroll
-      for (int pr = 0; pr < 4; ++pr) {
-        const int q = pr < 2 ? 1 + pr : 5 + (pr - 2);
-        const int qb = q + 2;
-        const float wq = pr < 2 ? (1.0f / 9.0f) : (1.0f / 36.0f);
-        const float cxq = (float)kCX[q], cyq = (float)kCY[q];
-        const float cu = cxq * ux + cyq * uy;
-        const float cF = cxq * Fx + cyq * Fy;
-        const float eqp = wq * (drho + rho * (4.5f * cu * cu - base));
-        const float eqm = wq * rho * 3.0f * cu;
-        const float Sp = wq * (9.0f * cu * cF - 3.0f * uF);
-        const float Sm = wq * 3.0f * cF;
-        const float gp = 0.5f * (g[q] + g[qb]);
-        const float gm = 0.5f * (g[q] - g[qb]);
-        const float relp = -op * (gp - eqp) + sp * Sp;
-        const float relm = -om * (gm - eqm) + sm * Sm;
-        out[q] = g[q] + relp + relm;
-        out[qb] = g[qb] + relp - relm;
-      }
-  #pragma unroll
-      for (int q = 0; q < 9; ++q) {
-        const int xn = wrap_near(x + kCX[q], nx);
-        const int yn = wrap_near(y + kCY[q], ny);
-        // (non-temporal: the next read is a step away; the caches keep
-        // what the following kernels read instead)
-        __builtin_nontemporal_store(out[q], (float*)(dst + (size_t)q * ncell + (size_t)yn * nx + xn));
-      }
+      if (!(uv.x * uv.x + uv.y * uv.y <= w.u_max2)) atomicOr((unsigned*)glb(w.flags), kFlagUnstable);
+      collide(w, g, F, uv, drho, out);
+      // (non-temporal: the next read is a step away; the caches keep what the
+      // following kernels read instead)
+      push(x, y, nx, ny, out, [&](int q, int c, float v) {
+        __builtin_nontemporal_store(v, (float*)(dst + (size_t)q * ncell) + c);
+      });
     }
   }
 }
@@ -1181,33 +1346,15 @@ __global__ __launch_bounds__(PACK) void k_integrate(const WorldDev* __restrict__
 // ---------------------------------------------------------------------------
 // Binned worlds: the node gather of S7 (u) per tile.  The field is staged in
 // LDS for the tile plus the support margin (cells x0-1 .. x0+TILE+1)
-// with coalesced loads; every node whose home cell lies in the tile (its bin)
+// with coalesced loads; every node whose home cell lies in the tile (its own)
 // gathers its 4x4 window from LDS.  (The S4 gather of binned worlds happens
 // inside k_spread.)
 // ---------------------------------------------------------------------------
-// Stage a vector field over the cells (x0 - 1 - E .. x0 + TILE + 1 + E) of
-// each axis (side TILE + 3 + 2E): every support of a node whose home lies in
-// the tile (E = 0), or of its two-layer markers (E = 1: a marker's home lies
+// The field is staged over the cells (x0 - 1 - E .. x0 + TILE + 1 + E) of each
+// axis (side TILE + 3 + 2E): every support of a node whose home lies in the
+// tile (E = 0), or of its two-layer markers (E = 1: a marker's home lies
 // within one cell of its node's).
-template <int TILE, int E = 0>
-__device__ __forceinline__ void stage_field(const MC_GLOBAL vf2* f, int nx, int ny, int x0, int y0, vf2* st) {
-  constexpr int kStage = TILE + 3 + 2 * E, kThreads = TileCfg<TILE>::kThreads;
-  constexpr int kIt = (kStage * kStage + kThreads - 1) / kThreads;
-  vf2 v[kIt];
-#pragma unroll
-  for (int i = 0; i < kIt; ++i) {              // all loads in flight before the stores
-    const int k = min((int)threadIdx.x + kThreads * i, kStage * kStage - 1);
-    const int r = k / kStage, c = k - (k / kStage) * kStage;
-    v[i] = f[(size_t)wrap_index(y0 - 1 - E + r, ny) * nx + wrap_index(x0 - 1 - E + c, nx)];
-  }
-#pragma unroll
-  for (int i = 0; i < kIt; ++i) {
-    const int k = (int)threadIdx.x + kThreads * i;
-    if (k < kStage * kStage) st[k] = v[i];
-  }
-}
-
-// 4x4 kernel-weighted sum of a staged vector field (stage_field<TILE, E>)
+// 4x4 kernel-weighted sum of a staged vector field
 // at a point whose support starts at staged cell (lx, ly) (a node with home
 // cell (lx, ly) of the tile when E = 0; weights wx, wy along x and y).
 template <int TILE, int E = 0>
@@ -1231,47 +1378,188 @@ __device__ __forceinline__ vf2 gather_staged(const vf2* st, int lx, int ly, cons
   return out;
 }
 
-// MK: the two-layer variant (worlds with markers, which the plain variant
-// skips): a node moves with the mean of its two markers' velocities.
-template <int TILE, bool MK>
-__global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_integrate_tile(const WorldDev* __restrict__ W, Tables T) {
-  constexpr int kE = MK ? 1 : 0;
-  constexpr int kStage = TILE + 3 + 2 * kE, kThreads = TileCfg<TILE>::kThreads;
-  __shared__ vf2 s_u[kStage * kStage];        // staged velocity, x and y interleaved
-  const int nt = n_tiles<TILE>(T);
-  const XcdLoop tiles(nt);
-  for (int it = tiles.first; it < tiles.end; it += tiles.step) {
-    const int2 tl = tile_entry<TILE>(T, it);
-    const WorldDev& w = W[tl.x];
-    if (w.mode != kBinned || w.ctl_src->remaining <= 0) continue;
-    if (MK != (w.d_marker != nullptr)) continue;
-    const int nx = w.nx, ny = w.ny, N = w.n_part;
-    const int x0 = tile_x(tl.y) * TILE;
-    const int y0 = tile_y(tl.y) * TILE;
-    const MC_GLOBAL vi4* recs = glbv<const vi4>(w.bin_rec);
-    const MC_GLOBAL int* cell = glb(w.cell_in);
-    MC_GLOBAL int* cell_out = glb(w.cell_out);
-    MC_GLOBAL float* frac_out = glb(w.frac_out);
-    const int tile = tile_y(tl.y) * w.ntx + tile_x(tl.y);
-    const int e0 = glb(w.bin_start)[tile], e1 = glb(w.bin_start)[tile + 1];
-    // this thread's first two records and their cells are loaded beside the
-    // staged field, unconditionally (record 0 always exists: the record
-    // buffer holds at least one; an empty world has no positions at all)
-    const int ea = e0 + (int)threadIdx.x, eb = ea + kThreads;
-    const bool has0 = ea < e1, has1 = eb < e1;
-    const vi4 r0 = recs[has0 ? ea : 0];
-    const vi4 r1 = recs[has1 ? eb : 0];
-    stage_field<TILE, kE>(glbv<const vf2>(w.u), nx, ny, x0, y0, s_u);
-    int c0x = 0, c0y = 0, c1x = 0, c1y = 0;    // in flight across the barrier
-    if (N > 0) {
-      const int g0 = has0 ? r0.w : 0, g1 = has1 ? r1.w : 0;
-      c0x = cell[g0];
-      c0y = cell[N + g0];
-      c1x = cell[g1];
-      c1y = cell[N + g1];
+// Next step's lists from the block that integrated tile (bx, by): cursors of
+// the tile's own segment and of its segments in the eight neighbours' lists
+// (at kCntNear and kCntFar + q: in the list of the tile it is neighbour q of).
+template <int TILE>
+struct AppendLds {
+  static constexpr int kAxis = TILE + 2 * kSmallMove;
+  int cur[kListCounts];
+  int at[kListCounts], cap[kListCounts];         // where each segment begins, and how many it takes
+  unsigned char axis[2 * kAxis];                 // axis_pairs of the places along x, then y
+};
+template <int TILE>
+static __device__ __forceinline__ void init_append(const WorldDev& w, int bx, int by, AppendLds<TILE>& lds) {
+  constexpr int kAxis = AppendLds<TILE>::kAxis;
+  const int seg = threadIdx.x;
+  if (seg < 2 * kAxis) {
+    const bool y = seg >= kAxis;
+    const int l = seg - (y ? kAxis : 0) - kSmallMove;
+    lds.axis[seg] = (unsigned char)axis_pairs(axis_classes(Reach(w), l, y ? min(TILE, w.ny - by * TILE) : min(TILE, w.nx - bx * TILE),
+                                            y ? w.nty : w.ntx));
+  }
+  if (seg >= kListCounts) return;
+  lds.cur[seg] = 0;
+  int tile = by * w.ntx + bx, at = w.tl_strays, cap = w.tl_own;
+  if (seg >= kCntNear) {
+    const int q = (seg - kCntNear) & 7;
+    tile = nb_tile(by, nb_dy(q), w.nty) * w.ntx + nb_tile(bx, nb_dx(q), w.ntx);
+    at = nb_first(w, q);
+    cap = q < 4 ? w.tl_near_s : w.tl_near_c;
+    if (seg >= kCntFar) {
+      at += cap;
+      cap = q < 4 ? w.tl_far_s : w.tl_far_c;
     }
-    __syncthreads();
-    auto node = [&](const vi4& r, int cxo, int cyo) {
+  }
+  lds.at[seg] = tile * w.tl_stride + at;
+  lds.cap[seg] = cap;
+}
+// Record `slot` of the segment, or the flags of the lists that cannot be used
+// without it.
+template <int TILE>
+static __device__ __forceinline__ void append_record(const WorldDev& w, MC_GLOBAL vi4* lists, MC_GLOBAL int* counts,
+                                                     const AppendLds<TILE>& lds, int tx, int ty, int seg, int slot,
+                                                     const vi4& rec) {
+  if (slot < lds.cap[seg]) lists[lds.at[seg] + slot] = rec;
+  else flag_overflow(w, counts, tx, ty, seg);
+}
+
+// Appends up to PER nodes per thread (node index -1: none) to the lists of the
+// tiles they reach; called by every lane.
+template <int TILE, int PER>
+static __device__ __forceinline__ void append_nodes(const WorldDev& w, int bx, int by, const vi4* rec,
+                                                    AppendLds<TILE>& lds) {
+  constexpr int kAxis = AppendLds<TILE>::kAxis;
+  const int ntx = w.ntx, nty = w.nty;
+  MC_GLOBAL vi4* lists = glbv<vi4>(w.tl_rec_next);
+  MC_GLOBAL int* counts = glb(w.tl_cnt_next);
+#pragma unroll
+  for (int p = 0; p < PER; ++p) {
+    const vi4& r = rec[p];
+    const bool has = r.w >= 0;
+    const unsigned long long m = __ballot(has);
+    if (!m) continue;
+    // own segment: one LDS atomic per wavefront
+    const int lane = __lane_id(), leader = __ffsll(m) - 1;
+    int k = 0;
+    if (lane == leader) k = atomicAdd(&lds.cur[kCntOwn], __popcll(m));
+    const Place pl(w, TILE, bx, by, r.x & 0xffff, r.x >> 16);
+    const int ix = pl.inside ? pl.lx + kSmallMove : 0, iy = kAxis + (pl.inside ? pl.ly + kSmallMove : 0);
+    const Pairs a(lds.axis[ix], lds.axis[iy], !pl.inside);
+    k = __shfl(k, leader) + __popcll(m & ((1ull << lane) - 1ull));
+    if (!has) continue;
+    if (!__any(a.more)) {
+      // every lane for its own neighbours at once, the slots fetched together
+      const int q1 = class_segment(a.side_x, a.qx()), q2 = class_segment(a.side_y, a.qy()),
+                q3 = class_segment(a.corner, a.qc());
+      const auto listed = [](int cls) { return cls == 1 || cls == 2; };
+      int k1 = 0, k2 = 0, k3 = 0;
+      if (listed(a.side_x)) k1 = atomicAdd(&lds.cur[q1], 1);
+      if (listed(a.side_y)) k2 = atomicAdd(&lds.cur[q2], 1);
+      if (listed(a.corner)) k3 = atomicAdd(&lds.cur[q3], 1);
+      append_record(w, lists, counts, lds, bx, by, kCntOwn, k, r);
+      const int tx = nb_tile(bx, a.dx, ntx), ty = nb_tile(by, a.dy, nty);
+      if (listed(a.side_x)) append_record(w, lists, counts, lds, tx, by, q1, k1, r);
+      if (listed(a.side_y)) append_record(w, lists, counts, lds, bx, ty, q2, k2, r);
+      if (listed(a.corner)) append_record(w, lists, counts, lds, tx, ty, q3, k3, r);
+      if (a.side_x == 0 || a.side_y == 0 || a.corner == 0)   // it has left for that one
+        append_stray(w, lists, counts, a.side_y == 0 ? bx : tx, a.side_x == 0 ? by : ty, r);
+      continue;
+    }
+    append_record(w, lists, counts, lds, bx, by, kCntOwn, k, r);
+    const Classes c = neighbour_classes<TILE>(w, bx, by, r.x & 0xffff, r.x >> 16);
+#pragma unroll 1
+    for (int q = 0; q < 8; ++q) {
+      const int cls = c.of(q), tx = nb_tile(bx, nb_dx(q), ntx), ty = nb_tile(by, nb_dy(q), nty);
+      if (cls > 2) continue;
+      if (cls == 0) {
+        append_stray(w, lists, counts, tx, ty, r);
+        continue;
+      }
+      const int seg = class_segment(cls, q);
+      append_record(w, lists, counts, lds, tx, ty, seg, atomicAdd(&lds.cur[seg], 1), r);
+    }
+    if (c.beyond) append_strays<TILE>(w, lists, counts, bx, by, r);
+  }
+}
+
+// The counts of the segments this block wrote (after a barrier).
+template <int TILE>
+static __device__ __forceinline__ void store_counts(const WorldDev& w, int bx, int by, const AppendLds<TILE>& lds) {
+  const int seg = threadIdx.x;
+  if (seg == kCntStrays || seg >= kCntFlags) return;
+  const int q = (seg - kCntNear) & 7;
+  const int dx = seg < kCntNear ? 0 : nb_dx(q), dy = seg < kCntNear ? 0 : nb_dy(q);
+  if (!nb_exists(dx, w.ntx) || !nb_exists(dy, w.nty)) return;
+  const int tile = nb_tile(by, dy, w.nty) * w.ntx + nb_tile(bx, dx, w.ntx);
+  glb(w.tl_cnt_next)[tile * kListCounts + seg] = lds.cur[seg];
+}
+
+// A tile's nodes for its integration (its own and the strays): records and
+// unwrapped cells of up to kOwnPer nodes per thread, loaded together (the
+// first round's beside the staging of the velocity).  Every wavefront goes
+// through its runs of the list, or through every node of the world, on its own.
+constexpr int kOwnPer = 2;
+struct OwnNodes {
+  int total;                                     // of this wavefront
+  bool list;
+  vi4 rec[kOwnPer];
+  int cx[kOwnPer], cy[kOwnPer];
+};
+template <int TILE>
+static __device__ __forceinline__ void load_own(const WorldDev& w, int tile, const WaveRuns<1>& L, int base,
+                                                OwnNodes& o) {
+  constexpr int kThreads = TileCfg<TILE>::kThreads;
+  const int N = w.n_part, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const MC_GLOBAL int* cell = glb(w.cell_in);
+  const MC_GLOBAL vi4* recs = glbv<const vi4>(w.tl_rec) + (size_t)tile * w.tl_stride;
+  o.list = L.mode == 0;
+  o.total = o.list ? L.total : max(0, (N - 64 * wave + kThreads - 1) / kThreads * 64);
+  if (o.total == 0) return;
+#pragma unroll
+  for (int q = 0; q < kOwnPer; ++q) {            // clamped, so that every load is issued at once
+    const int e = min(base + q * 64 + lane, o.total - 1);
+    if (o.list) o.rec[q] = recs[L.record(e)];
+    else o.rec[q].w = min(e / 64 * kThreads + 64 * wave + (e & 63), N - 1);
+  }
+#pragma unroll
+  for (int q = 0; q < kOwnPer; ++q) {
+    const int gi = o.rec[q].w;
+    o.cx[q] = cell[gi];
+    o.cy[q] = cell[N + gi];
+    if (!o.list) {
+      o.rec[q].y = __float_as_int(glb(w.frac_in)[gi]);
+      o.rec[q].z = __float_as_int(glb(w.frac_in)[N + gi]);
+    }
+  }
+}
+
+// S7 of a tile's own nodes (o: the first round's, loaded), from the velocity
+// staged in s_u: the new positions and, unless this is the run's last step
+// (append), the next step's lists.  The cursors have been cleared.
+template <int TILE, bool MK>
+static __device__ __forceinline__ void integrate_own(const WorldDev& w, int tile, const WaveRuns<1>& L, OwnNodes& o,
+                                                     int packed, bool append, const vf2* s_u, AppendLds<TILE>& lds) {
+  constexpr int kThreads = TileCfg<TILE>::kThreads;
+  const int nx = w.nx, ny = w.ny, N = w.n_part;
+  const int x0 = tile_x(packed) * TILE, y0 = tile_y(packed) * TILE;
+  const int tw = min(TILE, nx - x0), th = min(TILE, ny - y0);
+  for (int base = 0; base < o.total; base += kOwnPer * 64) {
+    if (base > 0) load_own<TILE>(w, tile, L, base, o);
+#pragma unroll
+    for (int q = 0; q < kOwnPer; ++q) {
+      vi4& r = o.rec[q];
+      const int home = wrap_index(o.cx[q], nx) | (wrap_index(o.cy[q], ny) << 16);
+      const int e = base + q * 64 + (int)(threadIdx.x & 63);
+      bool has = e < o.total && (o.list || e / 64 * kThreads + (int)threadIdx.x < N);
+      if (o.list && has && r.x != home) atomicOr((unsigned*)glb(w.flags), kFlagBins);   // moved since its list was made
+      if (!o.list) r.x = home;
+      const int hlx = (r.x & 0xffff) - x0, hly = (r.x >> 16) - y0;   // (some only reach the tile, or left it)
+      has = has && hlx >= 0 && hlx < tw && hly >= 0 && hly < th;
+      if (!has) {
+        r.w = -1;
+        continue;
+      }
       const int lx = (r.x & 0xffff) - x0, ly = (r.x >> 16) - y0;
       const float fx = __int_as_float(r.y), fy = __int_as_float(r.z);
       const int gi = r.w;
@@ -1305,26 +1593,173 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_integrate_tile(cons
       }
       float nfx = fx + dux, nfy = fy + duy;
       const float flx = floorf(nfx), fly = floorf(nfy);
-      int ncx = cxo + (int)flx, ncy = cyo + (int)fly;
+      int ncx = o.cx[q] + (int)flx, ncy = o.cy[q] + (int)fly;
       nfx -= flx;
       nfy -= fly;
       if (nfx >= 1.0f) { nfx = 0.0f; ncx += 1; }
       if (nfy >= 1.0f) { nfy = 0.0f; ncy += 1; }
-      cell_out[gi] = ncx;
-      cell_out[N + gi] = ncy;
-      frac_out[gi] = nfx;
-      frac_out[N + gi] = nfy;
-      // next step's tile-bin counts
-      agg_atomic_inc(glb(w.bin_cnt), bin_of(wrap_index(ncx, nx), wrap_index(ncy, ny), w.ntx, TileCfg<TILE>::kShift),
-                     true);
-    };
-    // the first two records (already loaded), then any further ones
-    if (has0) node(r0, c0x, c0y);
-    if (has1) node(r1, c1x, c1y);
-    for (int e = eb + kThreads; e < e1; e += kThreads) {
-      const vi4 r = recs[e];
-      node(r, cell[r.w], cell[N + r.w]);
+      glb(w.cell_out)[gi] = ncx;
+      glb(w.cell_out)[N + gi] = ncy;
+      glb(w.frac_out)[gi] = nfx;
+      glb(w.frac_out)[N + gi] = nfy;
+      r.x = wrap_index(ncx, nx) | (wrap_index(ncy, ny) << 16);
+      r.y = __float_as_int(nfx);
+      r.z = __float_as_int(nfy);
     }
+    if (append) append_nodes<TILE, kOwnPer>(w, tile_x(packed), tile_y(packed), o.rec, lds);
+  }
+  if (append) {
+    __syncthreads();
+    store_counts(w, tile_x(packed), tile_y(packed), lds);
+  }
+}
+
+// MK: the two-layer variant (worlds with markers, which the plain variant
+// skips): a node moves with the mean of its two markers' velocities.
+template <int TILE, bool MK>
+__global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_integrate_tile(const WorldDev* __restrict__ W, Tables T) {
+  constexpr int kE = MK ? 1 : 0;
+  constexpr int kStage = TILE + 3 + 2 * kE, kThreads = TileCfg<TILE>::kThreads;
+  __shared__ vf2 s_u[kStage * kStage];        // staged velocity, x and y interleaved
+  __shared__ AppendLds<TILE> s_app;
+  const int nt = n_tiles<TILE>(T);
+  const XcdLoop tiles(nt);
+  for (int it = tiles.first; it < tiles.end; it += tiles.step) {
+    const int2 tl = tile_entry<TILE>(T, it);
+    const WorldDev& w = W[tl.x];
+    const int remaining = w.ctl_src->remaining;
+    if (w.mode != kBinned || remaining <= 0) continue;
+    if (MK != (w.d_marker != nullptr)) continue;
+    const int nx = w.nx, ny = w.ny;
+    const int x0 = tile_x(tl.y) * TILE;
+    const int y0 = tile_y(tl.y) * TILE;
+    const int tile = tile_y(tl.y) * w.ntx + tile_x(tl.y);
+    init_append(w, tile_x(tl.y), tile_y(tl.y), s_app);
+    const WindowLoads<kThreads, kStage> u(glbv<const vf2>(w.u), nx, ny, x0 - 1 - kE, y0 - 1 - kE);
+    const auto L = wave_runs<kThreads, 1>(w, tile);
+    OwnNodes own;
+    load_own<TILE>(w, tile, L, 0, own);
+    u.store(s_u);
+    __syncthreads();
+    integrate_own<TILE, MK>(w, tile, L, own, tl.y, w.tl_own > 0 && remaining > 1, s_u, s_app);
+    __syncthreads();
+  }
+}
+
+// ---------------------------------------------------------------------------
+// S4 - S7 of binned worlds without MDF in one tile kernel: the force spread
+// over the tile and the cells its nodes' supports reach, the fluid update of
+// the tile (and the velocity alone of the cells around it), and the
+// integration of its nodes, with the grid force and the velocity in LDS
+// throughout.  Where a launch lasts as long as its chain of dependent loads
+// whatever its work, three chains and two launches less cost (TILE + 3)^2 /
+// TILE^2 of the spread and of the population loads; where the populations stay
+// in the caches the grid force (read and written), the velocity and the
+// latencies saved count for more than that too.  Per step, separate kernels
+// and this one: 1000 nodes on 128^2 (16-cell tiles) 25.3 and 17.5 us, 65,536 on
+// 512^2 (16) 34.1 and 28.0, 262,144 on 1024^2 (32) 76.2 and 57.2.  Bound by
+// the vector instructions it issues at the latter size.  16-cell tiles load
+// their populations ahead of the spread (two cells a thread); 32-cell ones
+// have five a thread, and with those in registers half as many wavefronts fit
+// (1024^2: 75 us).  Non-temporal stores, which do k_lbm good, leave lines
+// that two tiles share half written (1024^2: 71 us).
+// The arithmetic is that of the separate kernels.
+// ---------------------------------------------------------------------------
+template <int TILE, bool MK>
+__global__ __launch_bounds__(TileCfg<TILE>::kThreads, MK ? 3 : 4) void k_fluid_tile(const WorldDev* __restrict__ W, Tables T) {
+  constexpr int kE = MK ? 1 : 0, LO = 1 + kE, HI = 2 + kE;
+  using SW = SpreadWin<TILE, LO, HI>;
+  constexpr int kThreads = TileCfg<TILE>::kThreads;
+  constexpr int kStage = TILE + LO + HI, kCells = kStage * kStage, kIt = (kCells + kThreads - 1) / kThreads;
+  constexpr int kGSide = MK ? SW::kGSide : SW::kSide;
+  constexpr bool kAhead = TILE == 16;
+  __shared__ __align__(16) long long s_fx[SW::kCells];
+  __shared__ __align__(16) long long s_fy[SW::kCells];
+  __shared__ vf2 s_g[kGSide * kGSide];          // density gradient, then the velocity
+  __shared__ AppendLds<TILE> s_app;
+  static_assert(kStage <= kGSide, "velocity in the gradient's place");
+  const XcdLoop tiles(n_tiles<TILE>(T));
+  for (int it = tiles.first; it < tiles.end; it += tiles.step) {
+    const int2 tl = tile_entry<TILE>(T, it);
+    const WorldDev& w = W[tl.x];
+    if (MK != (w.d_marker != nullptr)) continue;
+    const Ctl cs = *w.ctl_src;
+    const int tix = tile_y(tl.y) * w.ntx + tile_x(tl.y);
+    if (tix == 0 && threadIdx.x == 0) {
+      Ctl cd = cs;
+      if (cs.remaining > 0) { cd.t += 1; cd.remaining -= 1; }
+      *w.ctl_dst = cd;
+    }
+    if (cs.remaining <= 0) continue;
+    const int nx = w.nx, ny = w.ny, ncell = nx * ny;
+    const int x0 = tile_x(tl.y) * TILE, y0 = tile_y(tl.y) * TILE;
+    const int tw = min(TILE, nx - x0), th = min(TILE, ny - y0);
+    init_append(w, tile_x(tl.y), tile_y(tl.y), s_app);
+    // (the gradient's loads first: they need no other, and loads return in order)
+    const WindowLoads<kThreads, kGSide> grad(glbv<const vf2>(w.grad), nx, ny, x0 - LO - (MK ? 4 : 3), y0 - LO - (MK ? 4 : 3));
+    SpreadNodes<TILE> nodes(w, tix, glb(w.fel_el));
+    zero_lds_u64(s_fx, SW::kCells);
+    zero_lds_u64(s_fy, SW::kCells);
+    grad.store(s_g);
+    // the populations of the tile's cells and those around it, and the nodes
+    // to integrate, are on their way while the forces are spread
+    const MC_GLOBAL float* src = glb(w.f_src);
+    float g[kAhead ? kIt : 1][9];
+    const int cx0 = wrap_index(x0 - LO, nx), cy0 = wrap_index(y0 - LO, ny);
+    auto load = [&](int i, float* o) {
+      const int k = min((int)threadIdx.x + kThreads * i, kCells - 1);
+      const int r = k / kStage, c = k - r * kStage;
+      const size_t idx = (size_t)wrap_index(cy0 + r, ny) * nx + wrap_index(cx0 + c, nx);
+#pragma unroll
+      for (int q = 0; q < 9; ++q) o[q] = src[(size_t)q * ncell + idx];
+    };
+    if constexpr (kAhead) {
+#pragma unroll
+      for (int i = 0; i < kIt; ++i) load(i, g[i]);
+    }
+    const auto L = wave_runs<kThreads, 1>(w, tix);
+    OwnNodes own;
+    load_own<TILE>(w, tix, L, 0, own);
+    __syncthreads();
+    if constexpr (MK)
+      tile_spread_markers<TILE, true, LO, HI>(w, nodes, x0, y0, tw, th, 1.0f, s_fx, s_fy, s_g);
+    else
+      tile_spread_vec<TILE, true, false, LO, HI>(w, nodes, x0, y0, tw, th, 1.0f, s_fx, s_fy, s_g);
+    __syncthreads();
+    MC_GLOBAL float* dst = glb(w.f_dst);
+    const bool keep_u = w.keep_force || cs.remaining == 1;   // no later step of the call replaces it
+    auto cell = [&](int i, const float* g) {
+      const int k = (int)threadIdx.x + kThreads * i;
+      if (k >= kCells) return;
+      const int r = k / kStage, c = k - r * kStage;
+      vf2 F;
+      F.x = fix_to_float(spread_cell<SW::kSide>(s_fx, c, r, nx, ny));
+      F.y = fix_to_float(spread_cell<SW::kSide>(s_fy, c, r, nx, ny));
+      float drho;
+      const vf2 u = fluid_velocity(g, F, &drho);
+      s_g[k] = u;
+      if (c < LO || c >= LO + tw || r < LO || r >= LO + th) return;   // around the tile: the velocity alone
+      const int x = x0 + c - LO, y = y0 + r - LO;
+      const size_t idx = (size_t)y * nx + x;
+      if (keep_u) glbv<vf2>(w.u)[idx] = u;
+      if (w.keep_force) glbv<vf2>(w.Fg)[idx] = F;
+      if (!(u.x * u.x + u.y * u.y <= w.u_max2)) atomicOr((unsigned*)glb(w.flags), kFlagUnstable);
+      float out[9];
+      collide(w, g, F, u, drho, out);
+      push(x, y, nx, ny, out, [&](int q, int c, float v) { (dst + (size_t)q * ncell)[c] = v; });
+    };
+    if constexpr (kAhead) {
+#pragma unroll
+      for (int i = 0; i < kIt; ++i) cell(i, g[i]);
+    } else {
+#pragma unroll 1
+      for (int i = 0; i < kIt; ++i) {
+        load(i, g[0]);
+        cell(i, g[0]);
+      }
+    }
+    __syncthreads();
+    integrate_own<TILE, MK>(w, tix, L, own, tl.y, w.tl_own > 0 && cs.remaining > 1, s_g, s_app);
     __syncthreads();
   }
 }
@@ -1334,7 +1769,7 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_integrate_tile(cons
 // starting position and collects rate * e_i, which its filament's total
 // gains (summed in node order by the filament's first node) and the field
 // loses through the same kernel (k_energy_deplete: tile-binned worlds spread
-// it over the spread lists in 64-bit fixed point; others with float atomics).
+// it over the tile lists in 64-bit fixed point; others with float atomics).
 // ---------------------------------------------------------------------------
 template <int PACK>
 __global__ __launch_bounds__(PACK) void k_energy_gather(const WorldDev* __restrict__ W, Tables T) {
@@ -1396,9 +1831,9 @@ template <int TILE>
 __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_energy_deplete(const WorldDev* __restrict__ W,
                                                                              Tables T) {
   using C = TileCfg<TILE>;
-  constexpr int kThreads = C::kThreads, kSpreadCells = C::kSpreadCells, kSpreadCap = C::kSpreadCap;
-  __shared__ __align__(16) long long s_x[kSpreadCells];
-  __shared__ vi4 s_list[(kThreads / 64) * kWaveList];
+  using SW = SpreadWin<TILE>;
+  constexpr int kThreads = C::kThreads;
+  __shared__ __align__(16) long long s_x[SW::kCells];
   const int nt = n_tiles<TILE>(T);
   const XcdLoop tiles(nt);
   for (int it = tiles.first; it < tiles.end; it += tiles.step) {
@@ -1408,37 +1843,18 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_energy_deplete(cons
     const int nx = w.nx, ny = w.ny;
     const int x0 = tile_x(tl.y) * TILE, y0 = tile_y(tl.y) * TILE;
     const int tw = min(TILE, nx - x0), th = min(TILE, ny - y0);
-    zero_lds_u64(s_x, kSpreadCells);
-    __syncthreads();
     const int tix = tile_y(tl.y) * w.ntx + tile_x(tl.y);
-    const int cnt = glb(w.sp_cnt)[tix];
-    // the tile's spread list of this step (the records of the step's
-    // starting positions), or the bins if it overflowed; a two-layer world's
-    // list also holds nodes one cell further out (for their markers), which
-    // the keep test drops here
-    if (cnt >= 0 && cnt <= kSpreadCap) {
-      BinFetch f;
-      f.n = 1;
-      f.b0 = tix * kSpreadCap;
-      f.len = __lane_id() == 0 ? cnt : 0;
-      if (w.d_marker)
-        tile_spread_vec<TILE, false, false, true>(w, x0, y0, tw, th, glb(w.e_node), -w.energy_rate, s_x, nullptr,
-                                                  s_list, glbv<const vi4>(w.sp_rec), f, nullptr);
-      else
-        tile_spread_vec<TILE, false, true, true>(w, x0, y0, tw, th, glb(w.e_node), -w.energy_rate, s_x, nullptr,
-                                                 s_list, glbv<const vi4>(w.sp_rec), f, nullptr);
-    } else {
-      tile_spread_vec<TILE, false, false, true>(w, x0, y0, tw, th, glb(w.e_node), -w.energy_rate, s_x, nullptr,
-                                                s_list, glbv<const vi4>(w.bin_rec), spread_fetch<TILE>(w, x0, y0),
-                                                nullptr);
-    }
+    SpreadNodes<TILE, true> nodes(w, tix, glb(w.e_node));
+    zero_lds_u64(s_x, SW::kCells);
+    __syncthreads();
+    tile_spread_vec<TILE, false, true>(w, nodes, x0, y0, tw, th, -w.energy_rate, s_x, nullptr, nullptr);
     __syncthreads();
     MC_GLOBAL float* E = glb(w.energy);
     for (int k = threadIdx.x; k < TILE * TILE; k += kThreads) {
       const int ly = k >> C::kShift, lx = k & (TILE - 1);
       if (lx >= tw || ly >= th) continue;
       const size_t c = (size_t)(y0 + ly) * nx + x0 + lx;
-      E[c] += fix_to_float(spread_cell<TILE>(s_x, lx, ly, nx, ny));
+      E[c] += fix_to_float(spread_cell<SW::kSide>(s_x, lx, ly, nx, ny));
     }
     __syncthreads();
   }
@@ -1585,15 +2001,7 @@ __global__ __launch_bounds__(PACK) void k_markers(const WorldDev* __restrict__ W
       int a = gi, b = gi;                         // the nodes the tangent joins
       if (k > 0) a = gi - 1; else if (ring) a = first + n - 1;
       if (k < n - 1) b = gi + 1; else if (ring) b = first;
-      const int N = w.n_part;
-      const MC_GLOBAL int* cell = glb(w.cell_in);
-      const MC_GLOBAL float* frac = glb(w.frac_in);
-      const float tx = (float)(cell[b] - cell[a]) + (frac[b] - frac[a]);
-      const float ty = (float)(cell[N + b] - cell[N + a]) + (frac[N + b] - frac[N + a]);
-      const float len = sqrtf(tx * tx + ty * ty);
-      const float sc = len > 0.f ? w.marker_offset / len : 0.f;
-      glb(w.d_marker)[gi] = -ty * sc;
-      glb(w.d_marker)[N + gi] = tx * sc;
+      marker_displacement(w, gi, a, b);
     }
     __syncthreads();
   }
@@ -1738,7 +2146,7 @@ __global__ __launch_bounds__(PACK) void k_mdf_correct(const WorldDev* __restrict
 }
 
 // Binned transfer: the node passes of MDF as tile passes over the home-tile
-// bins, and the correction spread through the tiles' spread lists, summed in
+// own nodes, and the correction spread through the tiles' lists, summed in
 // LDS as 64-bit fixed point like the force spread: deterministic and without
 // HBM atomics.
 //   k_mdf_gather_tile<TILE, true>   U_d = I[j / rho] + F / 2 at the tile's nodes
@@ -1766,6 +2174,7 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_mdf_gather_tile(con
     const int x0 = tile_x(tl.y) * TILE, y0 = tile_y(tl.y) * TILE;
     const MC_GLOBAL vf4* m = glbv<const vf4>(w.rho_j);
     const MC_GLOBAL vf2* Fg = glbv<const vf2>(w.Fg);
+    const int tile = tile_y(tl.y) * w.ntx + tile_x(tl.y);
     vf4 mv[kIt];
     vf2 fv[kIt];
 #pragma unroll
@@ -1793,12 +2202,8 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_mdf_gather_tile(con
       }
     }
     __syncthreads();
-    const int tile = tile_y(tl.y) * w.ntx + tile_x(tl.y);
-    const int e0 = glb(w.bin_start)[tile], e1 = glb(w.bin_start)[tile + 1];
-    const MC_GLOBAL vi4* recs = glbv<const vi4>(w.bin_rec);
     MC_GLOBAL float* Ud = glb(w.U_d);
-    for (int e = e0 + (int)threadIdx.x; e < e1; e += kThreads) {
-      const vi4 r = recs[e];
+    for_own_records<kThreads>(w, tile, x0, y0, min(TILE, nx - x0), min(TILE, ny - y0), [&](const vi4& r) {
       const int lx = (r.x & 0xffff) - x0, ly = (r.x >> 16) - y0;
       const float fx = __int_as_float(r.y), fy = __int_as_float(r.z);
       const int gi = r.w;
@@ -1835,7 +2240,7 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_mdf_gather_tile(con
         glb(w.mdf_c)[gi] = 2.0f * (Ud[gi] - g.x);
         glb(w.mdf_c)[N + gi] = 2.0f * (Ud[N + gi] - g.y);
       }
-    }
+    });
     __syncthreads();
   }
 }
@@ -1844,10 +2249,10 @@ template <int TILE, bool MK>
 __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_mdf_spread_tile(const WorldDev* __restrict__ W, Tables T,
                                                                              int iter) {
   using C = TileCfg<TILE>;
-  constexpr int kThreads = C::kThreads, kSpreadCells = C::kSpreadCells, kSpreadCap = C::kSpreadCap;
-  __shared__ __align__(16) long long s_fx[kSpreadCells];
-  __shared__ __align__(16) long long s_fy[kSpreadCells];
-  __shared__ vi4 s_list[(kThreads / 64) * kWaveList];
+  using SW = SpreadWin<TILE>;
+  constexpr int kThreads = C::kThreads;
+  __shared__ __align__(16) long long s_fx[SW::kCells];
+  __shared__ __align__(16) long long s_fy[SW::kCells];
   const int nt = n_tiles<TILE>(T);
   const XcdLoop tiles(nt);
   for (int it = tiles.first; it < tiles.end; it += tiles.step) {
@@ -1858,30 +2263,15 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_mdf_spread_tile(con
     const int nx = w.nx, ny = w.ny;
     const int x0 = tile_x(tl.y) * TILE, y0 = tile_y(tl.y) * TILE;
     const int tw = min(TILE, nx - x0), th = min(TILE, ny - y0);
-    zero_lds_u64(s_fx, kSpreadCells);
-    zero_lds_u64(s_fy, kSpreadCells);
-    __syncthreads();
     const int tix = tile_y(tl.y) * w.ntx + tile_x(tl.y);
-    const int cnt = glb(w.sp_cnt)[tix];
-    if (cnt >= 0 && cnt <= kSpreadCap) {
-      BinFetch f;
-      f.n = 1;
-      f.b0 = tix * kSpreadCap;
-      f.len = __lane_id() == 0 ? cnt : 0;
-      if constexpr (MK)
-        tile_spread_markers<TILE, false, true>(w, x0, y0, tw, th, glb(w.mdf_c), 1.0f, s_fx, s_fy, s_list,
-                                               glbv<const vi4>(w.sp_rec), f, nullptr);
-      else
-        tile_spread_vec<TILE, false, true>(w, x0, y0, tw, th, glb(w.mdf_c), 1.0f, s_fx, s_fy, s_list,
-                                           glbv<const vi4>(w.sp_rec), f, nullptr);
-    } else {
-      if constexpr (MK)
-        tile_spread_markers<TILE, false>(w, x0, y0, tw, th, glb(w.mdf_c), 1.0f, s_fx, s_fy, s_list,
-                                         glbv<const vi4>(w.bin_rec), spread_fetch<TILE>(w, x0, y0), nullptr);
-      else
-        tile_spread_vec<TILE, false>(w, x0, y0, tw, th, glb(w.mdf_c), 1.0f, s_fx, s_fy, s_list,
-                                     glbv<const vi4>(w.bin_rec), spread_fetch<TILE>(w, x0, y0), nullptr);
-    }
+    SpreadNodes<TILE> nodes(w, tix, glb(w.mdf_c));
+    zero_lds_u64(s_fx, SW::kCells);
+    zero_lds_u64(s_fy, SW::kCells);
+    __syncthreads();
+    if constexpr (MK)
+      tile_spread_markers<TILE, false>(w, nodes, x0, y0, tw, th, 1.0f, s_fx, s_fy, nullptr);
+    else
+      tile_spread_vec<TILE, false>(w, nodes, x0, y0, tw, th, 1.0f, s_fx, s_fy, nullptr);
     __syncthreads();
     MC_GLOBAL vf2* Fg = glbv<vf2>(w.Fg);
     for (int k = threadIdx.x; k < TILE * TILE; k += kThreads) {
@@ -1889,8 +2279,8 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_mdf_spread_tile(con
       if (lx >= tw || ly >= th) continue;
       const size_t c = (size_t)(y0 + ly) * nx + x0 + lx;
       vf2 F = Fg[c];
-      F.x += fix_to_float(spread_cell<TILE>(s_fx, lx, ly, nx, ny));
-      F.y += fix_to_float(spread_cell<TILE>(s_fy, lx, ly, nx, ny));
+      F.x += fix_to_float(spread_cell<SW::kSide>(s_fx, lx, ly, nx, ny));
+      F.y += fix_to_float(spread_cell<SW::kSide>(s_fy, lx, ly, nx, ny));
       Fg[c] = F;
     }
     __syncthreads();
@@ -1937,10 +2327,10 @@ void launch_elastic(const WorldDev* W, const Tables& T, const Grid& G, hipStream
   }
 }
 
-void launch_bin_prepass(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s) {
-  if (!G.any_binned) return;
-  MC_PACK_DISPATCH(k_bin_count, G, W, T);
-  k_bin_scan<<<G.world_blocks, 1024, 0, s>>>(W, T, 0);
+void launch_list_prepass(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s) {
+  if (!G.any_lists) return;
+  k_lists_zero<<<dim3(G.world_blocks == 1 ? 64 : 8, G.world_blocks), 256, 0, s>>>(W, T);
+  MC_PACK_DISPATCH(k_lists_build, G, W, T);
 }
 
 void launch_sort(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s) {
@@ -1955,26 +2345,78 @@ void launch_sort(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t 
 
 // Tile kernels: one launch per tile family present.
 template <int TILE>
+static int filter_lds(const Grid& G) {
+  return filter_window_bytes<TILE>(G.max_radius) + filter_density_bytes<TILE>(G.max_radius);
+}
+
+// the largest dynamic LDS any launch of kernel F asks for (64-cell tiles exceed
+// 64 KiB), declared once per kernel and process
+template <int TILE, auto F>
+static void declare_lds() {
+  static const bool done = [] {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(F), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               filter_window_bytes<TILE>(kMaxRadius) + filter_density_bytes<TILE>(kMaxRadius)) ==
+           hipSuccess;
+  }();
+  (void)done;
+}
+
+template <int TILE>
 static void launch_filter_t(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s) {
   constexpr int f = TileCfg<TILE>::kFamily;
   if (G.tile_blocks[f] <= 0) return;
-  // the largest dynamic LDS any launch asks for (64-cell tiles exceed 64 KiB),
-  // declared once per process
-  static const bool lds_declared = [] {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_filter<TILE>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize,
-                               filter_window_bytes<TILE>(kMaxRadius) + filter_list_bytes<TILE>(kMaxRadius)) ==
-           hipSuccess;
-  }();
-  (void)lds_declared;
-  const int wb = filter_window_bytes<TILE>(G.max_radius);
-  k_filter<TILE><<<G.tile_blocks[f], TileCfg<TILE>::kThreads, wb + filter_list_bytes<TILE>(G.max_radius), s>>>(W, T, wb);
+  if constexpr (TILE == 64) declare_lds<TILE, &k_filter<TILE>>();
+  k_filter<TILE><<<G.tile_blocks[f], TileCfg<TILE>::kThreads, filter_lds<TILE>(G), s>>>(
+      W, T, filter_window_bytes<TILE>(G.max_radius));
 }
 
 void launch_filter(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s) {
   launch_filter_t<16>(W, T, G, s);
   launch_filter_t<32>(W, T, G, s);
   launch_filter_t<64>(W, T, G, s);
+}
+
+template <int TILE, int PACK>
+static void launch_prepare_t(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s) {
+  const int tr = (G.tile_blocks[TileCfg<TILE>::kFamily] + 7) / 8, pr = (G.node_blocks + 7) / 8;
+  const int wb = filter_window_bytes<TILE>(G.max_radius), lds = filter_lds<TILE>(G);
+  const auto go = [&](auto gen, auto br) {
+    constexpr bool GN = decltype(gen)::value, B = decltype(br)::value;
+    const int bytes = std::max(lds, (int)sizeof(ElasticLds<PACK, B>));
+    if constexpr (TILE == 64) declare_lds<TILE, &k_prepare<TILE, PACK, GN, B>>();
+    k_prepare<TILE, PACK, GN, B><<<8 * (tr + pr), PACK, bytes, s>>>(W, T, wb, tr, pr);
+  };
+  if (G.branches) go(std::true_type(), std::true_type());
+  else if (G.general) go(std::true_type(), std::false_type());
+  else go(std::false_type(), std::false_type());
+}
+
+// One launch where every world is binned and their tiles have one side whose
+// block fits the packs' (64-cell tiles take 1024 threads); else the elastic
+// force (which the sorted and direct transfers build on), then the rest.
+// Filaments of more than 256 nodes are packed by blocks of 1024 threads, which
+// suit a tile ill: up to one block per CU the launch saved counts for more (3000 nodes on
+// 128^2, 64 tiles: 27.0 -> 21.5 us per step), past it the separate kernels do
+// (200,000 on 1200^2: 68.4 against 90.2).
+constexpr int kWideTiles = 256;
+void launch_prepare(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s) {
+  const int families = (G.tile_blocks[0] > 0) + (G.tile_blocks[1] > 0) + (G.tile_blocks[2] > 0);
+  const int tiles = G.tile_blocks[0] + G.tile_blocks[1] + G.tile_blocks[2];
+  const bool merge = !G.any_node && G.any_binned && families == 1 && (G.tile_blocks[2] == 0 || G.pack == 1024) &&
+                     (G.pack == 256 || tiles <= kWideTiles);
+  if (!merge) {
+    launch_elastic(W, T, G, s);
+    launch_sort(W, T, G, s);
+    launch_filter(W, T, G, s);
+  } else if (G.tile_blocks[0] > 0) {
+    if (G.pack == 256) launch_prepare_t<16, 256>(W, T, G, s);
+    else launch_prepare_t<16, 1024>(W, T, G, s);
+  } else if (G.tile_blocks[1] > 0) {
+    if (G.pack == 256) launch_prepare_t<32, 256>(W, T, G, s);
+    else launch_prepare_t<32, 1024>(W, T, G, s);
+  } else {
+    launch_prepare_t<64, 1024>(W, T, G, s);
+  }
 }
 
 void launch_repulse(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s) {
@@ -1988,6 +2430,18 @@ void launch_spread(const WorldDev* W, const Tables& T, const Grid& G, hipStream_
     constexpr int TL = decltype(tile)::value;
     k_spread<TL, decltype(mk)::value><<<G.tile_blocks[TileCfg<TL>::kFamily], TileCfg<TL>::kThreads, 0, s>>>(W, T);
   });
+}
+
+void launch_fluid_tiles(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s) {
+  const auto go = [&](auto tile) {
+    constexpr int TL = decltype(tile)::value;
+    const int blocks = G.tile_blocks[TileCfg<TL>::kFamily];
+    if (blocks == 0) return;
+    if (!G.mk_only) k_fluid_tile<TL, false><<<blocks, TileCfg<TL>::kThreads, 0, s>>>(W, T);
+    if (G.any_markers) k_fluid_tile<TL, true><<<blocks, TileCfg<TL>::kThreads, 0, s>>>(W, T);
+  };
+  go(std::integral_constant<int, 16>());
+  go(std::integral_constant<int, 32>());
 }
 
 void launch_lbm(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s) {
@@ -2007,7 +2461,6 @@ void launch_integrate(const WorldDev* W, const Tables& T, const Grid& G, hipStre
       k_integrate_tile<TL, decltype(mk)::value>
           <<<G.tile_blocks[TileCfg<TL>::kFamily], TileCfg<TL>::kThreads, 0, s>>>(W, T);
     });
-    k_bin_scan<<<G.world_blocks, 1024, 0, s>>>(W, T, 1);  // bins of the new positions
   }
 }
 
@@ -2065,14 +2518,6 @@ void launch_energy_packets(int nx, int ny, int n_packets, const float* centres, 
                            const float* widths, float* field, hipStream_t s) {
   const int nt = ((nx + kPacketTile - 1) / kPacketTile) * ((ny + kPacketTile - 1) / kPacketTile);
   k_energy_packets<<<nt < 8192 ? nt : 8192, 256, 0, s>>>(nx, ny, n_packets, centres, amps, widths, field);
-}
-
-void launch_tile_ranges(int nx, int ny, int R, int tile, int2* out, hipStream_t s) {
-  const int nt = ((nx + tile - 1) / tile) * ((ny + tile - 1) / tile);
-  const int blocks = nt > 0 ? (nt + 255) / 256 : 1;
-  if (tile == 16) k_tile_ranges<16><<<blocks, 256, 0, s>>>(nx, ny, R, out);
-  else if (tile == 64) k_tile_ranges<64><<<blocks, 256, 0, s>>>(nx, ny, R, out);
-  else k_tile_ranges<32><<<blocks, 256, 0, s>>>(nx, ny, R, out);
 }
 
 void launch_set_ctl(Ctl* c, long long t, int remaining, hipStream_t s) {

@@ -110,13 +110,10 @@ struct WorldBufs {
   int* perm = nullptr;
   float4* rec = nullptr;
   int* part = nullptr;
-  int* bin_cnt = nullptr;
-  int* bin_fill = nullptr;
-  int* bin_start = nullptr;
-  int4* bin_rec = nullptr;
-  int2* tile_rng = nullptr;
-  int4* sp_rec = nullptr;
-  int* sp_cnt = nullptr;
+  int* cell_alt = nullptr;      // [2][N] the other set of positions (binned transfer: a step reads
+  float* frac_alt = nullptr;    // one set and writes the other, as with the populations)
+  int4* tl_rec[2] = {};         // tile lists of even and odd steps
+  int* tl_cnt[2] = {};
 };
 
 inline int mode_of(const sim_params& p) {
@@ -127,9 +124,92 @@ inline int tile_side(const sim_params& p) { return p.tile_side ? p.tile_side : 3
 inline int tile_family(const sim_params& p) { return mc::tile_family_of_side(tile_side(p)); }
 inline int tiles_x(const sim_params& p) { return (p.nx + tile_side(p) - 1) / tile_side(p); }
 inline int tiles_y(const sim_params& p) { return (p.ny + tile_side(p) - 1) / tile_side(p); }
-inline size_t n_bins(const sim_params& p) { return (size_t)tiles_x(p) * tiles_y(p); }
+inline size_t n_tiles_of(const sim_params& p) { return (size_t)tiles_x(p) * tiles_y(p); }
 
-void carve_world_bufs(Carver& c, const sim_params& p, int n_part, WorldBufs& b) {
+// Blocks for n items dealt out to the eight XCDs in equal shares: with a share
+// of n / 8 rounded up and a block less on some XCDs, those took a second round
+// for one item (12,000 nodes on 400^2, 625 tiles: 29.0 -> 21.5 us per step).
+constexpr size_t align8(size_t n) { return (n + 7) & ~size_t(7); }
+
+// The parameters with the tile side that n worlds of them run with.  Worlds of
+// few 32-cell tiles leave most of the chip idle (about one tile block per CU, or
+// less) and take 16-cell tiles instead: 16,000 nodes on 256^2 (64 tiles of 32)
+// 30.0 -> 19.9 us per step, 14,000 on 448^2 (196) 36.7 -> 23.5, 65,536 on 512^2
+// (256) 32.6 -> 29.2; at 768^2 (576) 32-cell tiles win, 31.4 against 49.8.
+// 64-cell tiles run as 32-cell ones: 1,048,576 nodes on 2048^2 230 -> 207,
+// 262,144 on 1024^2 77 -> 57.  Results do not depend on the side.
+constexpr size_t kSmallTiles = 320;
+sim_params with_side(const sim_params& p, int n_worlds) {
+  sim_params q = p;
+  q.tile_side = tile_side(p);
+  if (mode_of(p) != mc::kBinned) return q;
+  if (q.tile_side == 64) q.tile_side = 32;
+  if (q.tile_side == 32 && (size_t)n_worlds * n_tiles_of(q) <= kSmallTiles) q.tile_side = 16;
+  return q;
+}
+
+// Capacities of a tile's list segments.  Full (kFullLists): room for twice the
+// world's mean density, at least one node per cell, over each segment's cells;
+// smaller workspaces take a share of it (in eighths; 0: no lists, the tiles
+// test every node).  Worlds of at most kTestedNodes nodes need none: a tile
+// block tests that many nodes in no more loads than it has for its list.
+constexpr int kFullLists = 8;
+constexpr int kListShares[] = {8, 6, 4, 3, 2, 1, 0};
+constexpr int kTestedNodes = 512;
+// Most 16-cell and 32-cell tiles (of all worlds of a table) that run S4 - S7 as
+// one kernel: 262,144 nodes on 1024^2 (4096 tiles of 16) 94.6 -> 84.3 us per
+// step, as 1024 tiles of 32 76.2 -> 57.4, 800,000 on 1792^2 (3136) 171.5 ->
+// 168.2.  On 2048^2 (4096 tiles of 32) the two sets of populations pass the
+// 256 MB of the last cache level, and the separate kernels, which stream them
+// with non-temporal accesses, take 207 us against 215.
+constexpr size_t kFusedTiles16 = 4096, kFusedTiles32 = 3200;
+constexpr bool few_tiles(size_t n16, size_t n32, size_t n64) {
+  return n64 == 0 && n16 <= kFusedTiles16 && n32 <= kFusedTiles32;
+}
+struct ListCaps {
+  int own = 0, strays = 0, near_s = 0, far_s = 0, near_c = 0, far_c = 0;
+  size_t stride() const { return (size_t)own + strays + 4 * ((size_t)near_s + far_s + near_c + far_c); }
+  void set(mc::WorldDev& d) const {
+    d.tl_own = own;
+    d.tl_strays = strays;
+    d.tl_near_s = near_s;
+    d.tl_far_s = far_s;
+    d.tl_near_c = near_c;
+    d.tl_far_c = far_c;
+    d.tl_stride = (int)stride();
+  }
+};
+ListCaps list_caps(const sim_params& p, int n_part, int share) {
+  ListCaps k;
+  if (mode_of(p) != mc::kBinned || n_part <= kTestedNodes || share == 0) return k;
+  const bool mk = p.marker_offset > 0.f;
+  const double T = tile_side(p), r = mc::far_reach_before(p.repulse_radius, mk), n = mc::near_reach(mk);
+  const double per = std::max(1.0, 2.0 * n_part / ((double)p.nx * p.ny)) * share / kFullLists;
+  // (the smaller a region, the more its count varies around the mean)
+  auto cap = [&](double cells) {
+    return (int)std::min<double>(n_part, 8.0 * std::ceil((cells + 3.0 * std::sqrt(cells)) * per / 8.0));
+  };
+  k.own = cap(T * T);
+  k.strays = cap(4 * T);
+  k.near_s = cap(n * T);
+  k.far_s = cap((r - n) * T);
+  k.near_c = cap(n * n);
+  k.far_c = cap(r * r - n * n);
+  // records are numbered in 32 bits
+  if (k.stride() * n_tiles_of(p) > 0x7fffffffull) return list_caps(p, n_part, share - 1);
+  return k;
+}
+
+// Bytes the binned transfer's node records took before the tile lists: the
+// least a workspace, a pool slot or a tape slot has to offer for them.
+size_t least_list_bytes(const sim_params& p, int n_part) {
+  if (mode_of(p) != mc::kBinned) return 0;
+  const size_t nt = n_tiles_of(p), N = std::max(n_part, 1), T = tile_side(p);
+  return 3 * align_up(nt * 4) + align_up((nt + 1) * 4) + align_up(N * 16) + align_up(nt * 128) +
+         align_up(nt * T * T * 16);
+}
+
+void carve_world_bufs(Carver& c, const sim_params& p, int n_part, int share, WorldBufs& b) {
   const size_t ncell = (size_t)p.nx * p.ny;
   const size_t N = std::max(n_part, 1);
   b.f_alt = c.take<float>(9 * ncell);
@@ -156,14 +236,14 @@ void carve_world_bufs(Carver& c, const sim_params& p, int n_part, WorldBufs& b) 
       b.u_mdf = c.take<float2>(ncell);
     }
   } else {
-    const size_t nt = n_bins(p);
-    b.bin_cnt = c.take<int>(nt);
-    b.bin_fill = c.take<int>(nt);
-    b.bin_start = c.take<int>(nt + 1);
-    b.bin_rec = c.take<int4>(N);
-    b.tile_rng = c.take<int2>((size_t)tiles_x(p) * tiles_y(p) * 2 * mc::kRunStride);
-    b.sp_rec = c.take<int4>((size_t)tiles_x(p) * tiles_y(p) * mc::spread_cap_of_side(tile_side(p)));
-    b.sp_cnt = c.take<int>((size_t)tiles_x(p) * tiles_y(p));
+    b.cell_alt = c.take<int>(2 * N);
+    b.frac_alt = c.take<float>(2 * N);
+    const ListCaps k = list_caps(p, n_part, share);
+    if (k.own > 0)
+      for (int j = 0; j < 2; ++j) {
+        b.tl_cnt[j] = c.take<int>(n_tiles_of(p) * mc::kListCounts);
+        b.tl_rec[j] = c.take<int4>(n_tiles_of(p) * k.stride());
+      }
     if (p.marker_offset > 0.f) b.d_marker = c.take<float>(2 * N);
     if (p.mdf_iters > 1) {
       b.U_d = c.take<float>(2 * N);
@@ -175,12 +255,14 @@ void carve_world_bufs(Carver& c, const sim_params& p, int n_part, WorldBufs& b) 
 
 struct Slot {
   bool used = false;
-  sim_params p{};
+  sim_params p{};               // with the tile side it runs with (with_side)
+  sim_params asked{};           // as given
   int n_fil = 0, n_part = 0, max_len = 0;
   std::vector<int> h_off;
   int* fil_offset = nullptr;
-  int* cell = nullptr;
+  int* cell = nullptr;          // positions before an even step (and after a run)
   float* frac = nullptr;
+  int list_share = kFullLists;  // size of the tile lists (list_caps)
   float* rest_angle = nullptr;
   float* rest_length = nullptr;
   float* amp = nullptr;
@@ -201,7 +283,7 @@ struct Slot {
   float* fbuf[2] = {nullptr, nullptr};
   float* u = nullptr;
   WorldBufs b;
-  int cur = 0;          // populations buffer that holds the state
+  int cur = 0;          // populations (and positions) buffer that holds the state
   int remaining = 0;    // host mirror of the steps left (batch)
   size_t pool_off = 0, pool_len = 0;
   bool needs_zero = false;   // cnt must be cleared before first use
@@ -245,10 +327,12 @@ mc::WorldDev world_desc(const Slot& s, int parity, const mc::Ctl* ctl_src, mc::C
     for (int k = 0; k <= mc::kMaxRadius; ++k) d.gtap[k] = k <= p.repulse_radius ? (float)(g[k] / sum) : 0.f;
   }
   d.fil_offset = s.fil_offset;
-  d.cell_in = s.cell;
-  d.frac_in = s.frac;
-  d.cell_out = s.cell;
-  d.frac_out = s.frac;
+  const int src = parity == 0 ? s.cur : 1 - s.cur;
+  const bool two = s.b.cell_alt != nullptr;      // two sets of positions (binned transfer)
+  d.cell_in = two && src ? s.b.cell_alt : s.cell;
+  d.frac_in = two && src ? s.b.frac_alt : s.frac;
+  d.cell_out = two && !src ? s.b.cell_alt : s.cell;
+  d.frac_out = two && !src ? s.b.frac_alt : s.frac;
   d.rest_angle = s.rest_angle;
   d.rest_length = s.rest_length;
   d.act_amp = s.amp;
@@ -273,7 +357,6 @@ mc::WorldDev world_desc(const Slot& s, int parity, const mc::Ctl* ctl_src, mc::C
   d.mdf_c = s.b.mdf_c;
   d.rho_j = s.b.rho_j;
   d.u_mdf = s.b.u_mdf;
-  const int src = parity == 0 ? s.cur : 1 - s.cur;
   d.f_src = s.fbuf[src];
   d.f_dst = s.fbuf[1 - src];
   d.u = (float2*)s.u;
@@ -292,20 +375,52 @@ mc::WorldDev world_desc(const Slot& s, int parity, const mc::Ctl* ctl_src, mc::C
   d.perm = s.b.perm;
   d.rec = s.b.rec;
   d.part = s.b.part;
-  d.bin_cnt = s.b.bin_cnt;
-  d.bin_fill = s.b.bin_fill;
-  d.bin_start = s.b.bin_start;
-  d.bin_start_next = s.b.bin_start;
-  d.bin_rec = s.b.bin_rec;
-  d.tile_rng = s.b.tile_rng;
-  d.sp_rec = s.b.sp_rec;
-  d.sp_cnt = s.b.sp_cnt;
+  const ListCaps k = list_caps(p, s.n_part, s.list_share);
+  k.set(d);
+  d.tl_rec = s.b.tl_rec[src];
+  d.tl_cnt = s.b.tl_cnt[src];
+  d.tl_rec_next = s.b.tl_rec[1 - src];
+  d.tl_cnt_next = s.b.tl_cnt[1 - src];
   return d;
+}
+
+// The state of a run with an odd number of steps, back from the alternate
+// buffers: the populations, and the positions where they alternate too.
+// skip (if not null): a device word that is set when the run did not happen.
+__global__ void k_copy_back(const int* skip, const float* f_src, float* f_dst, size_t nf, const int* cell_src,
+                            int* cell_dst, const float* frac_src, float* frac_dst, size_t n2) {
+  if (skip && *skip) return;
+  const size_t first = blockIdx.x * (size_t)blockDim.x + threadIdx.x, step = (size_t)gridDim.x * blockDim.x;
+  for (size_t i = first; i < n2; i += step) {
+    cell_dst[i] = cell_src[i];
+    frac_dst[i] = frac_src[i];
+  }
+  const float4* s4 = (const float4*)f_src;
+  float4* d4 = (float4*)f_dst;
+  const size_t n4 = ((uintptr_t)f_src % 16 || (uintptr_t)f_dst % 16) ? 0 : nf / 4;
+  for (size_t i = first; i < n4; i += step) d4[i] = s4[i];
+  for (size_t i = 4 * n4 + first; i < nf; i += step) f_dst[i] = f_src[i];
 }
 
 // Zero an int array with a kernel (never a memset node; see graph capture).
 __global__ void k_zero_i32(int* p, size_t n) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0;
+}
+
+// The launches of one step of every world of a table.
+void enqueue_step(const mc::WorldDev* d, const mc::Tables& tab, const mc::Grid& grid, hipStream_t s) {
+  mc::launch_prepare(d, tab, grid, s);
+  if (grid.fused) {
+    mc::launch_energy(d, tab, grid, s);
+    mc::launch_fluid_tiles(d, tab, grid, s);
+    return;
+  }
+  mc::launch_repulse(d, tab, grid, s);
+  mc::launch_spread(d, tab, grid, s);
+  mc::launch_mdf(d, tab, grid, s);
+  mc::launch_lbm(d, tab, grid, s);
+  mc::launch_energy(d, tab, grid, s);
+  mc::launch_integrate(d, tab, grid, s);
 }
 
 struct Engine {
@@ -464,12 +579,12 @@ struct Engine {
     for (int f = 0; f < mc::kTileFamilies; ++f) {
       if (n_tiles[f] > 0 && grid.tile_blocks[f] == 0) more = true;
       if (!fixed_grid)
-        grid.tile_blocks[f] = (int)n_tiles[f];        // one block per tile; 0: family not launched
+        grid.tile_blocks[f] = (int)align8(n_tiles[f]);   // one block per tile; 0: family not launched
       else if (n_tiles[f] > 0)
         grid.tile_blocks[f] = fixed_tile_blocks;      // stays launched once a world needed it
     }
     if (!fixed_grid) {
-      grid.item_blocks = (int)std::max<size_t>(1, n_items);
+      grid.item_blocks = (int)std::max<size_t>(1, align8(n_items));
       grid.node_blocks = (int)std::max<size_t>(1, n_packs);
       grid.scan_blocks = (int)std::max<size_t>(1, n_scan);
       grid.world_blocks = (int)std::max<size_t>(1, n_worlds);
@@ -479,6 +594,10 @@ struct Engine {
     for (const auto& sl : slots)
       if (sl.used && mode_of(sl.p) != mc::kBinned) any_node = true;
     more = more || (any_node && !grid.any_node);
+    bool any_lists = false;
+    for (const auto& sl : slots)
+      if (sl.used && sl.b.tl_cnt[0]) any_lists = true;
+    if (any_lists) grid.any_lists = 1;
     bool any_energy = false, any_markers = false;
     int mdf_max = 1;
     for (const auto& sl : slots) {
@@ -532,6 +651,17 @@ struct Engine {
       grid.max_radius = max_r;
       more = true;
     }
+    // one kernel for S4 - S7 while the tiles are few (a batch around the limit
+    // keeps its captured graphs until it is well past it)
+    const size_t slack = grid.fused || !fixed_grid ? 0 : 1;
+    const int fused = !any_node && !grid.any_node && any_binned && grid.tile_blocks[2] == 0 && mdf_max <= 1 &&
+                      grid.mdf_max <= 1 &&
+                      few_tiles(n_tiles[0] + slack * (kFusedTiles16 / 4), n_tiles[1] + slack * (kFusedTiles32 / 4),
+                                n_tiles[2]);
+    if (fused != grid.fused) {
+      grid.fused = fused;
+      more = true;
+    }
     grid.any_sorted |= any_sorted ? 1 : 0;
     grid.any_binned |= any_binned ? 1 : 0;
     grid.any_node |= any_node ? 1 : 0;
@@ -581,20 +711,7 @@ struct Engine {
     return SIM_OK;
   }
 
-  void enqueue_step(int parity, hipStream_t s) const { enqueue_step_with(desc[parity], grid, s); }
-
-  void enqueue_step_with(const mc::WorldDev* d, const mc::Grid& grid, hipStream_t s) const {
-    mc::launch_elastic(d, tab, grid, s);
-    mc::launch_markers(d, tab, grid, s);
-    mc::launch_sort(d, tab, grid, s);
-    mc::launch_filter(d, tab, grid, s);
-    mc::launch_repulse(d, tab, grid, s);
-    mc::launch_spread(d, tab, grid, s);
-    mc::launch_mdf(d, tab, grid, s);
-    mc::launch_lbm(d, tab, grid, s);
-    mc::launch_energy(d, tab, grid, s);
-    mc::launch_integrate(d, tab, grid, s);
-  }
+  void enqueue_step(int parity, hipStream_t s) const { ::enqueue_step(desc[parity], tab, grid, s); }
 
   sim_status capture(int steps, hipGraphExec_t* out) {
     hipGraph_t g = nullptr;
@@ -624,9 +741,9 @@ struct Engine {
   // tail step is launched directly with descriptor set A.
   sim_status run_steps(int n) {
     if (n <= 0) return SIM_OK;
-    // tile-bin counts of the current positions for the first step (each
-    // step's integrate then counts for the next)
-    mc::launch_bin_prepass(desc[0], tab, grid, stream);
+    // tile lists of the current positions for the first step (each step's
+    // integrate then makes the next one's)
+    mc::launch_list_prepass(desc[0], tab, grid, stream);
     if (n >= want_chunk && (!g_chunk || chunk_steps != want_chunk)) {
       if (g_chunk) hipGraphExecDestroy(g_chunk);
       g_chunk = nullptr;
@@ -675,20 +792,34 @@ struct sim_world {
 
 namespace {
 
-size_t world_table_bytes(const sim_params& p, int n_fil) {
-  const size_t ncell = (size_t)p.nx * p.ny;
-  size_t tiles[mc::kTileFamilies] = {0, 0, 0};
-  tiles[tile_family(p)] = (size_t)tiles_x(p) * tiles_y(p);
-  const size_t items = (ncell + mc::kCellsPerItem - 1) / mc::kCellsPerItem;
-  const size_t scans = (ncell + 1023) / 1024;
-  return Engine::table_bytes(1, std::max(n_fil, 1), tiles, items, scans);
-}
-
-size_t world_buf_bytes(const sim_params& p, int n_part) {
+size_t world_buf_bytes(const sim_params& p, int n_part, int share) {
   Carver c{nullptr};
   WorldBufs b;
-  carve_world_bufs(c, p, n_part, b);
+  carve_world_bufs(c, p, n_part, share, b);
   return c.off;
+}
+// With the least room for node records that is accepted (least_list_bytes).
+size_t least_buf_bytes(const sim_params& p, int n_part) {
+  const size_t without = world_buf_bytes(p, n_part, 0);
+  if (mode_of(p) != mc::kBinned) return without;
+  return without - 2 * align_up(2 * (size_t)std::max(n_part, 1) * 4) + least_list_bytes(p, n_part);
+}
+
+// Workspace bytes of n worlds (n = 1: sim_create) with tile lists of the given
+// share, or (share < 0) the least that is accepted.
+size_t worlds_bytes(const sim_params& asked, int n, const sim_arrays* arrays, int share) {
+  const sim_params p = share < 0 ? asked : with_side(asked, n);
+  const size_t ncell = (size_t)p.nx * p.ny;
+  size_t packs = 0, bufs = 0;
+  for (int i = 0; i < n; ++i) {
+    packs += std::max(arrays[i].n_filaments, 1);
+    bufs += share < 0 ? least_buf_bytes(p, arrays[i].n_particles) : world_buf_bytes(p, arrays[i].n_particles, share);
+  }
+  size_t tiles[mc::kTileFamilies] = {0, 0, 0};
+  tiles[tile_family(p)] = (size_t)n * n_tiles_of(p);
+  const size_t items = (size_t)n * ((ncell + mc::kCellsPerItem - 1) / mc::kCellsPerItem);
+  const size_t scans = (size_t)n * ((ncell + 1023) / 1024);
+  return Engine::table_bytes(n, packs, tiles, items, scans) + bufs;
 }
 
 sim_status read_offsets(const sim_arrays* a, hipStream_t stream, std::vector<int>& h) {
@@ -814,13 +945,16 @@ sim_status sim_workspace_size(const sim_params* p, int32_t n_filaments, int32_t 
   if (st) return st;
   if (!bytes) return fail(SIM_E_INVALID, "bytes is NULL");
   if (n_filaments < 0 || n_particles < 0) return fail(SIM_E_INVALID, "negative sizes");
-  *bytes = world_table_bytes(*p, n_filaments) + world_buf_bytes(*p, n_particles);
+  sim_arrays a{};
+  a.n_filaments = n_filaments;
+  a.n_particles = n_particles;
+  *bytes = std::max(worlds_bytes(*p, 1, &a, kFullLists), worlds_bytes(*p, 1, &a, -1));
   return SIM_OK;
 }
 
 // One world of a handle: validate and read its arrays' host-side facts
 // (offsets, branches, loops) and carve its buffers.
-static sim_status prepare_slot(const sim_params* p, const sim_arrays* a, hipStream_t s, Carver& c, Slot& sl) {
+static sim_status prepare_slot(const sim_params* p, const sim_arrays* a, int share, hipStream_t s, Carver& c, Slot& sl) {
   sim_status st;
   std::vector<int> h_off;
   if (a->n_filaments > 0) {
@@ -837,6 +971,7 @@ static sim_status prepare_slot(const sim_params* p, const sim_arrays* a, hipStre
                 max_len, mc::kMaxFilament);
   sl.used = true;
   sl.p = *p;
+  sl.asked = *p;
   sl.n_fil = a->n_filaments;
   sl.n_part = a->n_particles;
   sl.max_len = max_len;
@@ -861,15 +996,15 @@ static sim_status prepare_slot(const sim_params* p, const sim_arrays* a, hipStre
   sl.e_sensed = a->energy_sensed;
   sl.e_collected = a->energy_collected;
   if ((st = read_loops(a, s, &sl.any_loop))) return st;
-  carve_world_bufs(c, *p, a->n_particles, sl.b);
+  sl.list_share = share;
+  carve_world_bufs(c, *p, a->n_particles, share, sl.b);
   sl.fbuf[0] = a->f;
   sl.fbuf[1] = sl.b.f_alt;
   sl.u = a->u;
   return SIM_OK;
 }
 
-// Clear what a world's kernels expect to start at zero and build its tile
-// run tables.
+// Clear what a world's kernels expect to start at zero.
 static void init_slot_buffers(const Slot& sl, hipStream_t s) {
   const sim_params& p = sl.p;
   const size_t ncell = (size_t)p.nx * p.ny;
@@ -878,18 +1013,19 @@ static void init_slot_buffers(const Slot& sl, hipStream_t s) {
   if (sl.b.Fg) hipLaunchKernelGGL(k_zero_i32, dim3(256), dim3(256), 0, s, (int*)sl.b.Fg, 2 * ncell);
   if (sl.b.e_node)
     hipLaunchKernelGGL(k_zero_i32, dim3(64), dim3(256), 0, s, (int*)sl.b.e_node, (size_t)std::max(sl.n_part, 1));
-  if (sl.b.bin_cnt) {
-    const size_t nt = n_bins(p);
-    hipLaunchKernelGGL(k_zero_i32, dim3(64), dim3(256), 0, s, sl.b.bin_cnt, nt);
-    hipLaunchKernelGGL(k_zero_i32, dim3(64), dim3(256), 0, s, sl.b.bin_fill, nt);
-    mc::launch_tile_ranges(p.nx, p.ny, p.repulse_radius, tile_side(p), sl.b.tile_rng, s);
-    hipLaunchKernelGGL(k_zero_i32, dim3(64), dim3(256), 0, s, sl.b.sp_cnt, (size_t)tiles_x(p) * tiles_y(p));
-  }
 }
 
 // A handle over n worlds with the same parameters (n = 1: sim_create).
-static sim_status create_worlds(const sim_params* p, int n, const sim_arrays* arrays, void* workspace,
+static sim_status create_worlds(const sim_params* asked, int n, const sim_arrays* arrays, void* workspace,
                                 size_t ws_bytes, void* stream, sim_world** out) {
+  const sim_params side = with_side(*asked, n), *p = &side;
+  // the largest tile lists the workspace holds
+  int share = 0;
+  for (int k : kListShares) {
+    if (worlds_bytes(*asked, n, arrays, k) > ws_bytes) continue;
+    share = k;
+    break;
+  }
   hipStream_t s = (hipStream_t)stream;
   sim_world* w = new sim_world();
   w->arr = arrays[0];
@@ -912,10 +1048,11 @@ static sim_status create_worlds(const sim_params* p, int n, const sim_arrays* ar
   sim_status st;
   for (int i = 0; i < n; ++i) {
     Slot sl;
-    if ((st = prepare_slot(p, &arrays[i], s, c, sl))) {
+    if ((st = prepare_slot(p, &arrays[i], share, s, c, sl))) {
       delete w;
       return st;
     }
+    sl.asked = *asked;
     max_len = std::max(max_len, sl.max_len);
     e.slots.push_back(sl);
   }
@@ -948,8 +1085,7 @@ sim_status sim_create(const sim_params* p, const sim_arrays* a, void* workspace,
   if ((st = check_arrays(a))) return st;
   if (!out) return fail(SIM_E_INVALID, "out is NULL");
   if (!workspace || ((uintptr_t)workspace % kAlign)) return fail(SIM_E_WORKSPACE, "workspace must be 256-byte aligned");
-  size_t need = 0;
-  sim_workspace_size(p, a->n_filaments, a->n_particles, &need);
+  const size_t need = worlds_bytes(*p, 1, a, -1);
   if (ws_bytes < need) return fail(SIM_E_WORKSPACE, "workspace has %zu bytes, needs %zu", ws_bytes, need);
   return create_worlds(p, 1, a, workspace, ws_bytes, stream, out);
 }
@@ -958,18 +1094,9 @@ sim_status sim_set_workspace_size(const sim_params* p, int32_t n_worlds, const s
   sim_status st = check_params(p);
   if (st) return st;
   if (n_worlds < 1 || !arrays || !bytes) return fail(SIM_E_INVALID, "need n_worlds >= 1 and non-NULL arrays, bytes");
-  const size_t ncell = (size_t)p->nx * p->ny;
-  size_t packs = 0, bufs = 0;
-  for (int i = 0; i < n_worlds; ++i) {
+  for (int i = 0; i < n_worlds; ++i)
     if (arrays[i].n_filaments < 0 || arrays[i].n_particles < 0) return fail(SIM_E_INVALID, "negative sizes");
-    packs += std::max(arrays[i].n_filaments, 1);
-    bufs += world_buf_bytes(*p, arrays[i].n_particles);
-  }
-  size_t tiles[mc::kTileFamilies] = {0, 0, 0};
-  tiles[tile_family(*p)] = (size_t)n_worlds * tiles_x(*p) * tiles_y(*p);
-  const size_t items = (size_t)n_worlds * ((ncell + mc::kCellsPerItem - 1) / mc::kCellsPerItem);
-  const size_t scans = (size_t)n_worlds * ((ncell + 1023) / 1024);
-  *bytes = Engine::table_bytes(n_worlds, packs, tiles, items, scans) + bufs;
+  *bytes = std::max(worlds_bytes(*p, n_worlds, arrays, kFullLists), worlds_bytes(*p, n_worlds, arrays, -1));
   return SIM_OK;
 }
 
@@ -982,10 +1109,19 @@ sim_status sim_create_set(const sim_params* p, int32_t n_worlds, const sim_array
     if ((st = check_arrays(&arrays[i]))) return st;
   if (!out) return fail(SIM_E_INVALID, "out is NULL");
   if (!workspace || ((uintptr_t)workspace % kAlign)) return fail(SIM_E_WORKSPACE, "workspace must be 256-byte aligned");
-  size_t need = 0;
-  if ((st = sim_set_workspace_size(p, n_worlds, arrays, &need))) return st;
+  const size_t need = worlds_bytes(*p, n_worlds, arrays, -1);
   if (ws_bytes < need) return fail(SIM_E_WORKSPACE, "workspace has %zu bytes, needs %zu", ws_bytes, need);
   return create_worlds(p, n_worlds, arrays, workspace, ws_bytes, stream, out);
+}
+
+// Enqueue the copy of a world's populations and / or positions from the
+// alternate buffers into the caller's arrays.
+static void copy_back(const Slot& s, bool f, bool x, const int* skip, hipStream_t st) {
+  const size_t nf = f ? 9 * (size_t)s.p.nx * s.p.ny : 0, n2 = x ? 2 * (size_t)s.n_part : 0;
+  const size_t work = std::max(nf / 4, n2);
+  const int blocks = (int)std::min<size_t>(4096, work / 256 + 1);
+  hipLaunchKernelGGL(k_copy_back, dim3(blocks), dim3(256), 0, st, skip, (const float*)s.fbuf[1], s.fbuf[0], nf,
+                     (const int*)s.b.cell_alt, s.cell, (const float*)s.b.frac_alt, s.frac, n2);
 }
 
 static sim_status world_run(sim_world* w, int64_t t, int n) {
@@ -995,11 +1131,9 @@ static sim_status world_run(sim_world* w, int64_t t, int n) {
     if ((st = e.set_ctl(k, t, n))) return st;
   if ((st = e.run_steps(n))) return st;
   if (n & 1) {
-    // the state ended in the alternate populations buffers: copy them back
-    for (const Slot& s : e.slots) {
-      const size_t ncell = (size_t)s.p.nx * s.p.ny;
-      HIPCHK(hipMemcpyAsync(s.fbuf[0], s.fbuf[1], 9 * ncell * sizeof(float), hipMemcpyDeviceToDevice, e.stream));
-    }
+    // the state ended in the alternate buffers: copy them back
+    for (const Slot& s : e.slots) copy_back(s, true, s.b.cell_alt != nullptr, nullptr, e.stream);
+    HIPCHK(hipGetLastError());
   }
   return SIM_OK;
 }
@@ -1087,9 +1221,8 @@ sim_status sim_debug_substep(sim_world* w, int32_t which, int64_t t) {
   const mc::Grid& g = e.grid;
   switch (which) {
     case 0:
-      mc::launch_bin_prepass(d, e.tab, g, e.stream);
+      mc::launch_list_prepass(d, e.tab, g, e.stream);
       mc::launch_elastic(d, e.tab, g, e.stream);
-      mc::launch_markers(d, e.tab, g, e.stream);
       mc::launch_sort(d, e.tab, g, e.stream);
       break;
     case 1: mc::launch_filter(d, e.tab, g, e.stream); break;
@@ -1100,14 +1233,13 @@ sim_status sim_debug_substep(sim_world* w, int32_t which, int64_t t) {
       break;
     case 3: {
       mc::launch_lbm(d, e.tab, g, e.stream);
-      Slot& s = e.slots[0];
-      const size_t ncell = (size_t)s.p.nx * s.p.ny;
-      HIPCHK(hipMemcpyAsync(s.fbuf[0], s.fbuf[1], 9 * ncell * sizeof(float), hipMemcpyDeviceToDevice, e.stream));
+      copy_back(e.slots[0], true, false, nullptr, e.stream);
       break;
     }
     case 4:
       mc::launch_energy(d, e.tab, g, e.stream);
       mc::launch_integrate(d, e.tab, g, e.stream);
+      if (e.slots[0].b.cell_alt) copy_back(e.slots[0], false, true, nullptr, e.stream);
       break;
     default: return fail(SIM_E_INVALID, "unknown sub-step %d", which);
   }
@@ -1128,13 +1260,12 @@ sim_status sim_profile_steps(sim_world* w, int64_t t0, int32_t n_steps, float* m
   for (auto& x : fl) HIPCHK(hipEventCreate(&x));
   sim_status st = e.set_ctl(0, t0, n_steps);
   if (st) return st;
-  mc::launch_bin_prepass(e.desc[0], e.tab, e.grid, e.stream);
+  mc::launch_list_prepass(e.desc[0], e.tab, e.grid, e.stream);
   for (int k = 0; k < n_steps; ++k) {
     const mc::WorldDev* d = e.desc[k & 1];
     hipEvent_t* E = ev.data() + (size_t)k * (kGroups + 1);
     HIPCHK(hipEventRecord(E[0], e.stream));
     mc::launch_elastic(d, e.tab, e.grid, e.stream);
-    mc::launch_markers(d, e.tab, e.grid, e.stream);
     HIPCHK(hipEventRecord(E[1], e.stream));
     mc::launch_sort(d, e.tab, e.grid, e.stream);
     HIPCHK(hipEventRecord(E[2], e.stream));
@@ -1151,10 +1282,7 @@ sim_status sim_profile_steps(sim_world* w, int64_t t0, int32_t n_steps, float* m
     HIPCHK(hipEventRecord(E[6], e.stream));
     HIPCHK(hipGetLastError());
   }
-  if (n_steps & 1) {
-    const size_t ncell = (size_t)s.p.nx * s.p.ny;
-    HIPCHK(hipMemcpyAsync(s.fbuf[0], s.fbuf[1], 9 * ncell * sizeof(float), hipMemcpyDeviceToDevice, e.stream));
-  }
+  if (n_steps & 1) copy_back(s, true, s.b.cell_alt != nullptr, nullptr, e.stream);
   HIPCHK(hipStreamSynchronize(e.stream));
   for (int g = 0; g < kGroups; ++g) {
     double tot = 0.0;
@@ -1268,7 +1396,7 @@ struct NoallocLayout {
   size_t bytes = 0;
 };
 
-void carve_noalloc(char* base, const sim_params& p, int n_fil, int n_part, NoallocLayout& L) {
+void carve_noalloc(char* base, const sim_params& p, int n_fil, int n_part, int share, NoallocLayout& L) {
   Carver c{base};
   const size_t ncell = (size_t)p.nx * p.ny;
   L.desc = c.take<mc::WorldDev>(2);
@@ -1280,7 +1408,7 @@ void carve_noalloc(char* base, const sim_params& p, int n_fil, int n_part, Noall
   L.items = c.take<int2>((ncell + mc::kCellsPerItem - 1) / mc::kCellsPerItem);
   L.scan = c.take<int2>((ncell + 1023) / 1024);
   L.wlist = c.take<int2>(1);
-  carve_world_bufs(c, p, n_part, L.b);
+  carve_world_bufs(c, p, n_part, share, L.b);
   L.bytes = c.off;
 }
 
@@ -1337,14 +1465,6 @@ __global__ void k_noalloc_counts(NoallocLayout L, int n_packs, int n_tiles, int 
   if (!ok) L.ctl[0].remaining = 0;
 }
 
-// The step's populations back into the caller's array (skipped if the step
-// did not run).
-__global__ void k_noalloc_copy_back(const int* err, const float* src, float* dst, size_t n) {
-  if (*err) return;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-    dst[i] = src[i];
-}
-
 __global__ void k_noalloc_status(const int* err, const unsigned* flags, int32_t* status) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
   const unsigned f = *flags;
@@ -1355,22 +1475,30 @@ __global__ void k_noalloc_status(const int* err, const unsigned* flags, int32_t*
 
 extern "C" {
 
-sim_status sim_step_noalloc(const sim_params* p, const sim_arrays* a, int64_t t, int32_t* status, void* stream) {
-  sim_status st = check_params(p);
+sim_status sim_step_noalloc(const sim_params* asked, const sim_arrays* a, int64_t t, int32_t* status, void* stream) {
+  sim_status st = check_params(asked);
   if (st) return st;
+  const sim_params side = with_side(*asked, 1), *p = &side;
   if ((st = check_arrays(a))) return st;
   if (a->fil_parent) return fail(SIM_E_INVALID, "sim_step_noalloc does not take branched worlds (fil_parent)");
   NoallocLayout L;
-  carve_noalloc(nullptr, *p, a->n_filaments, a->n_particles, L);
-  if (L.bytes > kScratchBytes)
-    return fail(SIM_E_WORKSPACE, "world needs %zu bytes of scratch; sim_step_noalloc holds %zu", L.bytes,
-                kScratchBytes);
+  carve_noalloc(nullptr, *asked, a->n_filaments, a->n_particles, 0, L);
+  const size_t need = L.bytes - world_buf_bytes(*asked, a->n_particles, 0) + least_buf_bytes(*asked, a->n_particles);
+  if (need > kScratchBytes)
+    return fail(SIM_E_WORKSPACE, "world needs %zu bytes of scratch; sim_step_noalloc holds %zu", need, kScratchBytes);
+  int share = 0;                                  // the largest tile lists the array holds
+  for (int k : kListShares) {
+    carve_noalloc(nullptr, *p, a->n_filaments, a->n_particles, k, L);
+    share = k;
+    if (L.bytes <= kScratchBytes) break;
+  }
   void* base = nullptr;
   if ((st = scratch_address(&base))) return st;
-  carve_noalloc((char*)base, *p, a->n_filaments, a->n_particles, L);
+  L = NoallocLayout();
+  carve_noalloc((char*)base, *p, a->n_filaments, a->n_particles, share, L);
   hipStream_t s = (hipStream_t)stream;
   const size_t ncell = (size_t)p->nx * p->ny;
-  const size_t nt = n_bins(*p);
+  const size_t nt = n_tiles_of(*p);
   const int n_items = (int)((ncell + mc::kCellsPerItem - 1) / mc::kCellsPerItem);
   const int n_scan = (int)((ncell + 1023) / 1024);
   const int n_fil = a->n_filaments, n_part = a->n_particles;
@@ -1397,6 +1525,7 @@ sim_status sim_step_noalloc(const sim_params* p, const sim_arrays* a, int64_t t,
   sl.e_sensed = a->energy_sensed;
   sl.e_collected = a->energy_collected;
   sl.b = L.b;
+  sl.list_share = share;
   sl.fbuf[0] = a->f;
   sl.fbuf[1] = L.b.f_alt;
   sl.u = a->u;
@@ -1422,14 +1551,16 @@ sim_status sim_step_noalloc(const sim_params* p, const sim_arrays* a, int64_t t,
   mc::Grid g{};
   g.pack = 1024;                                  // one filament (<= 1024 nodes) per pack
   g.node_blocks = std::max(1, std::min(n_fil, 8192));
-  g.tile_blocks[fam] = (int)std::max<size_t>(1, nt);
-  g.item_blocks = std::max(1, n_items);
+  g.tile_blocks[fam] = (int)align8(std::max<size_t>(1, nt));
+  g.item_blocks = (int)align8(std::max(1, n_items));
   g.scan_blocks = std::max(1, n_scan);
   g.world_blocks = 1;
   const int mode = mode_of(*p);
   g.any_sorted = mode == mc::kSorted;
   g.any_binned = mode == mc::kBinned;
   g.any_node = mode != mc::kBinned;
+  g.any_lists = L.b.tl_cnt[0] != nullptr;
+  g.fused = mode == mc::kBinned && p->mdf_iters <= 1 && few_tiles(fam == 0 ? nt : 0, fam == 1 ? nt : 0, fam == 2 ? nt : 0);
   g.max_radius = p->repulse_radius;
   g.any_energy = p->energy_rate > 0.f && a->energy ? 1 : 0;
   g.any_markers = L.b.d_marker ? 1 : 0;
@@ -1444,30 +1575,14 @@ sim_status sim_step_noalloc(const sim_params* p, const sim_arrays* a, int64_t t,
   if (L.b.cnt) hipLaunchKernelGGL(k_zero_i32, dim3(256), dim3(256), 0, s, L.b.cnt, ncell);
   if (L.b.e_node)
     hipLaunchKernelGGL(k_zero_i32, dim3(64), dim3(256), 0, s, (int*)L.b.e_node, (size_t)std::max(n_part, 1));
-  if (L.b.bin_cnt) {
-    hipLaunchKernelGGL(k_zero_i32, dim3(64), dim3(256), 0, s, L.b.bin_cnt, nt);
-    hipLaunchKernelGGL(k_zero_i32, dim3(64), dim3(256), 0, s, L.b.bin_fill, nt);
-    hipLaunchKernelGGL(k_zero_i32, dim3(64), dim3(256), 0, s, L.b.sp_cnt, nt);
-    mc::launch_tile_ranges(p->nx, p->ny, p->repulse_radius, tile_side(*p), L.b.tile_rng, s);
-  }
   const int setup_n = std::max({n_fil, n_items, n_scan, 1});
   hipLaunchKernelGGL(k_noalloc_setup, dim3((setup_n + 255) / 256), dim3(256), 0, s, d0, d1, L, a->fil_offset, n_fil,
                      n_part, n_items, n_scan, (long long)t);
   hipLaunchKernelGGL(k_noalloc_counts, dim3(1), dim3(64), 0, s, L, n_fil, (int)nt, fam, n_scan, n_items);
   // the step itself: the kernels sim_step runs, with parity-0 descriptors
-  mc::launch_bin_prepass(L.desc, tab, g, s);
-  mc::launch_elastic(L.desc, tab, g, s);
-  mc::launch_markers(L.desc, tab, g, s);
-  mc::launch_sort(L.desc, tab, g, s);
-  mc::launch_filter(L.desc, tab, g, s);
-  mc::launch_repulse(L.desc, tab, g, s);
-  mc::launch_spread(L.desc, tab, g, s);
-  mc::launch_mdf(L.desc, tab, g, s);
-  mc::launch_lbm(L.desc, tab, g, s);
-  mc::launch_energy(L.desc, tab, g, s);
-  mc::launch_integrate(L.desc, tab, g, s);
-  hipLaunchKernelGGL(k_noalloc_copy_back, dim3(std::min<size_t>(2048, (9 * ncell + 255) / 256)), dim3(256), 0, s,
-                     L.err, (const float*)L.b.f_alt, a->f, 9 * ncell);
+  mc::launch_list_prepass(L.desc, tab, g, s);
+  enqueue_step(L.desc, tab, g, s);
+  copy_back(sl, true, L.b.cell_alt != nullptr, L.err, s);
   if (status) hipLaunchKernelGGL(k_noalloc_status, dim3(1), dim3(64), 0, s, L.err, L.flags, status);
   HIPCHK(hipGetLastError());
   return SIM_OK;
@@ -1556,8 +1671,7 @@ namespace {
 // Layout of the backward workspace for segments of up to m steps.
 struct AdjLayout {
   int m = 0;
-  size_t N = 0, ncell = 0, nt = 0;
-  int* cell[2] = {};           // unused placeholders for alignment bookkeeping
+  size_t N = 0, ncell = 0;
   size_t bytes = 0;
   // per tape slot
   std::vector<int*> x_cell;    // m+1 slots of [2][N]
@@ -1565,12 +1679,8 @@ struct AdjLayout {
   std::vector<float*> g;       // m+1 slots of [9][ncell]
   std::vector<float2*> grad, Fg, u;   // m slots of [ncell]
   std::vector<float*> F;       // m slots of [2][N]
-  std::vector<int*> bstart;    // m + 1 slots of [nt+1] (step j's bins; slot m is scratch)
-  std::vector<int4*> brec;     // m slots of [N]
-  std::vector<int4*> sprec;    // m slots of the spread lists the recomputed filter writes
-  std::vector<int*> spcnt;     // m slots of their lengths
-  int* bin_cnt = nullptr;
-  int* bin_fill = nullptr;
+  std::vector<int4*> tl_rec;   // m slots of the step's tile lists
+  std::vector<int*> tl_cnt;
   float* xbar[2] = {};
   float* gbar[2] = {};
   float2* ubar = nullptr;
@@ -1593,11 +1703,10 @@ struct AdjLayout {
   float* dbar_m = nullptr;           // [2][N] (with MDF)
 };
 
-void carve_adj(Carver& c, const sim_params& p, int n_part, int m, AdjLayout& L) {
+void carve_adj(Carver& c, const sim_params& p, int n_part, int m, int share, AdjLayout& L) {
   L.m = m;
   L.N = std::max(n_part, 1);
   L.ncell = (size_t)p.nx * p.ny;
-  L.nt = n_bins(p);
   L.x_cell.resize(m + 1);
   L.x_frac.resize(m + 1);
   L.g.resize(m + 1);
@@ -1610,24 +1719,19 @@ void carve_adj(Carver& c, const sim_params& p, int n_part, int m, AdjLayout& L) 
   L.Fg.resize(m);
   L.u.resize(m);
   L.F.resize(m);
-  L.bstart.resize(m + 1);
-  L.brec.resize(m);
-  L.sprec.resize(m);
-  L.spcnt.resize(m);
-  const size_t ntiles = (size_t)tiles_x(p) * tiles_y(p);
+  L.tl_rec.assign(m, nullptr);
+  L.tl_cnt.assign(m, nullptr);
+  const ListCaps caps = list_caps(p, n_part, share);
   for (int j = 0; j < m; ++j) {
     L.grad[j] = c.take<float2>(L.ncell);
     L.Fg[j] = c.take<float2>(L.ncell);
     L.u[j] = c.take<float2>(L.ncell);
     L.F[j] = c.take<float>(2 * L.N);
-    L.bstart[j] = c.take<int>(L.nt + 1);
-    L.brec[j] = c.take<int4>(L.N);
-    L.sprec[j] = c.take<int4>(ntiles * mc::spread_cap_of_side(tile_side(p)));
-    L.spcnt[j] = c.take<int>(ntiles);
+    if (caps.own > 0) {
+      L.tl_cnt[j] = c.take<int>(n_tiles_of(p) * mc::kListCounts);
+      L.tl_rec[j] = c.take<int4>(n_tiles_of(p) * caps.stride());
+    }
   }
-  L.bstart[m] = c.take<int>(L.nt + 1);
-  L.bin_cnt = c.take<int>(L.nt);
-  L.bin_fill = c.take<int>(L.nt);
   for (int k = 0; k < 2; ++k) {
     L.xbar[k] = c.take<float>(2 * L.N);
     L.gbar[k] = c.take<float>(9 * L.ncell);
@@ -1667,22 +1771,35 @@ struct AdjShared {
   mc::AdjDev* adj = nullptr;
 };
 
-static size_t carve_backward(Carver& c, const Engine& e, int m, std::vector<AdjLayout>& Ls, AdjShared& S) {
+static size_t carve_backward(Carver& c, const Engine& e, int m, int share, std::vector<AdjLayout>& Ls, AdjShared& S) {
   const size_t nw = e.slots.size();
   Ls.assign(nw, AdjLayout());
-  for (size_t w = 0; w < nw; ++w) carve_adj(c, e.slots[w].p, e.slots[w].n_part, m, Ls[w]);
+  for (size_t w = 0; w < nw; ++w) carve_adj(c, e.slots[w].p, e.slots[w].n_part, m, share, Ls[w]);
   S.desc = c.take<mc::WorldDev>((size_t)m * nw);
   S.adj = c.take<mc::AdjDev>((size_t)2 * m * nw);
   return c.off;
 }
 
-sim_status sim_backward_workspace_size(const sim_world* w, int32_t ckpt_every, size_t* bytes) {
-  if (!w || !bytes) return fail(SIM_E_INVALID, "NULL argument");
-  if (ckpt_every < 1) return fail(SIM_E_INVALID, "ckpt_every must be >= 1");
+// Bytes of the adjoint workspace with tape lists of the given share, or
+// (share < 0) the least that is accepted.
+static size_t backward_bytes(const Engine& e, int m, int share) {
   Carver c{nullptr};
   std::vector<AdjLayout> Ls;
   AdjShared S;
-  *bytes = carve_backward(c, w->eng, ckpt_every, Ls, S);
+  size_t bytes = carve_backward(c, e, m, std::max(share, 0), Ls, S);
+  if (share < 0)
+    for (const Slot& s : e.slots) {
+      const size_t nt = n_tiles_of(s.asked);
+      bytes += m * (least_list_bytes(s.asked, s.n_part) - 2 * align_up(nt * 4)) + align_up((nt + 1) * 4) +
+               2 * align_up(nt * 4) - m * align_up(nt * 128);
+    }
+  return bytes;
+}
+
+sim_status sim_backward_workspace_size(const sim_world* w, int32_t ckpt_every, size_t* bytes) {
+  if (!w || !bytes) return fail(SIM_E_INVALID, "NULL argument");
+  if (ckpt_every < 1) return fail(SIM_E_INVALID, "ckpt_every must be >= 1");
+  *bytes = std::max(backward_bytes(w->eng, ckpt_every, kFullLists), backward_bytes(w->eng, ckpt_every, -1));
   return SIM_OK;
 }
 
@@ -1700,19 +1817,26 @@ sim_status sim_backward(sim_world* w, int64_t t0, int32_t n_steps, int32_t ckpt_
                   mode_of(s.p) == mc::kSorted ? "SORTED" : "DIRECT");
     if (s.p.pbd_iters > 8) return fail(SIM_E_INVALID, "the adjoint supports at most 8 PBD iterations");
   }
-  size_t need = 0;
-  sim_backward_workspace_size(w, ckpt_every, &need);
+  const size_t need = backward_bytes(e, ckpt_every, -1);
   if (adj_ws_bytes < need) return fail(SIM_E_WORKSPACE, "adjoint workspace has %zu bytes, needs %zu", adj_ws_bytes, need);
+  int share = 0;                         // the largest tape lists the workspace holds
+  for (int k : kListShares) {
+    if (backward_bytes(e, ckpt_every, k) > adj_ws_bytes) continue;
+    share = k;
+    break;
+  }
   Carver c{(char*)adj_ws};
   std::vector<AdjLayout> Ls;
   AdjShared S;
-  carve_backward(c, e, ckpt_every, Ls, S);
+  carve_backward(c, e, ckpt_every, share, Ls, S);
   const int m_max = ckpt_every;
   const int nseg = (n_steps + ckpt_every - 1) / ckpt_every;
   const int K = std::max(e.slots[0].p.mdf_iters, 1);
   hipStream_t st = e.stream;
   mc::Grid g = e.grid;
   g.any_binned = 1;
+  g.any_lists = Ls[0].tl_cnt[0] != nullptr;
+  for (const AdjLayout& L : Ls) g.any_lists |= L.tl_cnt[0] != nullptr;
   g.pbd_max = 0;
   for (const Slot& s : e.slots) g.pbd_max = std::max(g.pbd_max, s.p.pbd_iters);
   g.any_sorted = 0;
@@ -1743,13 +1867,13 @@ sim_status sim_backward(sim_world* w, int64_t t0, int32_t n_steps, int32_t ckpt_
       d.Fg = L.Fg[j];
       d.u = L.u[j];
       d.fel = L.F[j];
-      d.bin_cnt = L.bin_cnt;
-      d.bin_fill = L.bin_fill;
-      d.bin_start = L.bstart[j];
-      d.bin_start_next = L.bstart[j + 1];
-      d.bin_rec = L.brec[j];
-      d.sp_rec = L.sprec[j];                   // step j's spread lists, for the adjoint spreads
-      d.sp_cnt = L.spcnt[j];
+      const ListCaps caps = list_caps(e.slots[k].p, e.slots[k].n_part, share);
+      caps.set(d);
+      d.keep_force = 1;
+      d.tl_rec = L.tl_rec[j];                  // step j's lists, for the adjoint too; the last step makes none
+      d.tl_cnt = L.tl_cnt[j];
+      d.tl_rec_next = j + 1 < m_max ? L.tl_rec[j + 1] : nullptr;
+      d.tl_cnt_next = j + 1 < m_max ? L.tl_cnt[j + 1] : nullptr;
       d.ctl_src = L.ctl + j;                   // the fluid kernel of step j advances it into j + 1
       d.ctl_dst = L.ctl + j + 1;
       d.s = nullptr;
@@ -1796,12 +1920,10 @@ sim_status sim_backward(sim_world* w, int64_t t0, int32_t n_steps, int32_t ckpt_
   HIPCHK(hipMemcpyAsync(S.desc, e.pinned, dbytes, hipMemcpyHostToDevice, st));
   HIPCHK(hipMemcpyAsync(S.adj, e.pinned + dbytes, abytes, hipMemcpyHostToDevice, st));
   HIPCHK(hipEventRecord(e.upload_done, st));
-  // dL/dx_T from the caller, dL/dg_T = 0, empty bins
+  // dL/dx_T from the caller, dL/dg_T = 0
   for (int k = 0; k < nw; ++k) {
     const AdjLayout& L = Ls[k];
     const size_t N = e.slots[k].n_part;
-    hipLaunchKernelGGL(k_zero_i32, dim3(64), dim3(256), 0, st, L.bin_cnt, L.nt);
-    hipLaunchKernelGGL(k_zero_i32, dim3(64), dim3(256), 0, st, L.bin_fill, L.nt);
     if (N) HIPCHK(hipMemcpyAsync(L.xbar[0], g_pos + 2 * noff[k], 2 * N * 4, hipMemcpyDeviceToDevice, st));
     hipLaunchKernelGGL(k_zero_i32, dim3(256), dim3(256), 0, st, (int*)L.gbar[0], 9 * L.ncell);
   }
@@ -1825,8 +1947,8 @@ sim_status sim_backward(sim_world* w, int64_t t0, int32_t n_steps, int32_t ckpt_
       mc::launch_set_ctl(L.ctl, t0 + k0, m, st);
     }
     // recompute the segment forward for every world, writing each step's fields to the tapes
-    mc::launch_bin_prepass(S.desc, e.tab, g, st);
-    for (int j = 0; j < m; ++j) e.enqueue_step_with(S.desc + (size_t)j * nw, g, st);
+    mc::launch_list_prepass(S.desc, e.tab, g, st);
+    for (int j = 0; j < m; ++j) enqueue_step(S.desc + (size_t)j * nw, e.tab, g, st);
     HIPCHK(hipGetLastError());
     // reverse the segment step by step, every world in the same launches
     for (int j = m - 1; j >= 0; --j) {
@@ -1864,7 +1986,7 @@ struct BatchWorldLayout {
   size_t bytes = 0;
 };
 
-void carve_batch_world(Carver& c, const sim_params& p, int n_fil, int n_part, Slot& s) {
+void carve_batch_world(Carver& c, const sim_params& p, int n_fil, int n_part, int share, Slot& s) {
   const size_t ncell = (size_t)p.nx * p.ny;
   const size_t N = std::max(n_part, 1), F = std::max(n_fil, 1);
   s.fil_offset = c.take<int>(F + 1);
@@ -1887,8 +2009,18 @@ void carve_batch_world(Carver& c, const sim_params& p, int n_fil, int n_part, Sl
   }
   s.fbuf[0] = c.take<float>(9 * ncell);
   s.u = c.take<float>(2 * ncell);
-  carve_world_bufs(c, p, n_part, s.b);
+  s.list_share = share;
+  carve_world_bufs(c, p, n_part, share, s.b);
   s.fbuf[1] = s.b.f_alt;
+}
+
+// Pool bytes of a world with tile lists of the given share, or (share < 0) the
+// least a world takes (sim_batch_world_bytes).
+size_t batch_world_bytes(const sim_params& p, int n_fil, int n_part, int share) {
+  Carver c{nullptr};
+  Slot s;
+  carve_batch_world(c, p, n_fil, n_part, std::max(share, 0), s);
+  return share >= 0 ? c.off : c.off - world_buf_bytes(p, n_part, 0) + least_buf_bytes(p, n_part);
 }
 
 bool pool_alloc(sim_batch* b, size_t bytes, size_t* off) {
@@ -1929,10 +2061,7 @@ sim_status sim_batch_world_bytes(const sim_params* p, int32_t n_filaments, int32
   sim_status st = check_params(p);
   if (st) return st;
   if (!bytes || n_filaments < 0 || n_particles < 0) return fail(SIM_E_INVALID, "bad argument");
-  Carver c{nullptr};
-  Slot s;
-  carve_batch_world(c, *p, n_filaments, n_particles, s);
-  *bytes = c.off;
+  *bytes = batch_world_bytes(*p, n_filaments, n_particles, -1);
   return SIM_OK;
 }
 
@@ -2037,13 +2166,26 @@ sim_status sim_batch_admit(sim_batch* b, const sim_params* p, const sim_arrays* 
     return fail(SIM_E_INVALID, "batched filaments (with those hanging from them) are limited to %d nodes", e.grid.pack);
   bool any_loop = false;
   if ((st = read_loops(init, e.stream, &any_loop))) return st;
-  size_t bytes = 0;
-  sim_batch_world_bytes(p, init->n_filaments, init->n_particles, &bytes);
+  // full tile lists while that leaves half of the pool free; then what the
+  // world's least share of it (sim_batch_world_bytes) holds
+  const size_t least = batch_world_bytes(*p, init->n_filaments, init->n_particles, -1);
+  size_t bytes = batch_world_bytes(*p, init->n_filaments, init->n_particles, kFullLists);
+  int share = kFullLists;
+  size_t free_bytes = 0;
+  for (const auto& f : b->free_list) free_bytes += f.second;
   size_t off = 0;
-  if (!pool_alloc(b, bytes, &off)) return fail(SIM_E_WORKSPACE, "pool exhausted (world needs %zu bytes)", bytes);
+  if (free_bytes < bytes + b->pool_bytes / 2 || bytes < least || !pool_alloc(b, bytes, &off)) {
+    for (int k : kListShares) {
+      share = k;
+      if (batch_world_bytes(*p, init->n_filaments, init->n_particles, k) <= least) break;
+    }
+    bytes = least;
+    if (!pool_alloc(b, bytes, &off)) return fail(SIM_E_WORKSPACE, "pool exhausted (world needs %zu bytes)", bytes);
+  }
   Slot s;
   s.used = true;
   s.p = *p;
+  s.asked = *p;
   s.n_fil = init->n_filaments;
   s.n_part = init->n_particles;
   s.max_len = max_len;
@@ -2051,7 +2193,7 @@ sim_status sim_batch_admit(sim_batch* b, const sim_params* p, const sim_arrays* 
   s.pool_off = off;
   s.pool_len = bytes;
   Carver c{b->pool + off};
-  carve_batch_world(c, *p, s.n_fil, s.n_part, s);
+  carve_batch_world(c, *p, s.n_fil, s.n_part, share, s);
   const size_t N = s.n_part, F = s.n_fil, ncell = (size_t)p->nx * p->ny;
   auto cp = [&](void* dst, const void* src, size_t by) -> sim_status {
     if (by) HIPCHK(hipMemcpyAsync(dst, src, by, hipMemcpyDeviceToDevice, e.stream));
@@ -2096,13 +2238,6 @@ sim_status sim_batch_admit(sim_batch* b, const sim_params* p, const sim_arrays* 
   if (s.b.cnt) hipLaunchKernelGGL(k_zero_i32, dim3(256), dim3(256), 0, e.stream, s.b.cnt, ncell);
   if (s.b.s) hipLaunchKernelGGL(k_zero_i32, dim3(256), dim3(256), 0, e.stream, (int*)s.b.s, ncell);
   if (s.b.Fg) hipLaunchKernelGGL(k_zero_i32, dim3(256), dim3(256), 0, e.stream, (int*)s.b.Fg, 2 * ncell);
-  if (s.b.bin_cnt) {
-    const size_t nt = n_bins(*p);
-    hipLaunchKernelGGL(k_zero_i32, dim3(64), dim3(256), 0, e.stream, s.b.bin_cnt, nt);
-    hipLaunchKernelGGL(k_zero_i32, dim3(64), dim3(256), 0, e.stream, s.b.bin_fill, nt);
-    mc::launch_tile_ranges(p->nx, p->ny, p->repulse_radius, tile_side(*p), s.b.tile_rng, e.stream);
-    hipLaunchKernelGGL(k_zero_i32, dim3(64), dim3(256), 0, e.stream, s.b.sp_cnt, (size_t)tiles_x(*p) * tiles_y(*p));
-  }
   hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, e.stream, (int*)(e.flags + w), (size_t)1);
   HIPCHK(hipGetLastError());
   s.cur = 0;
@@ -2149,8 +2284,9 @@ sim_status sim_batch_retire(sim_batch* b, int32_t slot, const sim_arrays* out) {
   if (out) {
     if (out->n_particles != s.n_part) return fail(SIM_E_INVALID, "output arrays have the wrong size");
     if (N) {
-      HIPCHK(hipMemcpyAsync(out->cell, s.cell, 2 * N * 4, hipMemcpyDeviceToDevice, e.stream));
-      HIPCHK(hipMemcpyAsync(out->frac, s.frac, 2 * N * 4, hipMemcpyDeviceToDevice, e.stream));
+      const bool alt = s.cur == 1 && s.b.cell_alt;
+      HIPCHK(hipMemcpyAsync(out->cell, alt ? s.b.cell_alt : s.cell, 2 * N * 4, hipMemcpyDeviceToDevice, e.stream));
+      HIPCHK(hipMemcpyAsync(out->frac, alt ? s.b.frac_alt : s.frac, 2 * N * 4, hipMemcpyDeviceToDevice, e.stream));
     }
     if (out->f) HIPCHK(hipMemcpyAsync(out->f, s.fbuf[s.cur], 9 * ncell * 4, hipMemcpyDeviceToDevice, e.stream));
     if (out->u) HIPCHK(hipMemcpyAsync(out->u, s.u, 2 * ncell * 4, hipMemcpyDeviceToDevice, e.stream));
