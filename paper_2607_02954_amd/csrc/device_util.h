@@ -334,17 +334,6 @@ struct AggGroup {
   }
 };
 
-// Wavefront-aggregated atomic increment: lanes that target the same counter
-// are served by one atomic from a leader lane.  Returns, for lanes with `has`,
-// a distinct slot (the counter's old value plus the lane's rank among the
-// matching lanes).  Must be called by every lane of the wavefront.
-static __device__ __forceinline__ int agg_atomic_inc(MC_GLOBAL int* counters, int key, bool has) {
-  const AggGroup g(key, has);
-  int base = 0;
-  if (has && g.leader == (int)__lane_id()) base = atomicAdd((int*)(counters + key), g.count);
-  return __shfl(base, g.leader) + g.rank;
-}
-
 // Block-wide exclusive scan of one int per thread (NT threads), wave
 // shuffles plus one LDS exchange (s_wave holds NT/64 ints).  Returns the
 // exclusive prefix; *total gets the block sum.  All threads must call it.
@@ -671,11 +660,6 @@ struct WindowLoads {
     }
   }
 };
-template <int NT, int SIDE>
-static __device__ __forceinline__ void stage_window(const MC_GLOBAL vf2* f, int nx, int ny, int ox, int oy, vf2* st) {
-  WindowLoads<NT, SIDE>(f, nx, ny, ox, oy).store(st);
-}
-
 // Tile spread: for every node whose 4x4 support meets the needed cells
 // [x0 - LO, x0 + tw + HI) x [y0 - LO, y0 + th + HI) of the tile [x0, x0 + tw) x
 // [y0, y0 + th), add scale * W(c - x_i) * (v[i], v[N + i]) to the window

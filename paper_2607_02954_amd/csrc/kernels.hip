@@ -15,6 +15,7 @@
 //                 contiguous cells; exports u
 //   k_integrate   S7 gather u at the nodes and move them; appends every node
 //                 to the tile lists of the next step (binned transfer)
+//   k_fluid_tile  S4 - S7 of binned worlds of few tiles in one kernel
 //
 // Particle -> grid transfer has three modes, chosen per world:
 //   binned  every grid tile has a list of the nodes it needs (its own and those
@@ -40,11 +41,10 @@
 
 namespace mc {
 
-
 // ---------------------------------------------------------------------------
 // S0 + S1: actuation and PBD elastic force.  Then, by transfer mode: the
-// node's record in its home-tile bin (binned), home-cell key and rank
-// (sorted) or the density deposit with global atomics (direct).
+// home-cell key and rank (sorted) or the density deposit with global atomics
+// (direct).
 // ---------------------------------------------------------------------------
 // Two-layer marker displacement of node gi (markers at x +- d): offset times
 // the unit normal of the tangent x_b - x_a, a and b its neighbours (or the node
@@ -2398,12 +2398,16 @@ static void launch_prepare_t(const WorldDev* W, const Tables& T, const Grid& G, 
 // suit a tile ill: up to one block per CU the launch saved counts for more (3000 nodes on
 // 128^2, 64 tiles: 27.0 -> 21.5 us per step), past it the separate kernels do
 // (200,000 on 1200^2: 68.4 against 90.2).
-constexpr int kWideTiles = 256;
+// Otherwise one launch, except where either role fills the chip for many rounds
+// by itself: 1,048,576 nodes on 2048^2 (4096 tiles, 5451 packs) 208.3 us per step
+// with one launch, 202.9 with two; 262,144 (1360 packs) 153.9 and 157.1; 1024^2
+// (1024 tiles) 56.2 and 58.1.
+constexpr int kWideTiles = 256, kMergedBlocks = 3000;
 void launch_prepare(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s) {
   const int families = (G.tile_blocks[0] > 0) + (G.tile_blocks[1] > 0) + (G.tile_blocks[2] > 0);
   const int tiles = G.tile_blocks[0] + G.tile_blocks[1] + G.tile_blocks[2];
   const bool merge = !G.any_node && G.any_binned && families == 1 && (G.tile_blocks[2] == 0 || G.pack == 1024) &&
-                     (G.pack == 256 || tiles <= kWideTiles);
+                     (G.pack == 256 ? std::min(tiles, G.node_blocks) <= kMergedBlocks : tiles <= kWideTiles);
   if (!merge) {
     launch_elastic(W, T, G, s);
     launch_sort(W, T, G, s);
