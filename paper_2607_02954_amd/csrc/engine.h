@@ -240,7 +240,8 @@ void launch_sort(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t 
 void launch_filter(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);
 void launch_repulse(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);
 void launch_spread(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);
-void launch_fluid_tiles(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);   // S4 - S7 (Grid::fused)
+// S4 - S7 (Grid::fused); keep: write the velocity whether or not it is the world's last step
+void launch_fluid_tiles(const WorldDev* W, const Tables& T, const Grid& G, bool keep, hipStream_t s);
 void launch_lbm(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);
 // the same launch with the dispatch's own start and end timestamps in two events
 void launch_lbm_timed(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s, hipEvent_t start,

@@ -1666,7 +1666,7 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_integrate_tile(cons
 // The arithmetic is that of the separate kernels.
 // ---------------------------------------------------------------------------
 template <int TILE, bool MK>
-__global__ __launch_bounds__(TileCfg<TILE>::kThreads, MK ? 3 : 4) void k_fluid_tile(const WorldDev* __restrict__ W, Tables T) {
+__global__ __launch_bounds__(TileCfg<TILE>::kThreads, MK ? 3 : 4) void k_fluid_tile(const WorldDev* __restrict__ W, Tables T, int keep) {
   constexpr int kE = MK ? 1 : 0, LO = 1 + kE, HI = 2 + kE;
   using SW = SpreadWin<TILE, LO, HI>;
   constexpr int kThreads = TileCfg<TILE>::kThreads;
@@ -1727,7 +1727,10 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads, MK ? 3 : 4) void k_fluid_t
       tile_spread_vec<TILE, true, false, LO, HI>(w, nodes, x0, y0, tw, th, 1.0f, s_fx, s_fy, s_g);
     __syncthreads();
     MC_GLOBAL float* dst = glb(w.f_dst);
-    const bool keep_u = w.keep_force || cs.remaining == 1;   // no later step of the call replaces it
+    // the velocity is written where no later step of the call replaces it: on
+    // the world's last step, and on the last of every launched group of steps
+    // of a batch, whose worlds can be retired with steps left
+    const bool keep_u = keep || w.keep_force || cs.remaining == 1;
     auto cell = [&](int i, const float* g) {
       const int k = (int)threadIdx.x + kThreads * i;
       if (k >= kCells) return;
@@ -2436,13 +2439,13 @@ void launch_spread(const WorldDev* W, const Tables& T, const Grid& G, hipStream_
   });
 }
 
-void launch_fluid_tiles(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s) {
+void launch_fluid_tiles(const WorldDev* W, const Tables& T, const Grid& G, bool keep, hipStream_t s) {
   const auto go = [&](auto tile) {
     constexpr int TL = decltype(tile)::value;
     const int blocks = G.tile_blocks[TileCfg<TL>::kFamily];
     if (blocks == 0) return;
-    if (!G.mk_only) k_fluid_tile<TL, false><<<blocks, TileCfg<TL>::kThreads, 0, s>>>(W, T);
-    if (G.any_markers) k_fluid_tile<TL, true><<<blocks, TileCfg<TL>::kThreads, 0, s>>>(W, T);
+    if (!G.mk_only) k_fluid_tile<TL, false><<<blocks, TileCfg<TL>::kThreads, 0, s>>>(W, T, keep);
+    if (G.any_markers) k_fluid_tile<TL, true><<<blocks, TileCfg<TL>::kThreads, 0, s>>>(W, T, keep);
   };
   go(std::integral_constant<int, 16>());
   go(std::integral_constant<int, 32>());

@@ -407,12 +407,13 @@ __global__ void k_zero_i32(int* p, size_t n) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0;
 }
 
-// The launches of one step of every world of a table.
-void enqueue_step(const mc::WorldDev* d, const mc::Tables& tab, const mc::Grid& grid, hipStream_t s) {
+// The launches of one step of every world of a table.  keep: the caller may
+// read the velocity after it although the worlds have steps left.
+void enqueue_step(const mc::WorldDev* d, const mc::Tables& tab, const mc::Grid& grid, bool keep, hipStream_t s) {
   mc::launch_prepare(d, tab, grid, s);
   if (grid.fused) {
     mc::launch_energy(d, tab, grid, s);
-    mc::launch_fluid_tiles(d, tab, grid, s);
+    mc::launch_fluid_tiles(d, tab, grid, keep, s);
     return;
   }
   mc::launch_repulse(d, tab, grid, s);
@@ -711,12 +712,16 @@ struct Engine {
     return SIM_OK;
   }
 
-  void enqueue_step(int parity, hipStream_t s) const { ::enqueue_step(desc[parity], tab, grid, s); }
+  // last: of a captured or directly launched group (a batch may be asked for
+  // its worlds' state after any of them; a world's own runs end on its last step)
+  void enqueue_step(int parity, bool last, hipStream_t s) const {
+    ::enqueue_step(desc[parity], tab, grid, last && fixed_grid, s);
+  }
 
   sim_status capture(int steps, hipGraphExec_t* out) {
     hipGraph_t g = nullptr;
     HIPCHK(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
-    for (int k = 0; k < steps; ++k) enqueue_step(k & 1, cap);
+    for (int k = 0; k < steps; ++k) enqueue_step(k & 1, k == steps - 1, cap);
     hipError_t le = hipGetLastError();
     hipError_t ee = hipStreamEndCapture(cap, &g);
     if (le != hipSuccess) {
@@ -765,7 +770,7 @@ struct Engine {
       left -= 2;
     }
     if (left == 1) {
-      enqueue_step(0, stream);
+      enqueue_step(0, true, stream);
       HIPCHK(hipGetLastError());
     }
     return SIM_OK;
@@ -1581,7 +1586,7 @@ sim_status sim_step_noalloc(const sim_params* asked, const sim_arrays* a, int64_
   hipLaunchKernelGGL(k_noalloc_counts, dim3(1), dim3(64), 0, s, L, n_fil, (int)nt, fam, n_scan, n_items);
   // the step itself: the kernels sim_step runs, with parity-0 descriptors
   mc::launch_list_prepass(L.desc, tab, g, s);
-  enqueue_step(L.desc, tab, g, s);
+  enqueue_step(L.desc, tab, g, false, s);
   copy_back(sl, true, L.b.cell_alt != nullptr, L.err, s);
   if (status) hipLaunchKernelGGL(k_noalloc_status, dim3(1), dim3(64), 0, s, L.err, L.flags, status);
   HIPCHK(hipGetLastError());
@@ -1948,7 +1953,7 @@ sim_status sim_backward(sim_world* w, int64_t t0, int32_t n_steps, int32_t ckpt_
     }
     // recompute the segment forward for every world, writing each step's fields to the tapes
     mc::launch_list_prepass(S.desc, e.tab, g, st);
-    for (int j = 0; j < m; ++j) enqueue_step(S.desc + (size_t)j * nw, e.tab, g, st);
+    for (int j = 0; j < m; ++j) enqueue_step(S.desc + (size_t)j * nw, e.tab, g, false, st);
     HIPCHK(hipGetLastError());
     // reverse the segment step by step, every world in the same launches
     for (int j = m - 1; j >= 0; --j) {
