@@ -1727,10 +1727,11 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads, MK ? 3 : 4) void k_fluid_t
       tile_spread_vec<TILE, true, false, LO, HI>(w, nodes, x0, y0, tw, th, 1.0f, s_fx, s_fy, s_g);
     __syncthreads();
     MC_GLOBAL float* dst = glb(w.f_dst);
-    // the velocity is written where no later step of the call replaces it: on
-    // the world's last step, and on the last of every launched group of steps
-    // of a batch, whose worlds can be retired with steps left
-    const bool keep_u = keep || w.keep_force || cs.remaining == 1;
+    // the velocity and the grid force are written where no later step of the
+    // call replaces them: on the world's last step, and the velocity on the last
+    // of every launched group of steps of a batch, whose worlds can be retired
+    // with steps left
+    const bool keep_F = w.keep_force || cs.remaining == 1, keep_u = keep || keep_F;
     auto cell = [&](int i, const float* g) {
       const int k = (int)threadIdx.x + kThreads * i;
       if (k >= kCells) return;
@@ -1745,7 +1746,7 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads, MK ? 3 : 4) void k_fluid_t
       const int x = x0 + c - LO, y = y0 + r - LO;
       const size_t idx = (size_t)y * nx + x;
       if (keep_u) glbv<vf2>(w.u)[idx] = u;
-      if (w.keep_force) glbv<vf2>(w.Fg)[idx] = F;
+      if (keep_F) glbv<vf2>(w.Fg)[idx] = F;
       if (!(u.x * u.x + u.y * u.y <= w.u_max2)) atomicOr((unsigned*)glb(w.flags), kFlagUnstable);
       float out[9];
       collide(w, g, F, u, drho, out);
