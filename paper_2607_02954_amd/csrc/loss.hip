@@ -305,7 +305,9 @@ void launch_density_loss(int nx, int ny, int n, int W, int H, float sigma, float
     // small windows leave most of a wavefront idle (25 pixels, 65,536 nodes:
     // 16.2 us by threads, 28.6 by wavefronts); larger ones make a thread's
     // loop long (121 pixels: 287 against 63 us)
-    if (win <= 32)
+    if (n == 0)
+      ;                                          // (no block of wavefronts: the image is the cleared accumulator)
+    else if (win <= 32)
       k_splat_image<1><<<thread_blocks, kLossBlock, 0, s>>>(g, cell, frac, acc);
     else
       k_splat_image<64><<<wave_blocks, kLossBlock, 0, s>>>(g, cell, frac, acc);

@@ -164,3 +164,18 @@ def test_folding_sizes_of_the_paper_vs_oracle():
     print(f"folding 1000 nodes 256^2 / 128^2, 250 steps: loss {L:.6e} (oracle {Lr:.6e}) "
           f"grad rel err {err:.2e} cos {cos:.6f}")
     assert abs(L - Lr) / Lr <= 1e-5 and err <= 1e-3 and cos >= 0.9999
+
+
+@pytest.mark.parametrize("W, H", [(1, 1), (9, 7), (512, 512), (700, 300)])
+def test_no_nodes_on_any_image(W, H):
+    # small images are summed tile by tile, large ones node by node: with no
+    # nodes the image is zero and the loss the target's mean square either way
+    sim = _sim()
+    T = torch.rand(H, W, generator=torch.Generator(device="cuda").manual_seed(W), device="cuda")
+    cell = torch.zeros(2, 0, dtype=torch.int32, device="cuda")
+    frac = torch.zeros(2, 0, dtype=torch.float32, device="cuda")
+    loss, image, g = sim.density_loss(256, 200, cell, frac, T, 2.0, 0.1)
+    torch.cuda.synchronize()
+    ref = float((T.double() ** 2).mean())
+    assert not image.any() and g.shape == (2, 0)
+    assert abs(float(loss) - ref) <= 1e-5 * ref
