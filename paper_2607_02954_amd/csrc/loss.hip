@@ -272,10 +272,10 @@ void launch_density_loss(int nx, int ny, int n, int W, int H, float sigma, float
   g.amp = amp;
   // a pixel k columns away from the node's own has its centre at least
   // (|k| - 1/2) hx away: columns up to 5 sigma / hx + 1/2 can be inside
-  const int rx = (int)floorf(5.0f * sigma / g.hx + 0.5f) + 1;
-  const int ry = (int)floorf(5.0f * sigma / g.hy + 0.5f) + 1;
-  g.rx = 2 * rx + 1 >= W ? -1 : rx;            // the window would wrap onto itself: all columns once
-  g.ry = 2 * ry + 1 >= H ? -1 : ry;
+  // (compared in floating point: half-widths past the integers' range too)
+  const float rx = floorf(5.0f * sigma / g.hx + 0.5f) + 1.0f, ry = floorf(5.0f * sigma / g.hy + 0.5f) + 1.0f;
+  g.rx = 2.0f * rx + 1.0f >= (float)W ? -1 : (int)rx;   // the window would wrap onto itself: all columns once
+  g.ry = 2.0f * ry + 1.0f >= (float)H ? -1 : (int)ry;
   const int P = W * H;
   const int nb = (P + kLossBlock - 1) / kLossBlock;
   char* base = (char*)ws;

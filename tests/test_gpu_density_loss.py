@@ -179,3 +179,24 @@ def test_no_nodes_on_any_image(W, H):
     ref = float((T.double() ** 2).mean())
     assert not image.any() and g.shape == (2, 0)
     assert abs(float(loss) - ref) <= 1e-5 * ref
+
+
+@pytest.mark.parametrize("sigma", [1e6, 3e8, 1e12])
+def test_sigma_far_larger_than_the_world(sigma):
+    # every node gives every pixel amp; exp(-r^2 / 2 sigma^2) is 1 and the gradient amp r / sigma^2 times the residual
+    sim = _sim()
+    rng = np.random.default_rng(3)
+    cell, frac = sim.split_positions(torch.tensor(rng.uniform(0, 20, (2, 7)), dtype=DT, device="cuda"))
+    T = torch.full((8, 16), 0.25, device="cuda")
+    loss, image, g = sim.density_loss(20, 20, cell, frac, T, sigma, 0.5)
+    torch.cuda.synchronize()
+    assert torch.equal(image, torch.full_like(image, 3.5))
+    assert float(loss) == 3.25 ** 2
+    # 128 pixels of 2 * 3.25 / 128 * 0.5 * d / sigma^2 with |d| <= 10: below 32.5 / sigma^2, and not lost
+    assert float(g.abs().max()) <= 32.5 / sigma ** 2 * 1.001
+    if sigma < 1e7:
+        x = (cell.double() + frac.double()).cpu()
+        x.requires_grad_(True)
+        L = O.density_loss(O.density_image(x, 20, 20, 16, 8, sigma, 0.5), T.cpu().double())
+        (ref,) = torch.autograd.grad(L, x)
+        assert float((g.cpu().double() - ref).abs().max()) <= 1e-4 * float(ref.abs().max())
