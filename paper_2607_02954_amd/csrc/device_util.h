@@ -367,9 +367,9 @@ static __device__ __forceinline__ int block_scan256(int v, int* s_wave, int* tot
 
 // ---------------------------------------------------------------------------
 // Tile lists (binned worlds; their layout: WorldDev).  A tile's list holds a
-// record of every node its kernels need, once each.  A segment that overflowed
-// its capacity (its count says so), or a world without lists, is read by
-// testing every node instead.
+// record of every node its kernels need, once each.  Where a segment overflowed,
+// the tile reads the own nodes of the tiles around it, which hold every node of
+// theirs once; a world without lists is read by testing every node.
 // ---------------------------------------------------------------------------
 // Class of home cell h (in [0, n)) for the tile [x0, x0 + tw) of a periodic
 // axis: 0 own, 1 near, 2 far, 3 out of reach.
@@ -397,11 +397,17 @@ static __device__ __forceinline__ constexpr int nb_dy(int q) { return q < 2 ? 0 
 static __device__ __forceinline__ bool nb_exists(int d, int nt) { return d == 0 || nt >= 3 || (nt == 2 && d == 1); }
 static __device__ __forceinline__ int nb_tile(int t, int d, int nt) { return wrap_near(t + d, nt); }
 
-// First record of neighbour q's segments (near, far): strays and own
-// nodes come first, then the sides, then the corners.
-static __device__ __forceinline__ int nb_first(const WorldDev& w, int q) {
-  const int s = w.tl_near_s + w.tl_far_s, c = w.tl_near_c + w.tl_far_c;
-  return w.tl_strays + w.tl_own + (q < 4 ? q * s : 4 * s + (q - 4) * c);
+// Place of segment `seg` in a tile's list and its capacity (strays and own
+// nodes come first, then the sides, then the corners, near before far).
+static __device__ __forceinline__ int segment_first(const WorldDev& w, int seg) {
+  if (seg < kCntNear) return seg == kCntOwn ? w.tl_strays : 0;
+  const int q = (seg - kCntNear) & 7, s = w.tl_near_s + w.tl_far_s, c = w.tl_near_c + w.tl_far_c;
+  return w.tl_strays + w.tl_own + (q < 4 ? q * s : 4 * s + (q - 4) * c) + (seg < kCntFar ? 0 : (q < 4 ? w.tl_near_s : w.tl_near_c));
+}
+static __device__ __forceinline__ int segment_cap(const WorldDev& w, int seg) {
+  if (seg < kCntNear) return seg == kCntOwn ? w.tl_own : w.tl_strays;
+  const int q = (seg - kCntNear) & 7;
+  return seg < kCntFar ? (q < 4 ? w.tl_near_s : w.tl_near_c) : (q < 4 ? w.tl_far_s : w.tl_far_c);
 }
 
 // f(tx, ty, class) for every tile that a node with home cell (hx, hy) reaches:
@@ -433,19 +439,36 @@ static __device__ __forceinline__ ListCounts list_counts(const WorldDev& w, int 
   return (ListCounts)(const int*)w.tl_cnt + (size_t)tile * kListCounts;
 }
 
+// Where a tile's nodes are read.
+enum ListMode : int {
+  kModeList = 0,     // its list
+  kModeAround = 1,   // the own nodes of the tiles around it
+  kModeAll = 2       // every node of the world
+};
+
+// How many tiles away along an axis of nt tiles of t cells (the last of `last`)
+// a block can have integrated a node that reaches tile `at`: the reach and a
+// small move are less than a tile, but not less than a narrow last one.
+static __device__ __forceinline__ int axis_span(int at, int nt, int t, int last) {
+  return last < t && (at == 0 || at == nt - 2) ? 2 : 1;
+}
+
 // The runs of records that one wavefront of a block takes from a tile's list,
 // all in scalar registers: its share of the strays and own nodes and (SEGS 2)
 // the near and (3) the far nodes of one side and one corner neighbour, shared
 // by the wavefronts that have the same pair.  Alone (SEGS 1), the own nodes go
 // out in rounds of 64, so that one wavefront and not all has the last, short
 // round.  Flat record f is record f + d[j], j the last run with pre[j] <= f.
-// mode 0: as said; 1: a segment overflowed: the two neighbours' own nodes in
-// place of their segments; 2: every node of the world.
-template <int SEGS>
+// Other modes have one run at a time, d0 its first entry (kModeAround: the own
+// nodes of every kWaves-th tile around; kModeAll: a part of the nodes).
+template <int NT, int SEGS>
 struct WaveRuns {
+  static constexpr int kWaves = NT / 64;
   int mode, total;
   int p1, p2, p3, p4;                            // pre of runs 1 .. (SEGS 3: 4, else 2)
   int d0, e1, e2, e3, e4;                        // d of run 0, and what each run adds to the one before
+  int next;                                      // kModeAround: this wavefront's next tile around
+  bool outgrows;                                 // a segment that the tile's block writes may outgrow its place
   // record number of flat record f (clamped by the caller to [0, total))
   __device__ __forceinline__ int record(int f) const {
     int x = f + d0;
@@ -453,64 +476,99 @@ struct WaveRuns {
     if constexpr (SEGS == 3) x += (f >= p3 ? e3 : 0) + (f >= p4 ? e4 : 0);
     return x;
   }
+  // The next tile around that has own nodes (kModeAround); false: no more.
+  __device__ __forceinline__ bool next_run(const WorldDev& w, int tile) {
+    const int ntx = w.ntx, nty = w.nty, side = 1 << w.tile_shift, ty = tile / ntx, tx = tile - ty * ntx;
+    const int sx = axis_span(tx, ntx, side, w.nx - (ntx - 1) * side), sy = axis_span(ty, nty, side, w.ny - (nty - 1) * side);
+    const int mx = min(2 * sx + 1, ntx), my = min(2 * sy + 1, nty);
+    total = 0;
+    while (next < mx * my) {
+      const int j = next / mx, i = next - j * mx;
+      next += kWaves;
+      const ListCounts c = list_counts(w, (my < nty ? wrap_near(ty - sy + j, nty) : j) * ntx +
+                                              (mx < ntx ? wrap_near(tx - sx + i, ntx) : i));
+      total = c[kCntOwn];
+      d0 = c[kFirst + kCntOwn];
+      if (total > 0) return true;
+    }
+    return false;
+  }
 };
 // The part of the wavefronts that share n records: number `part` of `of`.
 struct RunPart {
   int a, n;
   __device__ __forceinline__ RunPart(int all, int part, int of) : a(all * part / of), n(all * (part + 1) / of - a) {}
+  __device__ __forceinline__ RunPart(int a, int n) : a(a), n(n) {}
 };
+// The same in rounds of 64.
+static __device__ __forceinline__ RunPart round_part(int all, int part, int of) {
+  const int rounds = (int)((unsigned)(all + 63) >> 6), each = rounds / of, more = rounds % of;
+  const int a = min(64 * (part * each + min(part, more)), all);
+  return RunPart(a, min(64 * (each + (part < more ? 1 : 0)), all - a));
+}
 // A neighbour's segments as runs: near nodes, far nodes.
 template <int SEGS>
-static __device__ __forceinline__ void neighbour_runs(const WorldDev& w, int tile, ListCounts c, int mode, int q,
-                                                      int* first, int* n, int* far_first, int* far_n) {
+static __device__ __forceinline__ void neighbour_runs(const WorldDev& w, ListCounts c, int q, int* first, int* n,
+                                                      int* far_first, int* far_n) {
   *first = *n = *far_first = *far_n = 0;
-  if (!nb_exists(nb_dx(q), w.ntx) || !nb_exists(nb_dy(q), w.nty)) return;   // (nobody writes its counts)
-  if (mode == 0) {
-    *first = nb_first(w, q);
-    *n = c[kCntNear + q];
-    if (SEGS == 3) {
-      *far_first = *first + (q < 4 ? w.tl_near_s : w.tl_near_c);
-      *far_n = c[kCntFar + q];
-    }
-  } else {
-    const int ty = tile / w.ntx, tx = tile - ty * w.ntx;
-    const int t = nb_tile(ty, nb_dy(q), w.nty) * w.ntx + nb_tile(tx, nb_dx(q), w.ntx);
-    *n = list_counts(w, t)[kCntOwn];
-    *first = (t - tile) * w.tl_stride + w.tl_strays;
+  if (!nb_exists(nb_dx(q), w.ntx) || !nb_exists(nb_dy(q), w.nty)) return;   // (nobody writes its numbers)
+  *first = c[kFirst + kCntNear + q];
+  *n = c[kCntNear + q];
+  if (SEGS == 3) {
+    *far_first = c[kFirst + kCntFar + q];
+    *far_n = c[kCntFar + q];
   }
 }
 template <int NT, int SEGS>
-static __device__ __forceinline__ WaveRuns<SEGS> wave_runs(const WorldDev& w, int tile) {
+static __device__ __forceinline__ WaveRuns<NT, SEGS> wave_runs(const WorldDev& w, int tile) {
   constexpr int kWaves = NT / 64, kShare = kWaves / 4;
   static_assert(kWaves % 4 == 0, "four neighbour pairs");
-  int mode = 2, all = 0, first = 0, fs = 0, ns = 0, ffs = 0, nfs = 0, fc = 0, nc = 0, ffc = 0, nfc = 0;
+  int mode = kModeAll, strays = 0, own = 0, first = 0, fs = 0, ns = 0, ffs = 0, nfs = 0, fc = 0, nc = 0, ffc = 0, nfc = 0;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), pair = kWaves == 4 ? wave : wave & 3,
             share = kWaves == 4 ? 0 : wave >> 2;
-  if (w.tl_own > 0) {
-    const ListCounts c = list_counts(w, tile);
-    const int flags = c[kCntFlags];
-    if (!(flags & kOverOwn)) {
-      mode = SEGS > 1 && (flags & kOverSegment) ? 1 : 0;
-      const int strays = c[kCntStrays];
-      all = strays + c[kCntOwn];
-      first = w.tl_strays - strays;
-      if constexpr (SEGS > 1) {
-        neighbour_runs<SEGS>(w, tile, c, mode, pair, &fs, &ns, &ffs, &nfs);
-        neighbour_runs<SEGS>(w, tile, c, mode, pair + 4, &fc, &nc, &ffc, &nfc);
-      }
+  const ListCounts c = list_counts(w, tile);
+  bool outgrows = false;
+  if (w.tl_kind != kNoLists) {
+    int flags = c[kCntFlags], crowded = c[kCntCrowded];
+    strays = c[kCntStrays];
+    own = c[kCntOwn];
+    first = c[kFirst + kCntOwn];
+    if constexpr (SEGS > 1) {
+      neighbour_runs<SEGS>(w, c, pair, &fs, &ns, &ffs, &nfs);
+      neighbour_runs<SEGS>(w, c, pair + 4, &fc, &nc, &ffc, &nfc);
     }
+    // (everything is asked for before the flags are waited for)
+    asm volatile("" : "+s"(flags), "+s"(crowded), "+s"(strays), "+s"(own), "+s"(first), "+s"(ns), "+s"(nc));
+    outgrows = crowded || own + strays > w.tl_own;
+    if (w.tl_kind == kSegments && !(flags & (SEGS > 1 ? ~0 : kOverStrays | kOverOwn))) mode = kModeList;
+    else if (!(flags & kOverOwn) && !list_counts(w, w.ntx * w.nty)[kWordJump]) mode = kModeAround;
+  }
+  if (mode == kModeAll) {
+    const RunPart r = round_part(w.n_part, wave, kWaves);
+    return {mode, r.n, 0, 0, 0, 0, r.a, 0, 0, 0, 0, 0, outgrows};
+  }
+  if (mode == kModeAround) {
+    WaveRuns<NT, SEGS> L = {mode, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, wave, outgrows};
+    L.next_run(w, tile);
+    return L;
+  }
+  // strays and own nodes are one run, or where the own nodes lie in the spill
+  // area two, the first of them for wavefront 0
+  const int home = tile * w.tl_stride + w.tl_strays, all = strays + own;
+  const bool apart = first != home;
+  RunPart r0 = SEGS == 1 ? round_part(all, wave, kWaves) : RunPart(all, wave, kWaves);
+  int d0 = home - strays;
+  if (apart) {
+    r0 = wave == 0 ? RunPart(0, strays) : round_part(own, wave - 1, kWaves - 1);
+    d0 = wave == 0 ? d0 : first;
   }
   if constexpr (SEGS == 1) {
-    const int rounds = (all + 63) >> 6, each = rounds / kWaves, more = rounds % kWaves;
-    const int a = min(64 * (wave * each + min(wave, more)), all), n = min(64 * (each + (wave < more ? 1 : 0)), all - a);
-    return {mode, n, 0, 0, 0, 0, first + a, 0, 0, 0, 0};
+    return {mode, r0.n, 0, 0, 0, 0, d0 + r0.a, 0, 0, 0, 0, 0, outgrows};
   } else {
-    RunPart r0(all, wave, kWaves);
     // (with some 20 more scalar instructions the own nodes go out so that the
     // wavefronts' totals fill as few rounds of 64 as the tile needs, in the
     // tiles where equal shares may take more: 8 rounds for 256 own nodes, now 6)
-    if (kWaves == 4 && mode == 0 && all > 128 && w.ntx > 2 && w.nty > 2) {
-      const ListCounts c = list_counts(w, tile);
+    if (kWaves == 4 && all > 128 && w.ntx > 2 && w.nty > 2 && !apart) {
       const auto pair_n = [&](int q) {
         return c[kCntNear + q] + c[kCntNear + q + 4] + (SEGS == 3 ? c[kCntFar + q] + c[kCntFar + q + 4] : 0);
       };
@@ -524,30 +582,40 @@ static __device__ __forceinline__ WaveRuns<SEGS> wave_runs(const WorldDev& w, in
     }
     const RunPart r1(ns, share, kShare), r2(nfs, share, kShare), r3(nc, share, kShare),
         r4(nfc, share, kShare);
-    const int d0 = first + r0.a, p1 = r0.n, d1 = fs + r1.a - p1;
+    d0 += r0.a;
+    const int p1 = r0.n, d1 = fs + r1.a - p1;
     if constexpr (SEGS == 3) {
       const int p2 = p1 + r1.n, d2 = ffs + r2.a - p2, p3 = p2 + r2.n, d3 = fc + r3.a - p3, p4 = p3 + r3.n,
                 d4 = ffc + r4.a - p4;
-      return {mode, p4 + r4.n, p1, p2, p3, p4, d0, d1 - d0, d2 - d1, d3 - d2, d4 - d3};
+      return {mode, p4 + r4.n, p1, p2, p3, p4, d0, d1 - d0, d2 - d1, d3 - d2, d4 - d3, 0, outgrows};
     } else {
       const int p2 = p1 + r1.n, d2 = fc + r3.a - p2;
-      return {mode, p2 + r3.n, p1, p2, 0, 0, d0, d1 - d0, d2 - d1, 0, 0};
+      return {mode, p2 + r3.n, p1, p2, 0, 0, d0, d1 - d0, d2 - d1, 0, 0, 0, outgrows};
     }
   }
 }
 
+// The record of node i.
+static __device__ __forceinline__ vi4 node_record(const WorldDev& w, int i) {
+  const int N = w.n_part;
+  const MC_GLOBAL int* cell = glb(w.cell_in);
+  const MC_GLOBAL float* frac = glb(w.frac_in);
+  const int hx = wrap_index(cell[i], w.nx), hy = wrap_index(cell[N + i], w.ny);
+  const vi4 r = {hx | (hy << 16), __float_as_int(frac[i]), __float_as_int(frac[N + i]), i};
+  return r;
+}
+
 // The records of a tile's list (SEGS as in WaveRuns) for the NT threads of a
 // block, in any order, PER per thread in flight with the values v[node] (VALS
-// 1) and v[N + node] (2) of their nodes.  The first round is loaded where the
-// object is made, so that its chain of loads (counts, records, values) runs
-// beside what the block does before it needs them: at the sizes where a launch
-// lasts as long as that chain, and where the blocks of a CU go through their
-// phases together.
+// 1) and v[N + node] (2) of their nodes.  The first round of a list is loaded
+// where the object is made, so that its chain of loads (counts, records, values)
+// runs beside what the block does before it needs them: at the sizes where a
+// launch lasts as long as that chain, and where the blocks of a CU go through
+// their phases together.
 template <int NT, int SEGS, int PER, int VALS = 0>
 struct TileRecords {
   const MC_GLOBAL float* v;
-  WaveRuns<SEGS> L;
-  const MC_GLOBAL vi4* rec;
+  WaveRuns<NT, SEGS> L;
   int N, tile;
   vi4 r[PER];
   vf2 val[PER];
@@ -555,24 +623,23 @@ struct TileRecords {
     const vf2 x = {VALS > 0 ? v[node] : 0.f, VALS > 1 ? v[N + node] : 0.f};
     return x;
   }
-  __device__ __forceinline__ void load(int base) {
+  // The round from `base` of a list (clamped, so that every load is issued at once).
+  __device__ __forceinline__ void load(const WorldDev& w, int base) {
+    const MC_GLOBAL vi4* rec = glbv<const vi4>(w.tl_rec);
 #pragma unroll
-    for (int i = 0; i < PER; ++i)                 // clamped, so that every load is issued at once
-      r[i] = rec[L.record(min(base + i * 64 + (int)(threadIdx.x & 63), L.total - 1))];
+    for (int i = 0; i < PER; ++i) r[i] = rec[L.record(min(base + i * 64 + (int)(threadIdx.x & 63), L.total - 1))];
 #pragma unroll
     for (int i = 0; i < PER; ++i) val[i] = value(r[i].w);
   }
-  __device__ __forceinline__ TileRecords(const WorldDev& w, int tile, const MC_GLOBAL float* values = nullptr)
-      : v(values), L(wave_runs<NT, SEGS>(w, tile)), rec(glbv<const vi4>(w.tl_rec) + (size_t)tile * w.tl_stride),
-        N(w.n_part), tile(tile) {
-    if (L.mode < 2 && L.total > 0) load(0);
+  // Record of flat number f of another run.
+  __device__ __forceinline__ vi4 run_record(const WorldDev& w, int f) const {
+    const int e = L.d0 + f;
+    if (L.mode == kModeAround && w.tl_kind != kOwnIndices) return glbv<const vi4>(w.tl_rec)[e];
+    return node_record(w, L.mode == kModeAll ? e : glb((const int*)w.tl_rec)[e]);
   }
-  // Whether flat record f counts: a neighbour's own node that has moved to this
-  // tile is one of its strays as well.
-  __device__ __forceinline__ bool counts(const WorldDev& w, int f, const vi4& q) const {
-    if (f >= L.total) return false;
-    if (SEGS == 1 || L.mode == 0 || f < L.p1) return true;
-    return ((q.x >> 16) >> w.tile_shift) * w.ntx + ((q.x & 0xffff) >> w.tile_shift) != tile;
+  __device__ __forceinline__ TileRecords(const WorldDev& w, int tile, const MC_GLOBAL float* values = nullptr)
+      : v(values), L(wave_runs<NT, SEGS>(w, tile)), N(w.n_part), tile(tile) {
+    if (L.mode == kModeList && L.total > 0) load(w, 0);
   }
   // body(record, value) for each.  body must itself drop the records its window
   // does not hold (the list may hold more than needed, and where it cannot be
@@ -580,22 +647,21 @@ struct TileRecords {
   // work and LDS atomics.
   template <class Body>
   __device__ __forceinline__ void each(const WorldDev& w, Body body) {
-    if (L.mode < 2) {
+    if (L.mode == kModeList) {
       for (int base = 0; base < L.total; base += PER * 64) {
-        if (base > 0) load(base);
+        if (base > 0) load(w, base);
 #pragma unroll
         for (int i = 0; i < PER; ++i)
-          if (counts(w, base + i * 64 + (int)(threadIdx.x & 63), r[i])) body(r[i], val[i]);
+          if (base + i * 64 + (int)(threadIdx.x & 63) < L.total) body(r[i], val[i]);
       }
       return;
     }
-    const MC_GLOBAL int* cell = glb(w.cell_in);
-    const MC_GLOBAL float* frac = glb(w.frac_in);
-    for (int i = threadIdx.x; i < N; i += NT) {
-      const int hx = wrap_index(cell[i], w.nx), hy = wrap_index(cell[N + i], w.ny);
-      const vi4 q = {hx | (hy << 16), __float_as_int(frac[i]), __float_as_int(frac[N + i]), i};
-      body(q, value(i));
-    }
+    do {
+      for (int f = threadIdx.x & 63; f < L.total; f += 64) {
+        const vi4 q = run_record(w, f);
+        body(q, value(q.w));
+      }
+    } while (L.mode == kModeAround && L.next_run(w, tile));
   }
 };
 // (what a tile spread goes through)

@@ -47,14 +47,31 @@ __host__ __device__ constexpr int tile_shift_of_side(int side) { return side == 
 __host__ __device__ constexpr int near_reach(bool markers) { return markers ? 5 : 3; }
 __host__ __device__ constexpr int far_reach_before(int R, bool markers) { return R + 3 > near_reach(markers) ? R + 3 : near_reach(markers); }
 __host__ __device__ constexpr int far_reach_after(int R, bool markers) { return R + 2 > near_reach(markers) ? R + 2 : near_reach(markers); }
-// Ints of a tile's list counts: the nodes its block integrated, the strays (those
-// that came in from another tile, and those that reach it from beyond its
-// neighbours), the near and the far nodes of its eight neighbours, and the
-// overflow flags.
-constexpr int kListCounts = 20;      // (19 used)
-constexpr int kCntOwn = 0, kCntStrays = 1, kCntNear = 2, kCntFar = 10, kCntFlags = 18;
-constexpr int kOverSegment = 1;      // a neighbour's near or far nodes overflowed: read the neighbours' own nodes
-constexpr int kOverOwn = 2;          // its own nodes, a neighbour's or strays did: test every node
+// Ints of a tile's list: the number of its own nodes (those its block
+// integrated), of its strays (those that came in from another tile, and those
+// that reach it from beyond its neighbours) and of the near and the far nodes of
+// its eight neighbours; the flags; whether a segment that its block writes is
+// nearly full; and where each of these segments begins.
+// Numbers are of the nodes there are, also where a segment holds fewer.
+constexpr int kCntOwn = 0, kCntStrays = 1, kCntNear = 2, kCntFar = 10, kSegs = 18, kCntFlags = 18, kCntCrowded = 19;
+constexpr int kFirst = 20;           // + segment: its first entry (strays fill theirs from the end: not used)
+constexpr int kListCounts = 40;
+constexpr int kOverSegment = 1;      // near or far nodes overflowed: read the own nodes of the tiles around
+constexpr int kOverStrays = 2;       // strays overflowed: the same, and for its own nodes too
+constexpr int kOverOwn = 4;          // own nodes of a tile around (or its own) were lost: test every node
+// Words after the last tile's: entries of the next lists' spill area handed out
+// by this step, whether a node moved farther than kSmallMove beyond its tile (the
+// tiles around are then not enough); and of the pre-pass, whether a tile's
+// own nodes need the spill area, and entries of it handed out.
+constexpr int kListWords = 8;        // (4 used)
+constexpr int kWordSpill = 0, kWordJump = 1, kWordOver = 2, kWordOwnSpill = 3;
+// How a world's lists are kept.
+enum ListKind : int {
+  kNoLists = 0,      // not at all: every tile tests every node
+  kSegments = 1,     // own nodes, strays, near and far segments
+  kOwnRecords = 2,   // own nodes alone, in the spill area
+  kOwnIndices = 3    // the same as node indices (4 bytes a node)
+};
 constexpr int kSmallMove = 4;        // cells beyond its tile up to which a node reaches no farther than the neighbours
 constexpr int kCellsPerItem = 256;   // contiguous cells per fluid work item
 constexpr int kMaxRadius = 8;        // largest Gaussian truncation radius
@@ -140,13 +157,23 @@ struct WorldDev {
   // tile beyond the neighbours, goes to that tile's strays by an atomic.
   // (Strays fill their segment from its end: with the own nodes they are one
   // run.)
-  int4* tl_rec;                         // [ntx*nty][tl_stride]
-  int* tl_cnt;                          // [ntx*nty][kListCounts]
+  // A segment that is about to outgrow its place in the tile's list gets room in
+  // the world's spill area from the block that writes it: the number of a tile's
+  // own nodes is known beforehand to be at most that of its own and strays, the
+  // others from the step before.  A tile whose segments overflowed all the same
+  // reads the own nodes of the tiles around it.  (Before, such a tile and its
+  // neighbours tested every node of the world: 65,536 nodes in a quarter of
+  // 512^2 took 468 us per step, spread over all of it 31.)
+  int4* tl_rec;                         // [ntx*nty][tl_stride], then the spill area [tl_spill]
+                                        // (kOwnIndices: [tl_spill] ints)
+  int* tl_cnt;                          // [ntx*nty][kListCounts], then [kListWords]
   int4* tl_rec_next;
   int* tl_cnt_next;
-  int tl_own, tl_strays;                // segment capacities; tl_own 0: no lists, the tiles test every node
+  int tl_kind;                          // ListKind
+  int tl_own, tl_strays;                // segment capacities
   int tl_near_s, tl_far_s, tl_near_c, tl_far_c;   // of a side neighbour and of a corner neighbour
   int tl_stride;
+  int tl_spill;
   int keep_force;                       // the fused step kernel writes the grid force too (the adjoint's tape)
 };
 
@@ -175,6 +202,7 @@ struct Grid {
                                              // (any_node: a world not in binned mode)
   int max_radius;                            // largest Gaussian radius of any world (LDS sizing)
   int any_lists;                             // a binned world keeps tile lists
+  int any_spill;                             // and some tile's own segment may not hold its nodes
   int fused;                                 // S4 - S7 run as one tile kernel (few tiles, all worlds binned without MDF)
   int any_energy;                            // a world has an energy field
   int any_markers;                           // a world broadcasts two-layer markers
@@ -235,7 +263,9 @@ void launch_adjoint_debug(const WorldDev* W, const Tables& T, const Grid& G, int
 void launch_elastic(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);
 // elastic force and filter: one launch where every world is binned
 void launch_prepare(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);
-void launch_list_prepass(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);
+// the lists of the current positions; with n_steps >= 0 also sets the worlds' control
+// words for a run of n_steps steps from step t
+void launch_list_prepass(const WorldDev* W, const Tables& T, const Grid& G, long long t, int n_steps, hipStream_t s);
 void launch_sort(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);
 void launch_filter(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);
 void launch_repulse(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);

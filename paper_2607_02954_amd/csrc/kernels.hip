@@ -343,14 +343,31 @@ __global__ __launch_bounds__(PACK) void k_elastic(const WorldDev* __restrict__ W
 
 // ---------------------------------------------------------------------------
 // Binned transfer, pre-pass of a run: the tile lists of the current positions
-// (each step's integration then appends the next step's).
+// (each step's integration then appends the next step's).  Own nodes that their
+// tile's segment does not hold are counted by the pass that writes the others;
+// a pass over the tiles then hands out the spill area, and a last one over the
+// nodes fills it (both end at once where there are none, and leave the near and
+// far nodes that overflowed to the tiles around for one step: 1,048,576 nodes
+// on 2048^2, the two passes 24 us).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_lists_zero(const WorldDev* __restrict__ W, Tables T) {
+// Empty lists; and with n_steps >= 0 the control words of a run of that many
+// steps from step t (one launch rather than one more per world).
+__global__ __launch_bounds__(256) void k_lists_zero(const WorldDev* __restrict__ W, Tables T, long long t, int n_steps) {
   for (int k = blockIdx.y; k < *T.n_worlds; k += gridDim.y) {
     const WorldDev& w = W[T.worlds[k].x];
-    if (w.mode != kBinned || w.tl_own == 0 || w.ctl_src->remaining <= 0) continue;
-    const int n = w.ntx * w.nty * kListCounts;
-    for (int t = blockIdx.x * 256 + threadIdx.x; t < n; t += gridDim.x * 256) glb(w.tl_cnt)[t] = 0;
+    if (n_steps >= 0 && blockIdx.x == 0 && threadIdx.x == 0) {
+      Ctl c;
+      c.t = t;
+      c.remaining = n_steps;
+      c.pad = 0;
+      *(Ctl*)w.ctl_src = c;
+    }
+    if (w.mode != kBinned || w.tl_kind == kNoLists || (n_steps >= 0 ? n_steps : w.ctl_src->remaining) <= 0) continue;
+    const int nt = w.ntx * w.nty, n = nt * kListCounts + kListWords;
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
+      const int tile = i / kListCounts, seg = i - tile * kListCounts - kFirst;
+      glb(w.tl_cnt)[i] = tile < nt && seg >= 0 && seg < kSegs ? tile * w.tl_stride + segment_first(w, seg) : 0;
+    }
   }
 }
 
@@ -360,46 +377,32 @@ static __device__ __forceinline__ bool next_to(const WorldDev& w, int cx, int cy
   return (dx <= 1 || dx == w.ntx - 1) && (dy <= 1 || dy == w.nty - 1);
 }
 
+// The world's words after its tiles' counts.
+static __device__ __forceinline__ MC_GLOBAL int* list_words(const WorldDev& w, MC_GLOBAL int* counts) {
+  return counts + w.ntx * w.nty * kListCounts;
+}
+
 // Flags of the lists that cannot be used when segment seg of tile (tx, ty)'s
 // list is full.
 static __device__ __forceinline__ void flag_overflow(const WorldDev& w, MC_GLOBAL int* counts, int tx, int ty, int seg) {
-  const bool segment = seg >= kCntNear;          // (of near or far nodes)
-  atomicOr((int*)(counts + (ty * w.ntx + tx) * kListCounts + kCntFlags), segment ? kOverSegment : kOverOwn);
-  if (seg == kCntOwn)                            // the neighbours may have to read these own nodes
-#pragma unroll 1
-    for (int q = 0; q < 8; ++q) {
-      const int t = nb_tile(ty, nb_dy(q), w.nty) * w.ntx + nb_tile(tx, nb_dx(q), w.ntx);
-      atomicOr((int*)(counts + t * kListCounts + kCntFlags), kOverOwn);
-    }
-}
-
-// Record `slot` of the own nodes (kCntOwn), the strays (kCntStrays) or neighbour
-// q's near (kCntNear + q) or far nodes (kCntFar + q) in tile (tx, ty)'s list, or the flags of the lists that cannot be used
-// without it.
-static __device__ __forceinline__ void write_record(const WorldDev& w, MC_GLOBAL vi4* lists, MC_GLOBAL int* counts,
-                                                    int tx, int ty, int seg, int slot, const vi4& rec) {
-  const int tile = ty * w.ntx + tx;
-  int at, cap;
-  if (seg == kCntOwn) {
-    cap = w.tl_own;
-    at = w.tl_strays + slot;
-  } else if (seg == kCntStrays) {
-    cap = w.tl_strays;
-    at = w.tl_strays - 1 - slot;
-  } else {
-    const int q = (seg - kCntNear) & 7;
-    cap = q < 4 ? w.tl_near_s : w.tl_near_c;
-    at = nb_first(w, q) + slot;
-    if (seg >= kCntFar) {
-      at += cap;
-      cap = q < 4 ? w.tl_far_s : w.tl_far_c;
-    }
-  }
-  if (slot < cap) {
-    lists[(size_t)tile * w.tl_stride + at] = rec;
+  if (seg != kCntOwn) {
+    atomicOr((int*)(counts + (ty * w.ntx + tx) * kListCounts + kCntFlags),
+             seg == kCntStrays ? kOverStrays : kOverSegment);
     return;
   }
-  flag_overflow(w, counts, tx, ty, seg);
+  const int mx = min(w.ntx, 5), my = min(w.nty, 5);   // the tiles that may have to read these own nodes
+#pragma unroll 1
+  for (int k = 0; k < mx * my; ++k) {
+    const int j = k / mx, i = k - j * mx;
+    const int t = (w.nty <= 5 ? j : wrap_near(ty - 2 + j, w.nty)) * w.ntx + (w.ntx <= 5 ? i : wrap_near(tx - 2 + i, w.ntx));
+    atomicOr((int*)(counts + t * kListCounts + kCntFlags), kOverOwn);
+  }
+}
+
+// Entry e of the own nodes: their record, or their index alone.
+static __device__ __forceinline__ void write_entry(const WorldDev& w, MC_GLOBAL vi4* lists, int e, const vi4& rec) {
+  if (w.tl_kind == kOwnIndices) ((MC_GLOBAL int*)lists)[e] = rec.w;
+  else lists[e] = rec;
 }
 
 // Classes of a node with home (hx, hy) for the eight neighbours of tile
@@ -508,8 +511,10 @@ struct Pairs {
 
 static __device__ __forceinline__ void append_stray(const WorldDev& w, MC_GLOBAL vi4* lists, MC_GLOBAL int* counts,
                                                     int tx, int ty, const vi4& rec) {
-  const int k = atomicAdd((int*)(counts + (ty * w.ntx + tx) * kListCounts + kCntStrays), 1);
-  write_record(w, lists, counts, tx, ty, kCntStrays, k, rec);
+  const int tile = ty * w.ntx + tx;
+  const int k = atomicAdd((int*)(counts + tile * kListCounts + kCntStrays), 1);
+  if (k < w.tl_strays) lists[(size_t)tile * w.tl_stride + w.tl_strays - 1 - k] = rec;
+  else flag_overflow(w, counts, tx, ty, kCntStrays);
 }
 // The record as a stray of every tile it reaches beyond the 3x3 around (cx, cy).
 template <int TILE>
@@ -521,30 +526,45 @@ static __device__ __forceinline__ void append_strays(const WorldDev& w, MC_GLOBA
   });
 }
 
-template <int TILE>
-static __device__ __forceinline__ void build_lists_of_node(const WorldDev& w, int gi) {
+// Node gi into the segments of the lists it belongs to: the first pass counts
+// all and writes what its place in the list holds (and the strays), the second
+// (SPILL) fills the segments that lie in the spill area.  last: no second one follows.
+template <int TILE, bool SPILL>
+static __device__ __forceinline__ void build_lists_of_node(const WorldDev& w, int gi, bool last) {
   constexpr int sh = TileCfg<TILE>::kShift;
-  const int N = w.n_part;
-  const int hx = wrap_index(glb(w.cell_in)[gi], w.nx), hy = wrap_index(glb(w.cell_in)[N + gi], w.ny);
-  const vi4 rec = {hx | (hy << 16), __float_as_int(glb(w.frac_in)[gi]), __float_as_int(glb(w.frac_in)[N + gi]), gi};
-  const int cx = hx >> sh, cy = hy >> sh, own = cy * w.ntx + cx;
+  const vi4 rec = node_record(w, gi);
+  const int hx = rec.x & 0xffff, hy = rec.x >> 16;
+  const int cx = hx >> sh, cy = hy >> sh, ntx = w.ntx, nty = w.nty;
+  const bool segments = w.tl_kind == kSegments;
   MC_GLOBAL vi4* lists = glbv<vi4>(w.tl_rec);
   MC_GLOBAL int* counts = glb(w.tl_cnt);
   const Classes c = neighbour_classes<TILE>(w, cx, cy, hx, hy);
   const Pairs a(c);
+  const auto tile_at = [&](int dx, int dy) { return nb_tile(cy, dy, nty) * ntx + nb_tile(cx, dx, ntx); };
+  const auto wanted = [&](int tile, int seg) {
+    return !SPILL || counts[tile * kListCounts + kFirst + seg] >= ntx * nty * w.tl_stride;
+  };
+  const auto put = [&](int tile, int seg, int slot) {
+    if (SPILL || slot < segment_cap(w, seg))
+      write_entry(w, lists, (SPILL ? counts[tile * kListCounts + kFirst + seg] : tile * w.tl_stride + segment_first(w, seg)) + slot,
+                  rec);
+    else if (seg == kCntOwn && !last) list_words(w, counts)[kWordOver] = 1;
+    else flag_overflow(w, counts, tile % ntx, tile / ntx, seg);
+    if (!SPILL && seg != kCntOwn && slot >= segment_cap(w, seg)) counts[(cy * ntx + cx) * kListCounts + kCntCrowded] = 1;
+  };
   // one atomic per list segment and wavefront, whose nodes share few tiles;
   // every one is issued before the first result is used (1,048,576 nodes:
   // 32 us, 65.7 with one per node)
-  const auto at = [&](int q, int dx, int dy, int cls) {
-    return (nb_tile(cy, dy, w.nty) * w.ntx + nb_tile(cx, dx, w.ntx)) * kListCounts + class_segment(cls, q);
-  };
-  const int k0 = kListCounts * own, k1 = at(a.qx(), a.dx, 0, a.side_x), k2 = at(a.qy(), 0, a.dy, a.side_y),
-            k3 = at(a.qc(), a.dx, a.dy, a.corner);
-  const bool h1 = !a.more && a.side_x < 3, h2 = !a.more && a.side_y < 3, h3 = !a.more && a.corner < 3;
-  const AggGroup g0(k0, true), g1(k1, h1), g2(k2, h2), g3(k3, h3);
+  const int t0 = cy * ntx + cx, t1 = tile_at(a.dx, 0), t2 = tile_at(0, a.dy), t3 = tile_at(a.dx, a.dy);
+  const int q1 = class_segment(a.side_x, a.qx()), q2 = class_segment(a.side_y, a.qy()), q3 = class_segment(a.corner, a.qc());
+  const bool pairs = segments && !a.more;
+  const bool h0 = wanted(t0, kCntOwn), h1 = pairs && a.side_x < 3 && wanted(t1, q1),
+             h2 = pairs && a.side_y < 3 && wanted(t2, q2), h3 = pairs && a.corner < 3 && wanted(t3, q3);
+  const int k0 = kListCounts * t0 + kCntOwn, k1 = kListCounts * t1 + q1, k2 = kListCounts * t2 + q2, k3 = kListCounts * t3 + q3;
+  const AggGroup g0(k0, h0), g1(k1, h1), g2(k2, h2), g3(k3, h3);
   const int lane = __lane_id();
   int s0 = 0, s1 = 0, s2 = 0, s3 = 0;
-  if (g0.leader == lane) s0 = atomicAdd((int*)(counts + k0), g0.count);
+  if (h0 && g0.leader == lane) s0 = atomicAdd((int*)(counts + k0), g0.count);
   if (h1 && g1.leader == lane) s1 = atomicAdd((int*)(counts + k1), g1.count);
   if (h2 && g2.leader == lane) s2 = atomicAdd((int*)(counts + k2), g2.count);
   if (h3 && g3.leader == lane) s3 = atomicAdd((int*)(counts + k3), g3.count);
@@ -552,39 +572,73 @@ static __device__ __forceinline__ void build_lists_of_node(const WorldDev& w, in
   s1 = __shfl(s1, g1.leader) + g1.rank;
   s2 = __shfl(s2, g2.leader) + g2.rank;
   s3 = __shfl(s3, g3.leader) + g3.rank;
-  const auto put = [&](int dx, int dy, int seg, int slot) {
-    write_record(w, lists, counts, nb_tile(cx, dx, w.ntx), nb_tile(cy, dy, w.nty), seg, slot, rec);
-  };
-  put(0, 0, kCntOwn, s0);
-  if (h1) put(a.dx, 0, class_segment(a.side_x, a.qx()), s1);
-  if (h2) put(0, a.dy, class_segment(a.side_y, a.qy()), s2);
-  if (h3) put(a.dx, a.dy, class_segment(a.corner, a.qc()), s3);
-  if (!a.more) return;
+  if (h0) put(t0, kCntOwn, s0);
+  if (h1) put(t1, q1, s1);
+  if (h2) put(t2, q2, s2);
+  if (h3) put(t3, q3, s3);
+  if (!segments || !a.more) return;
   int slot[8];
   static_for<8>([&](auto qq) {
     constexpr int q = decltype(qq)::value;
-    slot[q] = 0;
-    if (c.of(q) <= 2) slot[q] = atomicAdd((int*)(counts + at(q, nb_dx(q), nb_dy(q), c.of(q))), 1);
+    const int t = tile_at(nb_dx(q), nb_dy(q)), seg = class_segment(c.of(q), q);
+    slot[q] = -1;
+    if (c.of(q) <= 2 && wanted(t, seg)) slot[q] = atomicAdd((int*)(counts + kListCounts * t + seg), 1);
   });
   static_for<8>([&](auto qq) {
     constexpr int q = decltype(qq)::value;
-    if (c.of(q) <= 2) put(nb_dx(q), nb_dy(q), class_segment(c.of(q), q), slot[q]);
+    if (slot[q] >= 0) put(tile_at(nb_dx(q), nb_dy(q)), class_segment(c.of(q), q), slot[q]);
   });
-  if (c.beyond) append_strays<TILE>(w, lists, counts, cx, cy, rec);
+  if (!SPILL && c.beyond) append_strays<TILE>(w, lists, counts, cx, cy, rec);
 }
 
-template <int PACK>
-__global__ __launch_bounds__(PACK) void k_lists_build(const WorldDev* __restrict__ W, Tables T) {
+// Room in the spill area for the segments that need it, where some tile's own
+// nodes do; their nodes are counted again as they are written.
+__global__ __launch_bounds__(256) void k_lists_reserve(const WorldDev* __restrict__ W, Tables T) {
+  for (int k = blockIdx.y; k < *T.n_worlds; k += gridDim.y) {
+    const WorldDev& w = W[T.worlds[k].x];
+    if (w.mode != kBinned || w.tl_kind == kNoLists || w.ctl_src->remaining <= 0) continue;
+    MC_GLOBAL int* counts = glb(w.tl_cnt);
+    MC_GLOBAL int* words = list_words(w, counts);
+    if (!words[kWordOver]) continue;
+    const int nt = w.ntx * w.nty, segs = w.tl_kind == kSegments ? kSegs : 1;
+    for (int t = blockIdx.x * 256 + threadIdx.x; t < nt; t += gridDim.x * 256) {
+      MC_GLOBAL int* c = counts + t * kListCounts;
+      const auto need = [&](int seg) { return seg == kCntStrays || c[seg] <= segment_cap(w, seg) ? 0 : c[seg]; };
+      int n = 0;
+      for (int seg = 0; seg < segs; ++seg) n += need(seg);
+      if (n == 0) continue;
+      int at = atomicAdd((int*)(words + kWordOwnSpill), n);
+      bool all = true;
+      for (int seg = 0; seg < segs; ++seg) {
+        const int m = need(seg);
+        if (m == 0) continue;
+        if (at >= 0 && m <= w.tl_spill - at) {
+          c[kFirst + seg] = nt * w.tl_stride + at;
+          c[seg] = 0;
+        } else {
+          flag_overflow(w, counts, t % w.ntx, t / w.ntx, seg);
+          all = false;
+        }
+        at += m;
+      }
+      if (all) atomicAnd((int*)(c + kCntFlags), ~kOverSegment);
+    }
+  }
+}
+
+template <int PACK, bool SPILL>
+__global__ __launch_bounds__(PACK) void k_lists_build(const WorldDev* __restrict__ W, Tables T, int last) {
   const int npk = *T.n_packs;
   for (int it = blockIdx.x; it < npk; it += gridDim.x) {
     const Pack pk = T.packs[it];
     const WorldDev& w = W[pk.world];
-    if (w.mode != kBinned || w.tl_own == 0 || w.ctl_src->remaining <= 0) continue;
+    if (w.mode != kBinned || w.tl_kind == kNoLists || w.ctl_src->remaining <= 0) continue;
+    if (SPILL && !list_words(w, glb(w.tl_cnt))[kWordOver]) continue;
     const int gi = pk.node_begin + threadIdx.x;
     if (gi >= pk.node_end) continue;
-    if (w.tile_shift == 4) build_lists_of_node<16>(w, gi);
-    else if (w.tile_shift == 5) build_lists_of_node<32>(w, gi);
-    else build_lists_of_node<64>(w, gi);
+    if (w.tile_shift == 4) build_lists_of_node<16, SPILL>(w, gi, last);
+    else if (w.tile_shift == 5) build_lists_of_node<32, SPILL>(w, gi, last);
+    else build_lists_of_node<64, SPILL>(w, gi, last);
   }
 }
 
@@ -841,6 +895,36 @@ static __device__ __forceinline__ void filter_passes(const float* s_regf, float*
   __syncthreads();
 }
 
+// Whether a segment with n nodes and room for cap may be outgrown by the next step.
+static __device__ __forceinline__ bool nearly_full(int n, int cap) { return n + (n >> 3) + 4 > cap; }
+// Places for the segments that the block of a tile will write in this step's
+// integration where one may outgrow its place, in the spill area for those that may outgrow theirs: its own nodes
+// and strays are all that it can come to integrate, of the others there will be
+// about as many as now.  Left in the next lists, the capacities in place of the
+// numbers.  (Here rather than in the integration, whose registers it would cost.)
+static __device__ __forceinline__ void reserve_segments(const WorldDev& w, int bx, int by) {
+  const int seg = threadIdx.x;
+  if (seg >= kSegs || seg == kCntStrays) return;
+  const bool own = seg == kCntOwn;
+  const int q = (seg - kCntNear) & 7, dx = own ? 0 : nb_dx(q), dy = own ? 0 : nb_dy(q);
+  if (!nb_exists(dx, w.ntx) || !nb_exists(dy, w.nty)) return;
+  const int tile = nb_tile(by, dy, w.nty) * w.ntx + nb_tile(bx, dx, w.ntx);
+  MC_GLOBAL int* now = glb(w.tl_cnt) + tile * kListCounts;
+  MC_GLOBAL int* next = glb(w.tl_cnt_next) + tile * kListCounts;
+  int at = tile * w.tl_stride + segment_first(w, seg), cap = segment_cap(w, seg);
+  int n = own ? now[kCntOwn] + now[kCntStrays] : now[seg];
+  if (own ? n > cap : (w.tl_kind == kSegments && nearly_full(n, cap))) {
+    if (!own) n += (n >> 2) + 8;
+    const int a = atomicAdd((int*)(list_words(w, glb(w.tl_cnt)) + kWordSpill), n);
+    if (a >= 0 && n <= w.tl_spill - a) {         // (none left: nodes that do not fit flag the tiles they are for)
+      at = w.ntx * w.nty * w.tl_stride + a;
+      cap = n;
+    }
+  }
+  next[kFirst + seg] = at;
+  next[seg] = cap;
+}
+
 template <int TILE, int NT>
 static __device__ __forceinline__ void filter_tile(const WorldDev& w, int packed, unsigned char* smem,
                                                    int window_bytes) {
@@ -865,9 +949,14 @@ static __device__ __forceinline__ void filter_tile(const WorldDev& w, int packed
       const int P = S + kWinPad;                  // row pitch
       TileRecords<NT, 3, NT == 256 && TILE == 32 ? 3 : 2> nodes(w, tix);
       zero_lds_u64(s_win, S * P);
-      if (tid == 0 && w.tl_own > 0 && w.ctl_src->remaining > 1) {   // (the other segments have one writer each)
-        glb(w.tl_cnt_next)[tix * kListCounts + kCntStrays] = 0;
-        glb(w.tl_cnt_next)[tix * kListCounts + kCntFlags] = 0;
+      if (w.tl_kind != kNoLists && w.ctl_src->remaining > 1) {
+        if (tid == 0) {                           // (the other numbers have one writer each)
+          MC_GLOBAL int* next = glb(w.tl_cnt_next);
+          next[tix * kListCounts + kCntStrays] = 0;
+          next[tix * kListCounts + kCntFlags] = next[tix * kListCounts + kCntCrowded] = 0;
+          if (tix == 0) list_words(w, next)[kWordSpill] = list_words(w, next)[kWordJump] = 0;
+        }
+        if (nodes.L.outgrows) reserve_segments(w, tile_x(packed), tile_y(packed));
       }
       const int ox = wrap_index(xo - 3, nx), oy = wrap_index(yo - 3, ny);
       const int keep_x = reg + 3 <= nx ? reg + 2 : nx;
@@ -1384,8 +1473,8 @@ __device__ __forceinline__ vf2 gather_staged(const vf2* st, int lx, int ly, cons
 template <int TILE>
 struct AppendLds {
   static constexpr int kAxis = TILE + 2 * kSmallMove;
-  int cur[kListCounts];
-  int at[kListCounts], cap[kListCounts];         // where each segment begins, and how many it takes
+  int cur[kSegs];
+  int at[kSegs], cap[kSegs];                     // where each segment begins, and how many it takes
   unsigned char axis[2 * kAxis];                 // axis_pairs of the places along x, then y
 };
 template <int TILE>
@@ -1398,21 +1487,25 @@ static __device__ __forceinline__ void init_append(const WorldDev& w, int bx, in
     lds.axis[seg] = (unsigned char)axis_pairs(axis_classes(Reach(w), l, y ? min(TILE, w.ny - by * TILE) : min(TILE, w.nx - bx * TILE),
                                             y ? w.nty : w.ntx));
   }
-  if (seg >= kListCounts) return;
+  if (seg >= kSegs) return;
+  const bool own = seg < kCntNear;
+  const int q = (seg - kCntNear) & 7, dx = own ? 0 : nb_dx(q), dy = own ? 0 : nb_dy(q);
+  const int tile = nb_tile(by, dy, w.nty) * w.ntx + nb_tile(bx, dx, w.ntx);
   lds.cur[seg] = 0;
-  int tile = by * w.ntx + bx, at = w.tl_strays, cap = w.tl_own;
-  if (seg >= kCntNear) {
-    const int q = (seg - kCntNear) & 7;
-    tile = nb_tile(by, nb_dy(q), w.nty) * w.ntx + nb_tile(bx, nb_dx(q), w.ntx);
-    at = nb_first(w, q);
-    cap = q < 4 ? w.tl_near_s : w.tl_near_c;
-    if (seg >= kCntFar) {
-      at += cap;
-      cap = q < 4 ? w.tl_far_s : w.tl_far_c;
-    }
-  }
-  lds.at[seg] = tile * w.tl_stride + at;
-  lds.cap[seg] = cap;
+  lds.at[seg] = tile * w.tl_stride + segment_first(w, seg);
+  lds.cap[seg] = segment_cap(w, seg);
+}
+// The places that the filter left in the next lists (reserve_segments).  By every
+// thread after its own init_append, before the barrier ahead of append_nodes.
+template <int TILE>
+static __device__ __forceinline__ void take_places(const WorldDev& w, int bx, int by, AppendLds<TILE>& lds) {
+  const int seg = threadIdx.x;
+  if (seg >= kSegs) return;
+  const int q = (seg - kCntNear) & 7, dx = seg < kCntNear ? 0 : nb_dx(q), dy = seg < kCntNear ? 0 : nb_dy(q);
+  if (seg == kCntStrays || !nb_exists(dx, w.ntx) || !nb_exists(dy, w.nty)) return;
+  const MC_GLOBAL int* c = glb(w.tl_cnt_next) + (nb_tile(by, dy, w.nty) * w.ntx + nb_tile(bx, dx, w.ntx)) * kListCounts;
+  lds.at[seg] = c[kFirst + seg];
+  lds.cap[seg] = c[seg];
 }
 // Record `slot` of the segment, or the flags of the lists that cannot be used
 // without it.
@@ -1433,6 +1526,11 @@ static __device__ __forceinline__ void append_nodes(const WorldDev& w, int bx, i
   const int ntx = w.ntx, nty = w.nty;
   MC_GLOBAL vi4* lists = glbv<vi4>(w.tl_rec_next);
   MC_GLOBAL int* counts = glb(w.tl_cnt_next);
+  const auto jump = [&](const Place& pl) {
+    if (pl.lx < -kSmallMove || pl.lx >= min(TILE, w.nx - bx * TILE) + kSmallMove || pl.ly < -kSmallMove ||
+        pl.ly >= min(TILE, w.ny - by * TILE) + kSmallMove)
+      atomicOr((int*)(list_words(w, counts) + kWordJump), 1);
+  };
 #pragma unroll
   for (int p = 0; p < PER; ++p) {
     const vi4& r = rec[p];
@@ -1448,6 +1546,16 @@ static __device__ __forceinline__ void append_nodes(const WorldDev& w, int bx, i
     const Pairs a(lds.axis[ix], lds.axis[iy], !pl.inside);
     k = __shfl(k, leader) + __popcll(m & ((1ull << lane) - 1ull));
     if (!has) continue;
+    if (w.tl_kind != kSegments) {                // own nodes alone
+      if (k < lds.cap[kCntOwn]) write_entry(w, lists, lds.at[kCntOwn] + k, r);
+      else flag_overflow(w, counts, bx, by, kCntOwn);
+      const int tx = (r.x & 0xffff) >> TileCfg<TILE>::kShift, ty = (r.x >> 16) >> TileCfg<TILE>::kShift;
+      if (tx != bx || ty != by) {                // (counted, so that its block knows how many it gets)
+        atomicAdd((int*)(counts + (ty * ntx + tx) * kListCounts + kCntStrays), 1);
+        jump(pl);
+      }
+      continue;
+    }
     if (!__any(a.more)) {
       // every lane for its own neighbours at once, the slots fetched together
       const int q1 = class_segment(a.side_x, a.qx()), q2 = class_segment(a.side_y, a.qy()),
@@ -1479,88 +1587,103 @@ static __device__ __forceinline__ void append_nodes(const WorldDev& w, int bx, i
       const int seg = class_segment(cls, q);
       append_record(w, lists, counts, lds, tx, ty, seg, atomicAdd(&lds.cur[seg], 1), r);
     }
-    if (c.beyond) append_strays<TILE>(w, lists, counts, bx, by, r);
+    if (c.beyond) {
+      jump(pl);
+      append_strays<TILE>(w, lists, counts, bx, by, r);
+    }
   }
 }
 
-// The counts of the segments this block wrote (after a barrier).
+// The numbers and places of the segments this block wrote (after a barrier).
 template <int TILE>
 static __device__ __forceinline__ void store_counts(const WorldDev& w, int bx, int by, const AppendLds<TILE>& lds) {
   const int seg = threadIdx.x;
-  if (seg == kCntStrays || seg >= kCntFlags) return;
+  if (seg == kCntStrays || seg >= kSegs) return;
   const int q = (seg - kCntNear) & 7;
   const int dx = seg < kCntNear ? 0 : nb_dx(q), dy = seg < kCntNear ? 0 : nb_dy(q);
   if (!nb_exists(dx, w.ntx) || !nb_exists(dy, w.nty)) return;
-  const int tile = nb_tile(by, dy, w.nty) * w.ntx + nb_tile(bx, dx, w.ntx);
-  glb(w.tl_cnt_next)[tile * kListCounts + seg] = lds.cur[seg];
+  MC_GLOBAL int* c = glb(w.tl_cnt_next) + (nb_tile(by, dy, w.nty) * w.ntx + nb_tile(bx, dx, w.ntx)) * kListCounts;
+  const int n = lds.cur[seg], at = lds.at[seg];
+  c[seg] = n;
+  c[kFirst + seg] = at;
+  // (in the spill area: the next step's may have to be there as well)
+  if (nearly_full(n, lds.cap[seg]) || at >= w.ntx * w.nty * w.tl_stride)
+    glb(w.tl_cnt_next)[(by * w.ntx + bx) * kListCounts + kCntCrowded] = 1;
 }
 
 // A tile's nodes for its integration (its own and the strays): records and
 // unwrapped cells of up to kOwnPer nodes per thread, loaded together (the
 // first round's beside the staging of the velocity).  Every wavefront goes
-// through its runs of the list, or through every node of the world, on its own.
+// through its share of them on its own.
 constexpr int kOwnPer = 2;
-struct OwnNodes {
-  int total;                                     // of this wavefront
-  bool list;
-  vi4 rec[kOwnPer];
-  int cx[kOwnPer], cy[kOwnPer];
-};
 template <int TILE>
-static __device__ __forceinline__ void load_own(const WorldDev& w, int tile, const WaveRuns<1>& L, int base,
-                                                OwnNodes& o) {
-  constexpr int kThreads = TileCfg<TILE>::kThreads;
-  const int N = w.n_part, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const MC_GLOBAL int* cell = glb(w.cell_in);
-  const MC_GLOBAL vi4* recs = glbv<const vi4>(w.tl_rec) + (size_t)tile * w.tl_stride;
-  o.list = L.mode == 0;
-  o.total = o.list ? L.total : max(0, (N - 64 * wave + kThreads - 1) / kThreads * 64);
-  if (o.total == 0) return;
+struct OwnNodes {
+  static constexpr int NT = TileCfg<TILE>::kThreads;
+  WaveRuns<NT, 1> L;
+  vi4 r[kOwnPer];
+  int cx[kOwnPer], cy[kOwnPer];
+  __device__ __forceinline__ void load(const WorldDev& w, int base) {
+    int e[kOwnPer];
 #pragma unroll
-  for (int q = 0; q < kOwnPer; ++q) {            // clamped, so that every load is issued at once
-    const int e = min(base + q * 64 + lane, o.total - 1);
-    if (o.list) o.rec[q] = recs[L.record(e)];
-    else o.rec[q].w = min(e / 64 * kThreads + 64 * wave + (e & 63), N - 1);
-  }
+    for (int q = 0; q < kOwnPer; ++q)              // clamped, so that every load is issued at once
+      e[q] = L.d0 + min(base + q * 64 + (int)(threadIdx.x & 63), L.total - 1);
+    if (!unlisted(w)) {
 #pragma unroll
-  for (int q = 0; q < kOwnPer; ++q) {
-    const int gi = o.rec[q].w;
-    o.cx[q] = cell[gi];
-    o.cy[q] = cell[N + gi];
-    if (!o.list) {
-      o.rec[q].y = __float_as_int(glb(w.frac_in)[gi]);
-      o.rec[q].z = __float_as_int(glb(w.frac_in)[N + gi]);
+      for (int q = 0; q < kOwnPer; ++q) r[q] = glbv<const vi4>(w.tl_rec)[e[q]];
+#pragma unroll
+      for (int q = 0; q < kOwnPer; ++q) {
+        cx[q] = glb(w.cell_in)[r[q].w];
+        cy[q] = glb(w.cell_in)[w.n_part + r[q].w];
+      }
+      return;
+    }
+#pragma unroll
+    for (int q = 0; q < kOwnPer; ++q) {
+      const int gi = L.mode == kModeAll ? e[q] : glb((const int*)w.tl_rec)[e[q]];
+      cx[q] = glb(w.cell_in)[gi];
+      cy[q] = glb(w.cell_in)[w.n_part + gi];
+      r[q].y = __float_as_int(glb(w.frac_in)[gi]);
+      r[q].z = __float_as_int(glb(w.frac_in)[w.n_part + gi]);
+      r[q].w = gi;
     }
   }
-}
+  // Whether the entries are nodes alone.
+  __device__ __forceinline__ bool unlisted(const WorldDev& w) const {
+    return L.mode == kModeAll || (L.mode == kModeAround && w.tl_kind == kOwnIndices);
+  }
+  __device__ __forceinline__ OwnNodes(const WorldDev& w, int tile) : L(wave_runs<NT, 1>(w, tile)) {
+    if (L.total > 0) load(w, 0);
+  }
+};
 
 // S7 of a tile's own nodes (o: the first round's, loaded), from the velocity
 // staged in s_u: the new positions and, unless this is the run's last step
 // (append), the next step's lists.  The cursors have been cleared.
 template <int TILE, bool MK>
-static __device__ __forceinline__ void integrate_own(const WorldDev& w, int tile, const WaveRuns<1>& L, OwnNodes& o,
-                                                     int packed, bool append, const vf2* s_u, AppendLds<TILE>& lds) {
-  constexpr int kThreads = TileCfg<TILE>::kThreads;
+static __device__ __forceinline__ void integrate_own(const WorldDev& w, OwnNodes<TILE>& o, int packed, bool append,
+                                                     const vf2* s_u, AppendLds<TILE>& lds) {
   const int nx = w.nx, ny = w.ny, N = w.n_part;
   const int x0 = tile_x(packed) * TILE, y0 = tile_y(packed) * TILE;
   const int tw = min(TILE, nx - x0), th = min(TILE, ny - y0);
-  for (int base = 0; base < o.total; base += kOwnPer * 64) {
-    if (base > 0) load_own<TILE>(w, tile, L, base, o);
+  const int tile = tile_y(packed) * w.ntx + tile_x(packed);
+  bool loaded = true;                            // (the first round)
+  do {
+  for (int base = 0; base < o.L.total; base += kOwnPer * 64) {
+    if (!loaded) o.load(w, base);
+    loaded = false;
 #pragma unroll
     for (int q = 0; q < kOwnPer; ++q) {
-      vi4& r = o.rec[q];
+      vi4& r = o.r[q];
       const int home = wrap_index(o.cx[q], nx) | (wrap_index(o.cy[q], ny) << 16);
-      const int e = base + q * 64 + (int)(threadIdx.x & 63);
-      bool has = e < o.total && (o.list || e / 64 * kThreads + (int)threadIdx.x < N);
-      if (o.list && has && r.x != home) atomicOr((unsigned*)glb(w.flags), kFlagBins);   // moved since its list was made
-      if (!o.list) r.x = home;
-      const int hlx = (r.x & 0xffff) - x0, hly = (r.x >> 16) - y0;   // (some only reach the tile, or left it)
-      has = has && hlx >= 0 && hlx < tw && hly >= 0 && hly < th;
+      bool has = base + q * 64 + (int)(threadIdx.x & 63) < o.L.total;
+      if (o.unlisted(w)) r.x = home;
+      if (has && r.x != home) atomicOr((unsigned*)glb(w.flags), kFlagBins);   // moved since its list was made
+      const int lx = (r.x & 0xffff) - x0, ly = (r.x >> 16) - y0;   // (some only reach the tile, or left it)
+      has = has && lx >= 0 && lx < tw && ly >= 0 && ly < th;
       if (!has) {
         r.w = -1;
         continue;
       }
-      const int lx = (r.x & 0xffff) - x0, ly = (r.x >> 16) - y0;
       const float fx = __int_as_float(r.y), fy = __int_as_float(r.z);
       const int gi = r.w;
       float dux, duy;
@@ -1606,8 +1729,9 @@ static __device__ __forceinline__ void integrate_own(const WorldDev& w, int tile
       r.y = __float_as_int(nfx);
       r.z = __float_as_int(nfy);
     }
-    if (append) append_nodes<TILE, kOwnPer>(w, tile_x(packed), tile_y(packed), o.rec, lds);
+    if (append) append_nodes<TILE, kOwnPer>(w, tile_x(packed), tile_y(packed), o.r, lds);
   }
+  } while (o.L.mode == kModeAround && o.L.next_run(w, tile));
   if (append) {
     __syncthreads();
     store_counts(w, tile_x(packed), tile_y(packed), lds);
@@ -1634,14 +1758,14 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_integrate_tile(cons
     const int x0 = tile_x(tl.y) * TILE;
     const int y0 = tile_y(tl.y) * TILE;
     const int tile = tile_y(tl.y) * w.ntx + tile_x(tl.y);
-    init_append(w, tile_x(tl.y), tile_y(tl.y), s_app);
+    const bool append = w.tl_kind != kNoLists && remaining > 1;
+    if (append) init_append(w, tile_x(tl.y), tile_y(tl.y), s_app);
     const WindowLoads<kThreads, kStage> u(glbv<const vf2>(w.u), nx, ny, x0 - 1 - kE, y0 - 1 - kE);
-    const auto L = wave_runs<kThreads, 1>(w, tile);
-    OwnNodes own;
-    load_own<TILE>(w, tile, L, 0, own);
+    OwnNodes<TILE> own(w, tile);
     u.store(s_u);
+    if (append && own.L.outgrows) take_places(w, tile_x(tl.y), tile_y(tl.y), s_app);
     __syncthreads();
-    integrate_own<TILE, MK>(w, tile, L, own, tl.y, w.tl_own > 0 && remaining > 1, s_u, s_app);
+    integrate_own<TILE, MK>(w, own, tl.y, append, s_u, s_app);
     __syncthreads();
   }
 }
@@ -1694,7 +1818,8 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads, MK ? 3 : 4) void k_fluid_t
     const int nx = w.nx, ny = w.ny, ncell = nx * ny;
     const int x0 = tile_x(tl.y) * TILE, y0 = tile_y(tl.y) * TILE;
     const int tw = min(TILE, nx - x0), th = min(TILE, ny - y0);
-    init_append(w, tile_x(tl.y), tile_y(tl.y), s_app);
+    const bool append = w.tl_kind != kNoLists && cs.remaining > 1;
+    if (append) init_append(w, tile_x(tl.y), tile_y(tl.y), s_app);
     // (the gradient's loads first: they need no other, and loads return in order)
     const WindowLoads<kThreads, kGSide> grad(glbv<const vf2>(w.grad), nx, ny, x0 - LO - (MK ? 4 : 3), y0 - LO - (MK ? 4 : 3));
     SpreadNodes<TILE> nodes(w, tix, glb(w.fel_el));
@@ -1717,14 +1842,13 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads, MK ? 3 : 4) void k_fluid_t
 #pragma unroll
       for (int i = 0; i < kIt; ++i) load(i, g[i]);
     }
-    const auto L = wave_runs<kThreads, 1>(w, tix);
-    OwnNodes own;
-    load_own<TILE>(w, tix, L, 0, own);
+    OwnNodes<TILE> own(w, tix);
     __syncthreads();
     if constexpr (MK)
       tile_spread_markers<TILE, true, LO, HI>(w, nodes, x0, y0, tw, th, 1.0f, s_fx, s_fy, s_g);
     else
       tile_spread_vec<TILE, true, false, LO, HI>(w, nodes, x0, y0, tw, th, 1.0f, s_fx, s_fy, s_g);
+    if (append && own.L.outgrows) take_places(w, tile_x(tl.y), tile_y(tl.y), s_app);
     __syncthreads();
     MC_GLOBAL float* dst = glb(w.f_dst);
     // the velocity and the grid force are written where no later step of the
@@ -1763,7 +1887,7 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads, MK ? 3 : 4) void k_fluid_t
       }
     }
     __syncthreads();
-    integrate_own<TILE, MK>(w, tix, L, own, tl.y, w.tl_own > 0 && cs.remaining > 1, s_g, s_app);
+    integrate_own<TILE, MK>(w, own, tl.y, append, s_g, s_app);
     __syncthreads();
   }
 }
@@ -2331,10 +2455,19 @@ void launch_elastic(const WorldDev* W, const Tables& T, const Grid& G, hipStream
   }
 }
 
-void launch_list_prepass(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s) {
+void launch_list_prepass(const WorldDev* W, const Tables& T, const Grid& G, long long t, int n_steps, hipStream_t s) {
+  if (!G.any_lists && n_steps < 0) return;
+  k_lists_zero<<<dim3(!G.any_lists ? 1 : G.world_blocks == 1 ? 64 : 8, G.world_blocks), 256, 0, s>>>(W, T, t, n_steps);
   if (!G.any_lists) return;
-  k_lists_zero<<<dim3(G.world_blocks == 1 ? 64 : 8, G.world_blocks), 256, 0, s>>>(W, T);
-  MC_PACK_DISPATCH(k_lists_build, G, W, T);
+  const auto build = [&](auto spill) {
+    constexpr bool S = decltype(spill)::value;
+    if (G.pack == 256) k_lists_build<256, S><<<G.node_blocks, 256, 0, s>>>(W, T, !G.any_spill);
+    else k_lists_build<1024, S><<<G.node_blocks, 1024, 0, s>>>(W, T, !G.any_spill);
+  };
+  build(std::false_type());
+  if (!G.any_spill) return;
+  k_lists_reserve<<<dim3(G.world_blocks == 1 ? 64 : 4, G.world_blocks), 256, 0, s>>>(W, T);
+  build(std::true_type());
 }
 
 void launch_sort(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s) {

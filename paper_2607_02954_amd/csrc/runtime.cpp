@@ -148,13 +148,16 @@ sim_params with_side(const sim_params& p, int n_worlds) {
   return q;
 }
 
-// Capacities of a tile's list segments.  Full (kFullLists): room for twice the
-// world's mean density, at least one node per cell, over each segment's cells;
-// smaller workspaces take a share of it (in eighths; 0: no lists, the tiles
-// test every node).  Worlds of at most kTestedNodes nodes need none: a tile
-// block tests that many nodes in no more loads than it has for its list.
-constexpr int kFullLists = 8;
-constexpr int kListShares[] = {8, 6, 4, 3, 2, 1, 0};
+// How much room a world's tile lists get, most first: segments for twice the
+// world's mean density and at least one node per cell (own nodes: three in four
+// cells) over each segment's cells (kFullLists), or near that without the floor
+// (kCompactLists: 267,756 nodes on 2048^2 406 MB of workspace for 640, 158.4 us
+// per step for 156.6); own nodes alone, as records or as indices; none (the tiles
+// test every node).  Crowds go to the spill area.  Worlds of at most kTestedNodes
+// nodes need no lists: a tile block tests that many nodes in no more loads than
+// it has for its list.
+enum ListLevel : int { kNoLists, kIndexLists, kOwnLists, kCompactLists, kFullLists };
+constexpr int kListLevels[] = {kFullLists, kCompactLists, kOwnLists, kIndexLists, kNoLists};
 constexpr int kTestedNodes = 512;
 // Most 16-cell and 32-cell tiles (of all worlds of a table) that run S4 - S7 as
 // one kernel: 262,144 nodes on 1024^2 (4096 tiles of 16) 94.6 -> 84.3 us per
@@ -167,9 +170,12 @@ constexpr bool few_tiles(size_t n16, size_t n32, size_t n64) {
   return n64 == 0 && n16 <= kFusedTiles16 && n32 <= kFusedTiles32;
 }
 struct ListCaps {
+  int kind = mc::kNoLists, spill = 0;
   int own = 0, strays = 0, near_s = 0, far_s = 0, near_c = 0, far_c = 0;
   size_t stride() const { return (size_t)own + strays + 4 * ((size_t)near_s + far_s + near_c + far_c); }
   void set(mc::WorldDev& d) const {
+    d.tl_kind = kind;
+    d.tl_spill = spill;
     d.tl_own = own;
     d.tl_strays = strays;
     d.tl_near_s = near_s;
@@ -179,25 +185,51 @@ struct ListCaps {
     d.tl_stride = (int)stride();
   }
 };
-ListCaps list_caps(const sim_params& p, int n_part, int share) {
+ListCaps list_caps(const sim_params& p, int n_part, int level) {
   ListCaps k;
-  if (mode_of(p) != mc::kBinned || n_part <= kTestedNodes || share == 0) return k;
+  if (mode_of(p) != mc::kBinned || n_part <= kTestedNodes || level == kNoLists) return k;
+  // every node, and what the blocks reserve for nodes that leave meanwhile
+  k.spill = n_part + n_part / 8 + 64;
+  k.kind = level == kIndexLists ? mc::kOwnIndices : level == kOwnLists ? mc::kOwnRecords : mc::kSegments;
+  if (k.kind != mc::kSegments) return k;
   const bool mk = p.marker_offset > 0.f;
   const double T = tile_side(p), r = mc::far_reach_before(p.repulse_radius, mk), n = mc::near_reach(mk);
-  const double per = std::max(1.0, 2.0 * n_part / ((double)p.nx * p.ny)) * share / kFullLists;
+  const double mean = n_part / ((double)p.nx * p.ny);
   // (the smaller a region, the more its count varies around the mean)
-  auto cap = [&](double cells) {
-    return (int)std::min<double>(n_part, 8.0 * std::ceil((cells + 3.0 * std::sqrt(cells)) * per / 8.0));
+  auto cap = [&](double cells, int lv, double row = 0, double floor = 1.0) {
+    const double c = lv == kFullLists ? std::max(floor, 2.0 * mean) * (cells + 3.0 * std::sqrt(cells))
+                                      : 2.0 * mean * cells + 6.0 * std::sqrt(mean * cells) + 12.0 + row;
+    return (int)std::min<double>(n_part, 8.0 * std::ceil(c / 8.0));
   };
-  k.own = cap(T * T);
-  k.strays = cap(4 * T);
-  k.near_s = cap(n * T);
-  k.far_s = cap((r - n) * T);
-  k.near_c = cap(n * n);
-  k.far_c = cap(r * r - n * n);
-  // records are numbered in 32 bits
-  if (k.stride() * n_tiles_of(p) > 0x7fffffffull) return list_caps(p, n_part, share - 1);
+  k.own = cap(T * T, level, 0, 0.75);
+  k.strays = cap(4 * T, kFullLists);
+  k.near_s = cap(n * T, level, T);                // (a filament that lies along the side)
+  k.far_s = cap((r - n) * T, level, T);
+  k.near_c = cap(n * n, level);
+  k.far_c = cap(r * r - n * n, level);
+  // (all nodes in crowds with their copies in the lists around, or half a million
+  // entries more than there are nodes)
+  const double copies = (T + 2 * r) * (T + 2 * r) / (T * T);
+  const double spill = std::min(1.2 * copies * n_part, n_part + 524288.0) + 1024;
+  // entries are numbered in 32 bits
+  if ((double)k.stride() * n_tiles_of(p) + spill > 2147483647.0) return list_caps(p, n_part, level - 1);
+  k.spill = (int)spill;
   return k;
+}
+// Whether the pre-pass gives crowds room in the spill area too.  In worlds of
+// few nodes the two launches that takes (5 us) cost more than a first step whose
+// crowded tiles test every node: a single step of 3072 nodes on 256^2 36.9 us
+// without them, 42.5 with them.
+constexpr int kSpillNodes = 4096;
+bool may_spill(const ListCaps& k, int n_part) {
+  return k.kind > mc::kSegments || (k.kind == mc::kSegments && n_part > kSpillNodes);
+}
+// One set of a world's lists.
+void carve_lists(Carver& c, const sim_params& p, const ListCaps& k, int** cnt, int4** rec) {
+  if (k.kind == mc::kNoLists) return;
+  *cnt = c.take<int>(n_tiles_of(p) * mc::kListCounts + mc::kListWords);
+  if (k.kind == mc::kOwnIndices) *rec = (int4*)c.take<int>(k.spill);
+  else *rec = c.take<int4>(n_tiles_of(p) * k.stride() + k.spill);
 }
 
 // Bytes the binned transfer's node records took before the tile lists: the
@@ -209,7 +241,7 @@ size_t least_list_bytes(const sim_params& p, int n_part) {
          align_up(nt * T * T * 16);
 }
 
-void carve_world_bufs(Carver& c, const sim_params& p, int n_part, int share, WorldBufs& b) {
+void carve_world_bufs(Carver& c, const sim_params& p, int n_part, int level, WorldBufs& b) {
   const size_t ncell = (size_t)p.nx * p.ny;
   const size_t N = std::max(n_part, 1);
   b.f_alt = c.take<float>(9 * ncell);
@@ -238,12 +270,8 @@ void carve_world_bufs(Carver& c, const sim_params& p, int n_part, int share, Wor
   } else {
     b.cell_alt = c.take<int>(2 * N);
     b.frac_alt = c.take<float>(2 * N);
-    const ListCaps k = list_caps(p, n_part, share);
-    if (k.own > 0)
-      for (int j = 0; j < 2; ++j) {
-        b.tl_cnt[j] = c.take<int>(n_tiles_of(p) * mc::kListCounts);
-        b.tl_rec[j] = c.take<int4>(n_tiles_of(p) * k.stride());
-      }
+    const ListCaps k = list_caps(p, n_part, level);
+    for (int j = 0; j < 2; ++j) carve_lists(c, p, k, &b.tl_cnt[j], &b.tl_rec[j]);
     if (p.marker_offset > 0.f) b.d_marker = c.take<float>(2 * N);
     if (p.mdf_iters > 1) {
       b.U_d = c.take<float>(2 * N);
@@ -262,7 +290,7 @@ struct Slot {
   int* fil_offset = nullptr;
   int* cell = nullptr;          // positions before an even step (and after a run)
   float* frac = nullptr;
-  int list_share = kFullLists;  // size of the tile lists (list_caps)
+  int list_level = kFullLists;  // room of the tile lists (list_caps)
   float* rest_angle = nullptr;
   float* rest_length = nullptr;
   float* amp = nullptr;
@@ -375,7 +403,7 @@ mc::WorldDev world_desc(const Slot& s, int parity, const mc::Ctl* ctl_src, mc::C
   d.perm = s.b.perm;
   d.rec = s.b.rec;
   d.part = s.b.part;
-  const ListCaps k = list_caps(p, s.n_part, s.list_share);
+  const ListCaps k = list_caps(p, s.n_part, s.list_level);
   k.set(d);
   d.tl_rec = s.b.tl_rec[src];
   d.tl_cnt = s.b.tl_cnt[src];
@@ -595,10 +623,14 @@ struct Engine {
     for (const auto& sl : slots)
       if (sl.used && mode_of(sl.p) != mc::kBinned) any_node = true;
     more = more || (any_node && !grid.any_node);
-    bool any_lists = false;
+    bool any_lists = false, any_spill = false;
     for (const auto& sl : slots)
-      if (sl.used && sl.b.tl_cnt[0]) any_lists = true;
-    if (any_lists) grid.any_lists = 1;
+      if (sl.used && sl.b.tl_cnt[0]) {
+        any_lists = true;
+        any_spill = any_spill || may_spill(list_caps(sl.p, sl.n_part, sl.list_level), sl.n_part);
+      }
+    if (any_lists) grid.any_lists = 1;            // (the pre-pass is not part of the captured graphs)
+    if (any_spill) grid.any_spill = 1;
     bool any_energy = false, any_markers = false;
     int mdf_max = 1;
     for (const auto& sl : slots) {
@@ -744,11 +776,13 @@ struct Engine {
 
   // Run n steps with parity starting at 0; n even uses graphs only.  An odd
   // tail step is launched directly with descriptor set A.
-  sim_status run_steps(int n) {
+  // t: if not null, every world runs n steps from step *t; else what its control
+  // word says.
+  sim_status run_steps(int n, const long long* t = nullptr) {
     if (n <= 0) return SIM_OK;
     // tile lists of the current positions for the first step (each step's
     // integrate then makes the next one's)
-    mc::launch_list_prepass(desc[0], tab, grid, stream);
+    mc::launch_list_prepass(desc[0], tab, grid, t ? *t : 0, t ? n : -1, stream);
     if (n >= want_chunk && (!g_chunk || chunk_steps != want_chunk)) {
       if (g_chunk) hipGraphExecDestroy(g_chunk);
       g_chunk = nullptr;
@@ -797,10 +831,10 @@ struct sim_world {
 
 namespace {
 
-size_t world_buf_bytes(const sim_params& p, int n_part, int share) {
+size_t world_buf_bytes(const sim_params& p, int n_part, int level) {
   Carver c{nullptr};
   WorldBufs b;
-  carve_world_bufs(c, p, n_part, share, b);
+  carve_world_bufs(c, p, n_part, level, b);
   return c.off;
 }
 // With the least room for node records that is accepted (least_list_bytes).
@@ -811,14 +845,14 @@ size_t least_buf_bytes(const sim_params& p, int n_part) {
 }
 
 // Workspace bytes of n worlds (n = 1: sim_create) with tile lists of the given
-// share, or (share < 0) the least that is accepted.
-size_t worlds_bytes(const sim_params& asked, int n, const sim_arrays* arrays, int share) {
-  const sim_params p = share < 0 ? asked : with_side(asked, n);
+// level, or (level < 0) the least that is accepted.
+size_t worlds_bytes(const sim_params& asked, int n, const sim_arrays* arrays, int level) {
+  const sim_params p = level < 0 ? asked : with_side(asked, n);
   const size_t ncell = (size_t)p.nx * p.ny;
   size_t packs = 0, bufs = 0;
   for (int i = 0; i < n; ++i) {
     packs += std::max(arrays[i].n_filaments, 1);
-    bufs += share < 0 ? least_buf_bytes(p, arrays[i].n_particles) : world_buf_bytes(p, arrays[i].n_particles, share);
+    bufs += level < 0 ? least_buf_bytes(p, arrays[i].n_particles) : world_buf_bytes(p, arrays[i].n_particles, level);
   }
   size_t tiles[mc::kTileFamilies] = {0, 0, 0};
   tiles[tile_family(p)] = (size_t)n * n_tiles_of(p);
@@ -959,7 +993,7 @@ sim_status sim_workspace_size(const sim_params* p, int32_t n_filaments, int32_t 
 
 // One world of a handle: validate and read its arrays' host-side facts
 // (offsets, branches, loops) and carve its buffers.
-static sim_status prepare_slot(const sim_params* p, const sim_arrays* a, int share, hipStream_t s, Carver& c, Slot& sl) {
+static sim_status prepare_slot(const sim_params* p, const sim_arrays* a, int level, hipStream_t s, Carver& c, Slot& sl) {
   sim_status st;
   std::vector<int> h_off;
   if (a->n_filaments > 0) {
@@ -1001,8 +1035,8 @@ static sim_status prepare_slot(const sim_params* p, const sim_arrays* a, int sha
   sl.e_sensed = a->energy_sensed;
   sl.e_collected = a->energy_collected;
   if ((st = read_loops(a, s, &sl.any_loop))) return st;
-  sl.list_share = share;
-  carve_world_bufs(c, *p, a->n_particles, share, sl.b);
+  sl.list_level = level;
+  carve_world_bufs(c, *p, a->n_particles, level, sl.b);
   sl.fbuf[0] = a->f;
   sl.fbuf[1] = sl.b.f_alt;
   sl.u = a->u;
@@ -1025,10 +1059,10 @@ static sim_status create_worlds(const sim_params* asked, int n, const sim_arrays
                                 size_t ws_bytes, void* stream, sim_world** out) {
   const sim_params side = with_side(*asked, n), *p = &side;
   // the largest tile lists the workspace holds
-  int share = 0;
-  for (int k : kListShares) {
+  int level = kNoLists;
+  for (int k : kListLevels) {
     if (worlds_bytes(*asked, n, arrays, k) > ws_bytes) continue;
-    share = k;
+    level = k;
     break;
   }
   hipStream_t s = (hipStream_t)stream;
@@ -1053,7 +1087,7 @@ static sim_status create_worlds(const sim_params* asked, int n, const sim_arrays
   sim_status st;
   for (int i = 0; i < n; ++i) {
     Slot sl;
-    if ((st = prepare_slot(p, &arrays[i], share, s, c, sl))) {
+    if ((st = prepare_slot(p, &arrays[i], level, s, c, sl))) {
       delete w;
       return st;
     }
@@ -1132,9 +1166,8 @@ static void copy_back(const Slot& s, bool f, bool x, const int* skip, hipStream_
 static sim_status world_run(sim_world* w, int64_t t, int n) {
   Engine& e = w->eng;
   sim_status st;
-  for (int k = 0; k < (int)e.slots.size(); ++k)
-    if ((st = e.set_ctl(k, t, n))) return st;
-  if ((st = e.run_steps(n))) return st;
+  const long long first = t;
+  if ((st = e.run_steps(n, &first))) return st;
   if (n & 1) {
     // the state ended in the alternate buffers: copy them back
     for (const Slot& s : e.slots) copy_back(s, true, s.b.cell_alt != nullptr, nullptr, e.stream);
@@ -1226,7 +1259,7 @@ sim_status sim_debug_substep(sim_world* w, int32_t which, int64_t t) {
   const mc::Grid& g = e.grid;
   switch (which) {
     case 0:
-      mc::launch_list_prepass(d, e.tab, g, e.stream);
+      mc::launch_list_prepass(d, e.tab, g, 0, -1, e.stream);
       mc::launch_elastic(d, e.tab, g, e.stream);
       mc::launch_sort(d, e.tab, g, e.stream);
       break;
@@ -1265,7 +1298,7 @@ sim_status sim_profile_steps(sim_world* w, int64_t t0, int32_t n_steps, float* m
   for (auto& x : fl) HIPCHK(hipEventCreate(&x));
   sim_status st = e.set_ctl(0, t0, n_steps);
   if (st) return st;
-  mc::launch_list_prepass(e.desc[0], e.tab, e.grid, e.stream);
+  mc::launch_list_prepass(e.desc[0], e.tab, e.grid, 0, -1, e.stream);
   for (int k = 0; k < n_steps; ++k) {
     const mc::WorldDev* d = e.desc[k & 1];
     hipEvent_t* E = ev.data() + (size_t)k * (kGroups + 1);
@@ -1401,7 +1434,7 @@ struct NoallocLayout {
   size_t bytes = 0;
 };
 
-void carve_noalloc(char* base, const sim_params& p, int n_fil, int n_part, int share, NoallocLayout& L) {
+void carve_noalloc(char* base, const sim_params& p, int n_fil, int n_part, int level, NoallocLayout& L) {
   Carver c{base};
   const size_t ncell = (size_t)p.nx * p.ny;
   L.desc = c.take<mc::WorldDev>(2);
@@ -1413,7 +1446,7 @@ void carve_noalloc(char* base, const sim_params& p, int n_fil, int n_part, int s
   L.items = c.take<int2>((ncell + mc::kCellsPerItem - 1) / mc::kCellsPerItem);
   L.scan = c.take<int2>((ncell + 1023) / 1024);
   L.wlist = c.take<int2>(1);
-  carve_world_bufs(c, p, n_part, share, L.b);
+  carve_world_bufs(c, p, n_part, level, L.b);
   L.bytes = c.off;
 }
 
@@ -1491,16 +1524,16 @@ sim_status sim_step_noalloc(const sim_params* asked, const sim_arrays* a, int64_
   const size_t need = L.bytes - world_buf_bytes(*asked, a->n_particles, 0) + least_buf_bytes(*asked, a->n_particles);
   if (need > kScratchBytes)
     return fail(SIM_E_WORKSPACE, "world needs %zu bytes of scratch; sim_step_noalloc holds %zu", need, kScratchBytes);
-  int share = 0;                                  // the largest tile lists the array holds
-  for (int k : kListShares) {
+  int level = kNoLists;                                  // the largest tile lists the array holds
+  for (int k : kListLevels) {
     carve_noalloc(nullptr, *p, a->n_filaments, a->n_particles, k, L);
-    share = k;
+    level = k;
     if (L.bytes <= kScratchBytes) break;
   }
   void* base = nullptr;
   if ((st = scratch_address(&base))) return st;
   L = NoallocLayout();
-  carve_noalloc((char*)base, *p, a->n_filaments, a->n_particles, share, L);
+  carve_noalloc((char*)base, *p, a->n_filaments, a->n_particles, level, L);
   hipStream_t s = (hipStream_t)stream;
   const size_t ncell = (size_t)p->nx * p->ny;
   const size_t nt = n_tiles_of(*p);
@@ -1530,7 +1563,7 @@ sim_status sim_step_noalloc(const sim_params* asked, const sim_arrays* a, int64_
   sl.e_sensed = a->energy_sensed;
   sl.e_collected = a->energy_collected;
   sl.b = L.b;
-  sl.list_share = share;
+  sl.list_level = level;
   sl.fbuf[0] = a->f;
   sl.fbuf[1] = L.b.f_alt;
   sl.u = a->u;
@@ -1565,6 +1598,7 @@ sim_status sim_step_noalloc(const sim_params* asked, const sim_arrays* a, int64_
   g.any_binned = mode == mc::kBinned;
   g.any_node = mode != mc::kBinned;
   g.any_lists = L.b.tl_cnt[0] != nullptr;
+  g.any_spill = may_spill(list_caps(*p, n_part, level), n_part);
   g.fused = mode == mc::kBinned && p->mdf_iters <= 1 && few_tiles(fam == 0 ? nt : 0, fam == 1 ? nt : 0, fam == 2 ? nt : 0);
   g.max_radius = p->repulse_radius;
   g.any_energy = p->energy_rate > 0.f && a->energy ? 1 : 0;
@@ -1585,7 +1619,7 @@ sim_status sim_step_noalloc(const sim_params* asked, const sim_arrays* a, int64_
                      n_part, n_items, n_scan, (long long)t);
   hipLaunchKernelGGL(k_noalloc_counts, dim3(1), dim3(64), 0, s, L, n_fil, (int)nt, fam, n_scan, n_items);
   // the step itself: the kernels sim_step runs, with parity-0 descriptors
-  mc::launch_list_prepass(L.desc, tab, g, s);
+  mc::launch_list_prepass(L.desc, tab, g, 0, -1, s);
   enqueue_step(L.desc, tab, g, false, s);
   copy_back(sl, true, L.b.cell_alt != nullptr, L.err, s);
   if (status) hipLaunchKernelGGL(k_noalloc_status, dim3(1), dim3(64), 0, s, L.err, L.flags, status);
@@ -1708,7 +1742,7 @@ struct AdjLayout {
   float* dbar_m = nullptr;           // [2][N] (with MDF)
 };
 
-void carve_adj(Carver& c, const sim_params& p, int n_part, int m, int share, AdjLayout& L) {
+void carve_adj(Carver& c, const sim_params& p, int n_part, int m, int level, AdjLayout& L) {
   L.m = m;
   L.N = std::max(n_part, 1);
   L.ncell = (size_t)p.nx * p.ny;
@@ -1726,16 +1760,13 @@ void carve_adj(Carver& c, const sim_params& p, int n_part, int m, int share, Adj
   L.F.resize(m);
   L.tl_rec.assign(m, nullptr);
   L.tl_cnt.assign(m, nullptr);
-  const ListCaps caps = list_caps(p, n_part, share);
+  const ListCaps caps = list_caps(p, n_part, level);
   for (int j = 0; j < m; ++j) {
     L.grad[j] = c.take<float2>(L.ncell);
     L.Fg[j] = c.take<float2>(L.ncell);
     L.u[j] = c.take<float2>(L.ncell);
     L.F[j] = c.take<float>(2 * L.N);
-    if (caps.own > 0) {
-      L.tl_cnt[j] = c.take<int>(n_tiles_of(p) * mc::kListCounts);
-      L.tl_rec[j] = c.take<int4>(n_tiles_of(p) * caps.stride());
-    }
+    carve_lists(c, p, caps, &L.tl_cnt[j], &L.tl_rec[j]);
   }
   for (int k = 0; k < 2; ++k) {
     L.xbar[k] = c.take<float>(2 * L.N);
@@ -1776,23 +1807,23 @@ struct AdjShared {
   mc::AdjDev* adj = nullptr;
 };
 
-static size_t carve_backward(Carver& c, const Engine& e, int m, int share, std::vector<AdjLayout>& Ls, AdjShared& S) {
+static size_t carve_backward(Carver& c, const Engine& e, int m, int level, std::vector<AdjLayout>& Ls, AdjShared& S) {
   const size_t nw = e.slots.size();
   Ls.assign(nw, AdjLayout());
-  for (size_t w = 0; w < nw; ++w) carve_adj(c, e.slots[w].p, e.slots[w].n_part, m, share, Ls[w]);
+  for (size_t w = 0; w < nw; ++w) carve_adj(c, e.slots[w].p, e.slots[w].n_part, m, level, Ls[w]);
   S.desc = c.take<mc::WorldDev>((size_t)m * nw);
   S.adj = c.take<mc::AdjDev>((size_t)2 * m * nw);
   return c.off;
 }
 
-// Bytes of the adjoint workspace with tape lists of the given share, or
-// (share < 0) the least that is accepted.
-static size_t backward_bytes(const Engine& e, int m, int share) {
+// Bytes of the adjoint workspace with tape lists of the given level, or
+// (level < 0) the least that is accepted.
+static size_t backward_bytes(const Engine& e, int m, int level) {
   Carver c{nullptr};
   std::vector<AdjLayout> Ls;
   AdjShared S;
-  size_t bytes = carve_backward(c, e, m, std::max(share, 0), Ls, S);
-  if (share < 0)
+  size_t bytes = carve_backward(c, e, m, std::max(level, 0), Ls, S);
+  if (level < 0)
     for (const Slot& s : e.slots) {
       const size_t nt = n_tiles_of(s.asked);
       bytes += m * (least_list_bytes(s.asked, s.n_part) - 2 * align_up(nt * 4)) + align_up((nt + 1) * 4) +
@@ -1824,16 +1855,16 @@ sim_status sim_backward(sim_world* w, int64_t t0, int32_t n_steps, int32_t ckpt_
   }
   const size_t need = backward_bytes(e, ckpt_every, -1);
   if (adj_ws_bytes < need) return fail(SIM_E_WORKSPACE, "adjoint workspace has %zu bytes, needs %zu", adj_ws_bytes, need);
-  int share = 0;                         // the largest tape lists the workspace holds
-  for (int k : kListShares) {
+  int level = kNoLists;                         // the largest tape lists the workspace holds
+  for (int k : kListLevels) {
     if (backward_bytes(e, ckpt_every, k) > adj_ws_bytes) continue;
-    share = k;
+    level = k;
     break;
   }
   Carver c{(char*)adj_ws};
   std::vector<AdjLayout> Ls;
   AdjShared S;
-  carve_backward(c, e, ckpt_every, share, Ls, S);
+  carve_backward(c, e, ckpt_every, level, Ls, S);
   const int m_max = ckpt_every;
   const int nseg = (n_steps + ckpt_every - 1) / ckpt_every;
   const int K = std::max(e.slots[0].p.mdf_iters, 1);
@@ -1841,7 +1872,11 @@ sim_status sim_backward(sim_world* w, int64_t t0, int32_t n_steps, int32_t ckpt_
   mc::Grid g = e.grid;
   g.any_binned = 1;
   g.any_lists = Ls[0].tl_cnt[0] != nullptr;
-  for (const AdjLayout& L : Ls) g.any_lists |= L.tl_cnt[0] != nullptr;
+  g.any_spill = 0;
+  for (size_t k = 0; k < Ls.size(); ++k) {
+    g.any_lists |= Ls[k].tl_cnt[0] != nullptr;
+    g.any_spill |= may_spill(list_caps(e.slots[k].p, e.slots[k].n_part, level), e.slots[k].n_part);
+  }
   g.pbd_max = 0;
   for (const Slot& s : e.slots) g.pbd_max = std::max(g.pbd_max, s.p.pbd_iters);
   g.any_sorted = 0;
@@ -1872,7 +1907,7 @@ sim_status sim_backward(sim_world* w, int64_t t0, int32_t n_steps, int32_t ckpt_
       d.Fg = L.Fg[j];
       d.u = L.u[j];
       d.fel = L.F[j];
-      const ListCaps caps = list_caps(e.slots[k].p, e.slots[k].n_part, share);
+      const ListCaps caps = list_caps(e.slots[k].p, e.slots[k].n_part, level);
       caps.set(d);
       d.keep_force = 1;
       d.tl_rec = L.tl_rec[j];                  // step j's lists, for the adjoint too; the last step makes none
@@ -1952,7 +1987,7 @@ sim_status sim_backward(sim_world* w, int64_t t0, int32_t n_steps, int32_t ckpt_
       mc::launch_set_ctl(L.ctl, t0 + k0, m, st);
     }
     // recompute the segment forward for every world, writing each step's fields to the tapes
-    mc::launch_list_prepass(S.desc, e.tab, g, st);
+    mc::launch_list_prepass(S.desc, e.tab, g, 0, -1, st);
     for (int j = 0; j < m; ++j) enqueue_step(S.desc + (size_t)j * nw, e.tab, g, false, st);
     HIPCHK(hipGetLastError());
     // reverse the segment step by step, every world in the same launches
@@ -1991,7 +2026,7 @@ struct BatchWorldLayout {
   size_t bytes = 0;
 };
 
-void carve_batch_world(Carver& c, const sim_params& p, int n_fil, int n_part, int share, Slot& s) {
+void carve_batch_world(Carver& c, const sim_params& p, int n_fil, int n_part, int level, Slot& s) {
   const size_t ncell = (size_t)p.nx * p.ny;
   const size_t N = std::max(n_part, 1), F = std::max(n_fil, 1);
   s.fil_offset = c.take<int>(F + 1);
@@ -2014,18 +2049,18 @@ void carve_batch_world(Carver& c, const sim_params& p, int n_fil, int n_part, in
   }
   s.fbuf[0] = c.take<float>(9 * ncell);
   s.u = c.take<float>(2 * ncell);
-  s.list_share = share;
-  carve_world_bufs(c, p, n_part, share, s.b);
+  s.list_level = level;
+  carve_world_bufs(c, p, n_part, level, s.b);
   s.fbuf[1] = s.b.f_alt;
 }
 
-// Pool bytes of a world with tile lists of the given share, or (share < 0) the
+// Pool bytes of a world with tile lists of the given level, or (level < 0) the
 // least a world takes (sim_batch_world_bytes).
-size_t batch_world_bytes(const sim_params& p, int n_fil, int n_part, int share) {
+size_t batch_world_bytes(const sim_params& p, int n_fil, int n_part, int level) {
   Carver c{nullptr};
   Slot s;
-  carve_batch_world(c, p, n_fil, n_part, std::max(share, 0), s);
-  return share >= 0 ? c.off : c.off - world_buf_bytes(p, n_part, 0) + least_buf_bytes(p, n_part);
+  carve_batch_world(c, p, n_fil, n_part, std::max(level, 0), s);
+  return level >= 0 ? c.off : c.off - world_buf_bytes(p, n_part, 0) + least_buf_bytes(p, n_part);
 }
 
 bool pool_alloc(sim_batch* b, size_t bytes, size_t* off) {
@@ -2174,14 +2209,14 @@ sim_status sim_batch_admit(sim_batch* b, const sim_params* p, const sim_arrays* 
   // full tile lists while that leaves half of the pool free; then what the
   // world's least share of it (sim_batch_world_bytes) holds
   const size_t least = batch_world_bytes(*p, init->n_filaments, init->n_particles, -1);
-  size_t bytes = batch_world_bytes(*p, init->n_filaments, init->n_particles, kFullLists);
-  int share = kFullLists;
+  int level = kFullLists;
+  size_t bytes = batch_world_bytes(*p, init->n_filaments, init->n_particles, level);
   size_t free_bytes = 0;
   for (const auto& f : b->free_list) free_bytes += f.second;
   size_t off = 0;
   if (free_bytes < bytes + b->pool_bytes / 2 || bytes < least || !pool_alloc(b, bytes, &off)) {
-    for (int k : kListShares) {
-      share = k;
+    for (int k : kListLevels) {
+      level = k;
       if (batch_world_bytes(*p, init->n_filaments, init->n_particles, k) <= least) break;
     }
     bytes = least;
@@ -2198,7 +2233,7 @@ sim_status sim_batch_admit(sim_batch* b, const sim_params* p, const sim_arrays* 
   s.pool_off = off;
   s.pool_len = bytes;
   Carver c{b->pool + off};
-  carve_batch_world(c, *p, s.n_fil, s.n_part, share, s);
+  carve_batch_world(c, *p, s.n_fil, s.n_part, level, s);
   const size_t N = s.n_part, F = s.n_fil, ncell = (size_t)p->nx * p->ny;
   auto cp = [&](void* dst, const void* src, size_t by) -> sim_status {
     if (by) HIPCHK(hipMemcpyAsync(dst, src, by, hipMemcpyDeviceToDevice, e.stream));
