@@ -314,6 +314,12 @@ struct Slot {
   int cur = 0;          // populations (and positions) buffer that holds the state
   int remaining = 0;    // host mirror of the steps left (batch)
   size_t pool_off = 0, pool_len = 0;
+  // batch: room for larger lists than the world's own part of the pool holds
+  // (ext_len 0: none), and the lists of that part
+  size_t ext_off = 0, ext_len = 0;
+  int own_level = kNoLists;
+  int* own_cnt[2] = {};
+  int4* own_rec[2] = {};
   bool needs_zero = false;   // cnt must be cleared before first use
 };
 
@@ -2093,6 +2099,75 @@ void pool_free(sim_batch* b, size_t off, size_t len) {
   }
 }
 
+// Larger tile lists than a world's own part of the pool holds lie where no
+// world is, from the end of the pool down.  A world that is admitted takes its
+// place as if they were not there, and worlds whose larger lists lay there go
+// back to their own: what a pool admits depends on sim_batch_world_bytes alone.
+// (The lists are made anew by every advance, and all of this is ordered on the
+// batch's stream.)
+void use_lists(Slot& s, int level, int* const* cnt, int4* const* rec) {
+  s.list_level = level;
+  for (int j = 0; j < 2; ++j) {
+    s.b.tl_cnt[j] = cnt[j];
+    s.b.tl_rec[j] = rec[j];
+  }
+}
+
+void drop_larger_lists(sim_batch* b, size_t off, size_t len) {
+  for (Slot& s : b->eng.slots) {
+    if (!s.used || s.ext_len == 0 || s.ext_off + s.ext_len <= off || off + len <= s.ext_off) continue;
+    s.ext_len = 0;
+    use_lists(s, s.own_level, s.own_cnt, s.own_rec);
+  }
+}
+
+// The highest place of `bytes` bytes in the pool that nothing lies in.
+bool find_free(const sim_batch* b, size_t bytes, size_t* off) {
+  std::map<size_t, size_t> ext;                  // larger lists, by their end
+  for (const Slot& s : b->eng.slots)
+    if (s.used && s.ext_len) ext[s.ext_off + s.ext_len] = s.ext_off;
+  for (auto it = b->free_list.rbegin(); it != b->free_list.rend(); ++it) {
+    size_t end = (it->first + it->second) / kAlign * kAlign;   // of what is left of the hole, from above
+    for (auto x = ext.rbegin(); x != ext.rend() && end > it->first; ++x) {
+      if (x->first > end || x->second < it->first) continue;
+      if (end - x->first >= bytes) break;
+      end = x->second;
+    }
+    if (end >= it->first + bytes) {
+      *off = end - bytes;
+      return true;
+    }
+  }
+  return false;
+}
+
+void give_larger_lists(sim_batch* b) {
+  size_t too_large = SIZE_MAX;                   // no room for this much
+  for (Slot& s : b->eng.slots) {
+    if (!s.used || s.ext_len) continue;
+    for (int level : kListLevels) {
+      if (level <= s.own_level || level < kCompactLists) break;
+      const ListCaps k = list_caps(s.p, s.n_part, level);
+      if (k.kind == mc::kNoLists) break;
+      int* cnt[2] = {};
+      int4* rec[2] = {};
+      Carver need{nullptr};
+      for (int j = 0; j < 2; ++j) carve_lists(need, s.p, k, &cnt[j], &rec[j]);
+      size_t off = 0;
+      if (need.off >= too_large || !find_free(b, need.off, &off)) {
+        too_large = std::min(too_large, need.off);
+        continue;
+      }
+      Carver c{b->pool + off};
+      for (int j = 0; j < 2; ++j) carve_lists(c, s.p, k, &cnt[j], &rec[j]);
+      s.ext_off = off;
+      s.ext_len = need.off;
+      use_lists(s, level, cnt, rec);
+      break;
+    }
+  }
+}
+
 }  // namespace
 
 extern "C" {
@@ -2206,22 +2281,17 @@ sim_status sim_batch_admit(sim_batch* b, const sim_params* p, const sim_arrays* 
     return fail(SIM_E_INVALID, "batched filaments (with those hanging from them) are limited to %d nodes", e.grid.pack);
   bool any_loop = false;
   if ((st = read_loops(init, e.stream, &any_loop))) return st;
-  // full tile lists while that leaves half of the pool free; then what the
-  // world's least share of it (sim_batch_world_bytes) holds
-  const size_t least = batch_world_bytes(*p, init->n_filaments, init->n_particles, -1);
-  int level = kFullLists;
-  size_t bytes = batch_world_bytes(*p, init->n_filaments, init->n_particles, level);
-  size_t free_bytes = 0;
-  for (const auto& f : b->free_list) free_bytes += f.second;
-  size_t off = 0;
-  if (free_bytes < bytes + b->pool_bytes / 2 || bytes < least || !pool_alloc(b, bytes, &off)) {
-    for (int k : kListLevels) {
-      level = k;
-      if (batch_world_bytes(*p, init->n_filaments, init->n_particles, k) <= least) break;
-    }
-    bytes = least;
-    if (!pool_alloc(b, bytes, &off)) return fail(SIM_E_WORKSPACE, "pool exhausted (world needs %zu bytes)", bytes);
+  // the world's own part of the pool, with the largest tile lists it holds
+  const size_t bytes = batch_world_bytes(*p, init->n_filaments, init->n_particles, -1);
+  int level = kNoLists;
+  for (int k : kListLevels) {
+    if (batch_world_bytes(*p, init->n_filaments, init->n_particles, k) > bytes) continue;
+    level = k;
+    break;
   }
+  size_t off = 0;
+  if (!pool_alloc(b, bytes, &off)) return fail(SIM_E_WORKSPACE, "pool exhausted (world needs %zu bytes)", bytes);
+  drop_larger_lists(b, off, bytes);
   Slot s;
   s.used = true;
   s.p = *p;
@@ -2234,6 +2304,11 @@ sim_status sim_batch_admit(sim_batch* b, const sim_params* p, const sim_arrays* 
   s.pool_len = bytes;
   Carver c{b->pool + off};
   carve_batch_world(c, *p, s.n_fil, s.n_part, level, s);
+  s.own_level = level;
+  for (int j = 0; j < 2; ++j) {
+    s.own_cnt[j] = s.b.tl_cnt[j];
+    s.own_rec[j] = s.b.tl_rec[j];
+  }
   const size_t N = s.n_part, F = s.n_fil, ncell = (size_t)p->nx * p->ny;
   auto cp = [&](void* dst, const void* src, size_t by) -> sim_status {
     if (by) HIPCHK(hipMemcpyAsync(dst, src, by, hipMemcpyDeviceToDevice, e.stream));
@@ -2284,6 +2359,7 @@ sim_status sim_batch_admit(sim_batch* b, const sim_params* p, const sim_arrays* 
   s.remaining = steps;
   e.slots[w] = s;
   if ((st = e.set_ctl(w, t0, steps))) return st;
+  give_larger_lists(b);
   if ((st = e.rebuild())) {
     e.slots[w] = Slot();
     pool_free(b, off, bytes);
@@ -2343,6 +2419,7 @@ sim_status sim_batch_retire(sim_batch* b, int32_t slot, const sim_arrays* out) {
   const unsigned fl = *hflag;
   pool_free(b, s.pool_off, s.pool_len);
   s = Slot();
+  give_larger_lists(b);
   sim_status st = e.rebuild();
   if (st) return st;
   if (fl & mc::kFlagBins) return fail(SIM_E_STATE, "world in slot %d: tile bins out of date", slot);
