@@ -131,20 +131,22 @@ inline size_t n_tiles_of(const sim_params& p) { return (size_t)tiles_x(p) * tile
 // for one item (12,000 nodes on 400^2, 625 tiles: 29.0 -> 21.5 us per step).
 constexpr size_t align8(size_t n) { return (n + 7) & ~size_t(7); }
 
-// The parameters with the tile side that n worlds of them run with.  Worlds of
-// few 32-cell tiles leave most of the chip idle (about one tile block per CU, or
-// less) and take 16-cell tiles instead: 16,000 nodes on 256^2 (64 tiles of 32)
-// 30.0 -> 19.9 us per step, 14,000 on 448^2 (196) 36.7 -> 23.5, 65,536 on 512^2
-// (256) 32.6 -> 29.2; at 768^2 (576) 32-cell tiles win, 31.4 against 49.8.
-// 64-cell tiles run as 32-cell ones: 1,048,576 nodes on 2048^2 230 -> 207,
-// 262,144 on 1024^2 77 -> 57.  Results do not depend on the side.
+// The tile side that binned worlds run with, from the 32-cell tiles that they
+// have together: worlds of few leave most of the chip idle (about one tile block
+// per CU, or less) and take 16-cell tiles, others 32-cell ones, whatever was asked
+// for; results do not depend on the side.  us per step with 16- and 32-cell tiles:
+// 16,000 nodes on 256^2 (64 tiles of 32) 19.9 and 30.0, 14,000 on 448^2 (196) 23.5
+// and 36.7, 65,536 on 512^2 (256) 29.2 and 32.6; 768^2 (576) 49.8 and 31.4,
+// 1,048,576 on 2048^2 295 and 203.  64-cell tiles lose to 32-cell ones at every
+// size: 2048^2 230 to 207, 262,144 on 1024^2 77 to 57, eight batched worlds of
+// 128^2 to 180^2 75 to 42.
 constexpr size_t kSmallTiles = 320;
+constexpr int side_of(size_t tiles32) { return tiles32 <= kSmallTiles ? 16 : 32; }
+size_t tiles32_of(const sim_params& p) { return (size_t)((p.nx + 31) / 32) * ((p.ny + 31) / 32); }
+// The parameters with the tile side that n worlds of them run with.
 sim_params with_side(const sim_params& p, int n_worlds) {
   sim_params q = p;
-  q.tile_side = tile_side(p);
-  if (mode_of(p) != mc::kBinned) return q;
-  if (q.tile_side == 64) q.tile_side = 32;
-  if (q.tile_side == 32 && (size_t)n_worlds * n_tiles_of(q) <= kSmallTiles) q.tile_side = 16;
+  q.tile_side = mode_of(p) == mc::kBinned ? side_of(n_worlds * tiles32_of(p)) : tile_side(p);
   return q;
 }
 
@@ -270,8 +272,6 @@ void carve_world_bufs(Carver& c, const sim_params& p, int n_part, int level, Wor
   } else {
     b.cell_alt = c.take<int>(2 * N);
     b.frac_alt = c.take<float>(2 * N);
-    const ListCaps k = list_caps(p, n_part, level);
-    for (int j = 0; j < 2; ++j) carve_lists(c, p, k, &b.tl_cnt[j], &b.tl_rec[j]);
     if (p.marker_offset > 0.f) b.d_marker = c.take<float>(2 * N);
     if (p.mdf_iters > 1) {
       b.U_d = c.take<float>(2 * N);
@@ -279,11 +279,14 @@ void carve_world_bufs(Carver& c, const sim_params& p, int n_part, int level, Wor
       b.rho_j = c.take<float4>(ncell);
     }
   }
+  // (last: a batch gives its worlds' lists other places)
+  const ListCaps k = list_caps(p, n_part, level);
+  for (int j = 0; j < 2; ++j) carve_lists(c, p, k, &b.tl_cnt[j], &b.tl_rec[j]);
 }
 
 struct Slot {
   bool used = false;
-  sim_params p{};               // with the tile side it runs with (with_side)
+  sim_params p{};               // with the tile side it runs with (side_of)
   sim_params asked{};           // as given
   int n_fil = 0, n_part = 0, max_len = 0;
   std::vector<int> h_off;
@@ -315,11 +318,8 @@ struct Slot {
   int remaining = 0;    // host mirror of the steps left (batch)
   size_t pool_off = 0, pool_len = 0;
   // batch: room for larger lists than the world's own part of the pool holds
-  // (ext_len 0: none), and the lists of that part
+  // (ext_len 0: none)
   size_t ext_off = 0, ext_len = 0;
-  int own_level = kNoLists;
-  int* own_cnt[2] = {};
-  int4* own_rec[2] = {};
   bool needs_zero = false;   // cnt must be cleared before first use
 };
 
@@ -609,14 +609,13 @@ struct Engine {
     n_scan = sc.size();
     n_worlds = wl.size();
     n_items = it.size();
-    // a kernel family stays in the captured graphs once any world needed it
     bool more = false;
     for (int f = 0; f < mc::kTileFamilies; ++f) {
-      if (n_tiles[f] > 0 && grid.tile_blocks[f] == 0) more = true;
-      if (!fixed_grid)
-        grid.tile_blocks[f] = (int)align8(n_tiles[f]);   // one block per tile; 0: family not launched
-      else if (n_tiles[f] > 0)
-        grid.tile_blocks[f] = fixed_tile_blocks;      // stays launched once a world needed it
+      int blocks = (int)align8(n_tiles[f]);       // one block per tile; 0: family not launched
+      if (fixed_grid) blocks = n_tiles[f] > 0 ? fixed_tile_blocks : 0;
+      if (fixed_grid && n_worlds == 0) blocks = grid.tile_blocks[f];   // (an empty batch keeps its graphs)
+      if ((blocks > 0) != (grid.tile_blocks[f] > 0)) more = true;
+      grid.tile_blocks[f] = blocks;
     }
     if (!fixed_grid) {
       grid.item_blocks = (int)std::max<size_t>(1, align8(n_items));
@@ -2105,19 +2104,50 @@ void pool_free(sim_batch* b, size_t off, size_t len) {
 // back to their own: what a pool admits depends on sim_batch_world_bytes alone.
 // (The lists are made anew by every advance, and all of this is ordered on the
 // batch's stream.)
-void use_lists(Slot& s, int level, int* const* cnt, int4* const* rec) {
+void carve_slot_lists(Slot& s, int level, Carver c) {
+  const ListCaps k = list_caps(s.p, s.n_part, level);
   s.list_level = level;
   for (int j = 0; j < 2; ++j) {
-    s.b.tl_cnt[j] = cnt[j];
-    s.b.tl_rec[j] = rec[j];
+    s.b.tl_cnt[j] = nullptr;
+    s.b.tl_rec[j] = nullptr;
+    carve_lists(c, s.p, k, &s.b.tl_cnt[j], &s.b.tl_rec[j]);
+  }
+}
+size_t lists_bytes(const Slot& s, int level) {
+  return batch_world_bytes(s.p, s.n_fil, s.n_part, level) - batch_world_bytes(s.p, s.n_fil, s.n_part, kNoLists);
+}
+
+// The largest lists that the world's own part of the pool holds.
+void use_own_lists(sim_batch* b, Slot& s) {
+  const size_t rest = batch_world_bytes(s.p, s.n_fil, s.n_part, kNoLists);
+  s.ext_len = 0;
+  for (int level : kListLevels) {
+    if (rest + lists_bytes(s, level) > s.pool_len) continue;
+    carve_slot_lists(s, level, Carver{b->pool + s.pool_off + rest});
+    break;
   }
 }
 
 void drop_larger_lists(sim_batch* b, size_t off, size_t len) {
+  for (Slot& s : b->eng.slots)
+    if (s.used && s.ext_len && s.ext_off < off + len && off < s.ext_off + s.ext_len) use_own_lists(b, s);
+}
+
+// The tile side of the batch's binned worlds (side_of); from 32 back to 16 cells
+// only once they are well below the limit, as a change drops the captured graphs.
+void choose_side(sim_batch* b) {
+  size_t tiles = 0;
+  int now = 16;
+  for (const Slot& s : b->eng.slots) {
+    if (!s.used || mode_of(s.p) != mc::kBinned) continue;
+    tiles += tiles32_of(s.p);
+    if (s.p.tile_side == 32) now = 32;
+  }
+  const int side = now == 32 && tiles > kSmallTiles * 3 / 4 ? 32 : side_of(tiles);
   for (Slot& s : b->eng.slots) {
-    if (!s.used || s.ext_len == 0 || s.ext_off + s.ext_len <= off || off + len <= s.ext_off) continue;
-    s.ext_len = 0;
-    use_lists(s, s.own_level, s.own_cnt, s.own_rec);
+    if (!s.used || mode_of(s.p) != mc::kBinned || s.p.tile_side == side) continue;
+    s.p.tile_side = side;
+    use_own_lists(b, s);
   }
 }
 
@@ -2144,25 +2174,19 @@ bool find_free(const sim_batch* b, size_t bytes, size_t* off) {
 void give_larger_lists(sim_batch* b) {
   size_t too_large = SIZE_MAX;                   // no room for this much
   for (Slot& s : b->eng.slots) {
-    if (!s.used || s.ext_len) continue;
+    if (!s.used || s.ext_len || mode_of(s.p) != mc::kBinned) continue;
     for (int level : kListLevels) {
-      if (level <= s.own_level || level < kCompactLists) break;
-      const ListCaps k = list_caps(s.p, s.n_part, level);
-      if (k.kind == mc::kNoLists) break;
-      int* cnt[2] = {};
-      int4* rec[2] = {};
-      Carver need{nullptr};
-      for (int j = 0; j < 2; ++j) carve_lists(need, s.p, k, &cnt[j], &rec[j]);
+      if (level <= s.list_level || level < kCompactLists) break;
+      const size_t bytes = lists_bytes(s, level);
       size_t off = 0;
-      if (need.off >= too_large || !find_free(b, need.off, &off)) {
-        too_large = std::min(too_large, need.off);
+      if (bytes == 0) break;
+      if (bytes >= too_large || !find_free(b, bytes, &off)) {
+        too_large = std::min(too_large, bytes);
         continue;
       }
-      Carver c{b->pool + off};
-      for (int j = 0; j < 2; ++j) carve_lists(c, s.p, k, &cnt[j], &rec[j]);
       s.ext_off = off;
-      s.ext_len = need.off;
-      use_lists(s, level, cnt, rec);
+      s.ext_len = bytes;
+      carve_slot_lists(s, level, Carver{b->pool + off});
       break;
     }
   }
@@ -2281,14 +2305,8 @@ sim_status sim_batch_admit(sim_batch* b, const sim_params* p, const sim_arrays* 
     return fail(SIM_E_INVALID, "batched filaments (with those hanging from them) are limited to %d nodes", e.grid.pack);
   bool any_loop = false;
   if ((st = read_loops(init, e.stream, &any_loop))) return st;
-  // the world's own part of the pool, with the largest tile lists it holds
+  // the world's own part of the pool
   const size_t bytes = batch_world_bytes(*p, init->n_filaments, init->n_particles, -1);
-  int level = kNoLists;
-  for (int k : kListLevels) {
-    if (batch_world_bytes(*p, init->n_filaments, init->n_particles, k) > bytes) continue;
-    level = k;
-    break;
-  }
   size_t off = 0;
   if (!pool_alloc(b, bytes, &off)) return fail(SIM_E_WORKSPACE, "pool exhausted (world needs %zu bytes)", bytes);
   drop_larger_lists(b, off, bytes);
@@ -2303,12 +2321,8 @@ sim_status sim_batch_admit(sim_batch* b, const sim_params* p, const sim_arrays* 
   s.pool_off = off;
   s.pool_len = bytes;
   Carver c{b->pool + off};
-  carve_batch_world(c, *p, s.n_fil, s.n_part, level, s);
-  s.own_level = level;
-  for (int j = 0; j < 2; ++j) {
-    s.own_cnt[j] = s.b.tl_cnt[j];
-    s.own_rec[j] = s.b.tl_rec[j];
-  }
+  carve_batch_world(c, *p, s.n_fil, s.n_part, kNoLists, s);
+  if (mode_of(*p) == mc::kBinned) s.p.tile_side = 0;   // (choose_side gives it one, and lists)
   const size_t N = s.n_part, F = s.n_fil, ncell = (size_t)p->nx * p->ny;
   auto cp = [&](void* dst, const void* src, size_t by) -> sim_status {
     if (by) HIPCHK(hipMemcpyAsync(dst, src, by, hipMemcpyDeviceToDevice, e.stream));
@@ -2359,6 +2373,7 @@ sim_status sim_batch_admit(sim_batch* b, const sim_params* p, const sim_arrays* 
   s.remaining = steps;
   e.slots[w] = s;
   if ((st = e.set_ctl(w, t0, steps))) return st;
+  choose_side(b);
   give_larger_lists(b);
   if ((st = e.rebuild())) {
     e.slots[w] = Slot();
@@ -2419,6 +2434,7 @@ sim_status sim_batch_retire(sim_batch* b, int32_t slot, const sim_arrays* out) {
   const unsigned fl = *hflag;
   pool_free(b, s.pool_off, s.pool_len);
   s = Slot();
+  choose_side(b);
   give_larger_lists(b);
   sim_status st = e.rebuild();
   if (st) return st;
