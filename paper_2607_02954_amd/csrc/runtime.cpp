@@ -478,7 +478,6 @@ struct Engine {
   mc::Grid grid{};
   bool fixed_grid = false;
   int fixed_tile_blocks = 2048;     // tile-kernel blocks per family when the grid is fixed
-  bool any_sorted = false;
   std::vector<Slot> slots;
   // host staging (pinned) for table uploads
   char* pinned = nullptr;
@@ -492,6 +491,12 @@ struct Engine {
 
   size_t n_packs = 0, n_items = 0, n_scan = 0, n_worlds = 0;
   size_t n_tiles[mc::kTileFamilies] = {};
+
+  // Kinds of launches that some world may need (Grid's fields, in this order).
+  enum { kNeedSorted, kNeedBinned, kNeedNode, kNeedEnergy, kNeedMarkers, kNeedMdf, kNeedGeneral, kNeedBranches,
+         kNeedRadius, kNeeds };
+  static constexpr int kStaleRebuilds = 4;
+  int stale = 0;                    // rebuilds since some of the launches were last needed
 
   // Device work-list lengths, in counts[]: packs, scan items, worlds, fluid
   // items, then the tiles of each tile family.
@@ -563,8 +568,6 @@ struct Engine {
   sim_status rebuild() {
     std::vector<mc::Pack> pk;
     std::vector<int2> tl[mc::kTileFamilies], sc, wl, it;
-    any_sorted = false;
-    bool any_binned = false;
     for (int w = 0; w < (int)slots.size(); ++w) {
       const Slot& s = slots[w];
       if (!s.used) continue;
@@ -595,11 +598,9 @@ struct Engine {
       wl.push_back(make_int2(w, 0));
       const int mode = mode_of(s.p);
       if (mode == mc::kSorted) {
-        any_sorted = true;
         const int nb = (ncell + 1023) / 1024;
         for (int b = 0; b < nb; ++b) sc.push_back(make_int2(w, b));
       }
-      if (mode == mc::kBinned) any_binned = true;
     }
     bool over = pk.size() > max_packs || it.size() > max_items || sc.size() > max_scan;
     for (int f = 0; f < mc::kTileFamilies; ++f) over = over || tl[f].size() > max_tiles[f];
@@ -623,86 +624,58 @@ struct Engine {
       grid.scan_blocks = (int)std::max<size_t>(1, n_scan);
       grid.world_blocks = (int)std::max<size_t>(1, n_worlds);
     }
-    more = more || (any_sorted && !grid.any_sorted) || (any_binned && !grid.any_binned);
-    bool any_node = false;
-    for (const auto& sl : slots)
-      if (sl.used && mode_of(sl.p) != mc::kBinned) any_node = true;
-    more = more || (any_node && !grid.any_node);
-    bool any_lists = false, any_spill = false;
-    for (const auto& sl : slots)
-      if (sl.used && sl.b.tl_cnt[0]) {
+    // what the worlds need of a step's launches
+    int want[kNeeds] = {};
+    bool any_lists = false, any_spill = false, tile_plain = false, tile_mk = false;
+    want[kNeedMdf] = want[kNeedRadius] = 1;       // (radius: the filter's LDS window is sized for it)
+    for (const auto& sl : slots) {
+      if (!sl.used) continue;
+      const int mode = mode_of(sl.p);
+      want[mode == mc::kBinned ? kNeedBinned : kNeedNode] = 1;
+      if (mode == mc::kSorted) want[kNeedSorted] = 1;
+      if (sl.p.energy_rate > 0.f && sl.energy) want[kNeedEnergy] = 1;
+      if (sl.b.d_marker) want[kNeedMarkers] = 1;
+      if (sl.b.U_d) want[kNeedMdf] = std::max(want[kNeedMdf], sl.p.mdf_iters);
+      if (slot_general(sl)) want[kNeedGeneral] = 1;
+      if (sl.fil_parent) want[kNeedBranches] = 1;
+      want[kNeedRadius] = std::max(want[kNeedRadius], sl.p.repulse_radius);
+      if (sl.b.tl_cnt[0]) {
         any_lists = true;
         any_spill = any_spill || may_spill(list_caps(sl.p, sl.n_part, sl.list_level), sl.n_part);
       }
-    if (any_lists) grid.any_lists = 1;            // (the pre-pass is not part of the captured graphs)
-    if (any_spill) grid.any_spill = 1;
-    bool any_energy = false, any_markers = false;
-    int mdf_max = 1;
-    for (const auto& sl : slots) {
-      if (!sl.used) continue;
-      if (sl.p.energy_rate > 0.f && sl.energy) any_energy = true;
-      if (sl.b.d_marker) any_markers = true;
-      if (sl.b.U_d) mdf_max = std::max(mdf_max, sl.p.mdf_iters);
+      if (mode == mc::kBinned && sl.b.d_marker) tile_mk = true;
+      else if (mode != mc::kDirect) tile_plain = true;
     }
-    if (any_energy && !grid.any_energy) {
-      grid.any_energy = 1;
-      more = true;
-    }
-    if (any_markers && !grid.any_markers) {
-      grid.any_markers = 1;
-      more = true;
-    }
-    // the one-layer tile variants are left out while every tile world has markers
-    bool tile_plain = false, tile_mk = false;
-    for (const auto& sl : slots) {
-      if (!sl.used || mode_of(sl.p) == mc::kDirect) continue;
-      if (mode_of(sl.p) == mc::kBinned && sl.b.d_marker) tile_mk = true;
-      else tile_plain = true;
-    }
-    const int mk_only = tile_mk && !tile_plain ? 1 : 0;
-    if (mk_only != grid.mk_only) {
+    grid.any_lists = any_lists;                   // (the pre-pass is not part of the captured graphs)
+    grid.any_spill = any_spill;
+    if (!fixed_grid || n_worlds > 0) {            // (an empty batch keeps its graphs)
+      // launches that a world needs are added at once; those that none does any
+      // more go after kStaleRebuilds admissions and retirements without one, so
+      // that worlds of a kind that come now and then cost no capture each
+      int* have[kNeeds] = {&grid.any_sorted, &grid.any_binned, &grid.any_node, &grid.any_energy, &grid.any_markers,
+                           &grid.mdf_max, &grid.general, &grid.branches, &grid.max_radius};
+      bool less = false, extra = false;
+      for (int k = 0; k < kNeeds; ++k) {
+        less = less || *have[k] < want[k];
+        extra = extra || *have[k] > want[k];
+      }
+      stale = extra ? stale + 1 : 0;
+      const bool drop = stale >= kStaleRebuilds;
+      if (drop) stale = 0;
+      for (int k = 0; k < kNeeds; ++k) *have[k] = drop ? want[k] : std::max(*have[k], want[k]);
+      more = more || less || drop;
+      // the one-layer tile variants are left out while every tile world has markers
+      const int mk_only = tile_mk && !tile_plain ? 1 : 0;
+      // one kernel for S4 - S7 while the tiles are few (a batch around the limit
+      // keeps its captured graphs until it is well past it)
+      const size_t slack = grid.fused || !fixed_grid ? 0 : 1;
+      const int fused = !grid.any_node && grid.any_binned && grid.tile_blocks[2] == 0 && grid.mdf_max <= 1 &&
+                        few_tiles(n_tiles[0] + slack * (kFusedTiles16 / 4), n_tiles[1] + slack * (kFusedTiles32 / 4),
+                                  n_tiles[2]);
+      more = more || mk_only != grid.mk_only || fused != grid.fused;
       grid.mk_only = mk_only;
-      more = true;
-    }
-    if (mdf_max > grid.mdf_max) {
-      grid.mdf_max = mdf_max;
-      more = true;
-    }
-    bool general = false;
-    for (const auto& sl : slots)
-      if (sl.used && slot_general(sl)) general = true;
-    if (general && !grid.general) {         // stays set once a world needed it
-      grid.general = 1;
-      more = true;
-    }
-    bool branches = false;
-    for (const auto& sl : slots)
-      if (sl.used && sl.fil_parent) branches = true;
-    if (branches && !grid.branches) {
-      grid.branches = 1;
-      more = true;
-    }
-    int max_r = 1;                          // the filter's LDS window is sized for this radius
-    for (const auto& sl : slots)
-      if (sl.used) max_r = std::max(max_r, sl.p.repulse_radius);
-    if (max_r > grid.max_radius) {
-      grid.max_radius = max_r;
-      more = true;
-    }
-    // one kernel for S4 - S7 while the tiles are few (a batch around the limit
-    // keeps its captured graphs until it is well past it)
-    const size_t slack = grid.fused || !fixed_grid ? 0 : 1;
-    const int fused = !any_node && !grid.any_node && any_binned && grid.tile_blocks[2] == 0 && mdf_max <= 1 &&
-                      grid.mdf_max <= 1 &&
-                      few_tiles(n_tiles[0] + slack * (kFusedTiles16 / 4), n_tiles[1] + slack * (kFusedTiles32 / 4),
-                                n_tiles[2]);
-    if (fused != grid.fused) {
       grid.fused = fused;
-      more = true;
     }
-    grid.any_sorted |= any_sorted ? 1 : 0;
-    grid.any_binned |= any_binned ? 1 : 0;
-    grid.any_node |= any_node ? 1 : 0;
     if (more) drop_graphs();
     // stage into pinned memory once the previous upload has been consumed
     HIPCHK(hipEventSynchronize(upload_done));
