@@ -365,8 +365,12 @@ sim_status sim_debug_buffer(sim_world *w, int32_t which, void **ptr);
  * 3 repulsion + spread, 4 fluid update, 5 gather + integrate.  Group 4 is the
  * fluid kernel's own execution time (its dispatch's start and end
  * timestamps); the other groups are event pairs around their launches and
- * include dispatch gaps.  The state advances exactly as with sim_rollout.
- * Synchronises the stream. */
+ * include dispatch gaps.  Where the step runs several groups as one kernel, its
+ * time is in one of them and the others are 0: groups 0 to 2 in 0 (binned
+ * worlds, but for those of the most tiles and nodes), 3 to 5 in 4, there an
+ * event pair too (binned worlds of few tiles without forcing iterations; 5 is
+ * then the energy field's time).  The state advances exactly as with
+ * sim_rollout.  Synchronises the stream. */
 sim_status sim_profile_steps(sim_world *w, int64_t t0, int32_t n_steps, float *ms_out);
 
 /* Measurement hook: throughput of the atomic adds a particle -> grid transfer

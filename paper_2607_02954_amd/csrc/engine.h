@@ -261,7 +261,8 @@ void launch_adjoint_debug(const WorldDev* W, const Tables& T, const Grid& G, int
 // Forward step launchers (kernels.hip).  `W` points at a device array of
 // world descriptors.
 void launch_elastic(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);
-// elastic force and filter: one launch where every world is binned
+// elastic force and filter: in one launch where prepare_merged
+bool prepare_merged(const Grid& G);
 void launch_prepare(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s);
 // the lists of the current positions; with n_steps >= 0 also sets the worlds' control
 // words for a run of n_steps steps from step t

@@ -2540,12 +2540,14 @@ static void launch_prepare_t(const WorldDev* W, const Tables& T, const Grid& G, 
 // with one launch, 202.9 with two; 262,144 (1360 packs) 153.9 and 157.1; 1024^2
 // (1024 tiles) 56.2 and 58.1.
 constexpr int kWideTiles = 256, kMergedBlocks = 3000;
-void launch_prepare(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s) {
+bool prepare_merged(const Grid& G) {
   const int families = (G.tile_blocks[0] > 0) + (G.tile_blocks[1] > 0) + (G.tile_blocks[2] > 0);
   const int tiles = G.tile_blocks[0] + G.tile_blocks[1] + G.tile_blocks[2];
-  const bool merge = !G.any_node && G.any_binned && families == 1 && (G.tile_blocks[2] == 0 || G.pack == 1024) &&
-                     (G.pack == 256 ? std::min(tiles, G.node_blocks) <= kMergedBlocks : tiles <= kWideTiles);
-  if (!merge) {
+  return !G.any_node && G.any_binned && families == 1 && (G.tile_blocks[2] == 0 || G.pack == 1024) &&
+         (G.pack == 256 ? std::min(tiles, G.node_blocks) <= kMergedBlocks : tiles <= kWideTiles);
+}
+void launch_prepare(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s) {
+  if (!prepare_merged(G)) {
     launch_elastic(W, T, G, s);
     launch_sort(W, T, G, s);
     launch_filter(W, T, G, s);

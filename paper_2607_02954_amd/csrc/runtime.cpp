@@ -1277,16 +1277,33 @@ sim_status sim_profile_steps(sim_world* w, int64_t t0, int32_t n_steps, float* m
   sim_status st = e.set_ctl(0, t0, n_steps);
   if (st) return st;
   mc::launch_list_prepass(e.desc[0], e.tab, e.grid, 0, -1, e.stream);
+  const bool merged = mc::prepare_merged(e.grid), fused = e.grid.fused;
   for (int k = 0; k < n_steps; ++k) {
     const mc::WorldDev* d = e.desc[k & 1];
     hipEvent_t* E = ev.data() + (size_t)k * (kGroups + 1);
     HIPCHK(hipEventRecord(E[0], e.stream));
-    mc::launch_elastic(d, e.tab, e.grid, e.stream);
-    HIPCHK(hipEventRecord(E[1], e.stream));
-    mc::launch_sort(d, e.tab, e.grid, e.stream);
-    HIPCHK(hipEventRecord(E[2], e.stream));
-    mc::launch_filter(d, e.tab, e.grid, e.stream);
-    HIPCHK(hipEventRecord(E[3], e.stream));
+    if (merged) {
+      mc::launch_prepare(d, e.tab, e.grid, e.stream);
+      HIPCHK(hipEventRecord(E[1], e.stream));
+    } else {
+      mc::launch_elastic(d, e.tab, e.grid, e.stream);
+      HIPCHK(hipEventRecord(E[1], e.stream));
+      mc::launch_sort(d, e.tab, e.grid, e.stream);
+      HIPCHK(hipEventRecord(E[2], e.stream));
+      mc::launch_filter(d, e.tab, e.grid, e.stream);
+      HIPCHK(hipEventRecord(E[3], e.stream));
+    }
+    if (fused) {
+      HIPCHK(hipEventRecord(E[5], e.stream));
+      mc::launch_energy(d, e.tab, e.grid, e.stream);
+      HIPCHK(hipEventRecord(E[6], e.stream));
+      HIPCHK(hipEventRecord(fl[2 * k], e.stream));
+      mc::launch_fluid_tiles(d, e.tab, e.grid, false, e.stream);
+      HIPCHK(hipEventRecord(fl[2 * k + 1], e.stream));
+      HIPCHK(hipGetLastError());
+      continue;
+    }
+    if (merged) HIPCHK(hipEventRecord(E[3], e.stream));
     mc::launch_repulse(d, e.tab, e.grid, e.stream);
     mc::launch_spread(d, e.tab, e.grid, e.stream);
     mc::launch_mdf(d, e.tab, e.grid, e.stream);
@@ -1302,6 +1319,8 @@ sim_status sim_profile_steps(sim_world* w, int64_t t0, int32_t n_steps, float* m
   HIPCHK(hipStreamSynchronize(e.stream));
   for (int g = 0; g < kGroups; ++g) {
     double tot = 0.0;
+    ms_out[g] = 0.f;                             // (done by another group's kernel)
+    if ((merged && (g == 1 || g == 2)) || (fused && (g == 3 || (g == 5 && !e.grid.any_energy)))) continue;
     for (int k = 0; k < n_steps; ++k) {
       float ms = 0.f;
       hipEvent_t* E = ev.data() + (size_t)k * (kGroups + 1);

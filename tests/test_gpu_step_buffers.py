@@ -44,3 +44,28 @@ def test_buffers_after_a_step_are_the_sub_steps(nx, ny, lens, offset):
         torch.cuda.synchronize()
         outs.append(out)
     assert torch.equal(*outs)
+
+
+@pytest.mark.parametrize("nx, n, kw, own_kernels", [
+    (72, 3, {}, (0, 4)),                             # S0 - S3 and S4 - S7 in a kernel each
+    (200, 100, {"energy_rate": 0.05}, (0, 4, 5)),
+    (200, 100, {"mdf_iters": 2}, (0, 3, 4, 5)),      # S4 - S7 apart
+    (96, 40, {"transfer": "sorted"}, (0, 1, 2, 3, 4, 5)),
+])
+def test_profile_times_the_kernels_a_step_runs(nx, n, kw, own_kernels):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import numpy as np
+    from paper_2607_02954_amd import sim
+    w = wl.random_world(3, nx, nx, [24] * n, amp=0.5)
+    if "energy_rate" in kw:
+        w.energy = np.ones((nx, nx), dtype=np.float32)
+    p = sim.Params(nx=nx, ny=nx, **kw)
+    A, B = sim.World(w, p), sim.World(w, p)
+    ms = A.profile(0, 7)
+    B.rollout(0, 7)
+    B.sync()
+    print([round(1e3 * v, 1) for v in ms], "us")
+    assert [k for k, v in enumerate(ms) if v > 0] == list(own_kernels)
+    for name in ("cell", "frac", "f", "u") + (("energy", "energy_collected") if "energy_rate" in kw else ()):
+        assert torch.equal(getattr(A.state, name), getattr(B.state, name)), name
