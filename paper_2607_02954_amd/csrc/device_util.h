@@ -377,7 +377,7 @@ struct Reach {
   int near_, before, after;
   __device__ __forceinline__ explicit Reach(const WorldDev& w) {
     const bool mk = w.d_marker != nullptr;
-    near_ = near_reach(mk);
+    near_ = w.tl_near;
     before = far_reach_before(w.radius, mk);
     after = far_reach_after(w.radius, mk);
   }

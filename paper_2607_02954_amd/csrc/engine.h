@@ -41,10 +41,11 @@ __host__ __device__ constexpr int tile_side_of_family(int f) { return 16 << f; }
 __host__ __device__ constexpr int tile_family_of_side(int side) { return side == 16 ? 0 : side == 64 ? 2 : 1; }
 __host__ __device__ constexpr int tile_shift_of_side(int side) { return side == 16 ? 4 : side == 64 ? 6 : 5; }
 // How far (cells) a home lies outside a tile, before and after it, at most for
-// the tile's list: the near nodes (what its spread, its fluid halo and their
-// two-layer markers can need) and the far ones (what else its filter of radius
-// R can need: supports that meet the tile, its ring and R cells of filter).
-__host__ __device__ constexpr int near_reach(bool markers) { return markers ? 5 : 3; }
+// the tile's list: the near nodes (what its spread and their two-layer markers
+// can need, in the one-kernel step on the tile and its fluid halo) and the far
+// ones (what else its filter of radius R can need: supports that meet the tile,
+// its ring and R cells of filter).
+__host__ __device__ constexpr int near_reach(bool markers, bool fused = true) { return (fused ? 3 : 2) + (markers ? (fused ? 2 : 1) : 0); }
 __host__ __device__ constexpr int far_reach_before(int R, bool markers) { return R + 3 > near_reach(markers) ? R + 3 : near_reach(markers); }
 __host__ __device__ constexpr int far_reach_after(int R, bool markers) { return R + 2 > near_reach(markers) ? R + 2 : near_reach(markers); }
 // Ints of a tile's list: the number of its own nodes (those its block
@@ -170,6 +171,7 @@ struct WorldDev {
   int4* tl_rec_next;
   int* tl_cnt_next;
   int tl_kind;                          // ListKind
+  int tl_near;                          // near_reach of the step it runs
   int tl_own, tl_strays;                // segment capacities
   int tl_near_s, tl_far_s, tl_near_c, tl_far_c;   // of a side neighbour and of a corner neighbour
   int tl_stride;

@@ -1741,7 +1741,7 @@ static __device__ __forceinline__ void integrate_own(const WorldDev& w, OwnNodes
 // MK: the two-layer variant (worlds with markers, which the plain variant
 // skips): a node moves with the mean of its two markers' velocities.
 template <int TILE, bool MK>
-__global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_integrate_tile(const WorldDev* __restrict__ W, Tables T) {
+__global__ __launch_bounds__(TileCfg<TILE>::kThreads, MK && TILE == 32 ? 5 : 1) void k_integrate_tile(const WorldDev* __restrict__ W, Tables T) {
   constexpr int kE = MK ? 1 : 0;
   constexpr int kStage = TILE + 3 + 2 * kE, kThreads = TileCfg<TILE>::kThreads;
   __shared__ vf2 s_u[kStage * kStage];        // staged velocity, x and y interleaved

@@ -206,9 +206,10 @@ ListCaps list_caps(const sim_params& p, int n_part, int level) {
   k.own = cap(T * T, level, 0, 0.75);
   k.strays = cap(4 * T, kFullLists);
   k.near_s = cap(n * T, level, T);                // (a filament that lies along the side)
-  k.far_s = cap((r - n) * T, level, T);
+  const double n0 = mc::near_reach(mk, false);    // (far nodes are what is left, most where few are near)
+  k.far_s = cap((r - n0) * T, level, T);
   k.near_c = cap(n * n, level);
-  k.far_c = cap(r * r - n * n, level);
+  k.far_c = cap(r * r - n0 * n0, level);
   // (all nodes in crowds with their copies in the lists around, or half a million
   // entries more than there are nodes)
   const double copies = (T + 2 * r) * (T + 2 * r) / (T * T);
@@ -329,7 +330,9 @@ bool slot_general(const Slot& s) { return s.fil_flags || s.kb || s.ks || s.ksh |
 
 // Device descriptor of a world whose buffers are described by s; parity 0
 // reads populations buffer s.cur, parity 1 the other one.
-mc::WorldDev world_desc(const Slot& s, int parity, const mc::Ctl* ctl_src, mc::Ctl* ctl_dst, unsigned* flags) {
+// fused: of a step that runs S4 - S7 as one kernel
+mc::WorldDev world_desc(const Slot& s, int parity, bool fused, const mc::Ctl* ctl_src, mc::Ctl* ctl_dst,
+                        unsigned* flags) {
   const sim_params& p = s.p;
   mc::WorldDev d{};
   d.nx = p.nx;
@@ -411,6 +414,7 @@ mc::WorldDev world_desc(const Slot& s, int parity, const mc::Ctl* ctl_src, mc::C
   d.part = s.b.part;
   const ListCaps k = list_caps(p, s.n_part, s.list_level);
   k.set(d);
+  d.tl_near = mc::near_reach(s.b.d_marker != nullptr, fused);
   d.tl_rec = s.b.tl_rec[src];
   d.tl_cnt = s.b.tl_cnt[src];
   d.tl_rec_next = s.b.tl_rec[1 - src];
@@ -561,7 +565,7 @@ struct Engine {
   }
 
   mc::WorldDev make_desc(int w, int parity) const {
-    return world_desc(slots[w], parity, ctl[parity] + w, ctl[1 - parity] + w, flags + w);
+    return world_desc(slots[w], parity, grid.fused, ctl[parity] + w, ctl[1 - parity] + w, flags + w);
   }
 
   // Rebuild work tables and descriptors from the slot list and upload them.
@@ -1565,11 +1569,12 @@ sim_status sim_step_noalloc(const sim_params* asked, const sim_arrays* a, int64_
   sl.fbuf[1] = L.b.f_alt;
   sl.u = a->u;
   sl.cur = 0;
-  const mc::WorldDev d0 = world_desc(sl, 0, L.ctl + 0, L.ctl + 1, L.flags);
-  const mc::WorldDev d1 = world_desc(sl, 1, L.ctl + 1, L.ctl + 0, L.flags);
+  const int fam = tile_family(*p), mode = mode_of(*p);
+  const bool fused = mode == mc::kBinned && p->mdf_iters <= 1 && few_tiles(fam == 0 ? nt : 0, fam == 1 ? nt : 0, fam == 2 ? nt : 0);
+  const mc::WorldDev d0 = world_desc(sl, 0, fused, L.ctl + 0, L.ctl + 1, L.flags);
+  const mc::WorldDev d1 = world_desc(sl, 1, fused, L.ctl + 1, L.ctl + 0, L.flags);
 
   mc::Tables tab{};
-  const int fam = tile_family(*p);
   tab.packs = L.packs;
   tab.n_packs = L.counts + Engine::kCntPacks;
   for (int f = 0; f < mc::kTileFamilies; ++f) {
@@ -1590,13 +1595,12 @@ sim_status sim_step_noalloc(const sim_params* asked, const sim_arrays* a, int64_
   g.item_blocks = (int)align8(std::max(1, n_items));
   g.scan_blocks = std::max(1, n_scan);
   g.world_blocks = 1;
-  const int mode = mode_of(*p);
   g.any_sorted = mode == mc::kSorted;
   g.any_binned = mode == mc::kBinned;
   g.any_node = mode != mc::kBinned;
   g.any_lists = L.b.tl_cnt[0] != nullptr;
   g.any_spill = may_spill(list_caps(*p, n_part, level), n_part);
-  g.fused = mode == mc::kBinned && p->mdf_iters <= 1 && few_tiles(fam == 0 ? nt : 0, fam == 1 ? nt : 0, fam == 2 ? nt : 0);
+  g.fused = fused;
   g.max_radius = p->repulse_radius;
   g.any_energy = p->energy_rate > 0.f && a->energy ? 1 : 0;
   g.any_markers = L.b.d_marker ? 1 : 0;
