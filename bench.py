@@ -42,7 +42,7 @@ STEP_BYTES_PER_NODE = 24      # whole-step algorithmic bytes per node
 KERNELS = ["elastic", "bin_or_sort", "filter", "repulse_spread", "fluid", "integrate"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_lbm_scaling_2048.json")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2607_02954_amd", "csrc", n)
-                  for n in ("kernels.hip", "device_util.h", "engine.h")]
+                  for n in ("kernels.hip", "device_util.h", "list_geometry.h", "engine.h")]
 
 
 def kernel_source_hash():

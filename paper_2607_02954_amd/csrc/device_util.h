@@ -7,6 +7,7 @@
 #include <utility>
 
 #include "engine.h"
+#include "list_geometry.h"
 
 namespace mc {
 
@@ -61,10 +62,6 @@ static __device__ __forceinline__ int n_tiles(const Tables& T) {
 // Tile table entries hold (world, tx | ty << 16).
 static __device__ __forceinline__ int tile_x(int packed) { return packed & 0xffff; }
 static __device__ __forceinline__ int tile_y(int packed) { return packed >> 16; }
-
-static __device__ __forceinline__ int wrap_near(int v, int n) {   // v in [-n, 2n)
-  return v < 0 ? v + n : (v >= n ? v - n : v);
-}
 
 // Map an angle difference into (-pi, pi] (the quotient by 2 pi is formed
 // with its reciprocal; that can only matter at the boundary itself).
@@ -371,32 +368,6 @@ static __device__ __forceinline__ int block_scan256(int v, int* s_wave, int* tot
 // the tile reads the own nodes of the tiles around it, which hold every node of
 // theirs once; a world without lists is read by testing every node.
 // ---------------------------------------------------------------------------
-// Class of home cell h (in [0, n)) for the tile [x0, x0 + tw) of a periodic
-// axis: 0 own, 1 near, 2 far, 3 out of reach.
-struct Reach {
-  int near_, before, after;
-  __device__ __forceinline__ explicit Reach(const WorldDev& w) {
-    const bool mk = w.d_marker != nullptr;
-    near_ = w.tl_near;
-    before = far_reach_before(w.radius, mk);
-    after = far_reach_after(w.radius, mk);
-  }
-  __device__ __forceinline__ int of_cell(int h, int x0, int tw, int n) const {
-    if (h >= x0 && h < x0 + tw) return 0;
-    const int a = h < x0 ? x0 - h : x0 - h + n;                  // cells before / after the tile (1 = next to it)
-    const int b = h >= x0 + tw ? h - (x0 + tw - 1) : h - (x0 + tw - 1) + n;
-    return a <= near_ || b <= near_ ? 1 : (a <= before || b <= after ? 2 : 3);
-  }
-};
-
-// Neighbour q (0..7) of a tile: sides first (-x, +x, -y, +y), then corners.
-static __device__ __forceinline__ constexpr int nb_dx(int q) { return q == 0 ? -1 : q == 1 ? 1 : q < 4 ? 0 : ((q & 1) ? 1 : -1); }
-static __device__ __forceinline__ constexpr int nb_dy(int q) { return q < 2 ? 0 : q == 2 ? -1 : q == 3 ? 1 : (q < 6 ? -1 : 1); }
-// Whether an axis of nt tiles has a neighbour in direction d of its own (two
-// tiles are each other's neighbour once: in direction +1).
-static __device__ __forceinline__ bool nb_exists(int d, int nt) { return d == 0 || nt >= 3 || (nt == 2 && d == 1); }
-static __device__ __forceinline__ int nb_tile(int t, int d, int nt) { return wrap_near(t + d, nt); }
-
 // Place of segment `seg` in a tile's list and its capacity (strays and own
 // nodes come first, then the sides, then the corners, near before far).
 static __device__ __forceinline__ int segment_first(const WorldDev& w, int seg) {
@@ -408,28 +379,6 @@ static __device__ __forceinline__ int segment_cap(const WorldDev& w, int seg) {
   if (seg < kCntNear) return seg == kCntOwn ? w.tl_own : w.tl_strays;
   const int q = (seg - kCntNear) & 7;
   return seg < kCntFar ? (q < 4 ? w.tl_near_s : w.tl_near_c) : (q < 4 ? w.tl_far_s : w.tl_far_c);
-}
-
-// f(tx, ty, class) for every tile that a node with home cell (hx, hy) reaches:
-// the up to five tiles around its own per axis are tested (a reach of at most
-// 11 cells spans a narrow last tile and the one beyond it).
-template <int TILE, class F>
-static __device__ __forceinline__ void for_reached_tiles(const WorldDev& w, int hx, int hy, F f) {
-  constexpr int sh = TileCfg<TILE>::kShift;
-  const Reach R(w);
-  const int cx = hx >> sh, cy = hy >> sh;
-  const int nx = w.nx, ny = w.ny, ntx = w.ntx, nty = w.nty;
-  const int mx = min(ntx, 5), my = min(nty, 5);
-  for (int j = 0; j < my; ++j) {
-    const int ty = nty <= 5 ? j : wrap_near(cy - 2 + j, nty);
-    const int y0 = ty << sh, ky = R.of_cell(hy, y0, min(TILE, ny - y0), ny);
-    if (ky > 2) continue;
-    for (int i = 0; i < mx; ++i) {
-      const int tx = ntx <= 5 ? i : wrap_near(cx - 2 + i, ntx);
-      const int x0 = tx << sh, kx = R.of_cell(hx, x0, min(TILE, nx - x0), nx);
-      if (kx <= 2) f(tx, ty, max(kx, ky));
-    }
-  }
 }
 
 // A tile's list counts (block-uniform: scalar loads; nothing in a kernel that
@@ -445,13 +394,6 @@ enum ListMode : int {
   kModeAround = 1,   // the own nodes of the tiles around it
   kModeAll = 2       // every node of the world
 };
-
-// How many tiles away along an axis of nt tiles of t cells (the last of `last`)
-// a block can have integrated a node that reaches tile `at`: the reach and a
-// small move are less than a tile, but not less than a narrow last one.
-static __device__ __forceinline__ int axis_span(int at, int nt, int t, int last) {
-  return last < t && (at == 0 || at == nt - 2) ? 2 : 1;
-}
 
 // The runs of records that one wavefront of a block takes from a tile's list,
 // all in scalar registers: its share of the strays and own nodes and (SEGS 2)

@@ -371,12 +371,6 @@ __global__ __launch_bounds__(256) void k_lists_zero(const WorldDev* __restrict__
   }
 }
 
-// Whether tile (tx, ty) is (cx, cy) or one of its eight neighbours.
-static __device__ __forceinline__ bool next_to(const WorldDev& w, int cx, int cy, int tx, int ty) {
-  const int dx = abs(tx - cx), dy = abs(ty - cy);
-  return (dx <= 1 || dx == w.ntx - 1) && (dy <= 1 || dy == w.nty - 1);
-}
-
 // The world's words after its tiles' counts.
 static __device__ __forceinline__ MC_GLOBAL int* list_words(const WorldDev& w, MC_GLOBAL int* counts) {
   return counts + w.ntx * w.nty * kListCounts;
@@ -405,109 +399,10 @@ static __device__ __forceinline__ void write_entry(const WorldDev& w, MC_GLOBAL 
   else lists[e] = rec;
 }
 
-// Classes of a node with home (hx, hy) for the eight neighbours of tile
-// (cx, cy), its home or the tile it just left, and whether it may reach a tile
-// beyond them.
-struct Classes {
-  int kx, ky;                                    // for the tiles before, at and after, 2 bits each
-  bool beyond;
-  __device__ __forceinline__ int of(int q) const {
-    return max((kx >> (2 * nb_dx(q) + 2)) & 3, (ky >> (2 * nb_dy(q) + 2)) & 3);
-  }
-};
-// Classes along one axis of nt tiles of a node at place l of a tile of t cells
-// (beside it by at most kSmallMove cells) that reaches no tile beyond its
-// neighbours (Place).
-static __device__ __forceinline__ int axis_classes(const Reach& R, int l, int t, int nt) {
-  int k0 = l < 0 ? 0 : (l < R.near_ ? 1 : (l < R.after ? 2 : 3));
-  int k1 = l < 0 ? (-l <= R.near_ ? 1 : 2) : (l >= t ? (l - t < R.near_ ? 1 : 2) : 0);
-  int k2 = l >= t ? 0 : (t - l <= R.near_ ? 1 : (t - l <= R.before ? 2 : 3));
-  if (nt < 3) {                                  // two tiles are neighbours on both sides
-    k2 = nt == 2 ? min(k0, k2) : 3;
-    k0 = 3;
-    if (nt == 1) k1 = 0;
-    else k1 = min(k1, 1);                        // (it may be nearer the other way round)
-  }
-  return k0 | (k1 << 2) | (k2 << 4);
-}
-// Place of home (hx, hy) relative to tile (cx, cy), the short way round, and
-// whether it is one from which a node reaches no tile beyond the neighbours:
-// at most kSmallMove cells beside the tile and, where a neighbour is the axis'
-// narrow last tile, no nearer to it than the reach past it.  (Testing every
-// tile around such nodes' own, as done for all nodes of a world with a narrow
-// last tile before: 700 nodes on 72 x 50, 30.8 us per step; now 27.5.)
-struct Place {
-  int lx, ly;
-  bool inside;
-  static __device__ __forceinline__ bool fits(const Reach& R, int l, int t, int c, int nt, int last) {
-    const int lo = nt > 2 && c == 0 ? max(-kSmallMove, R.after - last) : -kSmallMove;
-    const int hi = t + (nt > 2 && c == nt - 2 ? min(kSmallMove, last - R.before) : kSmallMove);
-    return l >= lo && l < hi;
-  }
-  __device__ __forceinline__ Place(const WorldDev& w, int side, int cx, int cy, int hx, int hy) {
-    const Reach R(w);
-    const int nx = w.nx, ny = w.ny, x0 = cx * side, y0 = cy * side, tw = min(side, nx - x0), th = min(side, ny - y0);
-    lx = hx - x0;
-    ly = hy - y0;
-    lx += lx >= tw && 2 * lx > nx ? -nx : (lx < 0 && -2 * lx > nx ? nx : 0);
-    ly += ly >= th && 2 * ly > ny ? -ny : (ly < 0 && -2 * ly > ny ? ny : 0);
-    inside = fits(R, lx, tw, cx, w.ntx, nx - (w.ntx - 1) * side) && fits(R, ly, th, cy, w.nty, ny - (w.nty - 1) * side);
-  }
-};
-template <int TILE>
-static __device__ __forceinline__ Classes neighbour_classes(const WorldDev& w, int cx, int cy, int hx, int hy) {
-  constexpr int sh = TileCfg<TILE>::kShift;
-  const Reach R(w);
-  const int nx = w.nx, ny = w.ny, ntx = w.ntx, nty = w.nty;
-  const Place p(w, TILE, cx, cy, hx, hy);
-  Classes c;
-  c.beyond = !p.inside;
-  if (!c.beyond) {
-    c.kx = axis_classes(R, p.lx, min(TILE, nx - cx * TILE), ntx);
-    c.ky = axis_classes(R, p.ly, min(TILE, ny - cy * TILE), nty);
-  } else {
-    c.kx = c.ky = 0;
-    for (int d = -1; d <= 1; ++d) {
-      const int tx = nb_tile(cx, d, ntx) << sh, ty = nb_tile(cy, d, nty) << sh;
-      c.kx |= (nb_exists(d, ntx) ? R.of_cell(hx, tx, min(TILE, nx - tx), nx) : 3) << (2 * d + 2);
-      c.ky |= (nb_exists(d, nty) ? R.of_cell(hy, ty, min(TILE, ny - ty), ny) : 3) << (2 * d + 2);
-    }
-  }
-  return c;
-}
-
 // Segment of neighbour q's nodes of class 1 (near) or 2 (far).
 static __device__ __forceinline__ int class_segment(int cls, int q) {
   return kCntNear - 8 + 8 * cls + q;
 }
-
-// What a node has to do with the neighbours along one axis: its class for the
-// one that it reaches (2 bits), for the tile itself (2), which side that is,
-// and whether it reaches both.
-static __device__ __forceinline__ int axis_pairs(int classes) {
-  const int k0 = classes & 3, k1 = (classes >> 2) & 3, k2 = classes >> 4;
-  return min(k0, k2) | (k1 << 2) | (k0 < 3 ? 0 : 16) | (max(k0, k2) < 3 ? 32 : 0);
-}
-// The neighbours of a node that reaches at most one tile along each axis
-// (more: it may reach others), as nearly all do: one beside it along x, one
-// along y and the corner between them, with their classes.
-struct Pairs {
-  int dx, dy, side_x, side_y, corner;
-  bool more;
-  __device__ __forceinline__ Pairs(int x, int y, bool beyond) {
-    const int kx = x & 3, ky = y & 3;
-    more = beyond || ((x | y) & 32) != 0;
-    dx = ((x >> 3) & 2) - 1;
-    dy = ((y >> 3) & 2) - 1;
-    side_x = max(kx, (y >> 2) & 3);
-    side_y = max((x >> 2) & 3, ky);
-    corner = max(kx, ky);
-  }
-  __device__ __forceinline__ explicit Pairs(const Classes& c) : Pairs(axis_pairs(c.kx), axis_pairs(c.ky), c.beyond) {}
-  __device__ __forceinline__ int qx() const { return dx > 0; }
-  __device__ __forceinline__ int qy() const { return 2 + (dy > 0); }
-  __device__ __forceinline__ int qc() const { return 4 + (dx > 0) + 2 * (dy > 0); }
-};
 
 static __device__ __forceinline__ void append_stray(const WorldDev& w, MC_GLOBAL vi4* lists, MC_GLOBAL int* counts,
                                                     int tx, int ty, const vi4& rec) {
