@@ -1277,20 +1277,18 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_adj_mdf_cell(const 
       KERNEL<1024><<<(G).node_blocks, 1024, 0, s>>>(__VA_ARGS__);                \
   } while (0)
 
-// One launch of a tile kernel per tile family present.
+// One launch of a tile kernel per tile family of binned worlds.
 #define MC_ADJ_TILES(KERNEL, G, ...)                                                              \
   do {                                                                                            \
     if ((G).tile_blocks[0] > 0) KERNEL<16><<<(G).tile_blocks[0], TileCfg<16>::kThreads, 0, s>>>(__VA_ARGS__); \
     if ((G).tile_blocks[1] > 0) KERNEL<32><<<(G).tile_blocks[1], TileCfg<32>::kThreads, 0, s>>>(__VA_ARGS__); \
-    if ((G).tile_blocks[2] > 0) KERNEL<64><<<(G).tile_blocks[2], TileCfg<64>::kThreads, 0, s>>>(__VA_ARGS__); \
   } while (0)
 
-// A tile kernel with a second template argument, once per tile family present.
+// A tile kernel with a second template argument, once per tile family of binned worlds.
 #define MC_ADJ_TILES2(KERNEL, ARG, G, ...)                                                        \
   do {                                                                                            \
     if ((G).tile_blocks[0] > 0) KERNEL<16, ARG><<<(G).tile_blocks[0], TileCfg<16>::kThreads, 0, s>>>(__VA_ARGS__); \
     if ((G).tile_blocks[1] > 0) KERNEL<32, ARG><<<(G).tile_blocks[1], TileCfg<32>::kThreads, 0, s>>>(__VA_ARGS__); \
-    if ((G).tile_blocks[2] > 0) KERNEL<64, ARG><<<(G).tile_blocks[2], TileCfg<64>::kThreads, 0, s>>>(__VA_ARGS__); \
   } while (0)
 
 // Single linear adjoint sub-steps, for transpose (dot-product) tests:
@@ -1305,9 +1303,14 @@ void launch_adjoint_debug(const WorldDev* W, const Tables& T, const Grid& G, int
   a.one = A;
   a.one.dbg_v = v;
   a.one.dbg_out = out;
-  if (which == 0) MC_ADJ_TILES(k_adj_spread, G, W, T, a, 4, 0);
-  else if (which == 1) MC_ADJ_TILES(k_adj_filter, G, W, T, a);
-  else k_adj_lbm<<<G.item_blocks, 256, 0, s>>>(W, T, a);
+  if (which == 0) {
+    MC_ADJ_TILES(k_adj_spread, G, W, T, a, 4, 0);
+  } else if (which == 1) {
+    MC_ADJ_TILES(k_adj_filter, G, W, T, a);
+    if (G.tile_blocks[2] > 0) k_adj_filter<64><<<G.tile_blocks[2], TileCfg<64>::kThreads, 0, s>>>(W, T, a);
+  } else {
+    k_adj_lbm<<<G.item_blocks, 256, 0, s>>>(W, T, a);
+  }
 }
 
 void launch_adjoint_step(const WorldDev* W, const Tables& T, const Grid& G, const AdjArg& A, int mdf, hipStream_t s) {

@@ -41,6 +41,7 @@ struct TileCfg {
   static constexpr int kShift = tile_shift_of_side(TILE);
   static constexpr int kFamily = tile_family_of_side(TILE);
   static constexpr int kThreads = TILE == 64 ? 1024 : 256;   // threads per tile block
+  static constexpr bool kBinned = TILE < 64;                 // (64-cell tiles: sorted and direct worlds alone)
 };
 
 // Tile table entry it of a tile family: (world, tx | ty << 16); computed
@@ -869,7 +870,7 @@ static inline bool tile_family_present(const Grid& G) {
 }
 
 // Host side: launch a tile kernel with a one-layer and a two-layer variant
-// (template argument MK last) for every tile family present, in the
+// (template argument MK last) for the tile families of binned worlds, in the
 // variants the grid needs: launch(Int<TILE>, Bool<MK>) launches one.  Each
 // variant skips the other's worlds; the two-layer one runs only where a
 // binned world has markers, the one-layer one unless every world has them.
@@ -883,10 +884,6 @@ static inline void for_tile_variants(const Grid& G, L launch) {
   if (tile_family_present<32>(G)) {
     if (plain) launch(std::integral_constant<int, 32>(), std::false_type());
     if (mk) launch(std::integral_constant<int, 32>(), std::true_type());
-  }
-  if (tile_family_present<64>(G)) {
-    if (plain) launch(std::integral_constant<int, 64>(), std::false_type());
-    if (mk) launch(std::integral_constant<int, 64>(), std::true_type());
   }
 }
 

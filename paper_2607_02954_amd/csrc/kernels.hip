@@ -532,8 +532,7 @@ __global__ __launch_bounds__(PACK) void k_lists_build(const WorldDev* __restrict
     const int gi = pk.node_begin + threadIdx.x;
     if (gi >= pk.node_end) continue;
     if (w.tile_shift == 4) build_lists_of_node<16, SPILL>(w, gi, last);
-    else if (w.tile_shift == 5) build_lists_of_node<32, SPILL>(w, gi, last);
-    else build_lists_of_node<64, SPILL>(w, gi, last);
+    else build_lists_of_node<32, SPILL>(w, gi, last);
   }
 }
 
@@ -838,7 +837,7 @@ static __device__ __forceinline__ void filter_tile(const WorldDev& w, int packed
     const float inv_reg = 1.0f / (float)reg;
     const int xo = x0 - R - 1, yo = y0 - R - 1;   // region origin (unwrapped)
     float* s_st = s_mid + reg * kRing;
-    if (mode == kBinned) {
+    if (C::kBinned && mode == kBinned) {
       const int tix = tile_y(packed) * w.ntx + tile_x(packed);
       const int S = reg + 6;                      // window side; window origin (xo - 3, yo - 3)
       const int P = S + kWinPad;                  // row pitch
@@ -1150,7 +1149,7 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_spread(const WorldD
     const int x0 = tile_x(tl.y) * TILE;
     const int y0 = tile_y(tl.y) * TILE;
     const int tw = min(TILE, nx - x0), th = min(TILE, ny - y0);
-    if (mode == kBinned) {
+    if (C::kBinned && mode == kBinned) {
       const int tix = tile_y(tl.y) * w.ntx + tile_x(tl.y);
       // S4 repulsion is formed here, per node, from the gradient staged over
       // the window (grid cells (x0 - 3 + i, y0 - 3 + j), periodic)
@@ -1174,7 +1173,7 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads) void k_spread(const WorldD
       const int ly = k >> C::kShift, lx = k & (TILE - 1);
       if (lx >= tw || ly >= th) continue;
       vf2 F;
-      if (mode == kBinned) {
+      if (C::kBinned && mode == kBinned) {
         F.x = fix_to_float(spread_cell<SW::kSide>(s_fx, lx, ly, nx, ny));
         F.y = fix_to_float(spread_cell<SW::kSide>(s_fy, lx, ly, nx, ny));
       } else {
@@ -2415,7 +2414,6 @@ static void launch_prepare_t(const WorldDev* W, const Tables& T, const Grid& G, 
   const auto go = [&](auto gen, auto br) {
     constexpr bool GN = decltype(gen)::value, B = decltype(br)::value;
     const int bytes = std::max(lds, (int)sizeof(ElasticLds<PACK, B>));
-    if constexpr (TILE == 64) declare_lds<TILE, &k_prepare<TILE, PACK, GN, B>>();
     k_prepare<TILE, PACK, GN, B><<<8 * (tr + pr), PACK, bytes, s>>>(W, T, wb, tr, pr);
   };
   if (G.branches) go(std::true_type(), std::true_type());
@@ -2423,8 +2421,7 @@ static void launch_prepare_t(const WorldDev* W, const Tables& T, const Grid& G, 
   else go(std::false_type(), std::false_type());
 }
 
-// One launch where every world is binned and their tiles have one side whose
-// block fits the packs' (64-cell tiles take 1024 threads); else the elastic
+// One launch where every world is binned and their tiles have one side; else the elastic
 // force (which the sorted and direct transfers build on), then the rest.
 // Filaments of more than 256 nodes are packed by blocks of 1024 threads, which
 // suit a tile ill: up to one block per CU the launch saved counts for more (3000 nodes on
@@ -2436,9 +2433,8 @@ static void launch_prepare_t(const WorldDev* W, const Tables& T, const Grid& G, 
 // (1024 tiles) 56.2 and 58.1.
 constexpr int kWideTiles = 256, kMergedBlocks = 3000;
 bool prepare_merged(const Grid& G) {
-  const int families = (G.tile_blocks[0] > 0) + (G.tile_blocks[1] > 0) + (G.tile_blocks[2] > 0);
-  const int tiles = G.tile_blocks[0] + G.tile_blocks[1] + G.tile_blocks[2];
-  return !G.any_node && G.any_binned && families == 1 && (G.tile_blocks[2] == 0 || G.pack == 1024) &&
+  const int tiles = G.tile_blocks[0] + G.tile_blocks[1];
+  return !G.any_node && G.any_binned && (G.tile_blocks[0] > 0) != (G.tile_blocks[1] > 0) &&
          (G.pack == 256 ? std::min(tiles, G.node_blocks) <= kMergedBlocks : tiles <= kWideTiles);
 }
 void launch_prepare(const WorldDev* W, const Tables& T, const Grid& G, hipStream_t s) {
@@ -2449,11 +2445,9 @@ void launch_prepare(const WorldDev* W, const Tables& T, const Grid& G, hipStream
   } else if (G.tile_blocks[0] > 0) {
     if (G.pack == 256) launch_prepare_t<16, 256>(W, T, G, s);
     else launch_prepare_t<16, 1024>(W, T, G, s);
-  } else if (G.tile_blocks[1] > 0) {
+  } else {
     if (G.pack == 256) launch_prepare_t<32, 256>(W, T, G, s);
     else launch_prepare_t<32, 1024>(W, T, G, s);
-  } else {
-    launch_prepare_t<64, 1024>(W, T, G, s);
   }
 }
 
@@ -2468,6 +2462,7 @@ void launch_spread(const WorldDev* W, const Tables& T, const Grid& G, hipStream_
     constexpr int TL = decltype(tile)::value;
     k_spread<TL, decltype(mk)::value><<<G.tile_blocks[TileCfg<TL>::kFamily], TileCfg<TL>::kThreads, 0, s>>>(W, T);
   });
+  if (G.tile_blocks[2] > 0) k_spread<64, false><<<G.tile_blocks[2], TileCfg<64>::kThreads, 0, s>>>(W, T);
 }
 
 void launch_fluid_tiles(const WorldDev* W, const Tables& T, const Grid& G, bool keep, hipStream_t s) {
@@ -2547,7 +2542,6 @@ void launch_energy(const WorldDev* W, const Tables& T, const Grid& G, hipStream_
   if (G.any_binned) {
     if (G.tile_blocks[0] > 0) k_energy_deplete<16><<<G.tile_blocks[0], TileCfg<16>::kThreads, 0, s>>>(W, T);
     if (G.tile_blocks[1] > 0) k_energy_deplete<32><<<G.tile_blocks[1], TileCfg<32>::kThreads, 0, s>>>(W, T);
-    if (G.tile_blocks[2] > 0) k_energy_deplete<64><<<G.tile_blocks[2], TileCfg<64>::kThreads, 0, s>>>(W, T);
   }
   if (G.any_node) MC_PACK_DISPATCH(k_energy_deplete_atomic, G, W, T);
 }
