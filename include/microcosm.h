@@ -85,9 +85,11 @@ typedef struct sim_params {
   uint32_t flags;          /* SIM_SPLAT_SORTED or SIM_SPLAT_DIRECT, else binned      */
   int32_t tile_side;       /* side of the square grid tiles the transfer and filter
                               kernels work on: 16, 32 or 64; 0 means 32.  A tuning
-                              choice: results do not depend on it beyond rounding
-                              (binned: not at all, and a world may run with
-                              another side where that is faster).                  */
+                              choice of the sorted and direct transfers, whose
+                              results depend on it by rounding alone.  Binned
+                              worlds run with 16 or 32, whichever suits the tiles
+                              they have together, whatever is asked for; their
+                              results do not depend on it.                         */
   float energy_rate;       /* energy field (sim_arrays.energy): fraction of the
                               sensed energy a node collects per step, in [0, 1];
                               0 disables the field                                 */
@@ -191,13 +193,15 @@ typedef struct sim_batch sim_batch;
  * one-layer coupling) for an nx x ny grid. */
 void sim_params_default(sim_params *p, int32_t nx, int32_t ny);
 
-/* Bytes of device workspace sim_create needs for a world of this size. */
+/* Bytes of device workspace for a world of this size.  (A binned world also
+ * runs with less, down to 16 bytes a cell and a node for its tile lists: they
+ * hold fewer nodes then, and it steps slower.) */
 sim_status sim_workspace_size(const sim_params *p, int32_t n_filaments, int32_t n_particles,
                               size_t *bytes);
 
 /* Create a world over caller arrays.  Reads fil_offset back to the host
  * (synchronous), validates it, lays out the workspace (256-byte aligned
- * pointer, ws_bytes >= sim_workspace_size) and uploads the work tables.
+ * pointer, ws_bytes: sim_workspace_size) and uploads the work tables.
  * The world's time index is set by each sim_step / sim_rollout call. */
 sim_status sim_create(const sim_params *p, const sim_arrays *a, void *workspace, size_t ws_bytes,
                       void *stream, sim_world **out);
@@ -391,7 +395,10 @@ sim_status sim_measure_atomics(void *buf, size_t buf_bytes, void *stream, double
  * same kernels in one persistent, graph-captured launch per chunk of steps.
  * World state lives in a caller-provided device pool (the HBM budget). ---- */
 
-/* Pool bytes one world of this size occupies inside a batch pool. */
+/* Pool bytes one world of this size occupies inside a batch pool: what a pool
+ * admits depends on these alone.  Pool space that no world occupies holds
+ * longer tile lists of the worlds that are there, which step faster with them;
+ * it is given back when an admission needs it. */
 sim_status sim_batch_world_bytes(const sim_params *p, int32_t n_filaments, int32_t n_particles,
                                  size_t *bytes);
 /* max_worlds slots; pool is a device buffer of pool_bytes (256-byte aligned). */

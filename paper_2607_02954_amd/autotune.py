@@ -1,7 +1,8 @@
 """Autotuner: chooses the grid tile side (16, 32 or 64 cells: the tile of the
-filter, spread and integrate kernels and of the node bins) per grid-size
-class, then the steps per captured chunk and the persistent grid sizes of
-the tile/cell kernels and the node kernels of the batched launch, by timing
+filter, spread and integrate kernels; binned worlds run with the 16- or
+32-cell tiles that suit them whatever is asked for) per grid-size class,
+then the steps per captured chunk and the persistent grid sizes of the
+tile/cell kernels and the node kernels of the batched launch, by timing
 candidate settings on scratch worlds.  A single large world gets its tile side
 the same way (tune_world_tile).
 

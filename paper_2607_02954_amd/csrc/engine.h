@@ -87,8 +87,8 @@ constexpr int kMaxFilament = 1024;   // longest filament a node pack can hold
 
 // Sticky per-world flag bits.
 constexpr unsigned kFlagUnstable = 1u;   // NaN or |u| > u_max
-constexpr unsigned kFlagBins = 2u;       // a node was not where its tile list said (positions changed
-                                         // without a list pre-pass)
+constexpr unsigned kFlagLists = 2u;      // a node was not where its tile list said (sub-steps run
+                                         // out of order, or positions changed between them)
 
 // Per-world control word, double-buffered by step parity: kernels of a step
 // read ctl_src; the fluid kernel writes the next step's values to ctl_dst.
@@ -139,7 +139,7 @@ struct WorldDev {
   float* fel;                           // node force [2][N]: total (elastic + repulsion)
   float* fel_el;                        // node elastic force [2][N]
   const Ctl* ctl_src; Ctl* ctl_dst;
-  unsigned* flags;                      // sticky: kFlagUnstable, kFlagBins
+  unsigned* flags;                      // sticky: kFlagUnstable, kFlagLists
   // deterministic sorted-segment transfer (SIM_SPLAT_SORTED)
   int* key;                             // [N] home cell of each node
   int* rank;                            // [N] arrival rank within its home cell

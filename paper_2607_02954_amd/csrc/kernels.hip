@@ -1571,7 +1571,7 @@ static __device__ __forceinline__ void integrate_own(const WorldDev& w, OwnNodes
       const int home = wrap_index(o.cx[q], nx) | (wrap_index(o.cy[q], ny) << 16);
       bool has = base + q * 64 + (int)(threadIdx.x & 63) < o.L.total;
       if (o.unlisted(w)) r.x = home;
-      if (has && r.x != home) atomicOr((unsigned*)glb(w.flags), kFlagBins);   // moved since its list was made
+      if (has && r.x != home) atomicOr((unsigned*)glb(w.flags), kFlagLists);   // moved since its list was made
       const int lx = (r.x & 0xffff) - x0, ly = (r.x >> 16) - y0;   // (some only reach the tile, or left it)
       has = has && lx >= 0 && lx < tw && ly >= 0 && ly < th;
       if (!has) {

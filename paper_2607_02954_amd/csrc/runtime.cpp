@@ -1217,7 +1217,7 @@ sim_status sim_sync(sim_world* w) {
   HIPCHK(hipMemcpy(fl.data(), e.flags, fl.size() * sizeof(unsigned), hipMemcpyDeviceToHost));
   unsigned f = 0;
   for (unsigned v : fl) f |= v;
-  if (f & mc::kFlagBins) return fail(SIM_E_STATE, "node positions changed without a tile-bin pre-pass");
+  if (f & mc::kFlagLists) return fail(SIM_E_STATE, "a node was not where its tile list said (sub-steps out of order?)");
   if (f) return fail(SIM_E_UNSTABLE, "world produced NaN or |u| > u_max");
   return SIM_OK;
 }
@@ -1346,7 +1346,7 @@ sim_status sim_debug_adjoint(sim_world* w, int32_t which, const void* in, void* 
   if (!w || !in || !out) return fail(SIM_E_INVALID, "NULL argument");
   Engine& e = w->eng;
   const Slot& s = e.slots[0];
-  if (which == 0 && mode_of(s.p) != mc::kBinned) return fail(SIM_E_INVALID, "the spread transpose needs bins");
+  if (which == 0 && mode_of(s.p) != mc::kBinned) return fail(SIM_E_INVALID, "the spread transpose needs the tile-binned transfer");
   if (which == 2 && !scratch) return fail(SIM_E_INVALID, "scratch is needed");
   if (which < 0 || which > 2) return fail(SIM_E_INVALID, "unknown adjoint sub-step %d", which);
   const size_t ncell = (size_t)s.p.nx * s.p.ny;
@@ -1507,7 +1507,7 @@ __global__ void k_noalloc_counts(NoallocLayout L, int n_packs, int n_tiles, int 
 __global__ void k_noalloc_status(const int* err, const unsigned* flags, int32_t* status) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
   const unsigned f = *flags;
-  *status = *err ? SIM_E_INVALID : (f & mc::kFlagBins) ? SIM_E_STATE : f ? SIM_E_UNSTABLE : SIM_OK;
+  *status = *err ? SIM_E_INVALID : (f & mc::kFlagLists) ? SIM_E_STATE : f ? SIM_E_UNSTABLE : SIM_OK;
 }
 
 }  // namespace
@@ -2434,7 +2434,7 @@ sim_status sim_batch_retire(sim_batch* b, int32_t slot, const sim_arrays* out) {
   give_larger_lists(b);
   sim_status st = e.rebuild();
   if (st) return st;
-  if (fl & mc::kFlagBins) return fail(SIM_E_STATE, "world in slot %d: tile bins out of date", slot);
+  if (fl & mc::kFlagLists) return fail(SIM_E_STATE, "world in slot %d: a node was not where its tile list said", slot);
   if (fl) return fail(SIM_E_UNSTABLE, "world in slot %d produced NaN or |u| > u_max", slot);
   return SIM_OK;
 }
