@@ -2428,9 +2428,11 @@ static void launch_prepare_t(const WorldDev* W, const Tables& T, const Grid& G, 
 // 128^2, 64 tiles: 27.0 -> 21.5 us per step), past it the separate kernels do
 // (200,000 on 1200^2: 68.4 against 90.2).
 // Otherwise one launch, except where either role fills the chip for many rounds
-// by itself: 1,048,576 nodes on 2048^2 (4096 tiles, 5451 packs) 208.3 us per step
-// with one launch, 202.9 with two; 262,144 (1360 packs) 153.9 and 157.1; 1024^2
-// (1024 tiles) 56.2 and 58.1.
+// by itself.  One launch and two, us per step: 1,048,623 nodes on 2048^2 (4096
+// tiles, 5435 packs) 207.1 and 203.7, 921,663 on 1920^2 (3600 tiles, 4786 packs)
+// 207.7 and 204.6, 802,912 on 1792^2 (3136, 4183) 167.3 and 167.4; 589,915 on
+// 1536^2 (2304, 3088) 123.9 and 125.1, 524,340 on 2048^2 (4096, 2739) 171.5 and
+// 172.3, 262,144 (1358) 155.0 and 158.0, 102,467 on 1280^2 (1600, 534) 59.9 and 64.5.
 constexpr int kWideTiles = 256, kMergedBlocks = 3000;
 bool prepare_merged(const Grid& G) {
   const int tiles = G.tile_blocks[0] + G.tile_blocks[1];

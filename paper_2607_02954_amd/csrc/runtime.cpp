@@ -153,8 +153,8 @@ sim_params with_side(const sim_params& p, int n_worlds) {
 // How much room a world's tile lists get, most first: segments for twice the
 // world's mean density and at least one node per cell (own nodes: three in four
 // cells) over each segment's cells (kFullLists), or near that without the floor
-// (kCompactLists: 267,756 nodes on 2048^2 406 MB of workspace for 640, 158.4 us
-// per step for 156.6); own nodes alone, as records or as indices; none (the tiles
+// (kCompactLists: 262,144 nodes on 2048^2 409 MB of step buffers for 603, 157.4 us
+// per step for 154.9); own nodes alone, as records or as indices; none (the tiles
 // test every node).  Crowds go to the spill area.  Worlds of at most kTestedNodes
 // nodes need no lists: a tile block tests that many nodes in no more loads than
 // it has for its list.
@@ -163,10 +163,14 @@ constexpr int kListLevels[] = {kFullLists, kCompactLists, kOwnLists, kIndexLists
 constexpr int kTestedNodes = 512;
 // Most 16-cell and 32-cell tiles (of all worlds of a table) that run S4 - S7 as
 // one kernel: 262,144 nodes on 1024^2 (4096 tiles of 16) 94.6 -> 84.3 us per
-// step, as 1024 tiles of 32 76.2 -> 57.4, 800,000 on 1792^2 (3136) 171.5 ->
-// 168.2.  On 2048^2 (4096 tiles of 32) the two sets of populations pass the
-// 256 MB of the last cache level, and the separate kernels, which stream them
-// with non-temporal accesses, take 207 us against 215.
+// step, as 1024 tiles of 32 76.2 -> 57.4.  On 2048^2 (4096 tiles of 32) the two
+// sets of populations pass the 256 MB of the last cache level, and the separate
+// kernels stream them with non-temporal accesses.  Separate and one kernel with
+// a node on 4, 8 and 16 cells: 1536^2 (2304 tiles) 137.5, 118.7, 108.3 and 124.0,
+// 91.4, 77.4; 1792^2 (3136) 170.1, 146.0, 132.6 and 167.6, 138.4, 122.2; 1920^2
+// (3600) 204.8, 176.9, 162.3 and 194.5, 161.3, 144.6; 2048^2 203.8, 171.5, 154.8
+// and 213.5, 177.2, 157.9.  So they cross between 3600 and 4096 tiles; the line is
+// on the safe side of that.
 constexpr size_t kFusedTiles16 = 4096, kFusedTiles32 = 3200;
 constexpr bool few_tiles(size_t n16, size_t n32, size_t n64) {
   return n64 == 0 && n16 <= kFusedTiles16 && n32 <= kFusedTiles32;
