@@ -346,9 +346,9 @@ __global__ __launch_bounds__(PACK) void k_elastic(const WorldDev* __restrict__ W
 // (each step's integration then appends the next step's).  Own nodes that their
 // tile's segment does not hold are counted by the pass that writes the others;
 // a pass over the tiles then hands out the spill area, and a last one over the
-// nodes fills it (both end at once where there are none, and leave the near and
-// far nodes that overflowed to the tiles around for one step: 1,048,576 nodes
-// on 2048^2, the two passes 24 us).
+// nodes fills it (both end at once where there are none, 9 us for 1,048,576 nodes
+// on 2048^2 in place of 24, and leave the near and far nodes that overflowed to
+// the tiles around for one step).
 // ---------------------------------------------------------------------------
 // Empty lists; and with n_steps >= 0 the control words of a run of that many
 // steps from step t (one launch rather than one more per world).
@@ -449,7 +449,7 @@ static __device__ __forceinline__ void build_lists_of_node(const WorldDev& w, in
   };
   // one atomic per list segment and wavefront, whose nodes share few tiles;
   // every one is issued before the first result is used (1,048,576 nodes:
-  // 32 us, 65.7 with one per node)
+  // 65.7 -> 32 us; 38 with the places of segments that may lie in the spill area)
   const int t0 = cy * ntx + cx, t1 = tile_at(a.dx, 0), t2 = tile_at(0, a.dy), t3 = tile_at(a.dx, a.dy);
   const int q1 = class_segment(a.side_x, a.qx()), q2 = class_segment(a.side_y, a.qy()), q3 = class_segment(a.corner, a.qc());
   const bool pairs = segments && !a.more;
@@ -1368,7 +1368,7 @@ template <int TILE>
 struct AppendLds {
   static constexpr int kAxis = TILE + 2 * kSmallMove;
   int cur[kSegs];
-  int at[kSegs], cap[kSegs];                     // where each segment begins, and how many it takes
+  int2 place[kSegs];                             // where each segment begins, and how many it takes
   unsigned char axis[2 * kAxis];                 // axis_pairs of the places along x, then y
 };
 template <int TILE>
@@ -1386,8 +1386,7 @@ static __device__ __forceinline__ void init_append(const WorldDev& w, int bx, in
   const int q = (seg - kCntNear) & 7, dx = own ? 0 : nb_dx(q), dy = own ? 0 : nb_dy(q);
   const int tile = nb_tile(by, dy, w.nty) * w.ntx + nb_tile(bx, dx, w.ntx);
   lds.cur[seg] = 0;
-  lds.at[seg] = tile * w.tl_stride + segment_first(w, seg);
-  lds.cap[seg] = segment_cap(w, seg);
+  lds.place[seg] = make_int2(tile * w.tl_stride + segment_first(w, seg), segment_cap(w, seg));
 }
 // The places that the filter left in the next lists (reserve_segments).  By every
 // thread after its own init_append, before the barrier ahead of append_nodes.
@@ -1398,16 +1397,13 @@ static __device__ __forceinline__ void take_places(const WorldDev& w, int bx, in
   const int q = (seg - kCntNear) & 7, dx = seg < kCntNear ? 0 : nb_dx(q), dy = seg < kCntNear ? 0 : nb_dy(q);
   if (seg == kCntStrays || !nb_exists(dx, w.ntx) || !nb_exists(dy, w.nty)) return;
   const MC_GLOBAL int* c = glb(w.tl_cnt_next) + (nb_tile(by, dy, w.nty) * w.ntx + nb_tile(bx, dx, w.ntx)) * kListCounts;
-  lds.at[seg] = c[kFirst + seg];
-  lds.cap[seg] = c[seg];
+  lds.place[seg] = make_int2(c[kFirst + seg], c[seg]);
 }
 // Record `slot` of the segment, or the flags of the lists that cannot be used
 // without it.
-template <int TILE>
 static __device__ __forceinline__ void append_record(const WorldDev& w, MC_GLOBAL vi4* lists, MC_GLOBAL int* counts,
-                                                     const AppendLds<TILE>& lds, int tx, int ty, int seg, int slot,
-                                                     const vi4& rec) {
-  if (slot < lds.cap[seg]) lists[lds.at[seg] + slot] = rec;
+                                                     int2 place, int tx, int ty, int seg, int slot, const vi4& rec) {
+  if (slot < place.y) lists[place.x + slot] = rec;
   else flag_overflow(w, counts, tx, ty, seg);
 }
 
@@ -1435,13 +1431,14 @@ static __device__ __forceinline__ void append_nodes(const WorldDev& w, int bx, i
     const int lane = __lane_id(), leader = __ffsll(m) - 1;
     int k = 0;
     if (lane == leader) k = atomicAdd(&lds.cur[kCntOwn], __popcll(m));
+    const int2 place = lds.place[kCntOwn];
     const Place pl(w, TILE, bx, by, r.x & 0xffff, r.x >> 16);
     const int ix = pl.inside ? pl.lx + kSmallMove : 0, iy = kAxis + (pl.inside ? pl.ly + kSmallMove : 0);
     const Pairs a(lds.axis[ix], lds.axis[iy], !pl.inside);
     k = __shfl(k, leader) + __popcll(m & ((1ull << lane) - 1ull));
     if (!has) continue;
     if (w.tl_kind != kSegments) {                // own nodes alone
-      if (k < lds.cap[kCntOwn]) write_entry(w, lists, lds.at[kCntOwn] + k, r);
+      if (k < place.y) write_entry(w, lists, place.x + k, r);
       else flag_overflow(w, counts, bx, by, kCntOwn);
       const int tx = (r.x & 0xffff) >> TileCfg<TILE>::kShift, ty = (r.x >> 16) >> TileCfg<TILE>::kShift;
       if (tx != bx || ty != by) {                // (counted, so that its block knows how many it gets)
@@ -1451,24 +1448,26 @@ static __device__ __forceinline__ void append_nodes(const WorldDev& w, int bx, i
       continue;
     }
     if (!__any(a.more)) {
-      // every lane for its own neighbours at once, the slots fetched together
+      // every lane for its own neighbours at once, slots and places fetched together
+      // (512^2, 65,536 nodes: 28.8 -> 28.5 us per step)
       const int q1 = class_segment(a.side_x, a.qx()), q2 = class_segment(a.side_y, a.qy()),
                 q3 = class_segment(a.corner, a.qc());
       const auto listed = [](int cls) { return cls == 1 || cls == 2; };
       int k1 = 0, k2 = 0, k3 = 0;
-      if (listed(a.side_x)) k1 = atomicAdd(&lds.cur[q1], 1);
-      if (listed(a.side_y)) k2 = atomicAdd(&lds.cur[q2], 1);
-      if (listed(a.corner)) k3 = atomicAdd(&lds.cur[q3], 1);
-      append_record(w, lists, counts, lds, bx, by, kCntOwn, k, r);
+      int2 p1, p2, p3;
+      if (listed(a.side_x)) k1 = atomicAdd(&lds.cur[q1], 1), p1 = lds.place[q1];
+      if (listed(a.side_y)) k2 = atomicAdd(&lds.cur[q2], 1), p2 = lds.place[q2];
+      if (listed(a.corner)) k3 = atomicAdd(&lds.cur[q3], 1), p3 = lds.place[q3];
+      append_record(w, lists, counts, place, bx, by, kCntOwn, k, r);
       const int tx = nb_tile(bx, a.dx, ntx), ty = nb_tile(by, a.dy, nty);
-      if (listed(a.side_x)) append_record(w, lists, counts, lds, tx, by, q1, k1, r);
-      if (listed(a.side_y)) append_record(w, lists, counts, lds, bx, ty, q2, k2, r);
-      if (listed(a.corner)) append_record(w, lists, counts, lds, tx, ty, q3, k3, r);
+      if (listed(a.side_x)) append_record(w, lists, counts, p1, tx, by, q1, k1, r);
+      if (listed(a.side_y)) append_record(w, lists, counts, p2, bx, ty, q2, k2, r);
+      if (listed(a.corner)) append_record(w, lists, counts, p3, tx, ty, q3, k3, r);
       if (a.side_x == 0 || a.side_y == 0 || a.corner == 0)   // it has left for that one
         append_stray(w, lists, counts, a.side_y == 0 ? bx : tx, a.side_x == 0 ? by : ty, r);
       continue;
     }
-    append_record(w, lists, counts, lds, bx, by, kCntOwn, k, r);
+    append_record(w, lists, counts, place, bx, by, kCntOwn, k, r);
     const Classes c = neighbour_classes<TILE>(w, bx, by, r.x & 0xffff, r.x >> 16);
 #pragma unroll 1
     for (int q = 0; q < 8; ++q) {
@@ -1479,7 +1478,7 @@ static __device__ __forceinline__ void append_nodes(const WorldDev& w, int bx, i
         continue;
       }
       const int seg = class_segment(cls, q);
-      append_record(w, lists, counts, lds, tx, ty, seg, atomicAdd(&lds.cur[seg], 1), r);
+      append_record(w, lists, counts, lds.place[seg], tx, ty, seg, atomicAdd(&lds.cur[seg], 1), r);
     }
     if (c.beyond) {
       jump(pl);
@@ -1497,11 +1496,11 @@ static __device__ __forceinline__ void store_counts(const WorldDev& w, int bx, i
   const int dx = seg < kCntNear ? 0 : nb_dx(q), dy = seg < kCntNear ? 0 : nb_dy(q);
   if (!nb_exists(dx, w.ntx) || !nb_exists(dy, w.nty)) return;
   MC_GLOBAL int* c = glb(w.tl_cnt_next) + (nb_tile(by, dy, w.nty) * w.ntx + nb_tile(bx, dx, w.ntx)) * kListCounts;
-  const int n = lds.cur[seg], at = lds.at[seg];
+  const int n = lds.cur[seg], at = lds.place[seg].x;
   c[seg] = n;
   c[kFirst + seg] = at;
   // (in the spill area: the next step's may have to be there as well)
-  if (nearly_full(n, lds.cap[seg]) || at >= w.ntx * w.nty * w.tl_stride)
+  if (nearly_full(n, lds.place[seg].y) || at >= w.ntx * w.nty * w.tl_stride)
     glb(w.tl_cnt_next)[(by * w.ntx + bx) * kListCounts + kCntCrowded] = 1;
 }
 
@@ -1713,12 +1712,12 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads, MK ? 3 : 4) void k_fluid_t
     const int x0 = tile_x(tl.y) * TILE, y0 = tile_y(tl.y) * TILE;
     const int tw = min(TILE, nx - x0), th = min(TILE, ny - y0);
     const bool append = w.tl_kind != kNoLists && cs.remaining > 1;
-    if (append) init_append(w, tile_x(tl.y), tile_y(tl.y), s_app);
     // (the gradient's loads first: they need no other, and loads return in order)
     const WindowLoads<kThreads, kGSide> grad(glbv<const vf2>(w.grad), nx, ny, x0 - LO - (MK ? 4 : 3), y0 - LO - (MK ? 4 : 3));
     SpreadNodes<TILE> nodes(w, tix, glb(w.fel_el));
     zero_lds_u64(s_fx, SW::kCells);
     zero_lds_u64(s_fy, SW::kCells);
+    if (append) init_append(w, tile_x(tl.y), tile_y(tl.y), s_app);
     grad.store(s_g);
     // the populations of the tile's cells and those around it, and the nodes
     // to integrate, are on their way while the forces are spread
