@@ -850,7 +850,7 @@ static __device__ __forceinline__ void filter_tile(const WorldDev& w, int packed
           next[tix * kListCounts + kCntFlags] = next[tix * kListCounts + kCntCrowded] = 0;
           if (tix == 0) list_words(w, next)[kWordSpill] = list_words(w, next)[kWordJump] = 0;
         }
-        if (nodes.L.outgrows) reserve_segments(w, tile_x(packed), tile_y(packed));
+        if (__builtin_expect(nodes.L.outgrows, 0)) reserve_segments(w, tile_x(packed), tile_y(packed));
       }
       const int ox = wrap_index(xo - 3, nx), oy = wrap_index(yo - 3, ny);
       const int keep_x = reg + 3 <= nx ? reg + 2 : nx;
@@ -1403,7 +1403,7 @@ static __device__ __forceinline__ void take_places(const WorldDev& w, int bx, in
 // without it.
 static __device__ __forceinline__ void append_record(const WorldDev& w, MC_GLOBAL vi4* lists, MC_GLOBAL int* counts,
                                                      int2 place, int tx, int ty, int seg, int slot, const vi4& rec) {
-  if (slot < place.y) lists[place.x + slot] = rec;
+  if (__builtin_expect(slot < place.y, 1)) lists[place.x + slot] = rec;
   else flag_overflow(w, counts, tx, ty, seg);
 }
 
@@ -1437,7 +1437,7 @@ static __device__ __forceinline__ void append_nodes(const WorldDev& w, int bx, i
     const Pairs a(lds.axis[ix], lds.axis[iy], !pl.inside);
     k = __shfl(k, leader) + __popcll(m & ((1ull << lane) - 1ull));
     if (!has) continue;
-    if (w.tl_kind != kSegments) {                // own nodes alone
+    if (__builtin_expect(w.tl_kind != kSegments, 0)) {   // own nodes alone
       if (k < place.y) write_entry(w, lists, place.x + k, r);
       else flag_overflow(w, counts, bx, by, kCntOwn);
       const int tx = (r.x & 0xffff) >> TileCfg<TILE>::kShift, ty = (r.x >> 16) >> TileCfg<TILE>::kShift;
@@ -1447,7 +1447,7 @@ static __device__ __forceinline__ void append_nodes(const WorldDev& w, int bx, i
       }
       continue;
     }
-    if (!__any(a.more)) {
+    if (__builtin_expect(!__any(a.more), 1)) {
       // every lane for its own neighbours at once, slots and places fetched together
       // (512^2, 65,536 nodes: 28.8 -> 28.5 us per step)
       const int q1 = class_segment(a.side_x, a.qx()), q2 = class_segment(a.side_y, a.qy()),
@@ -1463,7 +1463,7 @@ static __device__ __forceinline__ void append_nodes(const WorldDev& w, int bx, i
       if (listed(a.side_x)) append_record(w, lists, counts, p1, tx, by, q1, k1, r);
       if (listed(a.side_y)) append_record(w, lists, counts, p2, bx, ty, q2, k2, r);
       if (listed(a.corner)) append_record(w, lists, counts, p3, tx, ty, q3, k3, r);
-      if (a.side_x == 0 || a.side_y == 0 || a.corner == 0)   // it has left for that one
+      if (__builtin_expect(a.side_x == 0 || a.side_y == 0 || a.corner == 0, 0))   // it has left for that one
         append_stray(w, lists, counts, a.side_y == 0 ? bx : tx, a.side_x == 0 ? by : ty, r);
       continue;
     }
@@ -1500,7 +1500,7 @@ static __device__ __forceinline__ void store_counts(const WorldDev& w, int bx, i
   c[seg] = n;
   c[kFirst + seg] = at;
   // (in the spill area: the next step's may have to be there as well)
-  if (nearly_full(n, lds.place[seg].y) || at >= w.ntx * w.nty * w.tl_stride)
+  if (__builtin_expect(nearly_full(n, lds.place[seg].y) || at >= w.ntx * w.nty * w.tl_stride, 0))
     glb(w.tl_cnt_next)[(by * w.ntx + bx) * kListCounts + kCntCrowded] = 1;
 }
 
@@ -1520,7 +1520,7 @@ struct OwnNodes {
 #pragma unroll
     for (int q = 0; q < kOwnPer; ++q)              // clamped, so that every load is issued at once
       e[q] = L.d0 + min(base + q * 64 + (int)(threadIdx.x & 63), L.total - 1);
-    if (!unlisted(w)) {
+    if (__builtin_expect(!unlisted(w), 1)) {
 #pragma unroll
       for (int q = 0; q < kOwnPer; ++q) r[q] = glbv<const vi4>(w.tl_rec)[e[q]];
 #pragma unroll
@@ -1656,7 +1656,7 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads, MK && TILE == 32 ? 5 : 1) 
     const WindowLoads<kThreads, kStage> u(glbv<const vf2>(w.u), nx, ny, x0 - 1 - kE, y0 - 1 - kE);
     OwnNodes<TILE> own(w, tile);
     u.store(s_u);
-    if (append && own.L.outgrows) take_places(w, tile_x(tl.y), tile_y(tl.y), s_app);
+    if (__builtin_expect(append && own.L.outgrows, 0)) take_places(w, tile_x(tl.y), tile_y(tl.y), s_app);
     __syncthreads();
     integrate_own<TILE, MK>(w, own, tl.y, append, s_u, s_app);
     __syncthreads();
@@ -1741,7 +1741,7 @@ __global__ __launch_bounds__(TileCfg<TILE>::kThreads, MK ? 3 : 4) void k_fluid_t
       tile_spread_markers<TILE, true, LO, HI>(w, nodes, x0, y0, tw, th, 1.0f, s_fx, s_fy, s_g);
     else
       tile_spread_vec<TILE, true, false, LO, HI>(w, nodes, x0, y0, tw, th, 1.0f, s_fx, s_fy, s_g);
-    if (append && own.L.outgrows) take_places(w, tile_x(tl.y), tile_y(tl.y), s_app);
+    if (__builtin_expect(append && own.L.outgrows, 0)) take_places(w, tile_x(tl.y), tile_y(tl.y), s_app);
     __syncthreads();
     MC_GLOBAL float* dst = glb(w.f_dst);
     // the velocity and the grid force are written where no later step of the
