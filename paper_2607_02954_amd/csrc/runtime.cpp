@@ -769,7 +769,7 @@ struct Engine {
     // tile lists of the current positions for the first step (each step's
     // integrate then makes the next one's)
     if (t && !grid.any_lists && slots.size() == 1) {
-      sim_status st = set_ctl(0, *t, n);         // (no list words to clear: 18.9 -> 18.3 us for a single step of 32 nodes)
+      sim_status st = set_ctl(0, *t, n);         // (no list words to clear: a single step of 32 nodes 18.9 -> 18.4 us)
       if (st) return st;
     } else {
       mc::launch_list_prepass(desc[0], tab, grid, t ? *t : 0, t ? n : -1, stream);
